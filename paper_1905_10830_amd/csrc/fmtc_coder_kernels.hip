@@ -28,13 +28,12 @@ constexpr uint32_t kInf = 0xffffffffu;
 // ---------------------------------------------------------------------------
 struct TableLds {
     __attribute__((aligned(16))) uint32_t h[256];
-    uint32_t weight[260];       // leaf weights in (count, symbol) order (4 spare entries: reads just past the end)
-    uint32_t children[256];     // per merge: node ids of the two children (leaf i: i, internal j: 256 + j)
+    uint32_t weight[320];       // leaf weights in (count, symbol) order (64 spare entries: windows that reach past the end)
+    uint32_t children[64];      // small alphabets, per merge: node ids of the two children (leaf i: i, internal j: 256 + j)
     uint16_t leaf_parent[256];  // merge that consumed each sorted leaf
-    uint16_t int_parent[256];   // ... each internal node (numbered in creation order); then its 2^r-th ancestor
-    uint16_t depth[256];        // of the internal nodes
+    uint32_t node[256];         // internal nodes in creation order: parent | 1 << 16, then ancestor | distance << 16
     uint8_t len_sorted[256];    // code length of the sorted leaves
-    uint32_t rank[260];         // position of every used symbol in (count, symbol) order; reused by the serial merge
+    uint32_t rank[320];         // position of every used symbol in (count, symbol) order; then the internal nodes' weights
 };
 
 // LDS traffic of one wavefront completes in order; this keeps the compiler from moving it across the point
@@ -43,39 +42,69 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// The merge loop is serial by nature (n - 1 steps).
-// More than 64 used symbols: the queues in LDS and the whole loop in ONE lane.  A step is four LDS reads in flight
-// together, a dozen dependent operations and two LDS writes; spreading the queues over the lanes' registers
-// instead costs four cross-lane reads per queue entry and, measured, several times as long per step.
-// Internal node weights go where the ranks were (the caller holds those in registers by now).
-__device__ __forceinline__ void huffman_merge_serial(TableLds& L, int lane, int n) {
+// More than 64 used symbols: the merges in rounds.  With t the sum of the two lightest nodes, every node of weight at
+// most t is gone before any node made from now on (those weigh at least t, and leaves as well as older internal nodes
+// win ties; the internal nodes at hand all weigh at most t), so these nodes, in (weight, leaf first, age) order, pair
+// off all at once; the last one stays if their number is odd.  A round takes the first 62 of them, one per lane (a
+// shorter run of that order is just as good).  Which places of the order internal nodes hold is a 64-bit mask in
+// scalar registers: node k of the queue stands behind k others and the leaves not heavier than it.  A lane then finds
+// its node by counting mask bits below it, and a pair's sum is its neighbour's weight away.
+// 15 to 25 rounds for the 130 to 250 symbols of 7 and 8 bits, where one merge after the other in one lane took
+// 0.11 us each: 168 symbols 19.4 -> 11.2 us, issue-bound in one wavefront at about 100 instructions a round.  (Up to
+// 64 symbols the loop below stays: 70 ns a merge, and the small alphabets' steep counts need as many rounds.)
+// Leaves parents in leaf_parent and node (see TableLds).  Internal node weights go where the ranks were (the caller
+// holds those in registers by now).  One wavefront.
+__device__ __forceinline__ void huffman_merge_rounds(TableLds& L, int lane, int n) {
     uint32_t* iw = L.rank;
-    for (int i = lane; i < 260; i += 64) {
+    for (int i = lane; i < 320; i += 64) {
         iw[i] = kInf;
         if (i >= n) L.weight[i] = kInf;
     }
     wave_sync();
-    if (lane == 0) {
-        int nl = 0, ni = 0;
-        for (int made = 0; made < n - 1; made++) {
-            // a queue that has run out shows "infinity" (the arrays have spare entries behind index 255)
-            const uint32_t l0 = L.weight[nl], l1 = L.weight[nl + 1];
-            const uint32_t i0 = iw[ni], i1 = iw[ni + 1];
-            const bool a_leaf = l0 <= i0;  // first pick: a leaf wins over an internal node of equal weight
-            const uint32_t wa = a_leaf ? l0 : i0;
-            const uint32_t ida = a_leaf ? (uint32_t)nl : 256u + (uint32_t)ni;
-            const uint32_t ln = a_leaf ? l1 : l0, in = a_leaf ? i0 : i1;
-            const int nl1 = nl + (a_leaf ? 1 : 0), ni1 = ni + (a_leaf ? 0 : 1);
-            const bool b_leaf = ln <= in;
-            const uint32_t wb = b_leaf ? ln : in;
-            const uint32_t idb = b_leaf ? (uint32_t)nl1 : 256u + (uint32_t)ni1;
-            nl = nl1 + (b_leaf ? 1 : 0);
-            ni = ni1 + (b_leaf ? 0 : 1);
-            iw[made] = wa + wb;
-            L.children[made] = ida | (idb << 16);
+    int nl = 0, ni = 0, made = 0;
+    while (made < n - 1) {  // a round makes at least one node
+        const uint32_t lw = L.weight[nl + lane], iv = iw[ni + lane];  // (nl and ni at most 256: both arrays have 320 entries)
+        // the two lightest nodes: two leaves, one of each, or two internal nodes
+        auto add = [](uint32_t a, uint32_t b) { const uint32_t c = a + b; return c < a ? kInf : c; };
+        const uint32_t l0 = (uint32_t)__builtin_amdgcn_readlane((int)lw, 0), l1 = (uint32_t)__builtin_amdgcn_readlane((int)lw, 1);
+        const uint32_t i0 = (uint32_t)__builtin_amdgcn_readlane((int)iv, 0), i1 = (uint32_t)__builtin_amdgcn_readlane((int)iv, 1);
+        const uint32_t s0 = add(l0, l1), s1 = add(l0, i0), s2 = add(i0, i1);
+        const uint32_t t01 = s0 < s1 ? s0 : s1, t = t01 < s2 ? t01 : s2;
+        const int wait = made - ni;
+        // Places of internal nodes among the first 62 of the order (a place past them sets bit 63, which nobody looks
+        // at): four nodes per turn, their chains side by side.  Past the queue's end the weight is infinite, the place too.
+        unsigned long long places = 0;
+        int last = 0;
+        for (int k = 0; k < wait && last < 62; k += 4) {
+            int at[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)iv, k + u);
+                at[u] = k + u + __popcll(__ballot(lw <= w));  // (leaves not heavier than an internal node: at most t)
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++) places |= 1ull << (at[u] < 63 ? at[u] : 63);
+            last = at[3];
         }
+        const int all = __popcll(__ballot(lw <= t && nl + lane < n)) + wait;
+        const int count = all < 62 ? all & ~1 : 62;
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(places >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)places, 0u));
+        const bool internal = (places >> lane) & 1ull;
+        const uint32_t at = internal ? (uint32_t)ni + before : (uint32_t)(nl + lane) - before;
+        const uint32_t up = (uint32_t)made + ((uint32_t)lane >> 1);
+        if (lane < count) {
+            const uint32_t w = (internal ? iw : L.weight)[at];
+            if (internal) L.node[at] = up | (1u << 16);
+            else L.leaf_parent[at] = (uint16_t)up;
+            const uint32_t sum = w + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xf, 0xf, false);  // lane ^ 1
+            if (!(lane & 1)) iw[up] = sum;
+        }
+        wave_sync();
+        const int used = __popcll(places & ((1ull << count) - 1ull));
+        ni += used;
+        nl += count - used;
+        made += count >> 1;
     }
-    wave_sync();
 }
 
 // The same loop for at most 64 used symbols (one register per queue), written out by hand: the compiler's
@@ -187,26 +216,46 @@ __device__ __forceinline__ void sum_partials(TableLds& L, const uint32_t* __rest
     __syncthreads();
 }
 
-// Position of every used symbol in (count, symbol) order, into L.rank (zero on entry): the comparisons are shared
-// out over all wavefronts of the workgroup, wavefront w taking the w-th slice of the symbols to compare against.
+// Position of every used symbol in (count, symbol) order, into L.rank (zero on entry).  A wavefront takes one block of
+// 64 symbols (a symbol per lane) and one slice of the symbols to compare against, read four at a time as broadcasts:
+// symbols of a block before the lane's own count when they are not larger, of a block behind it when they are smaller,
+// and only inside the own block does the order of the symbols need a test per comparison.  Unused symbols compare as
+// the smallest of all and are taken off at the end.  256 symbols, 256 threads: 12.1 us with a test of everything in
+// every comparison, 4.3 us this way (issue-bound: two instructions per comparison).
 // All THREADS threads call it, after sum_partials; ends with a barrier.
 template <int THREADS>
 __device__ __forceinline__ void rank_symbols(TableLds& L, int bits) {
     constexpr int NW = THREADS / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int K = 1 << bits;
-    const int per = (K + NW - 1) / NW;
-    const int t0 = wave * per, t1 = (t0 + per < K) ? t0 + per : K;
-    for (int s = lane; s < K; s += 64) {
-        const uint32_t cnt = L.h[s];
-        uint32_t r = 0;
-#pragma unroll 16  // the reads of many steps in flight together: a step is one LDS round trip otherwise
-        for (int t = t0; t < t1; t++) {
-            const uint32_t o = L.h[t];  // same address in all lanes: a broadcast
-            r += (o != 0 && (o < cnt || (o == cnt && t < s))) ? 1u : 0u;
+    const int nb = (K + 63) >> 6, slices = NW / nb;  // (K at most 256, so at most as many blocks as wavefronts)
+    const int blk = wave % nb, slice = wave / nb;
+    const int s = 64 * blk + lane;
+    const int quads = K / 4, per = (quads + slices - 1) / slices;
+    const int q0 = slice * per, q1 = (q0 + per < quads) ? q0 + per : quads;
+    const uint32_t cnt = s < K ? L.h[s] : 0u;
+    const uint4* h4 = reinterpret_cast<const uint4*>(L.h);
+    uint32_t r = 0;
+    auto count = [&](int a, int b, auto less) {
+#pragma unroll 8  // the reads of many steps in flight together: a step is one LDS round trip otherwise
+        for (int q = a; q < b; q++) {
+            const uint4 o = h4[q];
+            r += (less(o.x, 4 * q) ? 1u : 0u) + (less(o.y, 4 * q + 1) ? 1u : 0u);
+            r += (less(o.z, 4 * q + 2) ? 1u : 0u) + (less(o.w, 4 * q + 3) ? 1u : 0u);
         }
-        if (r && cnt) atomicAdd(&L.rank[s], r);
+    };
+    auto within = [&](int q) { return q < q0 ? q0 : (q > q1 ? q1 : q); };
+    const int own0 = within(16 * blk), own1 = within(16 * blk + 16);
+    count(q0, own0, [&](uint32_t o, int) { return o <= cnt; });
+    count(own0, own1, [&](uint32_t o, int t) { return o < cnt || (o == cnt && t < s); });
+    count(own1, q1, [&](uint32_t o, int) { return o < cnt; });
+    if (slice == 0) {
+        uint32_t unused = 0;
+        for (int j = 0; j < nb; j++) unused += (uint32_t)__popcll(__ballot(64 * j + lane < K && L.h[64 * j + lane] == 0u));
+        r -= unused;  // (the sum over the slices is what counts: it may pass through negative values)
     }
+    if (r && cnt) atomicAdd(&L.rank[s], r);
     __syncthreads();
 }
 
@@ -220,34 +269,41 @@ struct TableOut {
 // Canonical codes from code lengths (len[j] of symbol 64 j + lane, 0 = unused; max_len the longest, the same in
 // every lane): codes of one length are numbered in symbol order, shorter codes first.  One wavefront; entry[] (256
 // words, LDS or global) is written whole.
-// scratch64: 64 words of LDS the wavefront may use (or NULL).
+// scratch: 64 NVS words of LDS the wavefront may use (or NULL).
 template <int NVS>
 __device__ __forceinline__ void canonical_entries(const uint32_t (&len)[NVS], int lane, uint32_t max_len,
-                                                  unsigned long long* entry_out, uint32_t* scratch64 = nullptr) {
+                                                  unsigned long long* entry_out, uint32_t* scratch = nullptr) {
     uint32_t before[NVS];
 #pragma unroll
     for (int j = 0; j < NVS; j++) before[j] = 0;
     // lane q ends up with the number of codes of length q
     uint32_t my_count = 0;
-    if (NVS == 1 && scratch64) {
-        // One symbol per lane: the lanes of equal length found with six ballots (one per bit of the length) instead
-        // of a loop over the lengths; the first lane of every length hands the group's size to the lane whose
-        // index is that length.
-        unsigned long long same = ~0ull;
+    if (scratch) {
+        // The lanes of equal length found with six ballots (one per bit of the length) instead of a loop over the
+        // lengths; the first lane of every length leaves the group's size in the scratch row of its block of 64
+        // symbols, and the rows before give the place of the block's codes among those of their length.
+        // (Lengths are at most kMaxLen < 64.)
 #pragma unroll
-        for (int bit = 0; bit < 6; bit++) {
-            const unsigned long long m = __ballot((len[0] >> bit) & 1u);
-            same &= ((len[0] >> bit) & 1u) ? m : ~m;
+        for (int j = 0; j < NVS; j++) scratch[64 * j + lane] = 0u;
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < NVS; j++) {
+            unsigned long long same = ~0ull;
+#pragma unroll
+            for (int bit = 0; bit < 6; bit++) {
+                const unsigned long long m = __ballot((len[j] >> bit) & 1u);
+                same &= ((len[j] >> bit) & 1u) ? m : ~m;
+            }
+            before[j] = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+            if (len[j] && before[j] == 0) scratch[64 * j + (int)len[j]] = (uint32_t)__popcll(same);
         }
-        before[0] = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-        const uint32_t group = (uint32_t)__popcll(same);
-        // (lengths are at most kMaxLen < 64: the lane that holds a length's count exists)
-        scratch64[lane] = 0u;
         wave_sync();
-        if (len[0] && before[0] == 0) scratch64[len[0]] = group;
-        wave_sync();
-        const uint32_t cnt_here = scratch64[lane];
-        my_count = cnt_here;
+#pragma unroll
+        for (int j = 0; j < NVS; j++) {
+#pragma unroll
+            for (int q = 0; q < j; q++) before[j] += scratch[64 * q + (int)len[j]];
+            my_count += scratch[64 * j + lane];
+        }
     } else {
         for (uint32_t q = 1; q <= max_len; q++) {
             uint32_t total = 0;
@@ -301,44 +357,46 @@ __device__ __forceinline__ void table_from_hist(TableLds& L, int lane, int K, Ta
     n = __builtin_amdgcn_readfirstlane(n);
     wave_sync();
     if (n >= 2) {
-        if (n <= 64) huffman_merge_small(L, lane, n);
-        else huffman_merge_serial(L, lane, n);
-        wave_sync();
-        const int root = n - 2;
-        for (int m = lane; m < n - 1; m += 64) {
-            const uint32_t c = L.children[m];
-            const uint32_t a = c & 0xffffu, b = c >> 16;
-            if (a < 256u) L.leaf_parent[a] = (uint16_t)m; else L.int_parent[a - 256u] = (uint16_t)m;
-            if (b < 256u) L.leaf_parent[b] = (uint16_t)m; else L.int_parent[b - 256u] = (uint16_t)m;
-            L.depth[m] = (m == root) ? 0 : 1;
+        const uint32_t root = (uint32_t)n - 2u;
+        if (n <= 64) {
+            huffman_merge_small(L, lane, n);
+            wave_sync();
+            if (lane < n - 1) {
+                const uint32_t c = L.children[lane];
+                const uint32_t a = c & 0xffffu, b = c >> 16, up = (uint32_t)lane | (1u << 16);
+                if (a < 256u) L.leaf_parent[a] = (uint16_t)lane; else L.node[a - 256u] = up;
+                if (b < 256u) L.leaf_parent[b] = (uint16_t)lane; else L.node[b - 256u] = up;
+            }
+        } else {
+            huffman_merge_rounds(L, lane, n);
         }
-        if (lane == 0) L.int_parent[root] = (uint16_t)root;
+        if (lane == 0) L.node[root] = root;
         wave_sync();
-        // depth of every internal node: distance to its 2^r-th ancestor, doubled until all reach the root
-        for (int r = 1; r < n - 1; r <<= 1) {
-            uint32_t d[4], pp[4];
+        // depth of every internal node: distance to an ancestor, doubled until that is the root for all of them
+        {
+            constexpr int NM = NVS == 1 ? 1 : 4;  // (an alphabet of up to 64 symbols makes up to 63 nodes)
+            uint32_t v[NM];
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int m = 64 * j + lane;
-                if (m < n - 1) {
-                    const uint32_t par = L.int_parent[m];
-                    d[j] = (uint32_t)L.depth[m] + (uint32_t)L.depth[par];
-                    pp[j] = L.int_parent[par];
-                }
-            }
-            wave_sync();
+            for (int j = 0; j < NM; j++) v[j] = 64 * j + lane < n - 1 ? L.node[64 * j + lane] : root;
+            for (;;) {
+                bool up = false;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int m = 64 * j + lane;
-                if (m < n - 1) {
-                    L.depth[m] = (uint16_t)d[j];
-                    L.int_parent[m] = (uint16_t)pp[j];
+                for (int j = 0; j < NM; j++) up |= (v[j] & 0xffffu) != root;
+                if (!__any(up)) break;
+                uint32_t w[NM];
+#pragma unroll
+                for (int j = 0; j < NM; j++) w[j] = L.node[v[j] & 0xffffu];
+                wave_sync();
+#pragma unroll
+                for (int j = 0; j < NM; j++) {
+                    v[j] = (v[j] & 0xffff0000u) + w[j];  // (distances add up, the ancestor's ancestor takes its place)
+                    if (64 * j + lane < n - 1) L.node[64 * j + lane] = v[j];
                 }
+                wave_sync();
             }
-            wave_sync();
         }
         for (int i = lane; i < n; i += 64) {
-            uint32_t l = (uint32_t)L.depth[L.leaf_parent[i]] + 1u;
+            uint32_t l = (L.node[L.leaf_parent[i]] >> 16) + 1u;
             // more than kMaxLen is unreachable for V < 2^32 (depth d needs a total count >= Fibonacci(d+2))
             L.len_sorted[i] = (uint8_t)(l > (uint32_t)kMaxLen ? (uint32_t)kMaxLen : l);
         }
