@@ -39,7 +39,7 @@ SHAPES = [("resnet18_n256_c64_56", 6), ("resnet18_n256_c128_28", 6), ("resnet18_
 
 # rocprofv3 kernel names -> the names fmtc_profile_* reports
 KERNEL_FAMILIES = [("k_project_quantize", "k_project_quantize"), ("k_huffman_table", "k_huffman_table"),
-                   ("k_chunk_bits", "k_chunk_bits"), ("k_pack", "k_pack"), ("k_decode", "k_decode"),
+                   ("k_pack", "k_pack"), ("k_decode", "k_decode"),
                    ("k_quantize_u8", "k_quantize_u8"), ("k_int8_tiles", "k_quantize_u8"), ("k_copy", "k_copy")]
 
 
@@ -228,15 +228,12 @@ class Bench:
         prof = self.kernel_times(step, steps)
         flops = 2.0 * C * V  # one direction of the dense C x C projection, as the method defines it
         stream_bytes = float(info["stream_bytes"])
-        n_chunks = float(info["n_chunks"])
         # Per launch (one launch = the whole tensor): algorithmic HBM bytes, and the matrix flops the kernel issues
         # for the method's 2*C*V (the fp32 contraction runs as 3 (forward) or 2 (inverse) f16 products).  A kernel is
         # held against the roof that takes longer at peak: bytes / 8 TB/s or issued flops / 2.5 PFLOP/s.
         alg = {
             # projection: reads the activations once, writes one symbol byte per value
             "k_project_quantize": (4.0 * V + V, 3.0 * flops),
-            # code bits of every chunk: reads the symbols, writes 4 bytes per chunk
-            "k_chunk_bits": (V + 4.0 * n_chunks, 0.0),
             # coder: reads the symbols once, writes the container
             "k_pack": (V + stream_bytes, 0.0),
             # decoder: reads the container, writes the activations

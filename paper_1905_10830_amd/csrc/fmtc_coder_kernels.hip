@@ -7,10 +7,12 @@
 //   k_huffman_table  one workgroup: sums the partial histograms and builds the code
 //                    (large tensors; small ones build it inside the pack kernel, every
 //                    workgroup for itself, which saves a launch on the critical path);
-//   k_pack           one wavefront per chunk, one lane per run of 64 symbols: run sizes,
-//                    the chunk's place in the payload (a running sum over the chunk
-//                    groups handed from workgroup to workgroup), then the code bits.
+//   k_pack           one wavefront per chunk: run sizes, the chunk's place in the payload
+//                    (a running sum over the chunk groups handed from workgroup to
+//                    workgroup), then the code bits;
+//   k_pack_stream    the same for large tensors, the groups claimed in turn.
 #include <atomic>
+#include <type_traits>
 
 #include "fmtc_device.h"
 #include "fmtc_internal.h"
@@ -170,9 +172,11 @@ __device__ __forceinline__ void huffman_merge_small(TableLds& L, int lane, int n
 }
 
 // Sum of the partial histograms into L.h.  All THREADS threads of the workgroup call it; ends with a barrier.
+// Workgroups that do this side by side start at rows of their own (`who`): reading the same rows at the same time they
+// would queue up at one part of the cache after the other.
 template <int THREADS>
 __device__ __forceinline__ void sum_partials(TableLds& L, const uint32_t* __restrict__ hist_parts, int n_parts,
-                                             int bits) {
+                                             int bits, uint32_t who = 0u) {
     const int tid = threadIdx.x;
     const int K = 1 << bits;
     if (tid < 256) {
@@ -183,12 +187,14 @@ __device__ __forceinline__ void sum_partials(TableLds& L, const uint32_t* __rest
     // a thread owns four neighbouring bins of every rstep-th row; sixteen independent 16-byte loads in flight
     const int tpr = K / 4, col = tid % tpr, row0 = tid / tpr, rstep = THREADS / tpr;
     const uint4* rows = reinterpret_cast<const uint4*>(hist_parts);
+    const int turn_by = (int)((who * 37u) % (uint32_t)n_parts);
+    auto row = [&](int q) { q += turn_by; return (size_t)(q < n_parts ? q : q - n_parts) * tpr + col; };
     uint4 acc = make_uint4(0, 0, 0, 0);
     int q = row0;
     for (; q + 15 * rstep < n_parts; q += 16 * rstep) {
         uint4 v[16];
 #pragma unroll
-        for (int j = 0; j < 16; j++) v[j] = rows[(size_t)(q + j * rstep) * tpr + col];
+        for (int j = 0; j < 16; j++) v[j] = rows[row(q + j * rstep)];
 #pragma unroll
         for (int j = 0; j < 16; j++) {
             acc.x += v[j].x; acc.y += v[j].y; acc.z += v[j].z; acc.w += v[j].w;
@@ -198,16 +204,11 @@ __device__ __forceinline__ void sum_partials(TableLds& L, const uint32_t* __rest
         uint4 v[15];
 #pragma unroll
         for (int j = 0; j < 15; j++)
-            v[j] = (q + j * rstep < n_parts) ? rows[(size_t)(q + j * rstep) * tpr + col] : make_uint4(0, 0, 0, 0);
+            v[j] = (q + j * rstep < n_parts) ? rows[row(q + j * rstep)] : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < 15; j++) {
             acc.x += v[j].x; acc.y += v[j].y; acc.z += v[j].z; acc.w += v[j].w;
         }
-        q = n_parts;
-    }
-    for (; q < n_parts; q += rstep) {
-        const uint4 v = rows[(size_t)q * tpr + col];
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
     if (acc.x) atomicAdd(&L.h[4 * col], acc.x);
     if (acc.y) atomicAdd(&L.h[4 * col + 1], acc.y);
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     // groups than the device holds workgroups of it, and workgroup g takes group g: within a part of the chip
     // workgroups start in index order, so the lowest unfinished group is either running or next in line for a
     // place that only other kernels' workgroups (which finish) or this kernel's finished ones can hold.  Larger
-    // tensors take the kernels below (k_chunk_bits, k_chunk_scan, k_pack_at), which never wait for each other.
+    // tensors take the kernel below, whose workgroups claim their groups.
     uint32_t w[16];
     const uint32_t group = blockIdx.x;  // the grid never has more workgroups than groups
     load_chunk_symbols(p, group * kPackWaves + (uint32_t)wave, lane, aligned4, w);  // in flight while the table is made
@@ -564,215 +565,574 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 }
 
 // ---------------------------------------------------------------------------
-// Large tensors (more chunk groups than the device holds pack workgroups): three kernels that
-// never wait for one another inside a launch, so nothing depends on which workgroups are
-// resident.  k_chunk_bits sums the code lengths of every chunk; k_chunk_scan (one workgroup)
-// turns them into the container's chunk offsets and writes the header; k_pack_at packs every
-// chunk at its known place.  The symbols are read twice (they were just written and mostly come
-// from the memory-side cache); the table is read from memory (k_huffman_table or a fixed one).
+// Large tensors (more chunk groups than the device holds pack workgroups): one pass over the symbols.
+// One workgroup of 16 wavefronts per compute unit: 15 pack, the 16th finds out where the chunks go.  A turn is a group of
+// 15 chunks; the packers take its chunks one by one (a fixed chunk per wavefront and turn left the wavefronts of a SIMD
+// up to three turns apart, and a turn waits for its last one).  Groups are claimed from a counter, so a group's predecessors have all been claimed by workgroups
+// that run; a group's size is published when its images are built, and its place is the sum of the sizes before it
+// (added up by one wavefront of the device).
+// A place is known 4 to 5 us after the group is packed, longer than a turn: a packer keeps up to three images waiting
+// in its part of the LDS (one or two where the code is longer, see images_for) and goes on with its next chunk, and the
+// 16th wavefront publishes a size as soon as it is there, between polls for the places of earlier groups.  The wavefronts of a workgroup meet in LDS counters and not in
+// barriers.  A size is published without waiting for any later group, so whatever shares the device the lowest
+// unpublished group can always go on; the wait for another workgroup is bounded all the same and ends in an invalid
+// stream.
+// Every workgroup builds the code table for itself (the first group's ticket and symbols arrive meanwhile).
+// (Before: a table kernel, a size pass over all chunks, a one-workgroup scan and a packing pass at known places.)
+//
+// Packing was bound by vector instructions and LDS operations per symbol (53 and 6 per 256 symbols).  A lane takes
+// eight neighbouring symbols per step, and up to 6 bits the table holds the joined code words of symbol pairs: four
+// lookups, one prefix sum over the lanes and two or three ORs into the image per 512 symbols.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_chunk_bits(PackParams p) {
-    __shared__ uint8_t s_len[256];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t stride = gridDim.x * kPackWaves;
-    uint32_t ch = blockIdx.x * kPackWaves + (uint32_t)wave;
-    // (lanes with four neighbouring symbols each, as in the pack kernel: 16-byte loads per lane were tried for this
-    // sum, where the order does not matter, and took 21 us against 12 us at 51 M symbols)
-    const bool aligned4 = (p.chunk_syms & 3u) == 0;
-    uint32_t w[16];
-    if (ch < p.n_chunks) load_chunk_symbols(p, ch, lane, aligned4, w);  // in flight while the lengths arrive
-    s_len[tid] = (uint8_t)(p.enc_table[tid] >> 56);
-    __syncthreads();
-    while (ch < p.n_chunks) {  // wavefront-uniform
-        const uint32_t clen = chunk_len_of(p, ch);
-        const uint32_t next = ch + stride;
-        uint32_t wn[16];
-        if (next < p.n_chunks) load_chunk_symbols(p, next, lane, aligned4, wn);
-        uint32_t bits = 0;
-        if (clen == 4096u) {
+constexpr int kStreamWaves = 15;        // packing wavefronts per workgroup = chunks per group
+constexpr uint32_t kStreamRoom = 2064;  // words a packer has for its images, each with 4 spare ones (see PackShared)
+constexpr uint32_t kSlots = 16;         // what a turn leaves in LDS is kept by turn modulo kSlots (see below)
+constexpr uint32_t kShortCode = 26;     // a table entry holds up to 26 code bits below 6 bits of length ...
+constexpr uint32_t kNoCode = 63u << kShortCode;  // ... or says that the code word is longer: any eight symbols with
+                                        // such an entry come to more than 64 bits
+constexpr unsigned long long kKnown = 1ull << 62;  // marks a group's published size, and its place
+
+struct StreamShared {
+    unsigned long long tab[256];                                   // bit-reversed code | length << 56
+    uint32_t image[kStreamWaves][kStreamRoom];
+    uint16_t runs[kStreamWaves][64];
+    uint32_t words[kSlots][16], bits[kSlots][16];                  // payload words and code bits of the chunks of a turn
+    uint32_t done[kSlots];                                         // packers that have left theirs (counted over all turns)
+    unsigned long long place[kSlots];                              // first payload word of the group
+    uint32_t ticket[kSlots];                                       // the group
+    uint32_t placed, drawn;                                        // turns whose place / whose group is known
+    uint32_t dealt;                                                // chunks taken by the packers, over all turns
+    unsigned long long payload_bits;
+    uint32_t codes[1];                                             // [4096] (pairs) or [256]: code | length << 26
+};
+// A word of LDS that another wavefront of the workgroup advances.
+__device__ __forceinline__ uint32_t peek_lds(const uint32_t* q) {
+    return __hip_atomic_load(q, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void post_lds(uint32_t* q, uint32_t v) {
+    __hip_atomic_store(q, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The symbols of a chunk: register q of lane l holds symbols 512q + 8l .. + 7 (zero past the chunk's end).
+__device__ __forceinline__ void load_chunk_octets(const PackParams& p, uint32_t ch, int lane, uint2 (&w)[8]) {
+    const uint32_t clen = chunk_len_of(p, ch);
+    const uint8_t* src = p.syms + (uint64_t)ch * p.chunk_syms;
+    if ((p.chunk_syms & 7u) == 0) {  // every chunk starts on an 8-byte boundary of the symbols
 #pragma unroll
-            for (int q = 0; q < 16; q++)
+        for (int q = 0; q < 8; q++) {
+            const uint32_t o = 512u * q + 8u * (uint32_t)lane;
+            w[q] = (o + 8u <= clen) ? *reinterpret_cast<const uint2*>(src + o) : make_uint2(0u, 0u);
+        }
+        if ((clen & 7u) == 0) return;
+    } else {
 #pragma unroll
-                for (int i = 0; i < 4; i++) bits += s_len[(w[q] >> (8 * i)) & 255u];
-        } else if (clen >= 3840u) {
-            // (whole chunks of channel counts that do not divide 4096 -- 4032 symbols at 144 channels, 3840 at 960:
-            // fifteen whole registers in one straight run, the tests for the last one only)
+        for (int q = 0; q < 8; q++) w[q] = make_uint2(0u, 0u);
+    }
+    // pieces that are not whole, or not aligned: byte by byte
+    const bool whole = (p.chunk_syms & 7u) == 0;
 #pragma unroll
-            for (int q = 0; q < 15; q++)
+    for (int q = 0; q < 8; q++) {
+        const uint32_t o = 512u * q + 8u * (uint32_t)lane;
+        if (o < clen && (!whole || o + 8u > clen)) {
+            uint32_t b[2] = {0u, 0u};
 #pragma unroll
-                for (int i = 0; i < 4; i++) bits += s_len[(w[q] >> (8 * i)) & 255u];
+            for (int i = 0; i < 8; i++)
+                if (o + i < clen) b[i >> 2] |= (uint32_t)src[o + i] << (8 * (i & 3));
+            w[q] = make_uint2(b[0], b[1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one register's loads at a time: this path is rare
+    }
+}
+
+// How many images a packer's room is divided into, and their words: as many as hold a chunk of the average size and a
+// third more.  (A larger chunk is finished window by window from its symbols, at several times the cost.)
+struct StreamImages {
+    uint32_t count, words;
+};
+__device__ __forceinline__ StreamImages images_for(unsigned long long payload_bits, uint32_t n_chunks) {
+    const unsigned long long need = payload_bits / 24u;  // words, and a third more
+    if (need <= 512ull * n_chunks) return {4u, 512u};
+    if (need <= 684ull * n_chunks) return {3u, 684u};
+    return {2u, 1024u};
+}
+
+// ORs the up to 64 bits of `c` into the image at bit `pos` of the chunk; what lies past the image's `words` goes to its
+// spare words.
+__device__ __forceinline__ void place_octet(unsigned long long c, uint32_t len, uint32_t pos, uint32_t* img, uint32_t words) {
+    const uint32_t at = (pos < words * 32u ? pos : words * 32u) >> 5, sh = pos & 31u;
+    const unsigned long long t0 = c << sh;
+    atomicOr(&img[at], (uint32_t)t0);
+    atomicOr(&img[at + 1u], (uint32_t)(t0 >> 32));
+    if (__any(len + sh > 64u)) atomicOr(&img[at + 2u], sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
+}
+
+// The code words of a lane's eight symbols.
+struct Octet {
+    unsigned long long lo, hi;  // of the first and of the last four
+    uint32_t l_lo, len;         // bits of the first four; of all
+};
+
+// PAIRS: `codes` holds the joined code words of symbol pairs s0 | s1 << 6; else of single symbols.
+template <bool PAIRS>
+__device__ __forceinline__ Octet look_up(uint32_t x, uint32_t y, bool past_end, const uint32_t* codes) {
+    const uint8_t* codes8 = reinterpret_cast<const uint8_t*>(codes);
+    constexpr uint32_t kCode = (1u << kShortCode) - 1u;
+    Octet o;
+    if constexpr (PAIRS) {
+        auto entry = [&](uint32_t v) { return *reinterpret_cast<const uint32_t*>(codes8 + (((v << 2) & 0xfcu) | (v & 0x3f00u))); };
+        uint32_t e0 = entry(x), e1 = entry(x >> 16), e2 = entry(y), e3 = entry(y >> 16);
+        if (past_end) e0 = e1 = e2 = e3 = 0u;
+        const uint32_t l0 = e0 >> kShortCode, l1 = e1 >> kShortCode, l2 = e2 >> kShortCode, l3 = e3 >> kShortCode;
+        o.lo = (unsigned long long)(e0 & kCode) | ((unsigned long long)(e1 & kCode) << l0);
+        o.hi = (unsigned long long)(e2 & kCode) | ((unsigned long long)(e3 & kCode) << l2);
+        o.l_lo = l0 + l1;
+        o.len = o.l_lo + l2 + l3;
+    } else {
+        auto entry = [&](uint32_t v4) { return *reinterpret_cast<const uint32_t*>(codes8 + (v4 & 0x3fcu)); };
+        uint32_t e[8] = {entry(x << 2), entry(x >> 6), entry(x >> 14), entry(x >> 22),
+                         entry(y << 2), entry(y >> 6), entry(y >> 14), entry(y >> 22)};
+        uint32_t l[8];
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                if (3840u + 4u * (uint32_t)lane + i < clen) bits += s_len[(w[15] >> (8 * i)) & 255u];
+        for (int i = 0; i < 8; i++) {
+            if (past_end) e[i] = 0u;
+            l[i] = e[i] >> kShortCode;
+            e[i] &= kCode;
+        }
+        const unsigned long long p0 = (unsigned long long)e[0] | ((unsigned long long)e[1] << l[0]);
+        const unsigned long long p1 = (unsigned long long)e[2] | ((unsigned long long)e[3] << l[2]);
+        const unsigned long long p2 = (unsigned long long)e[4] | ((unsigned long long)e[5] << l[4]);
+        const unsigned long long p3 = (unsigned long long)e[6] | ((unsigned long long)e[7] << l[6]);
+        const uint32_t l01 = l[0] + l[1], l45 = l[4] + l[5];
+        o.lo = p0 | (p1 << (l01 & 63u));
+        o.hi = p2 | (p3 << (l45 & 63u));
+        o.l_lo = l01 + l[2] + l[3];
+        o.len = o.l_lo + l45 + l[6] + l[7];
+    }
+    return o;
+}
+
+// An octet that 64 bits do not hold in at least one lane: its two halves one after the other, or (a code word that does
+// not fit its entry, halves of more than 64 bits, a chunk that ends inside a lane's eight symbols) every symbol by itself.
+// octet_length: the lane's bits (`len` where no entry is without its code word), with the top bit set where it has to be
+// symbol by symbol.
+__device__ __forceinline__ uint32_t octet_length(uint32_t x, uint32_t y, uint32_t first, uint32_t l_lo, uint32_t len,
+                                                 uint32_t clen, const unsigned long long* tab) {
+    // (an entry without its code word says 63 bits, and any other symbol at least one)
+    const bool part = first < clen && first + 8u > clen;
+    if (!__any(l_lo > 63u || len - l_lo > 63u || part)) return len;
+    uint32_t n = 0u;
+#pragma unroll 1
+    for (uint32_t i = 0; i < 8u; i++) {
+        const uint32_t sym = ((i < 4u ? x : y) >> (8u * (i & 3u))) & 255u;
+        n += first + i < clen ? (uint32_t)(tab[sym] >> 56) : 0u;
+    }
+    return n | 0x80000000u;
+}
+__device__ __forceinline__ void place_long_octet(uint32_t x, uint32_t y, uint32_t first, unsigned long long lo,
+                                                 unsigned long long hi, uint32_t l_lo, uint32_t len, bool single,
+                                                 uint32_t clen, const unsigned long long* tab, uint32_t pos,
+                                                 uint32_t* img, uint32_t words) {
+    if (!single) {
+        place_octet(lo, l_lo, pos, img, words);
+        place_octet(hi, len - l_lo, pos + l_lo, img, words);
+        return;
+    }
+#pragma unroll 1
+    for (uint32_t i = 0; i < 8u; i++) {
+        const uint32_t sym = ((i < 4u ? x : y) >> (8u * (i & 3u))) & 255u;
+        const unsigned long long e = first + i < clen ? tab[sym] : 0ull;
+        place_octet(e & 0x00ffffffffffffffull, (uint32_t)(e >> 56), pos, img, words);
+        pos += (uint32_t)(e >> 56);
+    }
+}
+
+// One chunk (`clen` symbols in w, see load_chunk_octets) into the first `words` words of its image.  Returns the chunk's
+// code bits and leaves the bit counts of its runs of 64 symbols (eight lanes; 64 of them, zeros past the end) in run_bits.
+// Two octets per lane and turn, 512 symbols apart: their chains run side by side, and one prefix sum over the lanes
+// serves both (16 bits each: a chunk has at most 64 x 8 x 48 bits in 512 symbols).
+template <bool PAIRS>
+__device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t clen, const unsigned long long* tab,
+                                                const uint32_t* codes, uint32_t* img, uint32_t words, int lane,
+                                                uint16_t* run_bits) {
+    uint32_t base = 0;
+    auto step = [&](uint32_t q, uint32_t x0, uint32_t y0, uint32_t x1, uint32_t y1, auto some_c) __attribute__((always_inline)) -> uint32_t {
+        constexpr bool some = decltype(some_c)::value;
+        const uint32_t f0 = 512u * q + 8u * (uint32_t)lane, f1 = f0 + 512u;
+        const Octet a = look_up<PAIRS>(x0, y0, some && f0 >= clen, codes);
+        const Octet b = look_up<PAIRS>(x1, y1, some && f1 >= clen, codes);
+        uint32_t len_a = a.len, len_b = b.len;
+        const uint32_t longer = a.len > b.len ? a.len : b.len;
+        const bool plain = !__any(longer > 64u) && !(some && (clen & 7u) != 0);
+        bool single_a = false, single_b = false;
+        if (__builtin_expect(!plain, 0)) {
+            len_a = octet_length(x0, y0, f0, a.l_lo, a.len, clen, tab);
+            len_b = octet_length(x1, y1, f1, b.l_lo, b.len, clen, tab);
+            single_a = __any(len_a >> 31) != 0;
+            single_b = __any(len_b >> 31) != 0;
+            len_a &= 0x7fffffffu;
+            len_b &= 0x7fffffffu;
+        }
+        // inclusive prefix sum over the lanes (see wave_inclusive_scan_rows; lanes 7 and 15 of a row of 16 hold
+        // their eight lanes' sum after three steps: a run of 64 symbols)
+        uint32_t v = len_a | (len_b << 16);
+        v = dpp_add<0x111, 0xf>(v);
+        v = dpp_add<0x112, 0xf>(v);
+        v = dpp_add<0x114, 0xf>(v);
+        const uint32_t run = v;
+        v = dpp_add<0x118, 0xf>(v);
+        v = dpp_add<0x142, 0xa>(v);
+        v = dpp_add<0x143, 0xc>(v);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+        const uint32_t pos_a = base + (v & 0xffffu) - len_a, pos_b = base + (total & 0xffffu) + (v >> 16) - len_b;
+        base += (total & 0xffffu) + (total >> 16);
+        if (__builtin_expect(plain, 1)) {
+            const unsigned long long ca = a.lo | (a.hi << (a.l_lo & 63u));  // (64 bits in `lo` leave none in `hi`)
+            const unsigned long long cb = b.lo | (b.hi << (b.l_lo & 63u));
+            const uint32_t limit = words * 32u;
+            const uint32_t at_a = (pos_a < limit ? pos_a : limit) >> 5, at_b = (pos_b < limit ? pos_b : limit) >> 5;
+            const uint32_t sh_a = pos_a & 31u, sh_b = pos_b & 31u;
+            const unsigned long long ta = ca << sh_a, tb = cb << sh_b;
+            atomicOr(&img[at_a], (uint32_t)ta);
+            atomicOr(&img[at_a + 1u], (uint32_t)(ta >> 32));
+            atomicOr(&img[at_b], (uint32_t)tb);
+            atomicOr(&img[at_b + 1u], (uint32_t)(tb >> 32));
+            const uint32_t reach_a = a.len + sh_a, reach_b = b.len + sh_b;
+            if (__any((reach_a > reach_b ? reach_a : reach_b) > 64u)) {
+                atomicOr(&img[at_a + 2u], sh_a ? (uint32_t)((ca >> 32) >> (32u - sh_a)) : 0u);
+                atomicOr(&img[at_b + 2u], sh_b ? (uint32_t)((cb >> 32) >> (32u - sh_b)) : 0u);
+            }
         } else {
-            // registers that lie inside the chunk whole need no per-symbol test
-#pragma unroll
-            for (int q = 0; q < 16; q++) {
-                if (256u * (q + 1) <= clen) {  // wavefront-uniform
-#pragma unroll
-                    for (int i = 0; i < 4; i++) bits += s_len[(w[q] >> (8 * i)) & 255u];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; i++)
-                        if (256u * q + 4u * (uint32_t)lane + i < clen) bits += s_len[(w[q] >> (8 * i)) & 255u];
-                }
-            }
+            place_long_octet(x0, y0, f0, a.lo, a.hi, a.l_lo, len_a, single_a, clen, tab, pos_a, img, words);
+            place_long_octet(x1, y1, f1, b.lo, b.hi, b.l_lo, len_b, single_b, clen, tab, pos_b, img, words);
         }
-        bits = wave_sum(bits);
-        if (lane == 0) p.chunk_bits[ch] = bits;
-        ch = next;
+        return run;
+    };
+    const uint32_t n_whole = clen >> 10;
+    uint32_t run[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int q = 0; q < 16; q++) w[q] = wn[q];
+    for (int q = 0; q < 4; q++)
+        if ((uint32_t)q < n_whole)  // wavefront-uniform
+            run[q] = step(2u * q, w[2 * q].x, w[2 * q].y, w[2 * q + 1].x, w[2 * q + 1].y, std::false_type{});
+    if (clen & 1023u) {
+        uint32_t x0 = w[0].x, y0 = w[0].y, x1 = w[1].x, y1 = w[1].y;
+#pragma unroll
+        for (int q = 1; q < 4; q++) {
+            x0 = (uint32_t)q == n_whole ? w[2 * q].x : x0;
+            y0 = (uint32_t)q == n_whole ? w[2 * q].y : y0;
+            x1 = (uint32_t)q == n_whole ? w[2 * q + 1].x : x1;
+            y1 = (uint32_t)q == n_whole ? w[2 * q + 1].y : y1;
+        }
+        const uint32_t last = step(2u * n_whole, x0, y0, x1, y1, std::true_type{});
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            if ((uint32_t)q == n_whole) run[q] = last;
+    }
+    if ((lane & 7) == 7) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            run_bits[16 * q + (lane >> 3)] = (uint16_t)run[q];
+            run_bits[16 * q + 8 + (lane >> 3)] = (uint16_t)(run[q] >> 16);
+        }
+    }
+    return base;
+}
+
+// A later window [win, win + words) of a chunk too large for its image, symbol by symbol from memory (rare).
+__device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, const unsigned long long* tab,
+                                            uint32_t* img, uint32_t words, uint32_t win, int lane) {
+    const uint32_t clen = chunk_len_of(p, ch);
+    const uint8_t* src = p.syms + (uint64_t)ch * p.chunk_syms;
+    uint32_t base = 0;
+#pragma unroll 1
+    for (uint32_t s0 = 0; s0 < clen; s0 += 64) {
+        const unsigned long long e = s0 + (uint32_t)lane < clen ? tab[src[s0 + lane]] : 0ull;
+        const uint32_t len = (uint32_t)(e >> 56);
+        uint32_t row, half;
+        const uint32_t incl = wave_inclusive_scan_rows(len, row, half), pos = base + incl - len;
+        const unsigned long long c = e & 0x00ffffffffffffffull;
+        const uint32_t sh = pos & 31u, rel = (pos >> 5) - win;
+        const unsigned long long t0 = c << sh;
+        const uint32_t t2 = sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u;
+        if (rel < words) atomicOr(&img[rel], (uint32_t)t0);
+        if (rel + 1u < words) atomicOr(&img[rel + 1u], (uint32_t)(t0 >> 32));
+        if (rel + 2u < words) atomicOr(&img[rel + 2u], t2);
+        base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
 }
 
-// One workgroup: chunk_off[i] = words of the chunks before chunk i (a chunk starts on a word), the header, the
-// stream size and the zero bytes of the alignment gaps.  The stream is marked invalid if it would outgrow the buffer.
-// Rounds of kScanTile chunks: a thread takes kScanPer neighbouring entries (16-byte loads, all in flight together;
-// the array's allocation is a multiple of 256 bytes, so a piece that starts inside it ends inside it), scans them in
-// registers, the threads' sums are scanned across the workgroup, and the offsets leave as 16-byte stores (the offset
-// table starts 320 bytes into the container, itself 16-byte aligned).
-constexpr int kScanThreads = 1024, kScanPer = 16, kScanTile = kScanThreads * kScanPer;
-__global__ __launch_bounds__(kScanThreads) void k_chunk_scan(PackParams p) {
-    __shared__ unsigned long long s_wave[2][kScanThreads / 64];
-    __shared__ unsigned long long s_bits[kScanThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t n = p.n_chunks;
-    uint32_t* chunk_off = reinterpret_cast<uint32_t*>(p.stream + kHeaderBytes + kLenTableBytes);
-    unsigned long long carry = 0, bits = 0;
-    int flip = 0;
-    for (uint32_t base = 0; base < n; base += kScanTile, flip ^= 1) {
-        const uint32_t i0 = base + (uint32_t)tid * kScanPer;
-        uint32_t v[kScanPer];
-#pragma unroll
-        for (int k = 0; k < kScanPer; k += 4) {
-            uint4 q = make_uint4(0u, 0u, 0u, 0u);
-            if (i0 + k < n) q = *reinterpret_cast<const uint4*>(p.chunk_bits + i0 + k);
-            v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
-        }
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < kScanPer; k++) {
-            if (i0 + k >= n) v[k] = 0u;  // past the last chunk: whatever the workspace holds there
-            bits += v[k];
-            v[k] = (v[k] + 31u) >> 5;
-            sum += v[k];
-        }
-        const unsigned long long incl = wave_inclusive_scan64(sum, lane);
-        if (lane == 63) s_wave[flip][wave] = incl;
-        __syncthreads();  // (the other buffer is what the round before used: no second barrier needed)
-        unsigned long long before = carry + incl - sum, total = 0;
-        for (int q = 0; q < kScanThreads / 64; q++) {
-            if (q < wave) before += s_wave[flip][q];
-            total += s_wave[flip][q];
-        }
-        uint32_t off[kScanPer];
-#pragma unroll
-        for (int k = 0; k < kScanPer; k++) {
-            off[k] = (uint32_t)before;
-            before += v[k];
-        }
-#pragma unroll
-        for (int k = 0; k < kScanPer; k += 4) {
-            if (i0 + k + 3 < n) {
-                *reinterpret_cast<uint4*>(chunk_off + i0 + k) = make_uint4(off[k], off[k + 1], off[k + 2], off[k + 3]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    if (i0 + k + j < n) chunk_off[i0 + k + j] = off[k + j];
-            }
-        }
-        carry += total;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) bits += __shfl_xor(bits, o, 64);
-    if (lane == 0) s_bits[wave] = bits;
-    __syncthreads();
-    if (tid == 0) {
-        const unsigned long long total_words = carry;
-        unsigned long long total_bits = 0;
-        for (int q = 0; q < kScanThreads / 64; q++) total_bits += s_bits[q];
-        chunk_off[n] = (uint32_t)total_words;
-        Header hdr = p.hdr;
-        hdr.payload_words = total_words;
-        hdr.payload_bits = total_bits;
-        if (total_words > p.cap_words || total_words > 0xffffffffull) hdr.magic = 0u;  // does not fit: not valid
-        *reinterpret_cast<Header*>(p.stream) = hdr;
-        if (p.out_bytes) *p.out_bytes = (uint64_t)p.off_payload + 4 * total_words;
-        // alignment gaps between the sections are part of the stream: keep them zero
-        for (size_t o = kHeaderBytes + kLenTableBytes + 4 * ((size_t)n + 1); o < p.off_sub_bits; o++) p.stream[o] = 0;
-        for (size_t o = p.off_sub_bits + 2 * (size_t)n * p.subs_per_chunk; o < p.off_payload; o++) p.stream[o] = 0;
-    }
-}
-
-// Packs every chunk at the place k_chunk_scan gave it.  One wavefront per chunk and turn, no barriers after the
-// table is in LDS, the next chunk's symbols in flight while this one is packed.  STATIC: the table is a fixed one
-// (its longest code comes with the parameters, and the block that holds chunk 0 writes the container's length
-// table); otherwise k_huffman_table has left both.
-template <bool STATIC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_pack_at(PackParams p) {
-    __shared__ PackShared S;
+// STATIC: the table is a fixed one, and the code bits of the tensor are added up on the way; otherwise every workgroup
+// builds the table from the partial histograms.
+template <bool STATIC, bool PAIRS>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_pack_stream(PackParams p) {
+    extern __shared__ __align__(16) uint8_t dyn_lds[];
+    StreamShared& S = *reinterpret_cast<StreamShared*>(dyn_lds);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool aligned4 = (p.chunk_syms & 3u) == 0;
-    uint32_t ch = blockIdx.x * kPackWaves + (uint32_t)wave;
-    uint32_t w[16];
-    if (ch < p.n_chunks) load_chunk_symbols(p, ch, lane, aligned4, w);
-    S.tab[tid] = p.enc_table[tid];
-    if (STATIC && blockIdx.x == 0) p.stream[kHeaderBytes + tid] = (uint8_t)(p.enc_table[tid] >> 56);
-    pack_clear_image(S, wave, lane);
-    __syncthreads();
-    const uint32_t max_len = STATIC ? p.static_max_len : p.ctrl->max_len;
-    uint32_t* img = S.stage[wave];
-    uint16_t* sub_bits = reinterpret_cast<uint16_t*>(p.stream + p.off_sub_bits);
-    const uint32_t* chunk_off = reinterpret_cast<const uint32_t*>(p.stream + kHeaderBytes + kLenTableBytes);
-    uint32_t* payload = reinterpret_cast<uint32_t*>(p.stream + p.off_payload);
-    const uint32_t n_runs = p.subs_per_chunk;
+    const bool packer = wave < kStreamWaves;  // wavefront-uniform
+    const uint32_t n_groups = (p.n_chunks + kStreamWaves - 1) / kStreamWaves;
+    auto claim = [&]() -> uint32_t {
+        return __hip_atomic_fetch_add(&p.ctrl->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     auto sync_wave = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    while (ch < p.n_chunks) {  // wavefront-uniform
-        const uint32_t clen = chunk_len_of(p, ch);
-        const uint32_t next = ch + gridDim.x * kPackWaves;
-        uint32_t wn[16];
-        if (next < p.n_chunks) load_chunk_symbols(p, next, lane, aligned4, wn);
-        const uint32_t word0 = chunk_off[ch], word1 = chunk_off[ch + 1];
-        auto build_window = [&](uint32_t win, uint32_t win_words, uint16_t* run_bits) -> uint32_t {
-            uint32_t total;
-            if (win == 0) {
-                if (max_len <= 32) total = pack_chunk<false, true>(w, clen, S.tab, img, win, win_words, lane, run_bits, n_runs);
-                else total = pack_chunk<true, true>(w, clen, S.tab, img, win, win_words, lane, run_bits, n_runs);
-            } else {
-                if (max_len <= 32) total = pack_chunk<false, false>(w, clen, S.tab, img, win, win_words, lane, run_bits, n_runs);
-                else total = pack_chunk<true, false>(w, clen, S.tab, img, win, win_words, lane, run_bits, n_runs);
+    if (tid < (int)kSlots) S.done[tid] = 0u;
+    if (tid == 0) {
+        S.dealt = 0u;
+        S.placed = 0u;
+        S.drawn = 0u;
+    }
+    TableLds& L = *reinterpret_cast<TableLds*>(&S.image[0][0]);  // shares LDS with the first wavefront's images
+    static_assert(sizeof(TableLds) <= sizeof(S.image[0]), "table scratch must fit a wavefront's images");
+    if constexpr (!STATIC) {
+        sum_partials<1024>(L, p.hist_parts, p.n_parts, p.bits, blockIdx.x);
+        rank_symbols<1024>(L, p.bits);
+    } else {
+        if (tid < 256) S.tab[tid] = p.enc_table[tid];
+        __syncthreads();
+    }
+    // While the first wavefront builds the table, the others clear their images and request their first symbols.
+    // (A ticket takes up to 4 us with all workgroups drawing theirs.)
+    if (tid == 64 * kStreamWaves) {
+        S.ticket[0] = claim();
+        post_lds(&S.drawn, 1u);
+        S.ticket[1] = claim();
+        post_lds(&S.drawn, 2u);
+    }
+    if (!STATIC && wave == 0) {
+        TableOut out;
+        out.entry = S.tab;
+        table_from_hist_any(L, lane, p.bits, out);
+        if (lane == 0) S.payload_bits = out.payload_bits;
+    }
+    auto ticket_of = [&](uint32_t turn) {
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)S.ticket[turn % kSlots]);
+    };
+    auto wait_drawn = [&](uint32_t n) {  // (nobody draws while waiting for something)
+        while (peek_lds(&S.drawn) < n) __builtin_amdgcn_s_sleep(1);
+    };
+    // The next chunk for this wavefront, as its number among those of the workgroup.  (Never waits: the ticket of its
+    // turn may depend on the chunk the wavefront has at hand.)
+    auto take = [&]() -> uint32_t {
+        uint32_t n = 0;
+        if (lane == 0) n = __hip_atomic_fetch_add(&S.dealt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+    };
+    // ... and its number among those of the tensor, once the ticket is known (past the last chunk: the chunk is empty;
+    // past the last group: no more chunks)
+    auto chunk_of = [&](uint32_t n) { return ticket_of(n / kStreamWaves) * (uint32_t)kStreamWaves + n % kStreamWaves; };
+    auto have_group = [&](uint32_t n) { return ticket_of(n / kStreamWaves) < n_groups; };
+    uint32_t n = 0;
+    uint2 w[8];
+    if (packer) {
+        for (uint32_t i = lane; i < kStreamRoom; i += 64) S.image[wave][i] = 0u;
+        n = take();  // (of turn 0)
+        wait_drawn(1u);
+        if (have_group(n)) load_chunk_octets(p, chunk_of(n), lane, w);
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid < 256) p.stream[kHeaderBytes + tid] = (uint8_t)(S.tab[tid] >> 56);  // the container's length table
+    for (int i = tid; i < (PAIRS ? 4096 : 256); i += 1024) {
+        const unsigned long long e0 = S.tab[PAIRS ? i & 63 : i], e1 = PAIRS ? S.tab[i >> 6] : 0ull;
+        const uint32_t l0 = (uint32_t)(e0 >> 56), l1 = (uint32_t)(e1 >> 56);
+        const bool fits = l0 + l1 <= kShortCode;
+        S.codes[i] = fits ? (uint32_t)e0 | ((uint32_t)e1 << (l0 & 31u)) | ((l0 + l1) << kShortCode) : kNoCode;
+    }
+    __syncthreads();
+    uint32_t* chunk_off = reinterpret_cast<uint32_t*>(p.stream + kHeaderBytes + kLenTableBytes);
+    const uint32_t n_runs = p.subs_per_chunk;  // at most 64
+
+    if (packer) {
+        uint16_t* sub_bits = reinterpret_cast<uint16_t*>(p.stream + p.off_sub_bits);
+        uint32_t* payload = reinterpret_cast<uint32_t*>(p.stream + p.off_payload);
+        const StreamImages im = STATIC ? StreamImages{2u, 1024u} : images_for(S.payload_bits, p.n_chunks);
+        const uint32_t n_images = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.count);
+        const uint32_t words = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.words);
+        // The images wait in a ring: `filled` chunks are packed, `stored` of them have left.  What is known of those
+        // waiting sits in the lanes of `held`: chunk number among the workgroup's, by image.
+        uint32_t filled = 0, stored = 0, next_image = 0, next_stored = 0, held = 0;
+        auto turn_of_oldest = [&]() { return (uint32_t)__builtin_amdgcn_readlane((int)held, (int)next_stored) / kStreamWaves; };
+        auto store = [&]() {  // (its place is known)
+            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)held, (int)next_stored);
+            const uint32_t turn = m / kStreamWaves, at = m % kStreamWaves, slot = turn % kSlots;
+            const uint32_t c = ticket_of(turn) * kStreamWaves + at;
+            uint32_t* img = S.image[wave] + next_stored * (words + 4u);
+            stored++;
+            next_stored = next_stored + 1u < n_images ? next_stored + 1u : 0u;
+            const uint32_t other = lane < kStreamWaves ? S.words[slot][lane] : 0u;
+            const uint32_t n_words = (uint32_t)__builtin_amdgcn_readlane((int)other, (int)at);
+            const unsigned long long place = S.place[slot];
+            const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_sum((uint32_t)lane < at ? other : 0u));
+            const unsigned long long word0 =
+                before + ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)place) |
+                          ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(place >> 32)) << 32));
+            if (c >= p.n_chunks) return;  // (the last group's places past the last chunk: empty)
+            if (lane == 0) chunk_off[c] = (uint32_t)word0;
+            const bool fits = word0 + n_words <= p.cap_words;  // (else the header has been left invalid)
+            for (uint32_t win = 0; win < n_words; win += words) {
+                const uint32_t win_words = n_words - win < words ? n_words - win : words;
+                if (win) {
+                    pack_window(p, c, S.tab, img, words, win, lane);
+                    sync_wave();
+                }
+                for (uint32_t i = lane; i < win_words; i += 64) {
+                    if (fits) payload[(size_t)word0 + win + i] = img[i];
+                    img[i] = 0u;
+                }
+                sync_wave();  // the image is read and clear before the next window or chunk writes it
             }
-            sync_wave();  // the ORs of all lanes precede the reads that follow
-            return total;
         };
-        uint16_t* runs_out = sub_bits + (size_t)ch * n_runs;
-        const bool staged = n_runs <= 64u;
-        const uint32_t total_bits = build_window(0, kStageWords, staged ? S.runs[wave] : runs_out);
-        if (staged && (uint32_t)lane < n_runs) runs_out[lane] = S.runs[wave][lane];
-        const uint32_t n_words = (total_bits + 31) >> 5;
-        // what the size pass counted must be what this pass produces (the same symbols and table); should the
-        // symbols have changed in between, or the payload not fit, nothing is written past the chunk's place and
-        // the stream is left invalid
-        const bool fits = word1 - word0 == n_words && (uint64_t)word0 + n_words <= p.cap_words;
-        if (!fits && lane == 0) *reinterpret_cast<uint32_t*>(p.stream) = 0u;  // the header's magic
-        for (uint32_t win = 0; win < n_words; win += kStageWords) {
-            const uint32_t win_words = (n_words - win < (uint32_t)kStageWords) ? n_words - win : (uint32_t)kStageWords;
-            if (win) build_window(win, win_words, nullptr);
-            for (uint32_t i = lane; i < win_words; i += 64) {
-                if (fits) payload[(size_t)word0 + win + i] = img[i];
-                img[i] = 0u;
+        while (have_group(n)) {
+            const uint32_t n_next = take();
+            const bool early = peek_lds(&S.drawn) > n_next / kStreamWaves;  // its symbols arrive while this chunk is packed
+            uint2 wn[8];
+            if (early && have_group(n_next)) load_chunk_octets(p, chunk_of(n_next), lane, wn);
+            // images whose place is known leave, and one has to where all are waiting
+            while (stored < filled && (filled - stored >= n_images || peek_lds(&S.placed) > turn_of_oldest())) {
+                while (peek_lds(&S.placed) <= turn_of_oldest()) __builtin_amdgcn_s_sleep(1);  // (the wait behind it is bounded)
+                store();
             }
-            sync_wave();  // the image is read and clear before the next window or chunk writes it
-        }
-        ch = next;
+            const uint32_t ch = chunk_of(n);
+            uint32_t bits = 0;
+            if (ch < p.n_chunks)
+                bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.codes, S.image[wave] + next_image * (words + 4u), words, lane, S.runs[wave]);
+            const uint32_t slot = n / kStreamWaves % kSlots;
+            if (lane == 0) {
+                S.words[slot][n % kStreamWaves] = (bits + 31u) >> 5;
+                S.bits[slot][n % kStreamWaves] = bits;
+                __hip_atomic_fetch_add(&S.done[slot], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            sync_wave();
+            if (ch < p.n_chunks && (uint32_t)lane < n_runs) (sub_bits + (size_t)ch * n_runs)[lane] = S.runs[wave][lane];
+            sync_wave();
+            held = (uint32_t)lane == next_image ? n : held;
+            filled++;
+            next_image = next_image + 1u < n_images ? next_image + 1u : 0u;
+            n = n_next;
+            if (!early) {
+                wait_drawn(n / kStreamWaves + 1u);
+                if (have_group(n)) load_chunk_octets(p, chunk_of(n), lane, wn);
+            }
 #pragma unroll
-        for (int q = 0; q < 16; q++) w[q] = wn[q];
+            for (int q = 0; q < 8; q++) w[q] = wn[q];
+        }
+        while (stored < filled) {
+            while (peek_lds(&S.placed) <= turn_of_oldest()) __builtin_amdgcn_s_sleep(1);
+            store();
+        }
+        return;
+    }
+
+    // ---- the 16th wavefront: turns [0, published) have published their sizes, turns [0, placed) know their places ----
+    // A turn's size is published when at most two turns before it are waiting for their places.  The ticket of turn t is
+    // drawn behind the size of turn t - 2, so all turns up to t - 5 have their places by then, and a packer that starts
+    // on a chunk of turn t lets go of what it holds of those.  Its next chunk is of turn t + 2 at the latest (turn t + 2
+    // has no ticket before turn t is published, so at most the packers' next chunks are of that turn), and until that one
+    // is packed no ticket beyond turn t + 3 is drawn: never more than eight turns are in use.
+    // The sizes of all groups are added up by ONE wavefront, that of the workgroup which drew the first ticket (so it
+    // runs, and it stays until every group has its place): it reads the published sizes in order, 256 at a time, and
+    // writes the places, for which the others look at one word each.  (Every workgroup reading back over the sizes
+    // before its own group, 4 KB a look, all at the same few cache lines, took 7 to 10 us per turn.)
+    wait_drawn(2u);
+    uint32_t published = 0, placed = 0;
+    uint32_t g = ticket_of(0);
+    unsigned long long* sizes = p.lookback;
+    unsigned long long* places = p.lookback + n_groups;
+    const bool adder = g == 0u;
+    uint32_t added = 0;                 // groups [0, added) have their places
+    unsigned long long total_words = 0;  // of those
+    uint32_t tries = 0;                 // looks without anything new
+    while (g < n_groups || placed < published || (adder && added < n_groups)) {
+        bool news = false;
+        if (g < n_groups && published - placed <= 2u && peek_lds(&S.done[published % kSlots]) == (uint32_t)kStreamWaves * (published / kSlots + 1u)) {
+            const uint32_t slot = published % kSlots;
+            unsigned long long size = lane < kStreamWaves ? S.words[slot][lane] : 0u;
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) size += __shfl_xor(size, o, 64);
+            if constexpr (STATIC) {
+                const uint32_t bits = wave_sum(lane < kStreamWaves ? S.bits[slot][lane] : 0u);
+                if (lane == 0) {
+                    // (the returned value is waited for: the bits are counted before the size can be seen)
+                    const unsigned long long was = __hip_atomic_fetch_add(&p.ctrl->payload_bits, (unsigned long long)bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    asm volatile("" : : "v"(was) : "memory");
+                }
+            }
+            if (lane == 0) publish64(&sizes[g], kKnown | size);
+            published++;
+            g = ticket_of(published);
+            // (a ticket is drawn two turns ahead, so that the symbols of the group can be requested one turn ahead)
+            if (lane == 0) {
+                S.ticket[(published + 1u) % kSlots] = g < n_groups ? claim() : 0xffffffffu;
+                post_lds(&S.drawn, published + 2u);
+            }
+            news = true;
+        }
+        if (adder && added < n_groups) {
+            unsigned long long e[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const uint32_t i = added + 64u * (uint32_t)j + (uint32_t)lane;
+                e[j] = i < n_groups ? peek64(&sizes[i]) : 0ull;
+            }
+            bool more = true;
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                if (!more) break;
+                const unsigned long long missing = __ballot(e[j] == 0ull);
+                const int ready = missing ? __ffsll((long long)missing) - 1 : 64;
+                const unsigned long long size = lane < ready ? e[j] & (kKnown - 1ull) : 0ull;
+                const unsigned long long incl = wave_inclusive_scan64(size, lane);
+                if (lane < ready) publish64(&places[added + (uint32_t)lane], kKnown | (total_words + incl - size));
+                total_words += __shfl(incl, 63, 64);
+                added += (uint32_t)ready;
+                more = ready == 64;
+                news |= ready != 0;
+            }
+            if (added == n_groups && lane == 0) {
+                chunk_off[p.n_chunks] = (uint32_t)total_words;
+                Header hdr = p.hdr;
+                hdr.payload_words = total_words;
+                // (STATIC: every group has added its bits before it published its size)
+                hdr.payload_bits = STATIC ? __hip_atomic_load(&p.ctrl->payload_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                          : S.payload_bits;
+                // somebody gave up waiting, or the payload outgrew the buffer: not valid
+                if (__hip_atomic_load(&p.ctrl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || total_words > p.cap_words ||
+                    total_words > 0xffffffffull)
+                    hdr.magic = 0u;
+                *reinterpret_cast<Header*>(p.stream) = hdr;
+                if (p.out_bytes) *p.out_bytes = (uint64_t)p.off_payload + 4 * total_words;
+                // alignment gaps between the sections are part of the stream: keep them zero
+                for (size_t o = kHeaderBytes + kLenTableBytes + 4 * ((size_t)p.n_chunks + 1); o < p.off_sub_bits; o++) p.stream[o] = 0;
+                for (size_t o = p.off_sub_bits + 2 * (size_t)p.n_chunks * n_runs; o < p.off_payload; o++) p.stream[o] = 0;
+            }
+        }
+        if (placed < published) {
+            unsigned long long e = peek64(&places[ticket_of(placed)]);  // (one word, the same for all lanes)
+            // (limits that are never reached: seconds.  The others wait longer than the one that adds up, whose own wait
+            // for a size ends in an invalid stream.)
+            if (!e && tries >= (adder ? kSpinLimit : 2u * kSpinLimit)) {
+                e = kKnown - 1ull;  // (past any buffer: nothing is stored)
+                if (lane == 0) {
+                    __hip_atomic_fetch_or(&p.ctrl->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    *reinterpret_cast<volatile uint32_t*>(p.stream) = 0u;  // the header's magic, should it be there already
+                }
+            }
+            if (e) {
+                if (lane == 0) {
+                    S.place[placed % kSlots] = e & (kKnown - 1ull);
+                    post_lds(&S.placed, placed + 1u);
+                }
+                placed++;
+                news = true;
+            }
+        }
+        tries = news ? 0u : tries + 1u;
+        if (tries > kSpinLimit && placed == published && g >= n_groups) {  // (only the adder waits here, for a size that never came)
+            if (lane == 0) *reinterpret_cast<volatile uint32_t*>(p.stream) = 0u;
+            break;
+        }
+        if (!news) __builtin_amdgcn_s_sleep(1);
     }
 }
 
@@ -805,7 +1165,6 @@ PackParams pack_params(const uint8_t* d_syms, const Geometry& g, int bits, float
     p.chunk_syms = g.chunk_syms;
     p.subs_per_chunk = g.subs_per_chunk;
     p.n_groups = cs.n_groups;
-    p.chunk_bits = cs.chunk_bits;
     p.bits = bits;
     p.hist_parts = cs.hist_parts;
     p.n_parts = n_parts;
@@ -831,18 +1190,20 @@ PackParams pack_params(const uint8_t* d_syms, const Geometry& g, int bits, float
     return p;
 }
 
-// Sizes, offsets and packing of a tensor with more chunk groups than the device holds pack workgroups.
+// Packing of a tensor with more chunk groups than the device holds pack workgroups.
 template <bool STATIC>
 static hipError_t launch_pack_large(const PackParams& p, hipStream_t s) {
-    if (!p.chunk_bits) return hipErrorInvalidValue;
-    const uint32_t n_groups = pack_groups(p.n_chunks);
-    const uint32_t cap = (uint32_t)pack_resident_groups<kPackTable>();
-    const uint32_t grid = n_groups < 2 * cap ? n_groups : 2 * cap;
-    hipError_t e = launch(K_CHUNK_BITS, k_chunk_bits, dim3(grid), dim3(256), 0, s, p);
+    const uint32_t n_groups = (p.n_chunks + kStreamWaves - 1) / kStreamWaves;
+    const unsigned grid = n_groups < 256u ? n_groups : 256u;  // one workgroup per compute unit: its images take most of the LDS
+    // (7 and 8 bits: a table of pairs would not fit beside the images)
+    const bool pairs = p.bits <= 6;
+    const size_t lds = sizeof(StreamShared) + sizeof(uint32_t) * (pairs ? 4096 : 256);
+    const void* fn = pairs ? reinterpret_cast<const void*>(&k_pack_stream<STATIC, true>)
+                           : reinterpret_cast<const void*>(&k_pack_stream<STATIC, false>);
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    e = launch(K_CHUNK_SCAN, k_chunk_scan, dim3(1), dim3(kScanThreads), 0, s, p);
-    if (e != hipSuccess) return e;
-    return launch(K_PACK, k_pack_at<STATIC>, dim3(n_groups < cap ? n_groups : cap), dim3(256), 0, s, p);
+    if (pairs) return launch(K_PACK, k_pack_stream<STATIC, true>, dim3(grid), dim3(1024), lds, s, p);
+    return launch(K_PACK, k_pack_stream<STATIC, false>, dim3(grid), dim3(1024), lds, s, p);
 }
 
 hipError_t launch_coder(const uint8_t* d_syms, const Geometry& g, int bits, float delta, const CoderScratch& cs,
@@ -850,14 +1211,13 @@ hipError_t launch_coder(const uint8_t* d_syms, const Geometry& g, int bits, floa
                         uint64_t* d_out_bytes, hipStream_t s) {
     PackParams p = pack_params(d_syms, g, bits, delta, cs, n_parts, d_enc_table, d_stream, cap_words, d_out_bytes);
     const uint32_t resident = (uint32_t)pack_resident_groups<kPackTable>();
-    const bool large = cs.n_groups > resident;
+    if (cs.n_groups > resident) return launch_pack_large<false>(p, s);
     // every pack workgroup sums the partial histograms itself while that is at most 64 KB to read
-    const bool build_in_pack = !large && ((size_t)n_parts << bits) * 4 <= 64 * 1024;
+    const bool build_in_pack = ((size_t)n_parts << bits) * 4 <= 64 * 1024;
     if (!build_in_pack) {
         hipError_t e = launch(K_TABLE, k_huffman_table, dim3(1), dim3(1024), 0, s, (const uint32_t*)cs.hist_parts,
                               n_parts, bits, (uint32_t*)nullptr, d_enc_table, d_stream + kHeaderBytes, cs.ctrl, 0u);
         if (e != hipSuccess) return e;
-        if (large) return launch_pack_large<false>(p, s);
         return launch(K_PACK, k_pack<kPackTable>, dim3(cs.n_groups), dim3(256), 0, s, p);
     }
     const uint32_t cap = (uint32_t)pack_resident_groups<kPackBuild>();

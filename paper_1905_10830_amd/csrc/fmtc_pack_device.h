@@ -44,7 +44,6 @@ struct PackParams {
     int n_parts;
     const uint64_t* enc_table;   // otherwise: the table (k_huffman_table's, or a static one)
     uint32_t static_max_len;     // kPackStatic: longest code of the table
-    uint32_t* chunk_bits;        // large tensors: code bits of every chunk (k_chunk_bits -> k_chunk_scan)
     CoderCtrl* ctrl;
     unsigned long long* lookback;
     Header hdr;

@@ -20,8 +20,7 @@ struct Profiler {
 Profiler g_prof;
 const char* const kNames[K_COUNT] = {"k_project_quantize", "k_histogram", "k_huffman_table",
                                      "k_pack",             "k_decode",    "k_copy",
-                                     "k_quantize_u8",      "k_reconstruct_u8", "k_chunk_bits",
-                                     "k_chunk_scan"};
+                                     "k_quantize_u8",      "k_reconstruct_u8"};
 
 void release() {
     for (int k = 0; k < K_COUNT; k++) {

@@ -57,3 +57,48 @@ def test_code_table_of_crafted_counts(fmtc, oracle, bits, kind):
     got = stream[:int(nbytes.item())].cpu().numpy()
     assert np.array_equal(got[64:320], ln), "code lengths"
     assert np.array_equal(got, ref)
+
+
+# Packer of large tensors: more than 4096 chunks.  Chunk sizes that are multiples of 8, of 4 only, of neither; one, two
+# and many groups per workgroup, a last group of one chunk; code words of more than 27 bits, chunks larger than an image.
+STREAM_CASES = [  # P, C, bits, chunk_syms, kind
+    (4097 * 4, 16, 6, 64, "steep"),
+    (15 * 300, 64, 6, 64, "steep"),
+    (40001, 12, 5, 64, "equal"),
+    (9999, 33, 4, 66, "steep"),
+    (70001, 9, 7, 99, "gaps"),
+    (4113 * 8, 128, 6, 1024, "steep"),
+    (4200 * 20, 100, 8, 2048, "steep"),
+    (4100 * 4, 1000, 3, 4096, "equal"),
+    (16400, 1024, 6, 4096, "fibonacci"),
+    (4100, 1024, 8, 1024, "fibonacci"),
+]
+
+
+@pytest.mark.parametrize("P,C,bits,chunk,kind", STREAM_CASES, ids=[f"P{c[0]}C{c[1]}b{c[2]}k{c[3]}{c[4]}" for c in STREAM_CASES])
+def test_packer_of_large_tensors(fmtc, oracle, P, C, bits, chunk, kind):
+    K, V = 1 << bits, P * C
+    if kind == "fibonacci":  # the longest codes that fit: counts 1, 1, 2, 3, 5, ...
+        f = [1, 1]
+        while sum(f) + f[-1] + f[-2] < V and len(f) < K:
+            f.append(f[-1] + f[-2])
+        counts = np.array(f + [0] * (K - len(f)), np.int64)
+    else:
+        counts = counts_of(kind, K).astype(np.float64)
+        counts = np.where(counts > 0, np.maximum(1, counts * (V / counts.sum()) * 0.9), 0).astype(np.int64)
+    counts[counts.argmax()] += V - counts.sum()
+    sym = np.repeat(np.arange(K), counts).astype(np.uint8)
+    np.random.default_rng(bits + C).shuffle(sym)
+    if kind == "fibonacci":  # the rare symbols together in one chunk: more code bits than an image holds
+        sym = np.sort(sym)
+        sym = np.concatenate([sym[chunk:], sym[:chunk]])
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, C, bits, 0.5, ln, oracle.canonical_codes(ln), chunk)
+    stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, 0.5, chunk)
+    torch.cuda.synchronize()
+    n = int(nbytes.item())
+    got = stream[:n].cpu().numpy()
+    assert n == len(ref) and np.array_equal(got, ref), f"first differing byte {int(np.argmax(got[:len(ref)] != ref[:n]))}"
+    back, err = fmtc.decode_symbols(stream, P, C, bits, nbytes=n)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0 and np.array_equal(back.cpu().numpy().reshape(-1), sym)
