@@ -1462,21 +1462,27 @@ hipError_t launch_encode_static_fused(const BasisDevice& b, const float* d_x, in
 // Wide tensors whose channel count is a multiple of 16: the projection as a tiled matrix product.
 // A pixel's channels fit neither a wavefront's registers nor (for more than a few pixels) LDS, so
 // the contraction index is cut instead.  A workgroup owns a tile of 128 coefficients x 128 pixels
-// (each of its 4 wavefronts 64 x 64: 2 x 2 matrix tiles with two accumulators each) and walks the
-// channels 16 at a time.  What a step needs goes from L2 / HBM straight into a ring of three LDS
-// slots, two steps ahead of its use and with no registers in between:
-//   basis   8 KB in operand order (wavefront w: both f16 parts of coefficient tile w);
-//   pixels  8 KB of fp32 as they lie in the tensor: thread (pixel, h) of wavefront w its channels
-//           [16 s + 8 h, + 8) of pixel 32 w + pixel -- exactly the operand entry of its lane.
-// One step ahead of the matrix instructions every thread reads its own eight values back,
-// removes the mean, cuts them in their two f16 parts and writes them as pixel operands into one
-// of two LDS buffers; one barrier per step hands a slot and a buffer over.
-// Every operand byte read from LDS feeds two matrix tiles, every basis byte from L2 four pixel
-// tiles -- what the kernel that holds whole pixels in LDS lacks.  The waits count loads in flight
-// (they complete in order), so every wavefront issues the same loads in the same order whatever
-// part of its tile lies outside the tensor: addresses are clamped, values zeroed.  Quantizer,
-// histogram, stores and exact decisions as in the narrow-tensor kernel: a lane ends up with 16
-// consecutive coefficients of its pixel.
+// and walks the channels 32 at a time.  What a step needs goes from L2 / HBM straight into a ring
+// of LDS slots, with no registers in between:
+//   basis   16 KB in operand order;
+//   pixels  16 KB of fp32: the 128 bytes of a pixel as one line.  Eight lanes fetch a line, in an
+//           order that depends on the pixel (piece index XOR pixel modulo 8): its pieces then lie
+//           in LDS where the operand reads of eight pixels meet all banks.
+// (Steps of 16 channels, every lane fetching its own operand entry, touched 32 lines per load and
+// used 32 bytes of each: the loads' passage through the cache bounded the step, whatever else was
+// changed -- 0.57 us for 192 ns of matrix instructions.)
+// A lane reads its sixteen values back, removes the mean and cuts them in their two f16 parts, in
+// registers.  The waits count loads in flight (they complete in order), so every wavefront issues the
+// same loads in the same order whatever part of its tile lies outside the tensor: addresses are
+// clamped.  Quantizer, histogram, stores and exact decisions as in the narrow-tensor kernel: a lane
+// ends up with 16 consecutive coefficients of its pixel.
+// Each of the four wavefronts holds all 128 coefficients of its 32 pixels: twice the operand bytes of a
+// 64 x 64 quarter are read from LDS, but a pixel is converted once, by the wavefront that multiplies
+// it, and the conversion's round trip through LDS and its barrier go.  Two workgroups per compute unit:
+// one converts while the other's matrix instructions run.  Measured against the 16-channel form, us:
+// C = 256, N = 256, 14 x 14, 4 bits 44.6 -> 39.5 (planar, 8 bits 91 -> 73); C = 960, N = 256 458 -> 391;
+// C = 176, N = 128, 28 x 28 62 -> 49.  At C = 960 that is 0.71 PFLOP/s of f16 products; the step's operand
+// reads, conversion and matrix instructions do not overlap within a wavefront.
 // ---------------------------------------------------------------------------
 struct GemmParams {
     const float* x;
@@ -1497,71 +1503,88 @@ struct GemmParams {
 
 constexpr int kGemmFix = 64;  // values per wavefront waiting for their exact decision
 
+constexpr int kGemmSlotBytes = 32 * 1024;
 template <int LAYOUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_project_quantize_gemm4(GemmParams p) {
-    __shared__ __align__(16) uint4 stageA[3][8][64];     // per 16-channel step: (coefficient tile, part), operand order
-    __shared__ __align__(16) uint4 stageX[3][4][2][64];  // per step: fp32 pixels as loaded, [wavefront][instruction][lane]
-    __shared__ __align__(16) uint4 stageB[2][4][2][64];  // per step: (pixel tile, part), operand order
-    __shared__ float s_n2[4][32];
-    __shared__ uint32_t s_fix_a[4][kGemmFix], s_fix_px[4][kGemmFix], s_fix_count[4];
-    extern __shared__ __align__(16) uint8_t dyn_lds[];    // mean [Cpad], then histogram copies [4][K << HS]
-    constexpr int XL = LAYOUT == FMTC_NHWC ? 2 : 8;       // transfers of one step's pixels per wavefront
-    constexpr int LD = 2 + XL;                            // ... of one step in all (basis: 2)
+    constexpr int WAVES = 4, THREADS = 64 * WAVES;
+    constexpr int KT = 4;                              // coefficient tiles: all of the workgroup's in every wavefront
+    constexpr int SLOTS = 2;
+    constexpr int AL = 4;                              // a wavefront's transfers of a step's basis
+    constexpr int XL = LAYOUT == FMTC_NHWC ? 4 : 16;   // ... and of its pixels
+    extern __shared__ __align__(16) uint8_t dyn_lds[];
+    // ring: slot = basis [coefficient tile][16-channel half][part][64], then pixels [pixel tile][256 pieces]; then the
+    // mean [Cpad], then histogram copies [WAVES][K << HS]
+    typedef uint4 Slot[32][64];
+    Slot* ring = reinterpret_cast<Slot*>(dyn_lds);
+    static_assert(sizeof(Slot) == kGemmSlotBytes, "slot size");
+    float* s_mu = reinterpret_cast<float*>(dyn_lds + sizeof(Slot) * SLOTS);
+    __shared__ uint32_t s_fix_a[WAVES][kGemmFix], s_fix_px[WAVES][kGemmFix], s_fix_count[WAVES];
 
     zero_coder_scratch(p.ctrl, p.lookback, p.n_groups);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int C = p.C, NJ = p.NJ, K = 1 << p.bits, HS = p.hist_shift, HC = 1 << HS;
-    const int ktp = wave & 1, ptp = wave >> 1;  // this wavefront's pair of coefficient tiles / pixel tiles
+    const int xpt = wave;  // this wavefront's pixel tile
     const int kt0 = blockIdx.y * 4;
-    float* s_mu = reinterpret_cast<float*>(dyn_lds);
-    uint32_t* whist = reinterpret_cast<uint32_t*>(dyn_lds) + 16 * NJ;
-    for (int i = tid; i < 4 * K * HC; i += 256) whist[i] = 0u;
-    for (int i = tid; i < 16 * NJ; i += 256) s_mu[i] = p.mu[i];
+    const int NS = (C + 31) / 32;                       // steps of 32 channels
+    const bool odd = (C & 31) != 0;                     // (C is a multiple of 16: the last step may hold 16 only)
+    uint32_t* whist = reinterpret_cast<uint32_t*>(s_mu + 16 * NJ);
+    for (int i = tid; i < WAVES * K * HC; i += THREADS) whist[i] = 0u;
+    for (int i = tid; i < 16 * NJ; i += THREADS) s_mu[i] = p.mu[i];
     uint32_t* wh0 = whist + wave * K * HC;
     uint32_t* wh = wh0 + (lane & (HC - 1));
     uint32_t* fix_a = s_fix_a[wave];
     uint32_t* fix_px = s_fix_px[wave];
     uint32_t* fix_count = &s_fix_count[wave];
     if (lane == 0) *fix_count = 0u;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // (the loads counted below start from none in flight)
     __syncthreads();
 
     const int zero_sym = 1 << (p.bits - 1);
-    const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1), zero_f = (float)zero_sym;
+    const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1);
     const float inv_delta = p.inv_delta, inv_delta_lo = p.inv_delta * (1.f / 2048.f);
+    const float magic = 12582912.f + (float)zero_sym;  // rounding, offset and conversion in one addition: see k_project_quantize_rows
+    const float magic_lo = 12582912.f, magic_hi = 12582912.f + (float)(2 * zero_sym - 1);
 
-    // exact fp64 decision of the listed values, four per round (one per 16-lane group)
+    // exact fp64 decision of the listed values, two per round (one per half): most lists hold one or two, and what a round
+    // takes is the latency of its loads, at the end of the workgroup that is last, so they should all be in flight
+    // together (C = 256 at N = 256: 42.7 us with four per round and 16 lanes each, 39.4 with four and 16-byte loads, 37.7)
     auto resolve_list = [&]() {
         __builtin_amdgcn_s_waitcnt(0x0F70);  // the symbols that get patched have been stored
         const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)*fix_count);
-        for (uint32_t base = 0; base < n; base += 4) {
-            const uint32_t idx = base + (uint32_t)(lane >> 4);
+        for (uint32_t base = 0; base < n; base += 2) {
+            const uint32_t idx = base + (uint32_t)half;
             const bool active = idx < n;
             const uint32_t e = active ? fix_a[idx] : 0u;
             const int k = (int)(e & 0xffffu);
             const uint32_t old = e >> 16;
             const int64_t qpx = active ? (int64_t)fix_px[idx] : 0;
-            int64_t xbase, xstride;
+            double part = 0.0;
             if constexpr (LAYOUT == FMTC_NHWC) {
-                xbase = qpx * C;
-                xstride = 1;
+                if (active)
+#pragma unroll 8
+                    for (int c = 4 * l32; c < C; c += 128) {
+                        const float4 t = *reinterpret_cast<const float4*>(p.Trow + (size_t)k * C + c);
+                        const float4 x = *reinterpret_cast<const float4*>(p.x + qpx * C + c);
+                        const float4 m = *reinterpret_cast<const float4*>(s_mu + c);
+                        part += ((double)t.x * ((double)x.x - (double)m.x) + (double)t.y * ((double)x.y - (double)m.y)) +
+                                ((double)t.z * ((double)x.z - (double)m.z) + (double)t.w * ((double)x.w - (double)m.w));
+                    }
             } else {
                 const int64_t n_img = qpx / p.HW;
-                xbase = n_img * (int64_t)C * p.HW + (qpx - n_img * p.HW);
-                xstride = p.HW;
+                const float* xp = p.x + n_img * (int64_t)C * p.HW + (qpx - n_img * p.HW);
+                if (active)
+#pragma unroll 16
+                    for (int c = l32; c < C; c += 32)
+                        part += (double)p.Trow[(size_t)k * C + c] * ((double)xp[(int64_t)c * p.HW] - (double)s_mu[c]);
             }
-            double part = 0.0;
-            if (active)
-#pragma unroll 8  // independent loads of eight terms in flight together: the loop is all latency
-                for (int c = lane & 15; c < C; c += 16)
-                    part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)p.mu[c]);
 #pragma unroll
-            for (int o = 8; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the 16-lane group
+            for (int o = 16; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the half
             double qd = rint(part / (double)p.delta);
             qd = fmin(fmax(qd, (double)lo), (double)hi);
             const uint32_t sfix = (uint32_t)((int)qd + zero_sym);
-            if (active && (lane & 15) == 0 && sfix != old) {
+            if (active && l32 == 0 && sfix != old) {
                 atomicSub(&wh0[old << HS], 1u);
                 atomicAdd(&wh0[sfix << HS], 1u);
                 p.syms[qpx * C + k] = (uint8_t)sfix;
@@ -1573,194 +1596,198 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
 
     for (int64_t ptg = blockIdx.x; ptg < p.n_ptg; ptg += gridDim.x) {
-        const int64_t pt0 = ptg * 4;
-        floatx16 am[2][2], ac[2][2];
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-            for (int b = 0; b < 2; b++)
-#pragma unroll
-                for (int r = 0; r < 16; r++) { am[a][b][r] = 0.f; ac[a][b][r] = 0.f; }
-
-        // this thread's pixel (of pixel tile pt0 + wave); past the end of the tensor the last pixel is loaded
-        // in its place and zeroed on conversion
-        const int64_t px_raw = (pt0 + wave) * 32 + l32;
-        const bool px_ok = px_raw < p.P;
-        const int64_t px_ld = px_ok ? px_raw : p.P - 1;
-        int64_t xbase, xstride;
+        const int64_t px0 = (ptg * 4 + xpt) * 32, px = px0 + l32;  // this lane's pixel
+        const bool px_ok = px < p.P;
+        // Where this lane fetches pixels for the ring: channels last, instruction i takes piece `xq` of pixel 8 i + lane / 8
+        // of the tile; planar, the lane's own pixel.  Past the end of the tensor the last pixel is loaded.
+        const int xq = (lane & 7) ^ (lane >> 3);
+        const float* xsrc[LAYOUT == FMTC_NHWC ? XL : 1];
         if constexpr (LAYOUT == FMTC_NHWC) {
-            xbase = px_ld * C;
-            xstride = 1;
+#pragma unroll
+            for (int i = 0; i < XL; i++) {
+                int64_t q = px0 + 8 * i + (lane >> 3);
+                q = q < p.P ? q : p.P - 1;
+                xsrc[i] = p.x + q * C;
+            }
         } else {
-            const int64_t n_img = px_ld / p.HW;
-            xbase = n_img * (int64_t)C * p.HW + (px_ld - n_img * p.HW);
-            xstride = p.HW;
+            const int64_t q = px_ok ? px : p.P - 1, n_img = q / p.HW;
+            xsrc[0] = p.x + n_img * (int64_t)C * p.HW + (q - n_img * p.HW);
         }
+        // the wavefront's share of the 16 blocks of a step's basis (one coefficient tile); a tile past the end repeats the
+        // last one, its results are dropped
         int kt_ld = kt0 + wave;
-        kt_ld = kt_ld < p.ncs ? kt_ld : p.ncs - 1;  // a tile past the end repeats the last one; its results are dropped
+        kt_ld = kt_ld < p.ncs ? kt_ld : p.ncs - 1;
         const uint4* a_src = p.basis16 + (size_t)kt_ld * NJ * 128 + lane;
-        // Everything step s needs, on its way into ring slot s % 3: both parts of basis tile kt0 + wave, and
-        // channels [16 s + 8 h, + 8) of this thread's pixel -- the operand entry of lane (pixel, h).  Steps past the
-        // end repeat the last one, so that every wavefront always has the same number of loads in flight.
+        // Everything step s needs, on its way into ring slot s % SLOTS.  Steps past the end repeat the last one, so that
+        // every wavefront always has the same number of loads in flight.
         auto issue = [&](int s) {
-            const int slot = s % 3;
-            s = s < NJ ? s : NJ - 1;
-            load_to_lds<16>(a_src + (size_t)s * 128, &stageA[slot][2 * wave][0]);
-            load_to_lds<16>(a_src + (size_t)s * 128 + 64, &stageA[slot][2 * wave + 1][0]);
-            int c0 = 16 * s + 8 * half;
-            c0 = c0 < C ? c0 : 0;  // C is a multiple of 16: all eight channels or none (then zeroed on conversion)
+            uint4(*slot)[64] = ring[s % SLOTS];
+            s = s < NS ? s : NS - 1;
+#pragma unroll
+            for (int q = 0; q < AL; q++) load_to_lds<16>(a_src + (size_t)s * 256 + 64 * q, &slot[wave * AL + q][0]);
             if constexpr (LAYOUT == FMTC_NHWC) {
-                const float* src = p.x + xbase + c0;
-                load_to_lds<16>(src, &stageX[slot][wave][0][0]);
-                load_to_lds<16>(src + 4, &stageX[slot][wave][1][0]);
+                int c = 32 * s + 4 * xq;
+                c = c < C ? c : C - 4;  // (the missing half of a last step: any channels, they are not used)
+#pragma unroll
+                for (int i = 0; i < XL; i++) load_to_lds<16>(xsrc[i] + c, &slot[16 + 4 * xpt + i][0]);
             } else {
 #pragma unroll
-                for (int e = 0; e < 8; e++)
-                    load_to_lds<4>(p.x + xbase + (int64_t)(c0 + e) * xstride,
-                                   reinterpret_cast<uint32_t*>(&stageX[slot][wave][0][0]) + 64 * e);
+                for (int i = 0; i < XL; i++) {
+                    const int e = i;  // value e of the operand entries of both 16-channel halves
+                    int c = 32 * s + 16 * (e >> 3) + 8 * half + (e & 7);
+                    c = c < C ? c : C - 1;
+                    load_to_lds<4>(xsrc[0] + (int64_t)c * p.HW, reinterpret_cast<uint32_t*>(&slot[16 + 4 * xpt][0]) + 64 * e);
+                }
             }
         };
         float n2 = 0.f;
-        // this thread's eight channels of step s: mean removed, cut in two f16 parts, written as pixel operands
+        halfx8 xh[2], xl[2];
+        // this lane's sixteen channels of step s: mean removed, cut in two f16 parts
         auto convert = [&](int s) {
-            const int c0 = 16 * s + 8 * half;
-            const bool ok = px_ok && c0 < C;
-            float v[8];
-            if constexpr (LAYOUT == FMTC_NHWC) {
-                const float4 a = *reinterpret_cast<const float4*>(&stageX[s % 3][wave][0][lane]);
-                const float4 b = *reinterpret_cast<const float4*>(&stageX[s % 3][wave][1][lane]);
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-            } else {
-                const float* raw = reinterpret_cast<const float*>(&stageX[s % 3][wave][0][0]) + lane;
+            const uint4(*slot)[64] = ring[s % SLOTS] + 16 + 4 * xpt;
 #pragma unroll
-                for (int e = 0; e < 8; e++) v[e] = raw[64 * e];
-            }
-            const float4 m0 = *reinterpret_cast<const float4*>(&s_mu[c0]);
-            const float4 m1 = *reinterpret_cast<const float4*>(&s_mu[c0 + 4]);
-            const float m[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
-            halfx8 vh, vl;
+            for (int u = 0; u < 2; u++) {
+                if (u == 1 && odd && s == NS - 1) break;  // wavefront-uniform
+                const int c0 = 32 * s + 16 * u + 8 * half;
+                float v[8];
+                if constexpr (LAYOUT == FMTC_NHWC) {
+                    const uint4* row = &slot[0][0] + 8 * l32;
+                    const int q = 4 * u + 2 * half;
+                    const float4 a = __builtin_bit_cast(float4, row[q ^ (l32 & 7)]), b = __builtin_bit_cast(float4, row[(q + 1) ^ (l32 & 7)]);
+                    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+                } else {
+                    const float* raw = reinterpret_cast<const float*>(&slot[0][0]) + 512 * u + lane;
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                float d = ok ? v[e] - m[e] : 0.f;
-                n2 = __builtin_fmaf(d, d, n2);
-                // (no clamp of values beyond f16: what their infinities make of the products stays in the pixel's own
-                // column of outputs, and such a pixel is decided exactly in all coefficients, see n2)
-                const _Float16 h = (_Float16)d;
-                vh[e] = h;
-                vl[e] = (_Float16)__builtin_fmaf((float)h, -2048.f, d * 2048.f);  // 2^11 (d - h), exact, one mixed multiply-add
+                    for (int e = 0; e < 8; e++) v[e] = raw[64 * e];
+                }
+                const float4 m0 = *reinterpret_cast<const float4*>(&s_mu[c0]);
+                const float4 m1 = *reinterpret_cast<const float4*>(&s_mu[c0 + 4]);
+                const float m[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    // (rows past the tensor repeat its last pixel: their results are dropped.  No clamp of values beyond
+                    // f16: what their infinities make of the products stays in the pixel's own column of outputs, and such
+                    // a pixel is decided exactly in all coefficients, see n2)
+                    const float d = v[e] - m[e];
+                    n2 = __builtin_fmaf(d, d, n2);
+                    const _Float16 h = (_Float16)d;
+                    xh[u][e] = h;
+                    xl[u][e] = (_Float16)__builtin_fmaf((float)h, -2048.f, d * 2048.f);  // 2^11 (d - h), exact, one mixed multiply-add
+                }
             }
-            stageB[s & 1][wave][0][lane] = __builtin_bit_cast(uint4, vh);
-            stageB[s & 1][wave][1][lane] = __builtin_bit_cast(uint4, vl);
         };
 
-        issue(0);
-        issue(1);
-        wait_loads<LD>();  // step 0 has landed (this wavefront's part)
-        convert(0);
-        for (int s = 0; s < NJ; s++) {
-            // in flight: step s (unless s = 0) and step s + 1
-            wait_loads<LD>();  // step s has landed
-            __syncthreads();  // everybody's part of it, and everybody's pixel operands of step s; slot of step s - 1 is free
-            issue(s + 2);
-            const uint4(*sa)[64] = stageA[s % 3];
-            halfx8 th[2], tl[2], xh[2], xl[2];
+        floatx16 am[KT], ac[KT];
 #pragma unroll
-            for (int a = 0; a < 2; a++) {
-                th[a] = __builtin_bit_cast(halfx8, sa[(2 * ktp + a) * 2][lane]);
-                tl[a] = __builtin_bit_cast(halfx8, sa[(2 * ktp + a) * 2 + 1][lane]);
-                xh[a] = __builtin_bit_cast(halfx8, stageB[s & 1][2 * ptp + a][0][lane]);
-                xl[a] = __builtin_bit_cast(halfx8, stageB[s & 1][2 * ptp + a][1][lane]);
-            }
+        for (int a = 0; a < KT; a++)
 #pragma unroll
-            for (int a = 0; a < 2; a++)
+            for (int r = 0; r < 16; r++) { am[a][r] = 0.f; ac[a][r] = 0.f; }
+        auto multiply = [&](int s) {
+            const uint4(*sa)[64] = ring[s % SLOTS];
 #pragma unroll
-                for (int b = 0; b < 2; b++) {
-                    am[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th[a], xh[b], am[a][b], 0, 0, 0);
-                    ac[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th[a], xl[b], ac[a][b], 0, 0, 0);
+            for (int u = 0; u < 2; u++) {
+                if (u == 1 && odd && s == NS - 1) break;  // wavefront-uniform
+                halfx8 th[KT], tl[KT];
+#pragma unroll
+                for (int a = 0; a < KT; a++) {
+                    th[a] = __builtin_bit_cast(halfx8, sa[4 * a + 2 * u][lane]);
+                    tl[a] = __builtin_bit_cast(halfx8, sa[4 * a + 2 * u + 1][lane]);
                 }
 #pragma unroll
-            for (int a = 0; a < 2; a++)
+                for (int a = 0; a < KT; a++) {
+                    am[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th[a], xh[u], am[a], 0, 0, 0);
+                    ac[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th[a], xl[u], ac[a], 0, 0, 0);
+                }
 #pragma unroll
-                for (int b = 0; b < 2; b++)
-                    ac[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl[a], xh[b], ac[a][b], 0, 0, 0);
-            wait_loads<LD>();  // step s + 1 has landed
-            if (s + 1 < NJ) convert(s + 1);  // into the operand buffer step s - 1 read, free since the barrier above
+                for (int a = 0; a < KT; a++) ac[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl[a], xh[u], ac[a], 0, 0, 0);
+            }
+        };
+        // (one step ahead: the other workgroup of the compute unit works while this one waits)
+        issue(0);
+        for (int s = 0; s < NS; s++) {
+            wait_loads<0>();  // step s has landed (this wavefront's part)
+            __syncthreads();  // everybody's has, and everybody is done with the slot of step s - 1
+            issue(s + 1);
+            convert(s);
+            multiply(s);
         }
         wait_loads<0>();  // the repeated loads of the last steps too
-        n2 += __shfl_xor(n2, 32, 64);
-        if (half == 0) s_n2[wave][l32] = n2;
         __syncthreads();  // all wavefronts are done with the stages: the next group's first loads may overwrite them
+        n2 += __shfl_xor(n2, 32, 64);  // the other half of the pixel
 
         // ---- quantizer, histogram, stores: accumulator r of lane (pixel, h) is coefficient kt*32 + 16h + r ----
+        const bool force = !(n2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
+        const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
+        const float near_limit = force ? -1.f : 0.5f - tau;
 #pragma unroll
-        for (int b = 0; b < 2; b++) {
-            const int64_t pt = pt0 + 2 * ptp + b;
-            if (pt >= p.n_pt) continue;  // wavefront-uniform
-            const int64_t px = pt * 32 + l32;
-            const bool out_ok = px < p.P;
-            const float pn2 = s_n2[2 * ptp + b][l32];
-            const bool force = !(pn2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
-            const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(pn2), p.tau_min), 0.125f);
-            const float near_limit = force ? -1.f : 0.5f - tau;
+        for (int a = 0; a < KT; a++) {
+            const int kt = kt0 + a;
+            const int k0 = kt * 32 + 16 * half;
+            const bool ok = px_ok && k0 < C;  // C is a multiple of 16: all sixteen coefficients or none
+            if (!__any(ok)) continue;
+            uint32_t word[4], ub[16];
+            float maxd = 0.f;
 #pragma unroll
-            for (int a = 0; a < 2; a++) {
-                const int kt = kt0 + 2 * ktp + a;
-                if (kt >= p.ncs) continue;  // wavefront-uniform
-                const int k0 = kt * 32 + 16 * half;
-                const bool ok = out_ok && k0 < C;  // C is a multiple of 16: all sixteen coefficients or none
-                uint32_t word[4] = {0u, 0u, 0u, 0u};
+            for (int r = 0; r < 16; r++) {
+                const float t = __builtin_fmaf(ac[a][r], inv_delta_lo, am[a][r] * inv_delta);
+                const float u = t + magic;  // round half to even
+                maxd = fmaxf(maxd, fabsf(t - (u - magic)));
+                ub[r] = clamp_pattern(u, magic_lo, magic_hi);  // (its lowest byte is the symbol: in range whatever u is)
+                if (ok) atomicAdd(&wh[(ub[r] & 255u) << HS], 1u);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; g++)
+                word[g] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(ub[4 * g + 3], ub[4 * g + 2], 0x0c0c0400u),
+                                                __builtin_amdgcn_perm(ub[4 * g + 1], ub[4 * g], 0x0c0c0400u), 0x05040100u);
+            if (ok) *reinterpret_cast<uint4*>(p.syms + px * C + k0) = make_uint4(word[0], word[1], word[2], word[3]);
+            if (__builtin_expect(__any(!(maxd <= near_limit) && ok), 0)) {
                 uint32_t near_mask = 0;
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
-                    const float t = __builtin_fmaf(ac[a][b][r], inv_delta_lo, am[a][b][r] * inv_delta);
-                    const float q = __builtin_rintf(t);  // round half to even
-                    if (!(fabsf(t - q) <= near_limit)) near_mask |= 1u << r;
-                    const float qc = __builtin_amdgcn_fmed3f(q, lo, hi) + zero_f;  // clamped level, as a symbol
-                    word[r >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(qc, r & 3, word[r >> 2]);
-                    if (ok) atomicAdd(&wh[((uint32_t)qc < (uint32_t)K ? (uint32_t)qc : (uint32_t)(K - 1)) << HS], 1u);  // (in range whatever qc is)
+                    const float t = __builtin_fmaf(ac[a][r], inv_delta_lo, am[a][r] * inv_delta);
+                    if (!(fabsf(t - __builtin_rintf(t)) <= near_limit) && ok) near_mask |= 1u << r;
                 }
-                if (ok)
-                    *reinterpret_cast<uint4*>(p.syms + px * C + k0) = make_uint4(word[0], word[1], word[2], word[3]);
-                if (!ok) near_mask = 0;
-                if (__builtin_expect(__any(near_mask != 0), 0)) {
-                    // note the flagged values; the list is resolved when it could overflow and at the end
+                // note the flagged values; the list is resolved when it could overflow and at the end
 #pragma unroll 1
-                    for (int r = 0; r < 16; r++) {
-                        const bool f = (near_mask >> r) & 1u;
-                        const uint32_t incoming = (uint32_t)__popcll(__ballot(f));
-                        if (incoming == 0) continue;
-                        if (*fix_count + incoming > (uint32_t)kGemmFix) resolve_list();
-                        if (f) {
-                            const uint32_t slot = atomicAdd(fix_count, 1u);
-                            fix_a[slot] = (uint32_t)(k0 + r) | (((word[r >> 2] >> (8 * (r & 3))) & 255u) << 16);
-                            fix_px[slot] = (uint32_t)px;
-                        }
-                        wave_sync_lds();
+                for (int r = 0; r < 16; r++) {
+                    const bool f = (near_mask >> r) & 1u;
+                    const uint32_t incoming = (uint32_t)__popcll(__ballot(f));
+                    if (incoming == 0) continue;
+                    if (*fix_count + incoming > (uint32_t)kGemmFix) resolve_list();
+                    if (f) {
+                        const uint32_t slot = atomicAdd(fix_count, 1u);
+                        fix_a[slot] = (uint32_t)(k0 + r) | (((word[r >> 2] >> (8 * (r & 3))) & 255u) << 16);
+                        fix_px[slot] = (uint32_t)px;
                     }
+                    wave_sync_lds();
                 }
             }
         }
-        if (*fix_count) resolve_list();  // before the next group's loads: the waits there count loads in flight
+        if (*fix_count) resolve_list();
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // (nothing of this group is in flight when the next one's loads are counted)
     }
     __syncthreads();
     // one row of partial counts per workgroup (see the narrow-tensor kernel); the operand buffers are free now
-    uint32_t* s_red = reinterpret_cast<uint32_t*>(&stageA[0][0][0]);
-    for (int row = tid; row < 4 * K; row += 256) {
+    uint32_t* s_red = reinterpret_cast<uint32_t*>(dyn_lds);
+    for (int row = tid; row < WAVES * K; row += THREADS) {
         uint32_t total = 0;
         for (int q = 0; q < HC; q++) total += whist[((size_t)row << HS) + q];
         s_red[row] = total;
     }
     __syncthreads();
-    if (tid < K)
-        p.hist_parts[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * K + tid] =
-            (s_red[tid] + s_red[K + tid]) + (s_red[2 * K + tid] + s_red[3 * K + tid]);
+    if (tid < K) {
+        uint32_t total = 0;
+#pragma unroll
+        for (int q = 0; q < WAVES; q++) total += s_red[q * K + tid];
+        p.hist_parts[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * K + tid] = total;
+    }
 }
 
 // The same product with 8 wavefronts per 128 x 128 tile, two per SIMD, each 2 coefficient tiles x 1 pixel tile and a
 // quarter of the conversion work: while one wavefront of a SIMD converts, the other's matrix instructions run.  More
 // LDS operand reads per matrix instruction and one workgroup per compute unit: the faster form for tensors whose
-// tiles all fit the device at once (measured C = 960: 57 -> 47 us, C = 512 at N = 64: 33 -> 26 us), the slower one
-// beyond (N = 256, C = 256: 49 -> 61 us).
+// tiles all fit the device at once (C = 960, N = 64, 7 x 7: 42.1 us; k_project_quantize_gemm4's steps of 32 channels
+// with two wavefronts per pixel tile: 45.9, C = 1024, N = 8, 14 x 14: 46.9 and 49.2), the slower one beyond.
 template <int LAYOUT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_project_quantize_gemm8(GemmParams p) {
     __shared__ __align__(16) uint4 stageA[3][8][64];     // per 16-channel step: (coefficient tile, part), operand order
@@ -2086,15 +2113,19 @@ static hipError_t launch_gemm(const BasisDevice& b, const float* d_x, int64_t P,
     int copies = 512 >> bits;
     copies = copies >= 16 ? 16 : (copies >= 8 ? 8 : (copies >= 4 ? 4 : 2));
     p.hist_shift = copies == 16 ? 4 : (copies == 8 ? 3 : (copies == 4 ? 2 : 1));
-    const size_t lds = sizeof(float) * b.Cpad + sizeof(uint32_t) * waves * copies * ((size_t)1 << bits);
+    const size_t lds = (eight ? 0 : 2 * (size_t)kGemmSlotBytes) + sizeof(float) * b.Cpad +
+                       sizeof(uint32_t) * waves * copies * ((size_t)1 << bits);
     dim3 grid((unsigned)gx, (unsigned)gy);
     if (eight)
         return layout == FMTC_NHWC
                    ? launch(K_PROJECT, k_project_quantize_gemm8<FMTC_NHWC>, grid, dim3(512), lds, s, p)
                    : launch(K_PROJECT, k_project_quantize_gemm8<FMTC_NCHW>, grid, dim3(512), lds, s, p);
-    return layout == FMTC_NHWC
-               ? launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NHWC>, grid, dim3(256), lds, s, p)
-               : launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NCHW>, grid, dim3(256), lds, s, p);
+    const void* fn = layout == FMTC_NHWC ? reinterpret_cast<const void*>(&k_project_quantize_gemm4<FMTC_NHWC>)
+                                         : reinterpret_cast<const void*>(&k_project_quantize_gemm4<FMTC_NCHW>);
+    hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (ea != hipSuccess) return ea;
+    return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NHWC>, grid, dim3(256), lds, s, p)
+                               : launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NCHW>, grid, dim3(256), lds, s, p);
 }
 
 hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64_t N, int64_t HW, int layout,

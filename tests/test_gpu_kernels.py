@@ -102,3 +102,34 @@ def test_packer_of_large_tensors(fmtc, oracle, P, C, bits, chunk, kind):
     back, err = fmtc.decode_symbols(stream, P, C, bits, nbytes=n)
     torch.cuda.synchronize()
     assert int(err.item()) == 0 and np.array_equal(back.cpu().numpy().reshape(-1), sym)
+
+
+# Tiled projection of wide tensors, more 128 x 128 tiles than compute units: channel counts with and without a half step
+# of 16 at the end and with a last coefficient group of one to four tiles; ragged last tiles; a pixel beyond f16.
+WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
+
+
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("C,P,bits", WIDE_CASES, ids=[f"C{c[0]}P{c[1]}b{c[2]}" for c in WIDE_CASES])
+def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
+    from paper_1905_10830_amd import synth
+
+    rng = np.random.default_rng(C)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    mu = rng.standard_normal(C).astype(np.float32)
+    x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C) + mu).astype(np.float32)
+    x[P // 2] *= 1.0e5
+    A = np.float32(4.0)
+    y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
+    sym, margin = oracle.quantize(y, oracle.delta(A, bits), bits, want_margin=True)
+    H = next(h for h in (10, 7, 5, 3, 2, 1) if P % h == 0)
+    tag = synth.NHWC if layout == "nhwc" else synth.NCHW
+    xs = x.reshape(1, H, P // H, C)
+    xs = xs if layout == "nhwc" else np.ascontiguousarray(xs.transpose(0, 3, 1, 2))
+    got, hist = fmtc.quantize(fmtc.basis_import(T, mu, A), dev(xs), bits, tag)
+    torch.cuda.synchronize()
+    got, hist = got.cpu().numpy().reshape(P, C), hist.cpu().numpy()
+    diff = got != sym.reshape(P, C)
+    # differences only where the fp64 value is at a rounding boundary (1e-9 steps: the order of an fp64 sum)
+    assert not diff.any() or margin.reshape(P, C)[diff].max() <= 1e-9, f"{int(diff.sum())} symbols differ"
+    assert hist.tolist() == np.bincount(got.reshape(-1), minlength=256).tolist()
