@@ -1135,8 +1135,24 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
                                         (uint8_t)(w[v >> 2] >> (8 * (v & 3)));
                         }
                     }
+                    // (one channel tile at a time: interleaved by the compiler, the tiles' accumulators and plane addresses
+                    // spill; 128 channels, N = 64, 28 x 28, 8 bits 53 -> 28 us)
+                    if constexpr (LAYOUT == FMTC_NCHW) __builtin_amdgcn_sched_barrier(0);
                 }
                 continue;
+            }
+            // planar, built for one channel count: the image the chunk starts in, the bytes of a plane, and this lane's
+            // pixel (and its half's four channels) as a 32-bit offset from channel 0 of that image
+            const int my_pxl = pt * 32 + l32;
+            uint32_t plane_bytes = 0, px_off = 0;
+            char* plane0 = nullptr;
+            if constexpr (LAYOUT == FMTC_NCHW && CFIX != 0 && !U8) {
+                const uint32_t HW = (uint32_t)p.HW, px = (uint32_t)px_chunk0 + (uint32_t)my_pxl;
+                const uint32_t n0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)px_chunk0 / HW));
+                const uint32_t n = px / HW;
+                plane_bytes = 4u * HW;
+                px_off = 4u * ((n - n0) * (uint32_t)CFIX * HW + (px - n * HW) + 4u * (uint32_t)half * HW);
+                plane0 = reinterpret_cast<char*>(p.xhat) + (uint64_t)n0 * (uint64_t)CFIX * plane_bytes;
             }
             // the levels of this lane's pixel as f16 operands, all contraction steps (coefficients past C meet zero
             // basis entries; whatever finite level the tile's bytes give there does not count)
@@ -1271,6 +1287,26 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
                                     dst[(size_t)(8 * (r >> 2) + (r & 3)) * C] = __builtin_fmaf(acc[r], delta, m_c);
                         }
                     }
+                } else if constexpr (CFIX != 0) {
+                    // A channel's plane starts at a wavefront-uniform address, the lane's place in it is a 32-bit offset
+                    // (the launcher has checked that both fit): no 64-bit address per value and lane.
+                    // (Without the streaming hint: a chunk's part of a plane mostly starts and ends inside a line, and
+                    // the cache joins it with the neighbouring chunk's; with the hint 14 x 14 images of 128 channels
+                    // take 94 us instead of 56, 55 x 55 of 64 channels 176 instead of 67, 28 x 28 of 128 44 instead of 49.)
+                    const float* const mu_t = &s_mu[ct * 32 + 4 * half];
+                    char* const plane = plane0 + (uint64_t)(ct * 32) * plane_bytes;
+                    if (my_pxl < TP) {
+#pragma unroll
+                        for (int g = 0; g < 4; g++) {
+                            if (ct * 32 + 8 * g >= CFIX) break;  // (known at build time: the last tile's padding)
+                            const float4 m = *reinterpret_cast<const float4*>(mu_t + 8 * g);
+                            const float mv[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+                            for (int e = 0; e < 4; e++)
+                                *reinterpret_cast<float*>(plane + (uint64_t)(8 * g + e) * plane_bytes + px_off) =
+                                    __builtin_fmaf(acc[4 * g + e], delta, mv[e]);
+                        }
+                    }
                 } else {
                     const int my_px = pt * 32 + l32;
                     if (my_px < TP) {
@@ -1322,7 +1358,15 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
     const bool al = (C % 4) == 0;
     hipError_t el = hipSuccess;
     // (five channel tiles: channels-last only, the planar stores take more registers than are left)
-    if (!d_syms && (ncs <= 4 || (ncs == 5 && layout == FMTC_NHWC))) {
+    // Planar tensors of 32, 64, 128 and 144 channels have the variants built for one channel count too, whose stores take
+    // 32-bit offsets: within the images that a chunk touches (an image and 4096 values) and of pixels.  (With the
+    // channel count left open and with it fixed, us: 128 channels, N = 256, 28 x 28, 6 bits 66 and 49; 64 channels,
+    // N = 256, 56 x 56 79 and 52; 144 channels, N = 64, 56 x 56, 5 bits, whose tiles of several chunks the kernel below
+    // took, 125 and 61.)
+    const bool planar32 = layout == FMTC_NCHW && (uint64_t)C * (uint64_t)HW + 4096u + 5u * (uint64_t)HW < (1ull << 30) &&
+                          (uint64_t)g.P + 64u < (1ull << 31);
+    const bool fixed_ok = layout == FMTC_NHWC || planar32;
+    if (!d_syms && (ncs <= 4 || (ncs == 5 && (layout == FMTC_NHWC || (C == 144 && planar32 && g.n_chunks > 2048))))) {
         // ---- one wavefront per chunk ----
         const size_t lds_basis = sizeof(float) * (size_t)ncs * 32 * ncs * 32;
         // The LDS copy of a chunk's payload holds what a chunk takes at the fixed-length rate of `bits` per symbol
@@ -1338,7 +1382,7 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
         // channel tiles.)
         int waves = 4;
         if (g.n_chunks > 1024 && ncs != 3 && ncs != 5) waves = 8;
-        if (g.n_chunks > 3072 && ncs <= 2 && C == ncs * 32 && layout == FMTC_NHWC && lds_all(16) <= 160 * 1024) waves = 16;
+        if (g.n_chunks > 3072 && ncs <= 2 && C == ncs * 32 && fixed_ok && lds_all(16) <= 160 * 1024) waves = 16;
         // 128 to 160 channels: three wavefronts per SIMD with the lower parts of the basis left in global memory
         // (k_decode_chunks<..., LOG>); built for the channel counts 128 and 144, channels last (with a channel count
         // left open the kernel does not fit the registers of three wavefronts)
@@ -1352,7 +1396,7 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
         const bool fits_lo = lds_all(log_waves) - lds_basis + lds_basis_for(nlo_want) <= 160 * 1024;
         const int nlo = fits_lo ? nlo_want : 0;
         const size_t lds_basis_log = lds_basis_for(nlo);
-        const bool log12 = (C == 128 || C == 144) && layout == FMTC_NHWC && g.n_chunks > 2048 &&
+        const bool log12 = (C == 128 || C == 144) && fixed_ok && g.n_chunks > 2048 &&
                            lds_all(log_waves) - lds_basis + lds_basis_log <= 160 * 1024;
         if (log12) {
             waves = log_waves;
@@ -1382,14 +1426,17 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
         else if (ncs == 3) FMTC_DECC(3, LAY, AL, 4);                                                             \
         else { if (waves == 8) FMTC_DECC(4, LAY, AL, 8); else FMTC_DECC(4, LAY, AL, 4); }                        \
     } while (0)
-        if (waves == 16) { if (ncs == 1) FMTC_DECC_F(1, FMTC_NHWC, true, 16, 32, false); else FMTC_DECC_F(2, FMTC_NHWC, true, 16, 64, false); }
-        else if (log12) {
-            if (C == 128) { if (nlo) FMTC_DECC_L(4, FMTC_NHWC, true, 12, 128, true, 2); else FMTC_DECC_L(4, FMTC_NHWC, true, 12, 128, true, 0); }
-            else { if (nlo) FMTC_DECC_L(5, FMTC_NHWC, true, 8, 144, true, 3); else FMTC_DECC_L(5, FMTC_NHWC, true, 8, 144, true, 0); }
-        }
+#define FMTC_DECC_FIXED(LAY)                                                                                     \
+    do {                                                                                                         \
+        if (waves == 16) { if (ncs == 1) FMTC_DECC_F(1, LAY, true, 16, 32, false); else FMTC_DECC_F(2, LAY, true, 16, 64, false); } \
+        else if (C == 128) { if (nlo) FMTC_DECC_L(4, LAY, true, 12, 128, true, 2); else FMTC_DECC_L(4, LAY, true, 12, 128, true, 0); } \
+        else { if (nlo) FMTC_DECC_L(5, LAY, true, 8, 144, true, 3); else FMTC_DECC_L(5, LAY, true, 8, 144, true, 0); } \
+    } while (0)
+        if (waves == 16 || log12) { if (layout == FMTC_NHWC) FMTC_DECC_FIXED(FMTC_NHWC); else FMTC_DECC_FIXED(FMTC_NCHW); }
         else if (ncs == 5) { if (al) FMTC_DECC(5, FMTC_NHWC, true, 4); else FMTC_DECC(5, FMTC_NHWC, false, 4); }
         else if (layout == FMTC_NHWC) { if (al) FMTC_DECC_N(FMTC_NHWC, true); else FMTC_DECC_N(FMTC_NHWC, false); }
         else                          { if (al) FMTC_DECC_N(FMTC_NCHW, true); else FMTC_DECC_N(FMTC_NCHW, false); }
+#undef FMTC_DECC_FIXED
 #undef FMTC_DECC_N
 #undef FMTC_DECC
 #undef FMTC_DECC_F

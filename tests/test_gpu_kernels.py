@@ -133,3 +133,41 @@ def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
     # differences only where the fp64 value is at a rounding boundary (1e-9 steps: the order of an fp64 sum)
     assert not diff.any() or margin.reshape(P, C)[diff].max() <= 1e-9, f"{int(diff.sum())} symbols differ"
     assert hist.tolist() == np.bincount(got.reshape(-1), minlength=256).tolist()
+
+
+# Planar decoder variants built for one channel count (32, 64: more than 3072 chunks; 128, 144: more than 2048), the
+# shared one below that; images larger and smaller than a chunk, chunks across images, ragged last chunks, both sizes of
+# payload buffers (4 and 8 bits), another chunk size than the nominal one.
+PLANAR_CASES = [  # C, H, W, N, bits, chunk
+    (32, 13, 11, 2751, 4, 4096), (64, 57, 61, 58, 6, 4096), (64, 3, 5, 13200, 8, 4096), (64, 40, 40, 8, 5, 4096),
+    (128, 7, 7, 1350, 4, 4096), (128, 1, 1, 66001, 8, 4096), (128, 31, 33, 66, 6, 3968), (128, 9, 9, 30, 5, 4096),
+    (144, 19, 17, 180, 5, 4096), (144, 7, 7, 1181, 8, 4096), (144, 14, 14, 20, 6, 4096),
+]
+
+
+@pytest.mark.parametrize("C,H,W,N,bits,chunk", PLANAR_CASES, ids=["_".join(map(str, c)) for c in PLANAR_CASES])
+def test_planar_decoder(fmtc, oracle, C, H, W, N, bits, chunk):
+    from paper_1905_10830_amd import synth
+
+    rng = np.random.default_rng(C + H)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    mu = rng.standard_normal(C).astype(np.float32)
+    P, A = N * H * W, np.float32(4.0)
+    d = oracle.delta(A, bits)
+    level = np.clip(np.rint(rng.laplace(0.0, 0.08 * (1 << bits), (P, C))), -(1 << (bits - 1)), (1 << (bits - 1)) - 1)
+    sym = (level + (1 << (bits - 1))).astype(np.uint8)
+    stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, float(d), chunk)
+    basis = fmtc.basis_import(T, mu, A)
+    torch.cuda.synchronize()
+    n = int(nbytes.item())
+    ref = (level * float(d)) @ T.astype(np.float64) + mu
+    # 22-bit basis entries and C fp32 additions, each relative to the sum of the products' magnitudes
+    tol = (2.0 ** -22 + C * 2.0 ** -24) * ((np.abs(level) * float(d)) @ np.abs(T.astype(np.float64)) + np.abs(mu)) + 1e-7
+    for tag in (synth.NCHW, synth.NHWC):
+        shape = (N, C, H, W) if tag == synth.NCHW else (N, H, W, C)
+        out, err = fmtc.decode(basis, stream, shape, bits, tag, nbytes=n)
+        torch.cuda.synchronize()
+        assert int(err.item()) == 0
+        out = out.cpu().numpy()
+        out = (out.transpose(0, 2, 3, 1) if tag == synth.NCHW else out).reshape(P, C)
+        assert (np.abs(out - ref) <= tol).all(), f"largest error {np.abs(out - ref).max():.3e}"
