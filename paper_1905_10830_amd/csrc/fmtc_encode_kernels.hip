@@ -978,7 +978,7 @@ void k_project_quantize_rows(RowParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// 128 to 160 channels, channels last, a multiple of 16 of them: the same projection with the loops the other way
+// 112 to 160 channels, a multiple of 16 of them: the same projection with the loops the other way
 // round.  k_project_quantize_rows holds a whole pixel tile twice (the fp32 values of the next tile on their way in, the
 // two f16 parts of this one) and one or two pairs of accumulators: 350 to 450 registers at four and five coefficient
 // tiles, one wavefront per SIMD -- where a vector instruction issues every 8 clocks instead of every 4 and nothing
@@ -991,7 +991,10 @@ void k_project_quantize_rows(RowParams p) {
 // the clamp of the quantizer keeps the histogram index in range whatever the value.
 // ---------------------------------------------------------------------------
 // NJA: the tensor's channel count / 16 (the launcher checks it), 2 NCT - 1 or 2 NCT.
-template <int NCT, int WAVES, int NJA>
+// Planar tensors: a channel's plane starts at a wavefront-uniform address (image of the tile's first pixel) and a lane's
+// place in it is one 32-bit offset (the launcher checks that it fits), so the loads of 16 channels per lane and pair
+// take no 64-bit address each -- which is what the registers of k_project_quantize_rows go to there.
+template <int NCT, int WAVES, int NJA, int LAYOUT>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4)))
 void k_project_quantize_stream(RowParams p) {
     constexpr int THREADS = WAVES * 64;
@@ -1013,26 +1016,54 @@ void k_project_quantize_stream(RowParams p) {
     constexpr int C = 16 * NJA;
     typedef float f4_t __attribute__((ext_vector_type(4)));
 
-    // this lane's channels [16 j + 8 half, + 8) of its pixel, steps 2 pr and 2 pr + 1, of pixel tile `tile`
-    auto load_pair = [&](int64_t tile, int pr, f4_t (&buf)[2][2]) __attribute__((always_inline)) {
-        int64_t px = tile * 32 + l32;
-        px = px < p.P ? px : p.P - 1;  // rows past the tensor repeat its last pixel; never stored or counted
-        const f4_t* row = reinterpret_cast<const f4_t*>(p.x + px * C) + 2 * half;
+    // where a tile's pixels lie: this lane's row, or (planar) channel 0 of the image that the tile starts in and this
+    // lane's offset from there (pixel and half)
+    struct Place {
+        const char* base;
+        uint32_t off;
+    };
+    auto place_of = [&](int64_t tile) __attribute__((always_inline)) {
+        Place at{};
+        if constexpr (LAYOUT == FMTC_NHWC) {
+            int64_t px = tile * 32 + l32;
+            px = px < p.P ? px : p.P - 1;  // rows past the tensor repeat its last pixel; never stored or counted
+            at.base = reinterpret_cast<const char*>(p.x + px * C + 8 * half);
+        } else {
+            const uint32_t HW = (uint32_t)p.HW, P = (uint32_t)p.P, px0 = (uint32_t)tile * 32u;
+            const uint32_t px = px0 + (uint32_t)l32 < P ? px0 + (uint32_t)l32 : P - 1u;
+            const uint32_t n0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(px0 / HW)), n = px / HW;
+            at.off = 4u * ((n - n0) * (uint32_t)C * HW + (px - n * HW) + 8u * (uint32_t)half * HW);
+            at.base = reinterpret_cast<const char*>(p.x) + (uint64_t)n0 * (uint64_t)(4 * C) * HW;
+        }
+        return at;
+    };
+    // this lane's channels [16 j + 8 half, + 8) of its pixel, steps 2 pr and 2 pr + 1
+    auto load_pair = [&](const Place& at, int pr, f4_t (&buf)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < 2; u++) {
             const int j = 2 * pr + u;
             if (j < NJ && j < NJA) {  // wavefront-uniform
-                buf[u][0] = row[4 * j];
-                buf[u][1] = row[4 * j + 1];
+                if constexpr (LAYOUT == FMTC_NHWC) {
+                    const f4_t* row = reinterpret_cast<const f4_t*>(at.base);
+                    buf[u][0] = row[4 * j];
+                    buf[u][1] = row[4 * j + 1];
+                } else {
+                    const uint64_t plane_bytes = 4u * (uint64_t)(uint32_t)p.HW;
+                    const char* plane = at.base + (uint64_t)(16 * j) * plane_bytes;
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        buf[u][e >> 2][e & 3] = *reinterpret_cast<const float*>(plane + (uint64_t)e * plane_bytes + at.off);
+                }
             }
         }
     };
     const int64_t stride = (int64_t)gridDim.x * WAVES;
     int64_t tile = (int64_t)blockIdx.x * WAVES + wave;
     f4_t bufA[2][2], bufB[2][2];
+    Place here = place_of(tile < p.n_tiles ? tile : 0);
     if (tile < p.n_tiles) {
-        load_pair(tile, 0, bufA);
-        if (NP > 1) load_pair(tile, 1, bufB);
+        load_pair(here, 0, bufA);
+        if (NP > 1) load_pair(here, 1, bufB);
     }
     zero_coder_scratch(p.ctrl, p.lookback, p.n_groups);
     {
@@ -1078,11 +1109,17 @@ void k_project_quantize_stream(RowParams p) {
             const int k = (int)(e & 255u), pl = (int)((e >> 8) & 31u);
             const uint32_t old = e >> 13;
             const int64_t qpx = (int64_t)fix_tile[idx < (uint32_t)kFixList ? idx : 0] * 32 + pl;
+            int64_t xbase = qpx * C, xstride = 1;
+            if constexpr (LAYOUT == FMTC_NCHW) {
+                const int64_t n_img = active ? qpx / p.HW : 0;
+                xbase = n_img * (int64_t)C * p.HW + (qpx - n_img * p.HW);
+                xstride = p.HW;
+            }
             double part = 0.0;
             if (active)
 #pragma unroll 5
                 for (int c = lane & 15; c < C; c += 16)
-                    part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[qpx * C + c] - (double)s_mu[c]);
+                    part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)s_mu[c]);
 #pragma unroll
             for (int o = 8; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the 16-lane group
             double qd = rint(part / (double)p.delta);
@@ -1103,6 +1140,7 @@ void k_project_quantize_stream(RowParams p) {
     auto tile_body = [&](auto swap_c, const int64_t tile) __attribute__((always_inline)) {
         constexpr bool SWAP = decltype(swap_c)::value;
         const int64_t next_tile = tile + stride;
+        const Place next = place_of(next_tile < p.n_tiles ? next_tile : 0);
         const int64_t px = tile * 32 + l32;
         const bool px_ok = px < p.P;
         floatx16 am[NCT], ac[NCT];
@@ -1153,11 +1191,12 @@ void k_project_quantize_stream(RowParams p) {
             }
             const int npr = pr + 2;
             if (npr < NP) {
-                if (in_b) load_pair(tile, npr, bufB); else load_pair(tile, npr, bufA);
+                if (in_b) load_pair(here, npr, bufB); else load_pair(here, npr, bufA);
             } else if (next_tile < p.n_tiles && npr - NP < NP) {
-                if (in_b) load_pair(next_tile, npr - NP, bufB); else load_pair(next_tile, npr - NP, bufA);
+                if (in_b) load_pair(next, npr - NP, bufB); else load_pair(next, npr - NP, bufA);
             }
         }
+        here = next;
         n2 += __shfl_xor(n2, 32, 64);  // the other half of the pixel
         const bool force = !(n2 < 1.0e9f);  // too large for f16 (or not finite): every coefficient decided exactly
         const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
@@ -1256,6 +1295,12 @@ void k_project_quantize_stream(RowParams p) {
     }
 }
 
+// Planar tensors: do a lane's offsets from the start of the image that its pixel tile starts in (at most 32 pixels and
+// an image further on, eight channels into it) and the pixel indices fit 32 bits?
+static bool planar_offsets_fit(int C, int64_t P, int64_t HW) {
+    return (uint64_t)C * ((uint64_t)HW + 32u) + 9u * (uint64_t)HW < (1ull << 30) && (uint64_t)P + 64u < (1ull << 31);
+}
+
 static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
                               int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
     RowParams p{};
@@ -1314,31 +1359,33 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     *n_parts = (int)gx;
     const bool vec = vec0;
     hipError_t el = hipSuccess;
-    // Four and five coefficient tiles, channels last, a multiple of 16 channels: the streaming form, four wavefronts.
+    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, four wavefronts.
     // (Measured: 144 channels, 28.9 M values, 79 -> 62 us; 128 channels, 3.2 M values, 15.9 -> 13.6 us.  With more
     // tiles than SIMDs at four coefficient tiles the eight-wavefront form of k_project_quantize_rows below stays: 50 us
     // at 25.7 M values against 53 us for this kernel with four wavefronts and 48 to 58 us with eight, whose registers
-    // fit or spill with the compiler's schedule.)
-    if ((nct == 5 || (nct == 4 && !eight)) && layout == FMTC_NHWC && (b.C % 16) == 0) {
+    // fit or spill with the compiler's schedule.  Planar: 128 channels, N = 256, 28 x 28 75 us in
+    // k_project_quantize_rows, 55.7 here; N = 32 16.7 and 11.7; 144 channels, N = 64, 28 x 28 42.9 in the tiled product,
+    // 26.1 here, with half of the basis truncated 28.1 and 23.8.)
+    if ((nct == 5 || (nct == 4 && !eight)) && (b.C % 16) == 0 && (layout == FMTC_NHWC || planar_offsets_fit(b.C, P, HW))) {
         const int swaves = 4;
         const bool whole = b.C == nct * 32;  // else 16 channels less
         const size_t slds = lds_for(swaves);
         int64_t sgx = (p.n_tiles + swaves - 1) / swaves;
         if (sgx > 256) sgx = 256;  // one workgroup per compute unit (the basis takes 64 to 100 KB of its LDS)
         *n_parts = (int)sgx;
-#define FMTC_STREAM_J(NCT, WV, NJA)                                                                              \
+#define FMTC_STREAM_J(NCT, WV, NJA, LAY)                                                                         \
     do {                                                                                                         \
-        hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_project_quantize_stream<NCT, WV, NJA>), \
+        hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_project_quantize_stream<NCT, WV, NJA, LAY>), \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)slds);             \
         if (ea != hipSuccess) return ea;                                                                         \
-        el = launch(K_PROJECT, k_project_quantize_stream<NCT, WV, NJA>, dim3((unsigned)sgx), dim3(WV * 64), slds, s, p); \
+        el = launch(K_PROJECT, k_project_quantize_stream<NCT, WV, NJA, LAY>, dim3((unsigned)sgx), dim3(WV * 64), slds, s, p); \
     } while (0)
-#define FMTC_STREAM(NCT, WV)                                                                                     \
+#define FMTC_STREAM(NCT, WV, LAY)                                                                                \
     do {                                                                                                         \
-        if (whole) FMTC_STREAM_J(NCT, WV, 2 * NCT); else FMTC_STREAM_J(NCT, WV, 2 * NCT - 1);                    \
+        if (whole) FMTC_STREAM_J(NCT, WV, 2 * NCT, LAY); else FMTC_STREAM_J(NCT, WV, 2 * NCT - 1, LAY);          \
     } while (0)
-        if (nct == 5) FMTC_STREAM(5, 4);
-        else FMTC_STREAM(4, 4);
+        if (layout == FMTC_NHWC) { if (nct == 5) FMTC_STREAM(5, 4, FMTC_NHWC); else FMTC_STREAM(4, 4, FMTC_NHWC); }
+        else                     { if (nct == 5) FMTC_STREAM(5, 4, FMTC_NCHW); else FMTC_STREAM(4, 4, FMTC_NCHW); }
 #undef FMTC_STREAM_J
 #undef FMTC_STREAM
         return el;
@@ -2132,9 +2179,9 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
                                    float delta, int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts,
                                    hipStream_t s) {
     const int64_t P = N * HW;
-    // 160 padded channels still fit the one-wavefront-per-32-pixels kernel for channels-last tensors (planar
-    // loads take more registers than it has left)
-    if (b.Cpad <= 128 || (b.Cpad == 160 && layout == FMTC_NHWC))
+    // 160 padded channels still fit the one-wavefront-per-32-pixels kernels; for planar tensors only the streaming form,
+    // with 32-bit offsets, whole groups of 16 channels and room in LDS for the histograms beside the basis (not at 8 bits)
+    if (b.Cpad <= 128 || (b.Cpad == 160 && (layout == FMTC_NHWC || (b.C % 16 == 0 && bits < 8 && planar_offsets_fit(b.C, P, HW)))))
         return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     // wide: the tiled matrix product needs whole groups of 16 channels; other channel counts keep the pixel-tile kernel
     if (b.C % 16 == 0) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);

@@ -109,11 +109,10 @@ def test_packer_of_large_tensors(fmtc, oracle, P, C, bits, chunk, kind):
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
 
 
-@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
-@pytest.mark.parametrize("C,P,bits", WIDE_CASES, ids=[f"C{c[0]}P{c[1]}b{c[2]}" for c in WIDE_CASES])
-def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
+def check_projection(fmtc, oracle, C, N, H, W, bits, layout):
     from paper_1905_10830_amd import synth
 
+    P = N * H * W
     rng = np.random.default_rng(C)
     T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
     mu = rng.standard_normal(C).astype(np.float32)
@@ -122,17 +121,34 @@ def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
     A = np.float32(4.0)
     y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
     sym, margin = oracle.quantize(y, oracle.delta(A, bits), bits, want_margin=True)
-    H = next(h for h in (10, 7, 5, 3, 2, 1) if P % h == 0)
-    tag = synth.NHWC if layout == "nhwc" else synth.NCHW
-    xs = x.reshape(1, H, P // H, C)
+    xs = x.reshape(N, H, W, C)
     xs = xs if layout == "nhwc" else np.ascontiguousarray(xs.transpose(0, 3, 1, 2))
-    got, hist = fmtc.quantize(fmtc.basis_import(T, mu, A), dev(xs), bits, tag)
+    got, hist = fmtc.quantize(fmtc.basis_import(T, mu, A), dev(xs), bits, synth.NHWC if layout == "nhwc" else synth.NCHW)
     torch.cuda.synchronize()
     got, hist = got.cpu().numpy().reshape(P, C), hist.cpu().numpy()
     diff = got != sym.reshape(P, C)
     # differences only where the fp64 value is at a rounding boundary (1e-9 steps: the order of an fp64 sum)
     assert not diff.any() or margin.reshape(P, C)[diff].max() <= 1e-9, f"{int(diff.sum())} symbols differ"
     assert hist.tolist() == np.bincount(got.reshape(-1), minlength=256).tolist()
+
+
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("C,P,bits", WIDE_CASES, ids=[f"C{c[0]}P{c[1]}b{c[2]}" for c in WIDE_CASES])
+def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
+    H = next(h for h in (10, 7, 5, 3, 2, 1) if P % h == 0)
+    check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
+
+
+# Planar projection of 112 to 160 channels: even and odd numbers of 32-channel pairs with and without a half step, tiles
+# across one and many images, ragged last tiles, fewer and more tiles than wavefronts; 8 bits (five coefficient tiles: the
+# tiled kernel, for LDS).
+PLANAR_PROJECTION_CASES = [(112, 40, 29, 31, 5), (128, 3, 1, 1, 6), (128, 700, 7, 7, 8), (128, 4100, 3, 3, 4), (144, 170, 14, 15, 7),
+                           (144, 1, 5, 5, 3), (144, 50, 9, 9, 8), (160, 36, 31, 31, 4), (160, 2000, 1, 1, 7)]
+
+
+@pytest.mark.parametrize("C,N,H,W,bits", PLANAR_PROJECTION_CASES, ids=["_".join(map(str, c)) for c in PLANAR_PROJECTION_CASES])
+def test_planar_projection(fmtc, oracle, C, N, H, W, bits):
+    check_projection(fmtc, oracle, C, N, H, W, bits, "nchw")
 
 
 # Planar decoder variants built for one channel count (32, 64: more than 3072 chunks; 128, 144: more than 2048), the
