@@ -100,7 +100,7 @@ def summarize(args):
     cmd = f"python3 bench.py --workload {args.workload} --bits {args.bits} --main-only"
     out = [f"rocprofv3 summary: bench.py --main-only on workload {args.workload}, b = {args.bits}, fp32 NHWC, "
            "4096-symbol chunks, one MI355X.",
-           "Commands (from the repository root, on the GPU box; the summary is written by",
+           "Commands (from the repository root; the summary is written by",
            f"  python3 bench.py --summarize STATS FETCH WRITE --workload {args.workload} --bits {args.bits}):",
            f"  rocprofv3 --kernel-trace --stats -d STATS -o run --output-format csv -- {cmd} --steps 100 --warmup 10",
            f"  rocprofv3 --kernel-trace --pmc FETCH_SIZE -d FETCH -o run --output-format csv -- {cmd} --steps 10 --warmup 2",
