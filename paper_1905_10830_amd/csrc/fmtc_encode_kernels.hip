@@ -539,6 +539,27 @@ void k_project_quantize_rows(RowParams p) {
                     xr[8 * j + 4 * q] = v.x; xr[8 * j + 4 * q + 1] = v.y;
                     xr[8 * j + 4 * q + 2] = v.z; xr[8 * j + 4 * q + 3] = v.w;
                 }
+        } else if constexpr (LAYOUT == FMTC_NCHW && VEC && !FUSED) {
+            // A multiple of 16 channels, 32-bit offsets (see k_project_quantize_stream for the addresses); rows past the
+            // tensor repeat its last pixel.  With a 64-bit address and a test per value these registers spilled: 64
+            // channels, N = 256, 56 x 56 95 -> 57 us; 96 channels, N = 64, 28 x 28 22 -> 14.6; 32 channels 14.4 -> 11.5.
+            const uint32_t HW = (uint32_t)p.HW, P = (uint32_t)p.P, px0 = (uint32_t)tile * 32u;
+            const uint32_t q = px0 + (uint32_t)l32 < P ? px0 + (uint32_t)l32 : P - 1u;
+            const uint32_t n0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(px0 / HW)), n = q / HW;
+            const uint32_t off = 4u * ((n - n0) * (uint32_t)C * HW + (q - n * HW) + 8u * (uint32_t)half * HW);
+            const uint64_t plane_bytes = 4u * (uint64_t)HW;
+            const char* image = reinterpret_cast<const char*>(p.x) + (uint64_t)n0 * (uint64_t)(uint32_t)C * plane_bytes;
+#pragma unroll
+            for (int j = 0; j < NJ; j++) {
+                if (16 * j < C) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        xr[8 * j + e] = *reinterpret_cast<const float*>(image + (uint64_t)(16 * j + e) * plane_bytes + off);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) xr[8 * j + e] = 0.f;
+                }
+            }
         } else {
             int64_t base = 0, stride = 1;
             if constexpr (LAYOUT == FMTC_NHWC) {
@@ -1357,7 +1378,8 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     const int64_t cap = 256 * (int64_t)per_cu;
     if (gx > cap) gx = cap;
     *n_parts = (int)gx;
-    const bool vec = vec0;
+    // planar: vec = a multiple of 16 channels and offsets within the images of a pixel tile that fit 32 bits
+    const bool vec = layout == FMTC_NHWC ? vec0 : b.C % 16 == 0 && planar_offsets_fit(b.C, P, HW);
     hipError_t el = hipSuccess;
     // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, four wavefronts.
     // (Measured: 144 channels, 28.9 M values, 79 -> 62 us; 128 channels, 3.2 M values, 15.9 -> 13.6 us.  With more
@@ -1412,7 +1434,9 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     } else if (nct == 5) {  // channels-last only (see launch_project_quantize)
         if (vec) FMTC_ROWS(5, FMTC_NHWC, true); else FMTC_ROWS(5, FMTC_NHWC, false);
     } else if (layout == FMTC_NHWC) { if (vec) FMTC_ROWS_N(FMTC_NHWC, true); else FMTC_ROWS_N(FMTC_NHWC, false); }
-    else                            { if (vec) FMTC_ROWS_N(FMTC_NCHW, true); else FMTC_ROWS_N(FMTC_NCHW, false); }
+    else if (vec) {  // (four coefficient tiles with such offsets: the streaming form above)
+        if (nct == 1) FMTC_ROWS(1, FMTC_NCHW, true); else if (nct == 2) FMTC_ROWS(2, FMTC_NCHW, true); else FMTC_ROWS(3, FMTC_NCHW, true);
+    } else FMTC_ROWS_N(FMTC_NCHW, false);
 #undef FMTC_ROWS_N
 #undef FMTC_ROWS
 #undef FMTC_ROWS_W

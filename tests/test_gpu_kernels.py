@@ -139,10 +139,11 @@ def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
     check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
 
 
-# Planar projection of 112 to 160 channels: even and odd numbers of 32-channel pairs with and without a half step, tiles
+# Planar projection of up to 160 channels: even and odd numbers of 32-channel pairs with and without a half step, tiles
 # across one and many images, ragged last tiles, fewer and more tiles than wavefronts; 8 bits (five coefficient tiles: the
-# tiled kernel, for LDS).
-PLANAR_PROJECTION_CASES = [(112, 40, 29, 31, 5), (128, 3, 1, 1, 6), (128, 700, 7, 7, 8), (128, 4100, 3, 3, 4), (144, 170, 14, 15, 7),
+# tiled kernel, for LDS); a channel count that is no multiple of 16.
+PLANAR_PROJECTION_CASES = [(16, 300, 11, 13, 8), (32, 2, 3, 3, 4), (32, 5000, 1, 1, 6), (48, 90, 27, 27, 5), (64, 16, 57, 61, 6),
+                           (64, 5000, 3, 5, 4), (80, 300, 14, 14, 8), (96, 33, 31, 29, 5), (100, 40, 9, 9, 5), (112, 40, 29, 31, 5), (128, 3, 1, 1, 6), (128, 700, 7, 7, 8), (128, 4100, 3, 3, 4), (144, 170, 14, 15, 7),
                            (144, 1, 5, 5, 3), (144, 50, 9, 9, 8), (160, 36, 31, 31, 4), (160, 2000, 1, 1, 7)]
 
 
