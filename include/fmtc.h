@@ -320,8 +320,9 @@ fmtc_status fmtc_profile_copy(void *d_dst, const void *d_src, size_t bytes, void
 /* Test support (not part of the method): forces one of two equivalent paths so
  * that a test can compare them.  option 0, value 1: fmtc_encode_static always
  * runs projection and packing as two kernels; option 1, value 1: the decoder of
- * wide tensors walks all channel groups of a tile in one workgroup.  Value 0
- * restores the library's own choice.  Process-wide. */
+ * wide tensors walks all channel groups of a tile in one workgroup.  Option 2,
+ * value 1: the packer of large tensors gives up its waits at once (the stream
+ * is left invalid).  Value 0 restores the library's own choice.  Process-wide. */
 fmtc_status fmtc_test_option(int option, int value);
 
 /* Text of the last error on the calling thread ("" if none). */

@@ -550,11 +550,11 @@ def stream_info(header_bytes):
                 delta=dlt.value, payload_bits=pbits.value, stream_bytes=sbytes.value)
 
 
-TEST_STATIC_TWO_KERNELS, TEST_DECODE_ONE_ROW = 0, 1
+TEST_STATIC_TWO_KERNELS, TEST_DECODE_ONE_ROW, TEST_SHORT_WAITS = 0, 1, 2
 
 
 def test_option(option, value):
-    """Forces one of two equivalent paths (tests only); value 0 restores the library's own choice."""
+    """Forces a path or the end of a wait (tests only); value 0 restores the library's own choice."""
     _check(load_library().fmtc_test_option(int(option), int(value)))
 
 

@@ -17,6 +17,7 @@
 #include "fmtc_device.h"
 #include "fmtc_internal.h"
 #include "fmtc_pack_device.h"
+#include "fmtc_pack_turns.h"
 
 namespace fmtc {
 
@@ -568,15 +569,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // Large tensors (more chunk groups than the device holds pack workgroups): one pass over the symbols.
 // One workgroup of 16 wavefronts per compute unit: 15 pack, the 16th finds out where the chunks go.  A turn is a group of
 // 15 chunks; the packers take its chunks one by one (a fixed chunk per wavefront and turn left the wavefronts of a SIMD
-// up to three turns apart, and a turn waits for its last one).  Groups are claimed from a counter, so a group's predecessors have all been claimed by workgroups
-// that run; a group's size is published when its images are built, and its place is the sum of the sizes before it
-// (added up by one wavefront of the device).
+// up to three turns apart, and a turn waits for its last one), though of a turn no more than they have images for (see
+// deal).  Groups are claimed from a counter, so a group's predecessors have all been claimed by workgroups that run; a
+// group's size is published when its images are built, and its place is the sum of the sizes before it (added up by one
+// wavefront of the device).
 // A place is known 4 to 5 us after the group is packed, longer than a turn: a packer keeps up to three images waiting
 // in its part of the LDS (one or two where the code is longer, see images_for) and goes on with its next chunk, and the
-// 16th wavefront publishes a size as soon as it is there, between polls for the places of earlier groups.  The wavefronts of a workgroup meet in LDS counters and not in
-// barriers.  A size is published without waiting for any later group, so whatever shares the device the lowest
-// unpublished group can always go on; the wait for another workgroup is bounded all the same and ends in an invalid
-// stream.
+// 16th wavefront publishes a size as soon as it is there, between polls for the places of earlier groups.  The
+// wavefronts of a workgroup meet in LDS counters and not in barriers.  A size is published without waiting for any later
+// group, so whatever shares the device the lowest unpublished group can always go on.  The 16th wavefront's waits are
+// bounded all the same: it ends them in an invalid stream and sends its packers, which wait for nobody else, home.
 // Every workgroup builds the code table for itself (the first group's ticket and symbols arrive meanwhile).
 // (Before: a table kernel, a size pass over all chunks, a one-workgroup scan and a packing pass at known places.)
 //
@@ -584,9 +586,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // eight neighbouring symbols per step, and up to 6 bits the table holds the joined code words of symbol pairs: four
 // lookups, one prefix sum over the lanes and two or three ORs into the image per 512 symbols.
 // ---------------------------------------------------------------------------
-constexpr int kStreamWaves = 15;        // packing wavefronts per workgroup = chunks per group
 constexpr uint32_t kStreamRoom = 2064;  // words a packer has for its images, each with 4 spare ones (see PackShared)
-constexpr uint32_t kSlots = 16;         // what a turn leaves in LDS is kept by turn modulo kSlots (see below)
 constexpr uint32_t kShortCode = 26;     // a table entry holds up to 26 code bits below 6 bits of length ...
 constexpr uint32_t kNoCode = 63u << kShortCode;  // ... or says that the code word is longer: any eight symbols with
                                         // such an entry come to more than 64 bits
@@ -600,8 +600,8 @@ struct StreamShared {
     uint32_t done[kSlots];                                         // packers that have left theirs (counted over all turns)
     unsigned long long place[kSlots];                              // first payload word of the group
     uint32_t ticket[kSlots];                                       // the group
-    uint32_t placed, drawn;                                        // turns whose place / whose group is known
-    uint32_t dealt;                                                // chunks taken by the packers, over all turns
+    uint32_t placed, drawn;                                        // turns whose place / whose group is known, or kGone
+    uint32_t dealt;                                                // which chunk is next (see deal)
     unsigned long long payload_bits;
     uint32_t codes[1];                                             // [4096] (pairs) or [256]: code | length << 26
 };
@@ -868,7 +868,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     StreamShared& S = *reinterpret_cast<StreamShared*>(dyn_lds);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool packer = wave < kStreamWaves;  // wavefront-uniform
+    const bool packer = wave < (int)kStreamWaves;  // wavefront-uniform
     const uint32_t n_groups = (p.n_chunks + kStreamWaves - 1) / kStreamWaves;
     auto claim = [&]() -> uint32_t {
         return __hip_atomic_fetch_add(&p.ctrl->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     }
     // While the first wavefront builds the table, the others clear their images and request their first symbols.
     // (A ticket takes up to 4 us with all workgroups drawing theirs.)
-    if (tid == 64 * kStreamWaves) {
+    if (tid == 64 * (int)kStreamWaves) {
         S.ticket[0] = claim();
         post_lds(&S.drawn, 1u);
         S.ticket[1] = claim();
@@ -909,26 +909,41 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     auto ticket_of = [&](uint32_t turn) {
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)S.ticket[turn % kSlots]);
     };
-    auto wait_drawn = [&](uint32_t n) {  // (nobody draws while waiting for something)
-        while (peek_lds(&S.drawn) < n) __builtin_amdgcn_s_sleep(1);
+    // Until n turns are drawn / placed; false: they never will be.  (The 16th wavefront, which draws and places, waits
+    // for nothing without a limit, and ends these waits when it gives up.)
+    auto wait_for = [&](const uint32_t* count, uint32_t n) -> bool {
+        uint32_t v;
+        while ((v = peek_lds(count)) < n) __builtin_amdgcn_s_sleep(1);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)v) != kGone;
     };
     // The next chunk for this wavefront, as its number among those of the workgroup.  (Never waits: the ticket of its
     // turn may depend on the chunk the wavefront has at hand.)
-    auto take = [&]() -> uint32_t {
+    uint32_t own_turn = 0, own = 0;  // the latest turn of which it has taken chunks, and how many
+    auto take = [&](uint32_t most) -> uint32_t {
         uint32_t n = 0;
-        if (lane == 0) n = __hip_atomic_fetch_add(&S.dealt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        if (lane == 0) {
+            uint32_t state = __hip_atomic_load(&S.dealt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            Dealt d;
+            do {
+                d = deal(state, own_turn, own, most);
+            } while (!__hip_atomic_compare_exchange_strong(&S.dealt, &state, d.state, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            n = d.n;
+        }
+        n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        own = n / kStreamWaves == own_turn ? own + 1u : 1u;
+        own_turn = n / kStreamWaves;
+        return n;
     };
     // ... and its number among those of the tensor, once the ticket is known (past the last chunk: the chunk is empty;
     // past the last group: no more chunks)
-    auto chunk_of = [&](uint32_t n) { return ticket_of(n / kStreamWaves) * (uint32_t)kStreamWaves + n % kStreamWaves; };
+    auto chunk_of = [&](uint32_t n) { return ticket_of(n / kStreamWaves) * kStreamWaves + n % kStreamWaves; };
     auto have_group = [&](uint32_t n) { return ticket_of(n / kStreamWaves) < n_groups; };
     uint32_t n = 0;
     uint2 w[8];
     if (packer) {
         for (uint32_t i = lane; i < kStreamRoom; i += 64) S.image[wave][i] = 0u;
-        n = take();  // (of turn 0)
-        wait_drawn(1u);
+        n = take(2u);  // (of turn 0)
+        (void)wait_for(&S.drawn, 1u);
         if (have_group(n)) load_chunk_octets(p, chunk_of(n), lane, w);
     }
     __syncthreads();
@@ -960,7 +975,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             uint32_t* img = S.image[wave] + next_stored * (words + 4u);
             stored++;
             next_stored = next_stored + 1u < n_images ? next_stored + 1u : 0u;
-            const uint32_t other = lane < kStreamWaves ? S.words[slot][lane] : 0u;
+            const uint32_t other = lane < (int)kStreamWaves ? S.words[slot][lane] : 0u;
             const uint32_t n_words = (uint32_t)__builtin_amdgcn_readlane((int)other, (int)at);
             const unsigned long long place = S.place[slot];
             const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_sum((uint32_t)lane < at ? other : 0u));
@@ -984,13 +999,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
         };
         while (have_group(n)) {
-            const uint32_t n_next = take();
-            const bool early = peek_lds(&S.drawn) > n_next / kStreamWaves;  // its symbols arrive while this chunk is packed
+            const uint32_t n_next = take(n_images);
+            const uint32_t drawn = (uint32_t)__builtin_amdgcn_readfirstlane((int)peek_lds(&S.drawn));
+            if (drawn == kGone) return;
+            const bool early = drawn > n_next / kStreamWaves;  // its symbols arrive while this chunk is packed
             uint2 wn[8];
             if (early && have_group(n_next)) load_chunk_octets(p, chunk_of(n_next), lane, wn);
-            // images whose place is known leave, and one has to where all are waiting
-            while (stored < filled && (filled - stored >= n_images || peek_lds(&S.placed) > turn_of_oldest())) {
-                while (peek_lds(&S.placed) <= turn_of_oldest()) __builtin_amdgcn_s_sleep(1);  // (the wait behind it is bounded)
+            // images whose place is known leave, and one has to where all are waiting (its turn is before this chunk's)
+            while (stored < filled && stores_first(filled - stored, n_images, peek_lds(&S.placed), turn_of_oldest())) {
+                if (!wait_for(&S.placed, turn_of_oldest() + 1u)) return;
                 store();
             }
             const uint32_t ch = chunk_of(n);
@@ -1011,14 +1028,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             next_image = next_image + 1u < n_images ? next_image + 1u : 0u;
             n = n_next;
             if (!early) {
-                wait_drawn(n / kStreamWaves + 1u);
+                if (!wait_for(&S.drawn, n / kStreamWaves + 1u)) return;
                 if (have_group(n)) load_chunk_octets(p, chunk_of(n), lane, wn);
             }
 #pragma unroll
             for (int q = 0; q < 8; q++) w[q] = wn[q];
         }
         while (stored < filled) {
-            while (peek_lds(&S.placed) <= turn_of_oldest()) __builtin_amdgcn_s_sleep(1);
+            if (!wait_for(&S.placed, turn_of_oldest() + 1u)) return;
             store();
         }
         return;
@@ -1034,7 +1051,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     // runs, and it stays until every group has its place): it reads the published sizes in order, 256 at a time, and
     // writes the places, for which the others look at one word each.  (Every workgroup reading back over the sizes
     // before its own group, 4 KB a look, all at the same few cache lines, took 7 to 10 us per turn.)
-    wait_drawn(2u);
+    (void)wait_for(&S.drawn, 2u);
     uint32_t published = 0, placed = 0;
     uint32_t g = ticket_of(0);
     unsigned long long* sizes = p.lookback;
@@ -1045,13 +1062,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     uint32_t tries = 0;                 // looks without anything new
     while (g < n_groups || placed < published || (adder && added < n_groups)) {
         bool news = false;
-        if (g < n_groups && published - placed <= 2u && peek_lds(&S.done[published % kSlots]) == (uint32_t)kStreamWaves * (published / kSlots + 1u)) {
+        if (g < n_groups && may_publish(published, placed) && peek_lds(&S.done[published % kSlots]) == kStreamWaves * (published / kSlots + 1u)) {
             const uint32_t slot = published % kSlots;
-            unsigned long long size = lane < kStreamWaves ? S.words[slot][lane] : 0u;
+            unsigned long long size = lane < (int)kStreamWaves ? S.words[slot][lane] : 0u;
 #pragma unroll
             for (int o = 8; o > 0; o >>= 1) size += __shfl_xor(size, o, 64);
             if constexpr (STATIC) {
-                const uint32_t bits = wave_sum(lane < kStreamWaves ? S.bits[slot][lane] : 0u);
+                const uint32_t bits = wave_sum(lane < (int)kStreamWaves ? S.bits[slot][lane] : 0u);
                 if (lane == 0) {
                     // (the returned value is waited for: the bits are counted before the size can be seen)
                     const unsigned long long was = __hip_atomic_fetch_add(&p.ctrl->payload_bits, (unsigned long long)bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1091,16 +1108,29 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
             if (added == n_groups && lane == 0) {
                 chunk_off[p.n_chunks] = (uint32_t)total_words;
-                Header hdr = p.hdr;
-                hdr.payload_words = total_words;
+                // (word by word: a copy of the header on the stack is one that every lane of the kernel would write)
+                Header* hdr = reinterpret_cast<Header*>(p.stream);
+                hdr->version = p.hdr.version;
+                hdr->bits = p.hdr.bits;
+                hdr->reserved0 = p.hdr.reserved0;
+                hdr->C = p.hdr.C;
+                hdr->px_per_chunk = p.hdr.px_per_chunk;
+                hdr->P = p.hdr.P;
+                hdr->n_chunks = p.hdr.n_chunks;
+                hdr->sub_syms = p.hdr.sub_syms;
+                hdr->delta = p.hdr.delta;
+                hdr->subs_per_chunk = p.hdr.subs_per_chunk;
+                hdr->payload_words = total_words;
                 // (STATIC: every group has added its bits before it published its size)
-                hdr.payload_bits = STATIC ? __hip_atomic_load(&p.ctrl->payload_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                          : S.payload_bits;
-                // somebody gave up waiting, or the payload outgrew the buffer: not valid
-                if (__hip_atomic_load(&p.ctrl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || total_words > p.cap_words ||
-                    total_words > 0xffffffffull)
-                    hdr.magic = 0u;
-                *reinterpret_cast<Header*>(p.stream) = hdr;
+                hdr->payload_bits = STATIC ? __hip_atomic_load(&p.ctrl->payload_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                           : S.payload_bits;
+                hdr->reserved1 = p.hdr.reserved1;
+                // The magic last, past this part of the chip's cache: somebody who gives up waiting says so first and then
+                // clears the magic the same way, so one of the two sees it.
+                const bool fits = total_words <= p.cap_words && total_words <= 0xffffffffull;
+                publish32(&hdr->magic, fits ? p.hdr.magic : 0u);
+                __builtin_amdgcn_s_waitcnt(0);
+                if (__hip_atomic_load(&p.ctrl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) publish32(&hdr->magic, 0u);
                 if (p.out_bytes) *p.out_bytes = (uint64_t)p.off_payload + 4 * total_words;
                 // alignment gaps between the sections are part of the stream: keep them zero
                 for (size_t o = kHeaderBytes + kLenTableBytes + 4 * ((size_t)p.n_chunks + 1); o < p.off_sub_bits; o++) p.stream[o] = 0;
@@ -1108,16 +1138,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
         }
         if (placed < published) {
-            unsigned long long e = peek64(&places[ticket_of(placed)]);  // (one word, the same for all lanes)
-            // (limits that are never reached: seconds.  The others wait longer than the one that adds up, whose own wait
-            // for a size ends in an invalid stream.)
-            if (!e && tries >= (adder ? kSpinLimit : 2u * kSpinLimit)) {
-                e = kKnown - 1ull;  // (past any buffer: nothing is stored)
-                if (lane == 0) {
-                    __hip_atomic_fetch_or(&p.ctrl->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    *reinterpret_cast<volatile uint32_t*>(p.stream) = 0u;  // the header's magic, should it be there already
-                }
-            }
+            const unsigned long long e = peek64(&places[ticket_of(placed)]);  // (one word, the same for all lanes)
             if (e) {
                 if (lane == 0) {
                     S.place[placed % kSlots] = e & (kKnown - 1ull);
@@ -1128,8 +1149,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             }
         }
         tries = news ? 0u : tries + 1u;
-        if (tries > kSpinLimit && placed == published && g >= n_groups) {  // (only the adder waits here, for a size that never came)
-            if (lane == 0) *reinterpret_cast<volatile uint32_t*>(p.stream) = 0u;
+        // (a limit that is never reached: seconds.  The one that adds up gives up first where a size does not come.)
+        if (tries > (adder ? p.spin_limit : 2u * p.spin_limit)) {
+            if (lane == 0) {
+                const uint32_t was = __hip_atomic_fetch_or(&p.ctrl->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("" : : "v"(was) : "memory");  // (the returned value is waited for)
+                publish32(reinterpret_cast<uint32_t*>(p.stream), 0u);  // the header's magic
+                post_lds(&S.placed, kGone);
+                post_lds(&S.drawn, kGone);
+            }
             break;
         }
         if (!news) __builtin_amdgcn_s_sleep(1);
@@ -1187,6 +1215,7 @@ PackParams pack_params(const uint8_t* d_syms, const Geometry& g, int bits, float
     p.stream = d_stream;
     p.out_bytes = d_out_bytes;
     p.static_max_len = 0;
+    p.spin_limit = test_option(kTestShortWaits) ? 1u : kSpinLimit;
     return p;
 }
 

@@ -124,8 +124,9 @@ struct BasisDevice {
     const float* T;        // [C][C] row major, unpacked
 };
 
-// Path choices a test can force (fmtc_test_option in fmtc.h): both only pick between paths a caller reaches anyway.
-enum TestOption { kTestStaticTwoKernels = 0, kTestDecodeOneRow = 1, kTestOptionCount };
+// What a test can force (fmtc_test_option in fmtc.h): two choices between paths that a caller reaches anyway, and the end
+// of the waits inside the packer of large tensors.
+enum TestOption { kTestStaticTwoKernels = 0, kTestDecodeOneRow = 1, kTestShortWaits = 2, kTestOptionCount };
 int test_option(int which);  // current value (0 unless a test set it)
 
 // ---- optional per-kernel timing (fmtc_profile_* in fmtc.h) ----

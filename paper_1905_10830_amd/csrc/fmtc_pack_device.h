@@ -49,6 +49,7 @@ struct PackParams {
     Header hdr;
     size_t off_sub_bits, off_payload;
     uint64_t cap_words;          // payload words the output buffer has room for
+    uint32_t spin_limit;         // large tensors: polls before a wait gives up
     uint8_t* stream;
     uint64_t* out_bytes;
 };

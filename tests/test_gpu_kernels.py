@@ -104,6 +104,48 @@ def test_packer_of_large_tensors(fmtc, oracle, P, C, bits, chunk, kind):
     assert int(err.item()) == 0 and np.array_equal(back.cpu().numpy().reshape(-1), sym)
 
 
+# ... and more: (chunks, symbols a chunk, ...) of four to six turns per workgroup, of a last group of one chunk and of one
+# chunk less than whole groups.
+TURN_CASES = [(15 * 256 * 4 + 1, 66, 33, 6, "steep"), (15 * 256 * 6 - 1, 64, 16, 4, "gaps"), (15 * 256 * 5 + 1, 99, 9, 7, "gaps"),
+              (15 * 256 * 4 + 16, 33, 33, 8, "steep")]
+
+
+@pytest.mark.parametrize("n_chunks,chunk,C,bits,kind", TURN_CASES, ids=[f"n{c[0]}k{c[1]}b{c[3]}" for c in TURN_CASES])
+def test_packer_of_many_turns(fmtc, oracle, n_chunks, chunk, C, bits, kind):
+    V = n_chunks * chunk
+    counts = counts_of(kind, 1 << bits).astype(np.float64)
+    counts = np.where(counts > 0, np.maximum(1, counts * (V / counts.sum()) * 0.9), 0).astype(np.int64)
+    counts[counts.argmax()] += V - counts.sum()
+    sym = np.repeat(np.arange(1 << bits), counts).astype(np.uint8)
+    np.random.default_rng(n_chunks).shuffle(sym)
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, C, bits, 0.5, ln, oracle.canonical_codes(ln), max(chunk, 64))
+    stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, 0.5, max(chunk, 64))
+    torch.cuda.synchronize()
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
+def test_packer_of_large_tensors_gives_up_its_waits(fmtc, oracle):
+    """With the limit of its waits at once reached the kernel ends, leaves an invalid stream and harms no later call."""
+    C, bits, chunk, n_chunks = 16, 6, 64, 15 * 256 * 2
+    sym = symbols_with_counts(np.full(64, n_chunks * chunk // 64), 5, C)
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, C, bits, 0.5, ln, oracle.canonical_codes(ln), chunk)
+    for short in (1, 0):
+        fmtc.test_option(fmtc.TEST_SHORT_WAITS, short)
+        try:
+            stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, 0.5, chunk)
+            torch.cuda.synchronize()
+        finally:
+            fmtc.test_option(fmtc.TEST_SHORT_WAITS, 0)
+        if short:
+            assert int(stream[:4].view(torch.int32).item()) == 0
+            _, err = fmtc.decode_symbols(stream, len(sym) // C, C, bits)
+            torch.cuda.synchronize()
+            assert int(err.item()) & 1  # the header
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
 # Tiled projection of wide tensors, more 128 x 128 tiles than compute units: channel counts with and without a half step
 # of 16 at the end and with a last coefficient group of one to four tiles; ragged last tiles; a pixel beyond f16.
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
