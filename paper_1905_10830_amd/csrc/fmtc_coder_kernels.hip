@@ -920,16 +920,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     // turn may depend on the chunk the wavefront has at hand.)
     uint32_t own_turn = 0, own = 0;  // the latest turn of which it has taken chunks, and how many
     auto take = [&](uint32_t most) -> uint32_t {
-        uint32_t n = 0;
-        if (lane == 0) {
-            uint32_t state = __hip_atomic_load(&S.dealt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            Dealt d;
-            do {
-                d = deal(state, own_turn, own, most);
-            } while (!__hip_atomic_compare_exchange_strong(&S.dealt, &state, d.state, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            n = d.n;
+        // (in scalar registers: a dozen instructions, where one lane's branches took 2 us of the kernel at N = 256, C = 64)
+        uint32_t state = (uint32_t)__builtin_amdgcn_readfirstlane((int)peek_lds(&S.dealt));
+        Dealt d;
+        for (;;) {
+            d = deal(state, own_turn, own, most);
+            uint32_t was = state;
+            if (lane == 0) (void)__hip_atomic_compare_exchange_strong(&S.dealt, &was, d.state, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            was = (uint32_t)__builtin_amdgcn_readfirstlane((int)was);
+            if (was == state) break;
+            state = was;
         }
-        n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        const uint32_t n = d.n;
         own = n / kStreamWaves == own_turn ? own + 1u : 1u;
         own_turn = n / kStreamWaves;
         return n;
