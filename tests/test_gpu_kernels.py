@@ -146,6 +146,38 @@ def test_packer_of_large_tensors_gives_up_its_waits(fmtc, oracle):
     assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
 
 
+def coder_us(fmtc, sym, C, bits, chunk):
+    """Shortest of 40 coder runs in us (kernels after the histogram)."""
+    P = len(sym) // C
+    d = dev(sym)
+    stream = torch.empty(fmtc.encode_bound(P, C, bits, chunk), dtype=torch.uint8, device="cuda")
+    nbytes = torch.zeros(1, dtype=torch.int64, device="cuda")
+    work = torch.empty(fmtc.workspace_size(P, C, bits, chunk), dtype=torch.uint8, device="cuda")
+    fmtc.profile_enable(40)
+    try:
+        for _ in range(40):
+            fmtc.code_symbols(d, C, bits, 0.5, chunk, stream, nbytes, work)
+        torch.cuda.synchronize()
+        return 1e3 * sum(v[1] for k, v in fmtc.profile_read().items() if "histogram" not in k)
+    finally:
+        fmtc.profile_enable(0)
+
+
+def normal_symbols(n_chunks, chunk, bits, spread, seed):
+    rng = np.random.default_rng(seed)
+    half = 1 << (bits - 1)
+    x = rng.standard_normal((n_chunks, chunk), dtype=np.float32) * np.float32(spread)
+    return np.clip(np.rint(x), -half, half - 1).astype(np.int16) + half
+
+
+def test_packer_takes_any_chunk_size_at_the_same_rate(fmtc):
+    """Chunks that are no multiple of eight symbols (4092, measured: the same time as 4096; fetched byte by byte, 2.1 times)."""
+    n = 6000
+    even = coder_us(fmtc, normal_symbols(n, 4096, 6, 0.5, 3).astype(np.uint8).reshape(-1), 64, 6, 4096)
+    odd = coder_us(fmtc, normal_symbols(n, 4092, 6, 0.5, 3).astype(np.uint8).reshape(-1), 33, 6, 4096)
+    assert odd < 1.5 * even, f"{odd:.1f} us, {even:.1f} us for whole pieces"
+
+
 # Tiled projection of wide tensors, more 128 x 128 tiles than compute units: channel counts with and without a half step
 # of 16 at the end and with a last coefficient group of one to four tiles; ragged last tiles; a pixel beyond f16.
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
