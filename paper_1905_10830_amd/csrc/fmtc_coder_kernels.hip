@@ -654,7 +654,7 @@ __device__ __forceinline__ void align_chunk_octets(const PackParams& p, uint32_t
 }
 
 // How many images a packer's room is divided into, and their words: as many as hold a chunk of the average size and a
-// third more.  (A larger chunk is finished window by window from its symbols, at several times the cost.)
+// third more.  (A larger chunk is finished window by window from its symbols in memory.)
 struct StreamImages {
     uint32_t count, words;
 };
@@ -785,16 +785,18 @@ __device__ __forceinline__ void place_long_octet(uint32_t x, uint32_t y, uint32_
 
 // One chunk (`clen` symbols in w, see load_chunk_octets) into the first `words` words of its image.  Returns the chunk's
 // code bits and leaves the bit counts of its runs of 64 symbols (eight lanes; 64 of them, zeros past the end) in run_bits.
+// last_from: the last step that starts inside the image (see pack_window).
 // Two octets per lane and turn, 512 symbols apart: their chains run side by side, and one prefix sum over the lanes
 // serves both (16 bits each: a chunk has at most 64 x 8 x 48 bits in 512 symbols).
 template <bool PAIRS>
 __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t clen, const unsigned long long* tab,
                                                 const uint32_t* codes, uint32_t* img, uint32_t words, int lane,
-                                                uint16_t* run_bits) {
+                                                uint16_t* run_bits, uint32_t& last_from) {
     uint32_t base = 0;
     auto step = [&](uint32_t q, uint32_t x0, uint32_t y0, uint32_t x1, uint32_t y1, auto some_c) __attribute__((always_inline)) -> uint32_t {
         constexpr bool some = decltype(some_c)::value;
         const uint32_t f0 = 512u * q + 8u * (uint32_t)lane, f1 = f0 + 512u;
+        last_from = base < words * 32u ? (512u * q) | (base << 12) : last_from;
         const Octet a = look_up<PAIRS, some>(x0, y0, (int)(clen - f0), codes, tab);
         const Octet b = look_up<PAIRS, some>(x1, y1, (int)(clen - f1), codes, tab);
         uint32_t len_a = a.len, len_b = b.len;
@@ -874,26 +876,64 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
     return base;
 }
 
-// A later window [win, win + words) of a chunk too large for its image, symbol by symbol from memory (rare).
-__device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, const unsigned long long* tab,
-                                            uint32_t* img, uint32_t words, uint32_t win, int lane) {
+// A later window [win, win + words) of a chunk too large for its image, once more from the symbols in memory: an octet per
+// lane and step, the next step's symbols on their way meanwhile, from the step in which the window starts (from: its first
+// symbol | code bits before it << 12; afterwards the next window's) to the one that ends behind it.  Words outside the
+// window go to the image's spare ones.  (Chunks of flat and of busy regions differ several times in size, so a tensor
+// can have many such chunks.  Symbol by symbol, 64 per step, a window took some 50 us: 12544 chunks of which every tenth
+// is large, 118 us for the kernel, 61 this way, and 62 where every wavefront had one image of 2048 words.)
+template <bool PAIRS>
+__device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, const unsigned long long* tab, const uint32_t* codes,
+                                            uint32_t* img, uint32_t words, uint32_t win, int lane, uint32_t& from) {
     const uint32_t clen = chunk_len_of(p, ch);
-    const uint8_t* src = p.syms + (uint64_t)ch * p.chunk_syms;
-    uint32_t base = 0;
-#pragma unroll 1
-    for (uint32_t s0 = 0; s0 < clen; s0 += 64) {
-        const unsigned long long e = s0 + (uint32_t)lane < clen ? tab[src[s0 + lane]] : 0ull;
-        const uint32_t len = (uint32_t)(e >> 56);
-        uint32_t row, half;
-        const uint32_t incl = wave_inclusive_scan_rows(len, row, half), pos = base + incl - len;
-        const unsigned long long c = e & 0x00ffffffffffffffull;
+    const uint64_t at = (uint64_t)ch * p.chunk_syms;
+    const uint8_t* src = p.syms + at;
+    const int64_t room = (int64_t)(p.V - at) - 8;
+    const int last = room < 4096 ? (int)room : 4096;
+    auto load = [&](uint32_t o) {  // (see load_chunk_octets)
+        return o < clen ? load_octet(src + ((int)o < last ? (int)o : last)) : make_uint2(0u, 0u);
+    };
+    auto put = [&](unsigned long long c, uint32_t pos) {
         const uint32_t sh = pos & 31u, rel = (pos >> 5) - win;
         const unsigned long long t0 = c << sh;
-        const uint32_t t2 = sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u;
-        if (rel < words) atomicOr(&img[rel], (uint32_t)t0);
-        if (rel + 1u < words) atomicOr(&img[rel + 1u], (uint32_t)(t0 >> 32));
-        if (rel + 2u < words) atomicOr(&img[rel + 2u], t2);
+        atomicOr(&img[rel < words ? rel : words], (uint32_t)t0);
+        atomicOr(&img[rel + 1u < words ? rel + 1u : words], (uint32_t)(t0 >> 32));
+        atomicOr(&img[rel + 2u < words ? rel + 2u : words], sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
+    };
+    const uint32_t end = 32u * (win + words);
+    uint32_t base = from >> 12, s0 = from & 0xfffu;
+    uint2 next = load(s0 + 8u * (uint32_t)lane);
+#pragma unroll 1
+    for (; s0 < clen && base < end; s0 += 512u) {
+        from = s0 | (base << 12);
+        const uint32_t first = s0 + 8u * (uint32_t)lane;
+        const uint2 xy = align_last_octet(next, (int)first, last);
+        const uint32_t x = xy.x, y = xy.y;
+        next = load(first + 512u);
+        const Octet o = look_up<PAIRS, true>(x, y, (int)(clen - first), codes, tab);
+        const bool plain = !__any(o.len > 64u);
+        uint32_t len = o.len;
+        if (__builtin_expect(!plain, 0)) len = octet_length(x, y, first, o.l_lo, o.len, clen, tab);
+        const bool single = __any(len >> 31) != 0;
+        len &= 0x7fffffffu;
+        uint32_t row, half;
+        const uint32_t incl = wave_inclusive_scan_rows(len, row, half);
+        uint32_t pos = base + incl - len;
         base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (__builtin_expect(plain, 1)) {
+            put(o.lo | (o.hi << (o.l_lo & 63u)), pos);
+        } else if (!single) {
+            put(o.lo, pos);
+            put(o.hi, pos + o.l_lo);
+        } else {
+#pragma unroll 1
+            for (uint32_t i = 0; i < 8u; i++) {
+                const uint32_t sym = ((i < 4u ? x : y) >> (8u * (i & 3u))) & 255u;
+                const unsigned long long e = first + i < clen ? tab[sym] : 0ull;
+                put(e & 0x00ffffffffffffffull, pos);
+                pos += (uint32_t)(e >> 56);
+            }
+        }
     }
 }
 
@@ -1004,11 +1044,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         const uint32_t n_images = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.count);
         const uint32_t words = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.words);
         // The images wait in a ring: `filled` chunks are packed, `stored` of them have left.  What is known of those
-        // waiting sits in the lanes of `held`: chunk number among the workgroup's, by image.
-        uint32_t filled = 0, stored = 0, next_image = 0, next_stored = 0, held = 0;
+        // waiting sits in the lanes of `held`: chunk number among the workgroup's, by image, and of `held_from`: where its
+        // second window starts.
+        uint32_t filled = 0, stored = 0, next_image = 0, next_stored = 0, held = 0, held_from = 0;
         auto turn_of_oldest = [&]() { return (uint32_t)__builtin_amdgcn_readlane((int)held, (int)next_stored) / kStreamWaves; };
         auto store = [&]() {  // (its place is known)
             const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)held, (int)next_stored);
+            uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)held_from, (int)next_stored);
             const uint32_t turn = m / kStreamWaves, at = m % kStreamWaves, slot = turn % kSlots;
             const uint32_t c = ticket_of(turn) * kStreamWaves + at;
             uint32_t* img = S.image[wave] + next_stored * (words + 4u);
@@ -1027,7 +1069,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             for (uint32_t win = 0; win < n_words; win += words) {
                 const uint32_t win_words = n_words - win < words ? n_words - win : words;
                 if (win) {
-                    pack_window(p, c, S.tab, img, words, win, lane);
+                    pack_window<PAIRS>(p, c, S.tab, S.codes, img, words, win, lane, from);
                     sync_wave();
                 }
                 for (uint32_t i = lane; i < win_words; i += 64) {
@@ -1050,10 +1092,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 store();
             }
             const uint32_t ch = chunk_of(n);
-            uint32_t bits = 0;
+            uint32_t bits = 0, from = 0;
             if (ch < p.n_chunks) {
                 align_chunk_octets(p, ch, lane, w);
-                bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.codes, S.image[wave] + next_image * (words + 4u), words, lane, S.runs[wave]);
+                bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.codes, S.image[wave] + next_image * (words + 4u), words, lane, S.runs[wave], from);
             }
             const uint32_t slot = n / kStreamWaves % kSlots;
             if (lane == 0) {
@@ -1065,6 +1107,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             if (ch < p.n_chunks && (uint32_t)lane < n_runs) (sub_bits + (size_t)ch * n_runs)[lane] = S.runs[wave][lane];
             sync_wave();
             held = (uint32_t)lane == next_image ? n : held;
+            held_from = (uint32_t)lane == next_image ? from : held_from;
             filled++;
             next_image = next_image + 1u < n_images ? next_image + 1u : 0u;
             n = n_next;

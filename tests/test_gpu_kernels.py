@@ -178,6 +178,38 @@ def test_packer_takes_any_chunk_size_at_the_same_rate(fmtc):
     assert odd < 1.5 * even, f"{odd:.1f} us, {even:.1f} us for whole pieces"
 
 
+def uneven_symbols(n_chunks, chunk, bits, seed=4):
+    """Every tenth chunk of a flat tensor nearly uniform over the alphabet: several times the average chunk's bits."""
+    sym = normal_symbols(n_chunks, chunk, bits, (1 << bits) / 128.0, seed)
+    loud = np.random.default_rng(seed).random(n_chunks) < 0.1
+    loud[-1] = True
+    sym[loud] = normal_symbols(int(loud.sum()), chunk, bits, (1 << bits) / 8.0, seed + 1)
+    return sym.astype(np.uint8).reshape(-1), loud
+
+
+@pytest.mark.parametrize("bits,chunk,C", [(6, 4096, 64), (8, 4096, 64), (6, 4092, 33), (7, 4090, 10), (5, 4032, 144)])
+def test_packer_of_uneven_chunks(fmtc, oracle, bits, chunk, C):
+    n = 4200
+    sym, loud = uneven_symbols(n, chunk, bits)
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, C, bits, 0.5, ln, oracle.canonical_codes(ln))
+    words = ln[sym.reshape(n, chunk)].sum(axis=1, dtype=np.int64) // 32
+    # (the images hold a third more than the average)
+    assert (words[loud] > max(512, 1.4 * words.mean())).mean() > 0.9, "large chunks do not exceed their images"
+    stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, 0.5)
+    torch.cuda.synchronize()
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
+def test_packer_is_not_held_up_by_uneven_chunks(fmtc):
+    """Every tenth chunk several times the others' size (measured: 1.6 times the flat tensor's time, for 1.3 times its bits;
+    with later windows built symbol by symbol, 3.1 times)."""
+    n = 12544
+    flat = coder_us(fmtc, normal_symbols(n, 4096, 6, 0.5, 3).astype(np.uint8).reshape(-1), 64, 6, 4096)
+    uneven = coder_us(fmtc, uneven_symbols(n, 4096, 6)[0], 64, 6, 4096)
+    assert uneven < 2.2 * flat, f"{uneven:.1f} us, {flat:.1f} us for the flat tensor"
+
+
 # Tiled projection of wide tensors, more 128 x 128 tiles than compute units: channel counts with and without a half step
 # of 16 at the end and with a last coefficient group of one to four tiles; ragged last tiles; a pixel beyond f16.
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
