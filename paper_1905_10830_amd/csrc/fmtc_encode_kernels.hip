@@ -2203,9 +2203,11 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
                                    float delta, int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts,
                                    hipStream_t s) {
     const int64_t P = N * HW;
-    // 160 padded channels still fit the one-wavefront-per-32-pixels kernels; for planar tensors only the streaming form,
-    // with 32-bit offsets, whole groups of 16 channels and room in LDS for the histograms beside the basis (not at 8 bits)
-    if (b.Cpad <= 128 || (b.Cpad == 160 && (layout == FMTC_NHWC || (b.C % 16 == 0 && bits < 8 && planar_offsets_fit(b.C, P, HW)))))
+    // 160 padded channels still fit the one-wavefront-per-32-pixels kernels (not at 8 bits, where the histograms find no room
+    // in LDS beside the basis: 100 + 64 KB); for planar tensors only the streaming form, with 32-bit offsets and whole groups
+    // of 16 channels
+    const bool fits160 = b.Cpad == 160 && bits < 8 && (layout == FMTC_NHWC || (b.C % 16 == 0 && planar_offsets_fit(b.C, P, HW)));
+    if (b.Cpad <= 128 || fits160)
         return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     // wide: the tiled matrix product needs whole groups of 16 channels; other channel counts keep the pixel-tile kernel
     if (b.C % 16 == 0) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);

@@ -258,6 +258,35 @@ def test_planar_projection(fmtc, oracle, C, N, H, W, bits):
     check_projection(fmtc, oracle, C, N, H, W, bits, "nchw")
 
 
+# 129 to 160 channels at 8 bits (and at 7, where the basis and the histograms still share LDS), both layouts
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("C,P,bits", [(129, 700, 8), (132, 2100, 8), (144, 4500, 8), (150, 33, 8), (160, 40000, 8), (160, 40000, 7), (144, 33, 7)])
+def test_129_to_160_channels_at_8_bits(fmtc, oracle, C, P, bits, layout):
+    from paper_1905_10830_amd import synth
+
+    check_projection(fmtc, oracle, C, 1, 1, P, bits, layout)
+    rng = np.random.default_rng(P)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C)).astype(np.float32)
+    mu, A = np.zeros(C, np.float32), np.float32(8.0)
+    basis, tag = fmtc.basis_import(T, mu, A), synth.NHWC if layout == "nhwc" else synth.NCHW
+    xs = x.reshape(1, 1, P, C) if layout == "nhwc" else np.ascontiguousarray(x.T).reshape(1, C, 1, P)
+    stream, nbytes = fmtc.encode(basis, dev(xs), bits, tag)
+    out, err = fmtc.decode(basis, stream, xs.shape, bits, tag, nbytes=int(nbytes.item()))
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0
+    out = out.cpu().numpy()
+    out = out.reshape(P, C) if layout == "nhwc" else out.reshape(C, P).T
+    d = float(oracle.delta(A, bits))
+    sym = oracle.quantize(x.astype(np.float64) @ T.T.astype(np.float64), np.float32(d), bits).reshape(P, C)
+    level = sym.astype(np.float64) - (1 << (bits - 1))
+    ref = (level * d) @ T.astype(np.float64)
+    # as in test_planar_decoder, and one step for a value at a rounding boundary
+    tol = (2.0 ** -22 + C * 2.0 ** -24) * ((np.abs(level) * d) @ np.abs(T.astype(np.float64))) + 1e-7
+    wrong = (np.abs(out - ref) > tol).any(axis=1)
+    assert wrong.sum() <= 1 and np.abs(out - ref).max() <= d
+
+
 # Planar decoder variants built for one channel count (32, 64: more than 3072 chunks; 128, 144: more than 2048), the
 # shared one below that; images larger and smaller than a chunk, chunks across images, ragged last chunks, both sizes of
 # payload buffers (4 and 8 bits), another chunk size than the nominal one.
