@@ -440,6 +440,10 @@ __device__ __forceinline__ uint32_t clamp_pattern(float u, float lo, float hi) {
     return (uint32_t)c;
 }
 
+// The larger of two values, NaN if either is: the largest distance of a tile's values to their levels must not pass over one
+// that the f16 parts could not hold (a basis entry beyond f16), so that it is decided exactly.
+__device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 constexpr int kHistLanes = 16;  // histogram copies per wavefront in the narrow-tensor kernel
 constexpr int kFixList = 64;    // values per wavefront waiting for their exact decision
 
@@ -766,7 +770,7 @@ void k_project_quantize_rows(RowParams p) {
                 for (int i = 0; i < 4; i++) {
                     const float t = __builtin_fmaf(ac[4 * g + i], inv_delta_lo, am[4 * g + i] * inv_delta);
                     const float q = __builtin_rintf(t);  // round half to even
-                    maxd = fmaxf(maxd, fabsf(t - q));
+                    maxd = max_or_nan(maxd, fabsf(t - q));
                     const float qc = __builtin_amdgcn_fmed3f(q, lo, hi) + zero_f;  // clamped level, as a symbol
                     word[g] = __builtin_amdgcn_cvt_pk_u8_f32(qc, i, word[g]);
                 }
@@ -845,7 +849,7 @@ void k_project_quantize_rows(RowParams p) {
                 for (int r = 0; r < 16; r++) {
                     const float t = __builtin_fmaf(ac[r], inv_delta_lo, am[r] * inv_delta);
                     const float u = t + magic;  // round half to even
-                    maxd = fmaxf(maxd, fabsf(t - (u - magic)));
+                    maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                     ub[r] = clamp_pattern(u, magic_lo, magic_hi);
                     if constexpr (!FUSED)
                         if (k_ok) hist_add(ub[r]);
@@ -879,7 +883,7 @@ void k_project_quantize_rows(RowParams p) {
                 auto quantize_value = [&](int r) {
                     const float t = __builtin_fmaf(ac[r], inv_delta_lo, am[r] * inv_delta);
                     const float u = t + magic;  // round half to even
-                    maxd = fmaxf(maxd, fabsf(t - (u - magic)));
+                    maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                     ub[r] = clamp_pattern(u, magic_lo, magic_hi);
                     if constexpr (!FUSED)
                         if (k_ok) hist_add(ub[r]);
@@ -1232,7 +1236,7 @@ void k_project_quantize_stream(RowParams p) {
             for (int r = 0; r < 16; r++) {
                 const float t = __builtin_fmaf(ac[kt][r], inv_delta_lo, am[kt][r] * inv_delta);
                 const float u = t + magic;  // round half to even
-                maxd = fmaxf(maxd, fabsf(t - (u - magic)));
+                maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                 ub[r] = clamp_pattern(u, magic_lo, magic_hi);
                 if (k_ok) hist_add(ub[r]);
             }
@@ -1802,7 +1806,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int r = 0; r < 16; r++) {
                 const float t = __builtin_fmaf(ac[a][r], inv_delta_lo, am[a][r] * inv_delta);
                 const float u = t + magic;  // round half to even
-                maxd = fmaxf(maxd, fabsf(t - (u - magic)));
+                maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                 ub[r] = clamp_pattern(u, magic_lo, magic_hi);  // (its lowest byte is the symbol: in range whatever u is)
                 if (ok) atomicAdd(&wh[(ub[r] & 255u) << HS], 1u);
             }

@@ -215,16 +215,18 @@ def test_packer_is_not_held_up_by_uneven_chunks(fmtc):
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
 
 
-def check_projection(fmtc, oracle, C, N, H, W, bits, layout):
+def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None):
     from paper_1905_10830_amd import synth
 
     P = N * H * W
     rng = np.random.default_rng(C)
     T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    if T_scale is not None:
+        T = T * np.asarray(T_scale, np.float32)[:, None]
     mu = rng.standard_normal(C).astype(np.float32)
     x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C) + mu).astype(np.float32)
     x[P // 2] *= 1.0e5
-    A = np.float32(4.0)
+    A = np.float32(4.0 if T_scale is None else 4.0 * np.max(T_scale))
     y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
     sym, margin = oracle.quantize(y, oracle.delta(A, bits), bits, want_margin=True)
     xs = x.reshape(N, H, W, C)
@@ -236,6 +238,16 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout):
     # differences only where the fp64 value is at a rounding boundary (1e-9 steps: the order of an fp64 sum)
     assert not diff.any() or margin.reshape(P, C)[diff].max() <= 1e-9, f"{int(diff.sum())} symbols differ"
     assert hist.tolist() == np.bincount(got.reshape(-1), minlength=256).tolist()
+
+
+# Rows of a basis with entries that f16 does not hold (not orthonormal, but accepted): every kernel family decides their
+# coefficients exactly.  Tiled product with four and eight wavefronts, streaming and rows form, pixel-tile kernel.
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("C,P", [(32, 500), (64, 3000), (100, 700), (128, 40000), (144, 5000), (176, 16411), (256, 2000), (250, 900)])
+def test_projection_with_basis_entries_beyond_f16(fmtc, oracle, C, P, layout):
+    scale = np.ones(C)
+    scale[[0, C // 2, C - 1]] = 3.0e6
+    check_projection(fmtc, oracle, C, 1, 1, P, 5, layout, scale)
 
 
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
