@@ -59,8 +59,9 @@ def test_code_table_of_crafted_counts(fmtc, oracle, bits, kind):
     assert np.array_equal(got, ref)
 
 
-# Packer of large tensors: more than 4096 chunks.  Chunk sizes that are multiples of 8, of 4 only, of neither; one, two
-# and many groups per workgroup, a last group of one chunk; code words of more than 27 bits, chunks larger than an image.
+# Packer of large tensors: more than 4096 chunks.  Chunk sizes that are multiples of 8, of 4 only, of neither; one to three
+# groups per workgroup (more: TURN_CASES); four images per packer (fewer: test_packer_with_two_to_four_images); code words of
+# more than 27 bits, chunks larger than an image.
 STREAM_CASES = [  # P, C, bits, chunk_syms, kind
     (4097 * 4, 16, 6, 64, "steep"),
     (15 * 300, 64, 6, 64, "steep"),
@@ -208,6 +209,76 @@ def test_packer_is_not_held_up_by_uneven_chunks(fmtc):
     flat = coder_us(fmtc, normal_symbols(n, 4096, 6, 0.5, 3).astype(np.uint8).reshape(-1), 64, 6, 4096)
     uneven = coder_us(fmtc, uneven_symbols(n, 4096, 6)[0], 64, 6, 4096)
     assert uneven < 2.2 * flat, f"{uneven:.1f} us, {flat:.1f} us for the flat tensor"
+
+
+# Images that a packer's room is divided into: four up to 3 bits a symbol of a whole chunk, three up to 4, two beyond; pairs
+# of symbols in the table up to 6 bits, single ones above.  Every tenth chunk is several times larger; the last group has
+# one chunk, or all but one.
+@pytest.mark.parametrize("images,bits,spread,n_chunks", [(4, 6, 0.8, 4111), (3, 6, 1.6, 4111), (3, 8, 1.2, 4124), (2, 6, 5.0, 4111),
+                                                         (2, 7, 6.0, 4124), (2, 8, 14.0, 4111), (2, 8, 40.0, 4096)])
+@pytest.mark.parametrize("chunk,C", [(4096, 64), (4092, 33)])
+def test_packer_with_two_to_four_images(fmtc, oracle, images, bits, spread, n_chunks, chunk, C):
+    if n_chunks <= 4096:
+        n_chunks += 1  # (up to 4096 chunks another kernel packs)
+    sym = normal_symbols(n_chunks, chunk, bits, spread, n_chunks + bits)
+    loud = np.random.default_rng(bits).random(n_chunks) < 0.1
+    sym[loud] = np.random.default_rng(bits + 1).integers(0, 1 << bits, (int(loud.sum()), chunk))
+    sym = sym.astype(np.uint8)
+    ln = oracle.huffman_lengths(oracle.histogram(sym.reshape(-1), bits))
+    per_chunk = ln[sym].sum(axis=1, dtype=np.int64)
+    need = int(per_chunk.sum()) // 24  # (the rule of images_for)
+    assert images == (4 if need <= 512 * n_chunks else 3 if need <= 684 * n_chunks else 2), per_chunk.mean() / chunk
+    sym = sym.reshape(-1)
+    ref = oracle.pack(sym, C, bits, 0.5, ln, oracle.canonical_codes(ln))
+    stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, 0.5)
+    torch.cuda.synchronize()
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
+def identity_activations(fmtc, sym, C, bits):
+    """A basis and activations [1, 1, P, C] whose symbols are these."""
+    top = (1 << (bits - 1)) - 1
+    basis = fmtc.basis_import(np.eye(C, dtype=np.float32), np.zeros(C, np.float32), np.float32(0.5 * top))
+    x = ((sym.astype(np.float32) - (top + 1)) * 0.5).reshape(1, 1, -1, C)
+    return basis, dev(x)
+
+
+# Fixed tables, more chunks than the small packer takes: pairs and single symbols in the table, whole and odd chunk sizes,
+# a code with words of more than 26 bits, chunks beyond the image's 1024 words.
+@pytest.mark.parametrize("bits,chunk,C,table", [(5, 256, 16, "fit"), (6, 250, 10, "long"), (7, 256, 16, "fit"), (7, 99, 9, "long"),
+                                                (8, 256, 32, "fit"), (8, 250, 10, "long"), (8, 4096, 64, "long"), (6, 4092, 33, "long")])
+def test_packer_of_large_tensors_with_a_fixed_table(fmtc, oracle, bits, chunk, C, table):
+    n_chunks, K = 4111, 1 << bits
+    sym = normal_symbols(n_chunks, chunk, bits, K / 16.0, bits).astype(np.uint8)
+    sym[::10] = np.random.default_rng(bits).integers(0, K, sym[::10].shape)
+    sym = sym.reshape(-1)
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits)[:K] + 1)
+    if table == "long":  # 1, 2, 3, ... 40 and the rest at one length (Kraft sum 1), the short words for the frequent symbols
+        short = 16 if K == 64 else 24
+        deep = short + int(np.ceil(np.log2(K - short)))
+        n_deep = 2 * (K - short) - (1 << (deep - short))  # the others one bit shorter
+        lengths = list(range(1, short + 1)) + [deep - 1] * (K - short - n_deep) + [deep] * n_deep
+        order = np.argsort(np.abs(np.arange(K) - K // 2), kind="stable")
+        ln = np.zeros_like(ln)
+        ln[order] = sorted(lengths)
+    assert sum(2.0 ** -int(v) for v in ln[:K]) == 1.0
+    basis, x = identity_activations(fmtc, sym, C, bits)
+    t = fmtc.table_import(ln[:K].astype(np.uint8), bits)
+    stream, nbytes = fmtc.encode_static(basis, t, x, chunk_syms=chunk)
+    torch.cuda.synchronize()
+    n = int(nbytes.item())
+    ref = oracle.pack(sym, C, bits, fmtc.delta(0.5 * (K // 2 - 1), bits), ln, oracle.canonical_codes(ln), chunk, cap=n + 4096)
+    got = stream[:n].cpu().numpy()
+    assert n == len(ref) and np.array_equal(got, ref), f"first differing byte {int(np.argmax(got[:len(ref)] != ref[:n]))}"
+    # a buffer that holds about half of the payload: nothing past it, and no valid stream
+    small = n - (n - 320 - 4 * (n_chunks + 1) - 2 * (-(-chunk // 64)) * n_chunks) // 2
+    guard = torch.full((small + 8192,), 0xAB, dtype=torch.uint8, device="cuda")
+    fmtc.encode_static(basis, t, x, chunk_syms=chunk, stream_out=guard[:small])
+    torch.cuda.synchronize()
+    assert (guard[small:] == 0xAB).all(), "wrote past the capacity it was given"
+    _, err = fmtc.decode_symbols(guard[:small], len(sym) // C, C, bits)
+    torch.cuda.synchronize()
+    assert int(err.item()) & 1  # the header
 
 
 # Tiled projection of wide tensors, more 128 x 128 tiles than compute units: channel counts with and without a half step
