@@ -1307,6 +1307,7 @@ PackParams pack_params(const uint8_t* d_syms, const Geometry& g, int bits, float
 template <bool STATIC>
 static hipError_t launch_pack_large(const PackParams& p, hipStream_t s) {
     const uint32_t n_groups = (p.n_chunks + kStreamWaves - 1) / kStreamWaves;
+    if (2u * n_groups > p.n_groups) return hipErrorInvalidValue;  // sizes and places would not fit the look-back words
     const unsigned grid = n_groups < 256u ? n_groups : 256u;  // one workgroup per compute unit: its images take most of the LDS
     // (7 and 8 bits: a table of pairs would not fit beside the images)
     const bool pairs = p.bits <= 6;

@@ -1433,6 +1433,7 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
         else { if (nlo) FMTC_DECC_L(5, LAY, true, 8, 144, true, 3); else FMTC_DECC_L(5, LAY, true, 8, 144, true, 0); } \
     } while (0)
         if (waves == 16 || log12) { if (layout == FMTC_NHWC) FMTC_DECC_FIXED(FMTC_NHWC); else FMTC_DECC_FIXED(FMTC_NCHW); }
+        else if (ncs == 5 && layout != FMTC_NHWC) return hipErrorInvalidValue;  // (planar 144 without LDS room: no bit depth gets here)
         else if (ncs == 5) { if (al) FMTC_DECC(5, FMTC_NHWC, true, 4); else FMTC_DECC(5, FMTC_NHWC, false, 4); }
         else if (layout == FMTC_NHWC) { if (al) FMTC_DECC_N(FMTC_NHWC, true); else FMTC_DECC_N(FMTC_NHWC, false); }
         else                          { if (al) FMTC_DECC_N(FMTC_NCHW, true); else FMTC_DECC_N(FMTC_NCHW, false); }

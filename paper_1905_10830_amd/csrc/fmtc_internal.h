@@ -82,8 +82,11 @@ struct Workspace {
     size_t off_ctrl;         // CoderCtrl
     size_t off_hist;         // u32 [256] final histogram
     size_t off_enc_table;    // u64 [256]: bit-reversed code | length << 56
-    size_t off_lookback;     // u64 [n_groups]: running payload word count per chunk group (flag << 32 | words)
-    size_t off_reserved;     // 4 bytes per chunk, not used (callers size their buffers by the total)
+    // u64 [pack_groups(n_chunks)], cleared by the first kernel of the call.  Small tensors and the fused encoder: payload
+    // words, unused bits and a flag per group of kPackWaves chunks.  Large tensors: the sizes, then the places of their
+    // groups of kStreamWaves chunks (fewer than half as many; launch_pack_large checks it)
+    size_t off_lookback;
+    size_t off_reserved;     // 4 bytes per chunk, not used: the total stays what buffers have been sized by
     size_t off_syms;         // u8 [V]
     size_t total;
 };
