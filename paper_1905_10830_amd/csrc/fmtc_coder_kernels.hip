@@ -619,8 +619,8 @@ __device__ __forceinline__ uint2 load_octet(const uint8_t* at) {
     __builtin_memcpy(&v, at, 8);
     return v;
 }
-// The symbols of a chunk: register q of lane l holds symbols 512q + 8l .. + 7.  Past the chunk's end there is anything (of
-// the next chunk: look_up takes none of it into account).  Nothing outside the tensor is read: where a piece would reach
+// The symbols of a chunk: register q of lane l holds symbols 512q + 8l .. + 7.  Past the chunk's end there is anything
+// (look_up takes none of it into account), so no load is masked: one address instruction each.  Nothing outside the tensor is read: where a piece would reach
 // past its end, the tensor's last eight symbols are loaded (more than eight there are, in a tensor of this kernel), and
 // align_last_octet shifts them into place.
 // (Chunks that are no multiple of 8 symbols, fetched byte by byte and their last piece coded symbol by symbol: 8000 chunks
@@ -628,13 +628,13 @@ __device__ __forceinline__ uint2 load_octet(const uint8_t* at) {
 __device__ __forceinline__ void load_chunk_octets(const PackParams& p, uint32_t ch, int lane, uint2 (&w)[8]) {
     const uint32_t clen = chunk_len_of(p, ch);
     const uint64_t at = (uint64_t)ch * p.chunk_syms;
-    const uint8_t* src = p.syms + at;
-    const int64_t room = (int64_t)(p.V - at) - 8;
-    const int last = room < 4096 ? (int)room : 4096;  // (negative where the last chunk has less than eight symbols)
+    const uint8_t* src = p.syms + at - 8;  // (the last chunk may have less than eight symbols)
+    const uint64_t room = p.V - at;
+    const uint32_t last = room < 4104u ? (uint32_t)room : 4104u;
 #pragma unroll
     for (int q = 0; q < 8; q++) {
-        const int o = 512 * q + 8 * lane;
-        w[q] = o < (int)clen ? load_octet(src + (o < last ? o : last)) : make_uint2(0u, 0u);
+        const uint32_t o = 512u * q + 8u * (uint32_t)lane + 8u;
+        if (512u * q < clen) w[q] = load_octet(src + (o < last ? o : last));  // wavefront-uniform
     }
 }
 // Octet `o` as loaded (at `last`, if that is before it).

@@ -1480,9 +1480,13 @@ static int fused_kernel_for(int C, int layout, const void** fn_out, size_t* lds_
 }
 
 // The one-kernel encoder is used where every chunk group gets a workgroup of its own: its workgroups work through
-// their groups in lock step (project, pack, wait for the position, store), which is the shortest path for a
-// tensor the device holds at once and loses to two specialised kernels beyond that (measured: 25 us against
-// 17 + 10 us at 196 groups, 135 us against 60 + 40 us at 1568).
+// their groups in lock step (project, pack, wait for the position, store), which loses to two specialised kernels for
+// tensors that the device does not hold at once (135 us against 60 + 40 us at 1568 groups).  Below that the line is due to
+// be drawn anew: it dates from a projection of 17 us at 128 channels and 196 groups, which takes 12 to 13.5 us now.
+// Measured with the present kernels, whole calls, one kernel against two, us: 64 channels, channels last, 6 bits 20.3
+// and 18.8 (13 groups), 22.7 and 23.4 (197), at 8 bits 25.2 and 29.3 (197); planar 26.2 and 23.6 (197), at 8 bits 28.7
+// and 30.0; 128 channels 23.9 and 21.6 (7), 26.4 and 26.1 (197), planar 30.6 and 25.9; 32 channels 20.3 and 17.1 (50),
+// 21.6 and 21.1 (184).  So one kernel is ahead at 64 channels and some 200 groups only.
 bool encode_static_fused_applies(int C, int layout, uint32_t chunk_syms, uint32_t n_groups) {
     const void* fn;
     size_t lds;
