@@ -801,7 +801,11 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
         const uint32_t f0 = 512u * q + 8u * (uint32_t)lane, f1 = f0 + 512u;
         last_from = base < words * 32u ? (512u * q) | (base << 12) : last_from;
         const Octet a = look_up<PAIRS, some>(x0, y0, (int)(clen - f0), codes, tab);
-        const Octet b = look_up<PAIRS, some>(x1, y1, (int)(clen - f1), codes, tab);
+        Octet b{0ull, 0ull, 0u, 0u};
+        // (Wavefront-uniform.  Chunks of up to 512 symbols are one such octet per lane; with an empty second one 138660
+        // chunks of 256 symbols took 266.7 us at 6 bits, 207.7 without, 249 in three kernels.)
+        const bool two = !some || 512u * q + 512u < clen;
+        if (two) b = look_up<PAIRS, some>(x1, y1, (int)(clen - f1), codes, tab);
         uint32_t len_a = a.len, len_b = b.len;
         const uint32_t longer = a.len > b.len ? a.len : b.len;
         const bool plain = !__any(longer > 64u);
@@ -836,8 +840,10 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
             const unsigned long long ta = ca << sh_a, tb = cb << sh_b;
             atomicOr(&img[at_a], (uint32_t)ta);
             atomicOr(&img[at_a + 1u], (uint32_t)(ta >> 32));
-            atomicOr(&img[at_b], (uint32_t)tb);
-            atomicOr(&img[at_b + 1u], (uint32_t)(tb >> 32));
+            if (two) {
+                atomicOr(&img[at_b], (uint32_t)tb);
+                atomicOr(&img[at_b + 1u], (uint32_t)(tb >> 32));
+            }
             const uint32_t reach_a = a.len + sh_a, reach_b = b.len + sh_b;
             if (__any((reach_a > reach_b ? reach_a : reach_b) > 64u)) {
                 atomicOr(&img[at_a + 2u], sh_a ? (uint32_t)((ca >> 32) >> (32u - sh_a)) : 0u);
@@ -1151,7 +1157,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     unsigned long long my_bits = 0;      // STATIC: code bits of those whose size this lane has read
     uint32_t tries = 0;                 // looks without anything new
     while (g < n_groups || placed < published || (adder && added < n_groups)) {
-        bool news = false;
+        bool news = false, draws = false;
+        uint32_t next_ticket = 0;
         if (g < n_groups && may_publish(published, placed) && peek_lds(&S.done[published % kSlots]) == kStreamWaves * (published / kSlots + 1u)) {
             const uint32_t slot = published % kSlots;
             unsigned long long size = lane < (int)kStreamWaves ? S.words[slot][lane] : 0u;
@@ -1162,11 +1169,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             if (lane == 0) publish64(&sizes[g], kKnown | size);
             published++;
             g = ticket_of(published);
-            // (a ticket is drawn two turns ahead, so that the symbols of the group can be requested one turn ahead)
-            if (lane == 0) {
-                S.ticket[(published + 1u) % kSlots] = g < n_groups ? claim() : 0xffffffffu;
-                post_lds(&S.drawn, published + 2u);
-            }
+            // (A ticket is drawn two turns ahead, so that the symbols of the group can be requested one turn ahead.  It is
+            // awaited below, together with the look at the places: 25088 chunks of 1024 symbols 80.0 -> 78.1 us.  Three or four
+            // turns ahead, with two to four images: 80.7 and 127, since every place then waits for groups that have been
+            // claimed longer.)
+            next_ticket = 0xffffffffu;
+            if (lane == 0 && g < n_groups) next_ticket = claim();
+            draws = true;
             news = true;
         }
         if (adder && added < n_groups) {
@@ -1225,8 +1234,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 for (size_t o = p.off_sub_bits + 2 * (size_t)p.n_chunks * n_runs; o < p.off_payload; o++) p.stream[o] = 0;
             }
         }
+        unsigned long long e = 0;
+        if (placed < published) e = peek64(&places[ticket_of(placed)]);  // (one word, the same for all lanes)
+        if (draws && lane == 0) {
+            S.ticket[(published + 1u) % kSlots] = next_ticket;
+            post_lds(&S.drawn, published + 2u);
+        }
         if (placed < published) {
-            const unsigned long long e = peek64(&places[ticket_of(placed)]);  // (one word, the same for all lanes)
             if (e) {
                 if (lane == 0) {
                     S.place[placed % kSlots] = e & (kKnown - 1ull);

@@ -211,6 +211,19 @@ def test_packer_is_not_held_up_by_uneven_chunks(fmtc):
     assert uneven < 2.2 * flat, f"{uneven:.1f} us, {flat:.1f} us for the flat tensor"
 
 
+# The packer's last step of a chunk: one octet per lane or two, whole and broken ones, after none, one and two whole steps.
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("chunk", [64, 505, 512, 513, 520, 1023, 1025, 1536, 1537, 1544, 2049, 2561, 3071])
+def test_packer_ends_of_chunks(fmtc, oracle, chunk, bits):
+    n = 4111
+    sym = normal_symbols(n, chunk, bits, (1 << bits) / 12.0, chunk).astype(np.uint8).reshape(-1)[:n * chunk - chunk // 2]
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, 1, bits, 0.5, ln, oracle.canonical_codes(ln), chunk)
+    stream, nbytes = fmtc.code_symbols(dev(sym), 1, bits, 0.5, chunk)
+    torch.cuda.synchronize()
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
 # Images that a packer's room is divided into: four up to 3 bits a symbol of a whole chunk, three up to 4, two beyond; pairs
 # of symbols in the table up to 6 bits, single ones above.  Every tenth chunk is several times larger; the last group has
 # one chunk, or all but one.
