@@ -224,6 +224,23 @@ def test_packer_ends_of_chunks(fmtc, oracle, chunk, bits):
     assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
 
 
+# Octets of eight symbols with long codes, all together: 65 to 96, 97 to 126 and more bits, code words beyond a table entry's
+# 26 bits (alone or as a pair), each next to short ones; across the ends of images and chunks.
+@pytest.mark.parametrize("bits,share,chunk", [(8, 0.2, 4096), (8, 0.03, 4096), (8, 0.03, 256), (8, 0.003, 512), (8, 0.0003, 1001),
+                                              (7, 0.01, 777), (6, 0.05, 256), (6, 0.01, 4096), (6, 0.0005, 4096)])
+def test_packer_of_long_octets(fmtc, oracle, bits, share, chunk):
+    n, K = 4113, 1 << bits
+    rng = np.random.default_rng(int(1e5 * share) + bits)
+    octets = -(-n * chunk // 8)
+    rare = rng.random(octets) < share
+    sym = np.where(np.repeat(rare, 8), rng.integers(8, K, 8 * octets), rng.integers(0, 8, 8 * octets))[:n * chunk].astype(np.uint8)
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, 1, bits, 0.5, ln, oracle.canonical_codes(ln), chunk)
+    stream, nbytes = fmtc.code_symbols(dev(sym), 1, bits, 0.5, chunk)
+    torch.cuda.synchronize()
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
 # Images that a packer's room is divided into: four up to 3 bits a symbol of a whole chunk, three up to 4, two beyond; pairs
 # of symbols in the table up to 6 bits, single ones above.  Every tenth chunk is several times larger; the last group has
 # one chunk, or all but one.
