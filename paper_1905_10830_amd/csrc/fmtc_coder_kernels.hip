@@ -589,7 +589,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 constexpr uint32_t kStreamRoom = 2064;  // words a packer has for its images, each with 4 spare ones (see PackShared)
 constexpr uint32_t kShortCode = 26;     // a table entry holds up to 26 code bits below 6 bits of length ...
 constexpr uint32_t kNoCode = 63u << kShortCode;  // ... or says that the code word is longer: any eight symbols with
-                                        // such an entry come to more than 64 bits
+                                        // such an entry come to more than 64 bits (less than eight: see look_up)
 // Marks a group's published size, and its place.  A size is the group's payload words; with a fixed table also its code
 // bits, from bit 32 on.  (Added up in memory before the size was published, a round trip per turn: 25088 chunks of 1024
 // symbols 55.5 -> 43.5 us without, the N = 256, C = 64 tensor at 6 bits 47.4 -> 42.5.)

@@ -333,7 +333,7 @@ def test_packer_is_no_slower_with_a_fixed_table(fmtc, oracle, bits, chunk, C):
         fixed = 1e3 * fmtc.profile_read()["k_pack"][1]
     finally:
         fmtc.profile_enable(0)
-    assert fixed < own, f"{fixed:.1f} us with the fixed table, {own:.1f} us with the tensor's own"
+    assert fixed < 1.05 * own, f"{fixed:.1f} us with the fixed table, {own:.1f} us with the tensor's own"
 
 
 # Tiled projection of wide tensors, more 128 x 128 tiles than compute units: channel counts with and without a half step
