@@ -96,7 +96,7 @@ __device__ __forceinline__ bool build_decode_tables(DecTables& T, int my_len, in
         const uint32_t c = in ? T.cnt_len[tid] : 0u;
         const unsigned long long w = (unsigned long long)c << (in ? kMaxLen - tid : 0);
         const unsigned long long incl = wave_inclusive_scan64(w, lane);
-        const uint32_t rank = wave_exclusive_scan(c, lane);
+        const uint32_t rank = wave_exclusive_scan(c);
         const unsigned long long kraft = __shfl(incl, 63, 64);
         T.first_code[tid] = in ? ((incl - w) >> (kMaxLen - tid)) : 0ull;
         T.first_rank[tid] = in ? rank : 0u;
@@ -293,9 +293,9 @@ hipError_t launch_build_decode_tables(const uint8_t* d_len_table, int bits, void
 }
 size_t prebuilt_decode_tables_bytes() { return sizeof(PrebuiltTables); }
 
-// Decodes the `cnt` symbols of one run (one lane) starting at bit `start` of a chunk into the symbol tile.
-// STAGED: the chunk's words are in LDS (`pw`, two zero words behind them); otherwise they are read from
-// global memory (`gw`), zero past the chunk's end.  Returns false if bits matched no code word.
+// Decodes the `cnt` symbols of one run (one lane) starting at bit `start` of a chunk too large for the LDS copy of the
+// payload into the symbol tile: its `nwords` words are read from global memory (`gw`), zero past their end.  Returns
+// false if bits matched no code word.
 // State: lo/hi are payload words widx and widx+1, sh the bit offset in lo, nxt word widx+2 (read ahead),
 // so 32 valid bits are at hand for every table lookup and a step crosses at most one word boundary.
 //
@@ -309,13 +309,10 @@ struct ByteOut {
         i++;
     }
 };
-template <bool STAGED, typename Out>
-__device__ __forceinline__ bool decode_run(const uint32_t* pw, const uint32_t* __restrict__ gw, uint32_t nwords,
-                                           uint32_t start, uint32_t cnt, const DecTables& T, Out out) {
-    auto fetch = [&](uint32_t rel) -> uint32_t {
-        if constexpr (STAGED) return pw[rel < nwords + 1 ? rel : nwords + 1];
-        else return (rel < nwords) ? gw[rel] : 0u;
-    };
+template <typename Out>
+__device__ __forceinline__ bool decode_run(const uint32_t* __restrict__ gw, uint32_t nwords, uint32_t start, uint32_t cnt,
+                                           const DecTables& T, Out out) {
+    auto fetch = [&](uint32_t rel) -> uint32_t { return (rel < nwords) ? gw[rel] : 0u; };
     // word index can not wrap: start <= 64 runs * 65535 bits
     uint32_t widx = start >> 5, sh = start & 31;
     uint32_t lo = fetch(widx), hi = fetch(widx + 1), nxt = fetch(widx + 2);
@@ -502,7 +499,8 @@ struct DecodeParams {
     int64_t HW;
     int C;
     int bits;
-    int G;             // chunks per tile
+    int tile_px;       // pixels of a workgroup tile (k_decode_tiles; its chunks follow from the stream's header)
+    uint32_t tile_bytes;  // ... and the LDS for its symbols
     int ncs;           // Cpad / 32
     const uint16_t* Bp16;  // inverse operand (T^T), f16 split, in operand order
     const float* mu;   // [Cpad]
@@ -566,7 +564,69 @@ __device__ __forceinline__ bool open_stream(const DecodeParams& p, StreamView* v
     return true;
 }
 
-constexpr int kPayWords = 918;  // LDS copy of a chunk's payload: up to ~7 bits/symbol; larger chunks read global memory
+// A unit: the neighbouring chunks that one wavefront decodes together, as many as leave a lane for each of their runs (one
+// where a chunk has more than 32 runs).  Lane l takes run l of them (their run sizes lie one behind the other in the
+// stream, and so do their words), whose symbols go to slot l of the unit's tile (see sym_addr).
+// (One chunk per wavefront and turn leaves three quarters of the lanes idle where chunks have 1024 symbols, pays every
+// chunk's latencies by itself, and made a wide tensor's tiles as many pixels smaller as its chunks are.  Kernel times, us:
+// 128 channels, 21 x 24, chunks of 1024 52 -> 20; 100 channels, N = 33, 27 x 31, chunks of 2048 35 -> 29; 384 channels,
+// N = 71, 11 x 11, 1024 106 -> 30; 1024 channels, 25 x 25, 1024 86 -> 31.)
+struct Unit {
+    uint32_t m, n_units;
+    uint32_t lane_ch, lane_run;  // this lane's chunk of the unit and run of the chunk
+    __device__ __forceinline__ Unit(const StreamView& v, int lane)
+        : m(1u), n_units(v.n_chunks), lane_ch((uint32_t)lane < v.spc ? 0u : 1u), lane_run((uint32_t)lane) {
+        if (v.spc <= 32u) {  // (no divisions before the first chunk otherwise)
+            m = 64u / v.spc;
+            n_units = (v.n_chunks + m - 1u) / m;
+            lane_ch = (uint32_t)lane / v.spc;
+            lane_run = (uint32_t)lane - lane_ch * v.spc;
+        }
+    }
+};
+// What the stream says about a unit of `count` chunks from chunk c0 on, requested ahead of its use.
+struct UnitInfo {
+    uint32_t off;  // first payload word of this lane's chunk (lane 0: of the unit; lanes without a chunk: anything)
+    uint32_t end;  // the unit's end
+    uint32_t run;  // bits of this lane's run
+    __device__ __forceinline__ void load(const StreamView& v, const Unit& un, uint32_t c0, uint32_t count, int lane) {
+        const bool in = un.lane_ch < count;
+        off = v.chunk_off[c0 + (in ? un.lane_ch : 0u)];
+        end = v.chunk_off[c0 + count];
+        run = in ? v.sub_bits[(size_t)c0 * v.spc + (uint32_t)lane] : 0u;
+    }
+};
+// The same checked, for the wavefront that is about to decode it.
+struct UnitBits {
+    uint32_t w0, n_words;  // the unit's words of the payload
+    uint32_t rel;          // ... of which this many come before this lane's chunk
+    uint32_t start;        // first bit of this lane's run in its chunk
+    uint32_t cnt;          // its symbols
+    bool bad;              // offsets out of order or past the payload: nothing of the unit is read
+};
+__device__ __forceinline__ UnitBits open_unit(const StreamView& v, const Unit& un, const UnitInfo& in, uint32_t c0, uint32_t count,
+                                              uint32_t last_syms, int lane) {
+    UnitBits b;
+    b.w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)in.off);
+    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)in.end);
+    b.bad = b.w0 > w1 || w1 > v.payload_words;
+    const bool mine = un.lane_ch < count;
+    b.start = wave_exclusive_scan(in.run);
+    b.rel = 0u;
+    if (count > 1u) {  // wavefront-uniform
+        const uint32_t next = (uint32_t)__shfl((int)in.off, lane + (int)v.spc, 64);
+        b.bad = b.bad || __any(mine && in.off > (un.lane_ch + 1u < count ? next : w1)) != 0;
+        b.start -= (uint32_t)__shfl((int)b.start, lane - (int)un.lane_run, 64);
+        b.rel = mine && !b.bad ? in.off - b.w0 : 0u;
+    }
+    b.n_words = b.bad ? 0u : w1 - b.w0;
+    if (b.bad) b.w0 = 0u;
+    const uint32_t syms = c0 + un.lane_ch == v.n_chunks - 1u ? last_syms : v.chunk_syms, r0 = un.lane_run * (uint32_t)kSubSyms;
+    b.cnt = mine && r0 < syms ? (syms - r0 < (uint32_t)kSubSyms ? syms - r0 : (uint32_t)kSubSyms) : 0u;
+    return b;
+}
+
+constexpr int kPayWords = 1216;  // LDS copy of a unit's payload: up to 9 bits a symbol; larger units read global memory
 
 // Wide tensors and the symbols-only mode: a tile of G chunks per workgroup is decoded into an LDS tile of symbol
 // bytes, one chunk per wavefront and round; the inverse transform of the tile's pixels then runs on the f16 matrix
@@ -581,8 +641,8 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
     constexpr int PTW = MT, CTW = 8, PPW = MT / 2;  // PPW: pixel tiles per wavefront
     // the chunks' payload words (one buffer per wavefront) while decoding, the basis blocks of three contraction
     // steps afterwards: the two uses are a workgroup barrier apart
-    // (a payload buffer: the chunk's words, two zero words, and the room a corrupt stream's cursor may run into)
-    constexpr int kPayStride = kPayWords + 2 + kPayOverrun;
+    // (a payload buffer: the unit's words and the room a corrupt stream's cursor may run into)
+    constexpr int kPayStride = kPayWords + kPayOverrun;
     constexpr size_t kPayBytes = sizeof(uint32_t) * 8 * kPayStride, kRingBytes = sizeof(uint4) * 3 * CTW * 2 * 64;
     __shared__ __align__(16) uint8_t s_shared[kPayBytes > kRingBytes ? kPayBytes : kRingBytes];
     uint32_t(*pay)[kPayStride] = reinterpret_cast<uint32_t(*)[kPayStride]>(s_shared);
@@ -605,17 +665,19 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
         if (tid == 0) atomicOr(p.err, FMTC_ERR_TABLE);
         return;
     }
-    const uint32_t n_chunks = sv.n_chunks, spc = sv.spc, chunk_syms = sv.chunk_syms;
-    const uint32_t payload_words = sv.payload_words;
-    const uint64_t ppc = sv.ppc;
-    const uint32_t* chunk_off = sv.chunk_off;
-    const uint16_t* sub_bits = sv.sub_bits;
-    const uint32_t* payload = sv.payload;
+    const uint32_t n_chunks = sv.n_chunks, spc = sv.spc, chunk_syms = sv.chunk_syms, ppc = (uint32_t)sv.ppc;
+    const uint32_t slot_bytes = 68u * spc;  // of a chunk in the symbol tile: every run has its place (see sym_addr)
     const uint64_t V = (uint64_t)p.P * (uint64_t)C;
+    const uint32_t last_syms = (uint32_t)(V - (uint64_t)(n_chunks - 1u) * chunk_syms);
+    const Unit un(sv, lane);
     __syncthreads();
 
     const float delta = sv.delta;
-    const int G = p.G;
+    // Chunks of a tile: what the stream's chunk size makes of the tile's pixels (symbols only: of a unit per wavefront), and
+    // what its LDS holds.
+    uint32_t G = p.syms_out ? 8u * un.m : (uint32_t)p.tile_px / ppc;
+    const uint32_t fits = p.tile_bytes / slot_bytes;
+    G = G < 1u ? 1u : (G > fits ? fits : G);
     const uint32_t n_tiles = (n_chunks + G - 1) / G;
     // 0x6400 | s is the f16 number 1024 + s: the level s - 2^(b-1) is that minus (1024 + 2^(b-1)), exactly
     const _Float16 level_off = (_Float16)(float)(1024 + (1 << (p.bits - 1)));
@@ -673,64 +735,49 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
     };
 
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        // ---- variable length decoding into the LDS tile ----
-        for (int j = wave; j < G; j += 8) {
-            const uint32_t ch = tile * G + j;
-            if (ch >= n_chunks) break;
-            const uint64_t c0 = (uint64_t)ch * chunk_syms;
-            const uint32_t clen = (uint32_t)((V - c0 < chunk_syms) ? (V - c0) : chunk_syms);
-            // chunk bounds are the same for all lanes: keep them in scalar registers
-            uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk_off[ch]);
-            uint32_t w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk_off[ch + 1]);
-            if (w0 > w1 || w1 > payload_words) {
-                if (lane == 0) atomicOr(p.err, FMTC_ERR_OFFSETS);
-                w0 = 0; w1 = 0;
-            }
-            const uint32_t run_bits = ((uint32_t)lane < spc) ? sub_bits[(size_t)ch * spc + lane] : 0u;
-            const uint32_t start = wave_exclusive_scan(run_bits, lane);
-            const uint32_t r0 = (uint32_t)lane * kSubSyms;
-            const uint32_t cnt = (r0 < clen) ? ((clen - r0 < (uint32_t)kSubSyms) ? clen - r0 : (uint32_t)kSubSyms) : 0u;
-            const uint32_t nwords = w1 - w0;
-            const uint32_t nbase = (uint32_t)j * chunk_syms + r0;
-            uint32_t* pw = pay[wave];
+        const uint32_t first_ch = tile * G;
+        const uint32_t tile_chunks = n_chunks - first_ch < G ? n_chunks - first_ch : G;
+        // ---- variable length decoding into the LDS tile, a unit per wavefront and round ----
+        for (uint32_t k0 = (uint32_t)wave * un.m; k0 < tile_chunks; k0 += 8u * un.m) {
+            const uint32_t count = tile_chunks - k0 < un.m ? tile_chunks - k0 : un.m;
+            UnitInfo info;
+            info.load(sv, un, first_ch + k0, count, lane);
+            const UnitBits ub = open_unit(sv, un, info, first_ch + k0, count, last_syms, lane);
+            if (ub.bad && lane == 0) atomicOr(p.err, FMTC_ERR_OFFSETS);
+            uint8_t* slots = symtile + slot_bytes * k0;
             bool ok_run = true;
-            if (nwords <= (uint32_t)kPayWords) {
-                // the chunk's payload goes to LDS with full-width loads
-                for (uint32_t i = lane; i < nwords + 2; i += 64) pw[i] = (i < nwords) ? payload[w0 + i] : 0u;
+            if (ub.n_words <= (uint32_t)kPayWords) {
+                // the unit's payload goes to LDS with full-width loads (what lies behind it there is never taken for a
+                // symbol of a run)
+                uint32_t* pw = pay[wave];
+                const uint32_t* src = sv.payload + ub.w0;
+                for (uint32_t i = lane; i < ub.n_words; i += 64) pw[i] = src[i];
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                if (cnt) {
-                    // Chunk sizes that are a multiple of 64 (every run starts a 68-byte slot of the tile, and only the
-                    // tensor's last run can be short) take the decoder of the narrow kernel: three table entries per
-                    // read of the stream.  It stores up to three bytes past a run's last symbol: with other chunk sizes
-                    // those would be the first symbols of the next chunk, which another wavefront writes.
-                    if ((chunk_syms & 63u) == 0) ok_run = decode_run_bytes(pw, nwords, start, cnt, T, symtile + sym_addr(nbase));
-                    else ok_run = decode_run<true>(pw, nullptr, nwords, start, cnt, T, ByteOut(symtile, nbase));
-                }
-                // the next chunk of this wavefront overwrites pay[]: all lanes are done reading here
+                if (ub.cnt) ok_run = decode_run_bytes(pw, ub.n_words, ub.start + 32u * ub.rel, ub.cnt, T, slots + 68u * (uint32_t)lane);
+                // the next unit of this wavefront overwrites pay[]: all lanes are done reading here
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-            } else if (cnt) {
-                // a chunk too large for the LDS copy is read in place
-                ok_run = decode_run<false>(nullptr, payload + w0, nwords, start, cnt, T, ByteOut(symtile, nbase));
+            } else if (ub.cnt) {
+                // a unit too large for the LDS copy is read in place
+                ok_run = decode_run(sv.payload + ub.w0 + ub.rel, ub.n_words - ub.rel, ub.start, ub.cnt, T, ByteOut(slots, 64u * (uint32_t)lane));
             }
             if (!ok_run) atomicOr(p.err, FMTC_ERR_CODE);
         }
         __syncthreads();
 
-        const uint32_t first_ch = tile * G;
-        const uint32_t tile_chunks = (n_chunks - first_ch < (uint32_t)G) ? n_chunks - first_ch : (uint32_t)G;
-        const uint64_t tile_s0 = (uint64_t)first_ch * chunk_syms;
-        const uint32_t tile_syms = (uint32_t)((V - tile_s0 < (uint64_t)tile_chunks * chunk_syms)
-                                                  ? (V - tile_s0) : (uint64_t)tile_chunks * chunk_syms);
-
         if (p.syms_out) {
-            if constexpr (ALIGNED4) {
-                for (uint32_t n = 4 * tid; n < tile_syms; n += 2048)
-                    *reinterpret_cast<uint32_t*>(p.syms_out + tile_s0 + n) =
-                        *reinterpret_cast<const uint32_t*>(symtile + sym_addr(n));
-            } else {
-                for (uint32_t n = tid; n < tile_syms; n += 512) p.syms_out[tile_s0 + n] = symtile[sym_addr(n)];
+            // (a chunk per wavefront and round)
+            for (uint32_t k = (uint32_t)wave; k < tile_chunks; k += 8u) {
+                const uint32_t syms = first_ch + k == n_chunks - 1u ? last_syms : chunk_syms;
+                const uint8_t* src = symtile + slot_bytes * k;
+                uint8_t* dst = p.syms_out + (uint64_t)(first_ch + k) * chunk_syms;
+                if constexpr (ALIGNED4) {
+                    for (uint32_t n = 4u * (uint32_t)lane; n < syms; n += 256u)
+                        *reinterpret_cast<uint32_t*>(dst + n) = *reinterpret_cast<const uint32_t*>(src + sym_addr(n));
+                } else {
+                    for (uint32_t n = (uint32_t)lane; n < syms; n += 64u) dst[n] = src[sym_addr(n)];
+                }
             }
         } else {
             // ---- inverse quantizer + inverse transform: a tiled matrix product over the workgroup's pixels ----
@@ -741,8 +788,8 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
             // load_to_lds).  The other operand is read from the symbol tile: lane (pixel, h) takes the eight symbols
             // 16 ks + 8 h .. + 7 of its pixel and turns them into f16 levels with two byte permutes each.
             const int64_t px_tile0 = (int64_t)first_ch * (int64_t)ppc;
-            int TP = (int)(tile_syms / (uint32_t)C);  // pixels in this tile
-            if (TP > PTW * 32) TP = PTW * 32;         // (a stream with other chunk geometry than the grid assumed)
+            int TP = p.P - px_tile0 < (int64_t)(tile_chunks * ppc) ? (int)(p.P - px_tile0) : (int)(tile_chunks * ppc);  // pixels in this tile
+            if (TP > PTW * 32) TP = PTW * 32;  // (not so: a chunk of a wide tensor has fewer pixels than a tile)
             const int n_cg = (p.ncs + CTW - 1) / CTW;
             const int ctp = wave & 3;   // this wavefront's pair of channel tiles ...
             const int ptp = wave >> 2;  // ... and its PPW pixel tiles
@@ -756,13 +803,16 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
                     for (int b = 0; b < PPW; b++)
 #pragma unroll
                         for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acl[a][b][r] = 0.f; }
-                uint32_t rowbase[PPW];
+                uint32_t rowbase[PPW];       // this lane's first symbol of a pixel in its chunk ...
+                const uint8_t* rows[PPW];    // ... which starts here
 #pragma unroll
                 for (int b = 0; b < PPW; b++) {
                     int pxl = (PPW * ptp + b) * 32 + l32;
                     if (pxl > TP - 1) pxl = TP - 1;  // rows past the tile repeat the last pixel; never stored
                     if (pxl < 0) pxl = 0;
-                    rowbase[b] = (uint32_t)pxl * (uint32_t)C + 8u * half;
+                    const uint32_t k = (uint32_t)pxl / ppc;
+                    rows[b] = symtile + slot_bytes * k;
+                    rowbase[b] = ((uint32_t)pxl - k * ppc) * (uint32_t)C + 8u * half;
                 }
                 // steps past the end repeat the last one: the number of loads in flight is the same in every step
                 auto issue = [&](int ks) {
@@ -796,13 +846,13 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
                         const uint32_t n = rowbase[b] + 16u * (uint32_t)ks;
                         uint32_t w0, w1;
                         if constexpr (ALIGNED4) {
-                            w0 = *reinterpret_cast<const uint32_t*>(symtile + sym_addr(n));
-                            w1 = *reinterpret_cast<const uint32_t*>(symtile + sym_addr(n + 4));
+                            w0 = *reinterpret_cast<const uint32_t*>(rows[b] + sym_addr(n));
+                            w1 = *reinterpret_cast<const uint32_t*>(rows[b] + sym_addr(n + 4));
                         } else {
-                            w0 = (uint32_t)symtile[sym_addr(n)] | ((uint32_t)symtile[sym_addr(n + 1)] << 8) |
-                                 ((uint32_t)symtile[sym_addr(n + 2)] << 16) | ((uint32_t)symtile[sym_addr(n + 3)] << 24);
-                            w1 = (uint32_t)symtile[sym_addr(n + 4)] | ((uint32_t)symtile[sym_addr(n + 5)] << 8) |
-                                 ((uint32_t)symtile[sym_addr(n + 6)] << 16) | ((uint32_t)symtile[sym_addr(n + 7)] << 24);
+                            w0 = (uint32_t)rows[b][sym_addr(n)] | ((uint32_t)rows[b][sym_addr(n + 1)] << 8) |
+                                 ((uint32_t)rows[b][sym_addr(n + 2)] << 16) | ((uint32_t)rows[b][sym_addr(n + 3)] << 24);
+                            w1 = (uint32_t)rows[b][sym_addr(n + 4)] | ((uint32_t)rows[b][sym_addr(n + 5)] << 8) |
+                                 ((uint32_t)rows[b][sym_addr(n + 6)] << 16) | ((uint32_t)rows[b][sym_addr(n + 7)] << 24);
                         }
                         const halfx2 q01 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x05010400u)) - level_off2;
                         const halfx2 q23 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x07030602u)) - level_off2;
@@ -945,18 +995,18 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             if (i < n) load_to_lds<4>(src + i, pw + 64u * k);
         }
     };
-    const bool guess = p.g_off_payload <= p.bytes && ch_first < p.g_n_chunks;
-    uint32_t pre_w0 = 0, pre_w1 = 0, pre_run = 0;
+    const bool guess = p.g_off_payload <= p.bytes && ch_first < p.g_n_chunks && p.g_spc > 32u;  // (a chunk is a unit)
+    UnitInfo cur{0u, 0u, 0u};
     bool pay_pre = false;
     if (guess) {
         const uint32_t* co = reinterpret_cast<const uint32_t*>(p.stream + p.g_off_chunk_off);
         const uint16_t* sb = reinterpret_cast<const uint16_t*>(p.stream + p.g_off_sub_bits);
-        pre_w0 = co[ch_first];
-        pre_w1 = co[ch_first + 1];
-        pre_run = ((uint32_t)lane < p.g_spc) ? sb[(size_t)ch_first * p.g_spc + lane] : 0u;
+        cur.off = co[ch_first];
+        cur.end = co[ch_first + 1];
+        cur.run = ((uint32_t)lane < p.g_spc) ? sb[(size_t)ch_first * p.g_spc + lane] : 0u;
         const size_t cap_words = (p.bytes - p.g_off_payload) / 4;
-        const uint32_t gw0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pre_w0);
-        const uint32_t gw1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pre_w1);
+        const uint32_t gw0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.off);
+        const uint32_t gw1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.end);
         pay_pre = gw0 <= gw1 && (size_t)gw1 <= cap_words && gw1 - gw0 <= pay_cap;
         if (pay_pre) request_payload(reinterpret_cast<const uint32_t*>(p.stream + p.g_off_payload), gw0, gw1 - gw0);
     }
@@ -966,15 +1016,11 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         return;
     }
     const bool guess_valid = guess && sv.n_chunks == p.g_n_chunks && sv.spc == p.g_spc;  // same section offsets
-    const uint32_t guess_w0 = pre_w0, guess_w1 = pre_w1;
-    if (!guess_valid) {
-        pre_w0 = 0; pre_w1 = 0; pre_run = 0;
-        if (ch_first < sv.n_chunks) {
-            pre_w0 = sv.chunk_off[ch_first];
-            pre_w1 = sv.chunk_off[ch_first + 1];
-            pre_run = ((uint32_t)lane < sv.spc) ? sv.sub_bits[(size_t)ch_first * sv.spc + lane] : 0u;
-        }
-    }
+    const uint32_t guess_w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.off);
+    const uint32_t guess_w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.end);
+    const Unit un(sv, lane);
+    auto chunks_of = [&](uint32_t u) { return sv.n_chunks - u * un.m < un.m ? sv.n_chunks - u * un.m : un.m; };
+    if (!guess_valid && ch_first < un.n_units) cur.load(sv, un, ch_first * un.m, chunks_of(ch_first), lane);
     if constexpr (!U8) {
         if (tid < NCT * 32) s_mu[tid] = p.mu[tid];
     } else {
@@ -990,9 +1036,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's part of the basis has landed in LDS
     __syncthreads();
-    const uint32_t n_chunks = sv.n_chunks, spc = sv.spc, chunk_syms = sv.chunk_syms;
     const uint32_t payload_words = sv.payload_words;
-    const uint64_t V = (uint64_t)p.P * (uint64_t)C;
+    const uint32_t last_syms = (uint32_t)((uint64_t)p.P * (uint64_t)C - (uint64_t)(sv.n_chunks - 1u) * sv.chunk_syms);
     const float delta = sv.delta;
     // contraction steps that meet a non-zero row of the basis (all of them unless the basis is truncated)
     const int NJA = p.active_steps < 1 ? 1 : (p.active_steps > NJ ? NJ : p.active_steps);
@@ -1001,62 +1046,46 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const halfx2 level_off2 = {level_off, level_off};
     uint8_t* tile = symtile[wave];
 
-    // Side information and payload of a chunk are requested one chunk ahead: its payload words right after the
-    // variable length decoding of the chunk before it (the LDS copy is free then; they arrive during the inverse
-    // transform), offsets and run sizes of the chunk after it once those words have landed (they arrive during the
-    // variable length decoding) -- a chunk would otherwise start with two dependent memory round trips.  cur_*:
-    // what is at hand for the chunk of this turn; pay_*: the offsets the words in the LDS copy were requested for.
-    uint32_t cur_w0 = pre_w0, cur_w1 = pre_w1, cur_run = pre_run;
+    // Side information and payload of a unit are requested one unit ahead: its payload words right after the
+    // variable length decoding of the unit before it (the LDS copy is free then; they arrive during the inverse
+    // transform), offsets and run sizes of the unit after it once those words have landed (they arrive during the
+    // variable length decoding) -- a unit would otherwise start with two dependent memory round trips.  cur:
+    // what is at hand for the unit of this turn; pay_*: the offsets the words in the LDS copy were requested for.
     bool pay_ok = guess_valid && pay_pre;
     uint32_t pay_w0 = guess_w0, pay_w1 = guess_w1;
-    const uint32_t ch_step = gridDim.x * WAVES;
-    for (uint32_t ch = ch_first; ch < n_chunks; ch += ch_step) {
-        // ---- variable length decoding of the chunk into the wavefront's tile ----
-        const uint64_t c0 = (uint64_t)ch * chunk_syms;
-        const uint32_t clen = (uint32_t)((V - c0 < chunk_syms) ? (V - c0) : chunk_syms);
-        uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur_w0);
-        uint32_t w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur_w1);
-        if (w0 > w1 || w1 > payload_words) {
-            if (lane == 0) atomicOr(p.err, FMTC_ERR_OFFSETS);
-            w0 = 0; w1 = 0;
-        }
-        const uint32_t run_bits = cur_run;
-        const uint32_t nwords = w1 - w0;
-        const bool staged = nwords <= pay_cap;
+    const uint32_t u_step = gridDim.x * WAVES;
+    for (uint32_t u = ch_first; u < un.n_units; u += u_step) {
+        // ---- variable length decoding of the unit into the wavefront's tile ----
+        const UnitBits ub = open_unit(sv, un, cur, u * un.m, chunks_of(u), last_syms, lane);
+        if (ub.bad && lane == 0) atomicOr(p.err, FMTC_ERR_OFFSETS);
+        const bool staged = ub.n_words <= pay_cap;
         // (whatever was requested for the LDS copy has landed before it is read or requested again; this also waits
-        // for the stores of the chunk before)
+        // for the stores of the unit before)
         wait_loads<0>();
-        if (staged && !(pay_ok && w0 == pay_w0 && w1 == pay_w1)) {
-            request_payload(sv.payload, w0, nwords);
+        if (staged && !(pay_ok && ub.w0 == pay_w0 && ub.w0 + ub.n_words == pay_w1)) {
+            request_payload(sv.payload, ub.w0, ub.n_words);
             wait_loads<0>();
         }
-        const uint32_t nch = ch + ch_step;
-        const bool have_next = nch < n_chunks && nch > ch;  // wavefront-uniform
-        if (have_next) {
-            cur_w0 = sv.chunk_off[nch];
-            cur_w1 = sv.chunk_off[nch + 1];
-            cur_run = ((uint32_t)lane < spc) ? sv.sub_bits[(size_t)nch * spc + lane] : 0u;
-        }
-        const uint32_t start = wave_exclusive_scan(run_bits, lane);
-        const uint32_t r0 = (uint32_t)lane * kSubSyms;
-        const uint32_t cnt = (r0 < clen) ? ((clen - r0 < (uint32_t)kSubSyms) ? clen - r0 : (uint32_t)kSubSyms) : 0u;
+        const uint32_t nu = u + u_step;
+        const bool have_next = nu < un.n_units && nu > u;  // wavefront-uniform
+        if (have_next) cur.load(sv, un, nu * un.m, chunks_of(nu), lane);
         bool ok_run = true;
         if (staged) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             // run `lane` goes to bytes [68 * lane, 68 * lane + 64) of the tile (sym_addr), 4 pad bytes behind it
-            if (cnt) ok_run = decode_run_bytes(pw, nwords, start, cnt, T, tile + 68u * (uint32_t)lane);
-        } else if (cnt) {
-            ok_run = decode_run<false>(nullptr, sv.payload + w0, nwords, start, cnt, T, ByteOut(tile, r0));
+            if (ub.cnt) ok_run = decode_run_bytes(pw, ub.n_words, ub.start + 32u * ub.rel, ub.cnt, T, tile + 68u * (uint32_t)lane);
+        } else if (ub.cnt) {
+            ok_run = decode_run(sv.payload + ub.w0 + ub.rel, ub.n_words - ub.rel, ub.start, ub.cnt, T, ByteOut(tile, 64u * (uint32_t)lane));
         }
-        // the next chunk's payload words: in flight during this chunk's inverse transform (every lane is done with
+        // the next unit's payload words: in flight during this unit's inverse transform (every lane is done with
         // the LDS copy: the reads of a wavefront complete in order, and each lane has used its last one)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         pay_ok = false;
         if (have_next) {
-            pay_w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur_w0);
-            pay_w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur_w1);
+            pay_w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.off);
+            pay_w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.end);
             pay_ok = pay_w0 <= pay_w1 && pay_w1 <= payload_words && pay_w1 - pay_w0 <= pay_cap;
             if (pay_ok) request_payload(sv.payload, pay_w0, pay_w1 - pay_w0);
         }
@@ -1065,12 +1094,19 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 
-        // ---- inverse quantizer + inverse transform of the chunk's pixels ----
-        const int TP = (int)(clen / (uint32_t)C);
-        const int64_t px_chunk0 = (int64_t)ch * (int64_t)sv.ppc;
+        // ---- inverse quantizer + inverse transform of the unit's pixels ----
+        const int64_t px_chunk0 = (int64_t)u * (int64_t)(un.m * (uint32_t)sv.ppc);
+        const int TP = p.P - px_chunk0 < (int64_t)(un.m * (uint32_t)sv.ppc) ? (int)(p.P - px_chunk0) : (int)(un.m * (uint32_t)sv.ppc);
         for (int pt = 0; pt * 32 < TP; pt++) {
             int pxl = pt * 32 + l32;
-            if (pxl > TP - 1) pxl = TP - 1;  // rows past the chunk repeat its last pixel; never stored
+            if (pxl > TP - 1) pxl = TP - 1;  // rows past the unit repeat its last pixel; never stored
+            // (chunks of whole runs lie in the tile as one chunk would; others each start a slot of their own)
+            const uint8_t* tile = symtile[wave];
+            if ((CFIX == 0 || CFIX % 64 != 0) && un.m > 1u && (sv.chunk_syms & 63u)) {  // wavefront-uniform
+                const uint32_t j = (uint32_t)pxl / (uint32_t)sv.ppc;
+                tile += 68u * sv.spc * j;
+                pxl -= (int)(j * (uint32_t)sv.ppc);
+            }
             const uint32_t rowbase = (uint32_t)pxl * (uint32_t)C + 8u * (uint32_t)half;
             if constexpr (U8) {
                 // Operands: lane (l32, half) holds the 8 symbols 16j + 8*half .. + 7 of its pixel as (s - 128),
@@ -1349,7 +1385,6 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
     p.syms_out = d_syms;
     p.err = d_err;
     p.prebuilt = d_prebuilt;
-    p.G = 1;
     p.g_off_chunk_off = g.off_chunk_off;
     p.g_off_sub_bits = g.off_sub_bits;
     p.g_off_payload = g.off_payload;
@@ -1458,7 +1493,6 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
     const bool wide = C > 512 || (uint64_t)((g.n_chunks + chunks_for(128) - 1) / chunks_for(128)) * n_cg < 128;
     int G = chunks_for(wide ? 64 : 128);
     if (d_syms) G = 8;  // symbols only: no projection to feed, one chunk per wavefront and as many workgroups as that gives
-    p.G = G;
     // the grid is sized from the nominal geometry; the kernel takes the real one from the header
     const uint32_t n_tiles = (g.n_chunks + G - 1) / G;
     // the channel groups (256 channels) of a tile go to workgroups of their own (each decodes the tile's
@@ -1474,7 +1508,11 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
     }
     unsigned gx = n_tiles < 1024u ? n_tiles : 1024u;
     dim3 grid(gx, (unsigned)groups);
-    const size_t lds = (size_t)G * 4096 + (size_t)G * 4096 / 16 + 128;
+    // (chunks of another size, whose last runs may be nearly empty, take more room for the same pixels: there is some to
+    // spare where a tile holds few pixels, and otherwise their tiles get smaller)
+    p.tile_px = wide ? 64 : 128;
+    p.tile_bytes = (uint32_t)G * 4352u;
+    const size_t lds = (size_t)p.tile_bytes + 128;
     // more than 64 KB of dynamic LDS has to be requested per kernel (the CU has 160 KB)
 #define FMTC_DEC(MT, LAY, AL)                                                                                \
     do {                                                                                                     \
@@ -1521,7 +1559,6 @@ hipError_t launch_decode_u8(const Basis8Device& b, const uint8_t* d_stream, size
     p.syms_out = nullptr;
     p.err = d_err;
     p.prebuilt = nullptr;
-    p.G = 1;
     p.g_off_chunk_off = g.off_chunk_off;
     p.g_off_sub_bits = g.off_sub_bits;
     p.g_off_payload = g.off_payload;

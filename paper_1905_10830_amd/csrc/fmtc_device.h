@@ -11,15 +11,29 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return v;
 }
 
+// x + (x of the lane the control word names), 0 where that lane does not exist or the row is masked out
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
+}
+// Inclusive prefix sum over the 64 lanes.  row: the sum within the lane's row of 16 lanes (lane 15 of a row
+// holds the row total); half: the sum within the lane's half of the wavefront (lanes 31 and 63 hold the totals).
+__device__ __forceinline__ uint32_t wave_inclusive_scan_rows(uint32_t v, uint32_t& row, uint32_t& half) {
+    v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);  // row_shr:8
+    row = v;
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    half = v;
+    v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // exclusive prefix sum over the 64 lanes
-__device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v, int lane) {
-    uint32_t incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
-    return incl - v;
+__device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v) {
+    uint32_t row, half;
+    return wave_inclusive_scan_rows(v, row, half) - v;
 }
 
 __device__ __forceinline__ unsigned long long wave_inclusive_scan64(unsigned long long v, int lane) {

@@ -54,25 +54,6 @@ struct PackParams {
     uint64_t* out_bytes;
 };
 
-// x + (x of the lane the control word names), 0 where that lane does not exist or the row is masked out
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp_add(uint32_t x) {
-    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
-}
-// Inclusive prefix sum over the 64 lanes.  row: the sum within the lane's row of 16 lanes (lane 15 of a row
-// holds the row total); half: the sum within the lane's half of the wavefront (lanes 31 and 63 hold the totals).
-__device__ __forceinline__ uint32_t wave_inclusive_scan_rows(uint32_t v, uint32_t& row, uint32_t& half) {
-    v = dpp_add<0x111, 0xf>(v);  // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);  // row_shr:2
-    v = dpp_add<0x114, 0xf>(v);  // row_shr:4
-    v = dpp_add<0x118, 0xf>(v);  // row_shr:8
-    row = v;
-    v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    half = v;
-    v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // ORs the bits of `c` (zero above its length) into the image at bit `pos` of the chunk.  The image is followed
 // by spare words: ORing zeros does no harm, so nothing here branches per lane.
 //   FIRST window: positions are cut off at the end of the image, what lies beyond lands in the spare words;

@@ -461,3 +461,63 @@ def test_planar_decoder(fmtc, oracle, C, H, W, N, bits, chunk):
         out = out.cpu().numpy()
         out = (out.transpose(0, 2, 3, 1) if tag == synth.NCHW else out).reshape(P, C)
         assert (np.abs(out - ref) <= tol).all(), f"largest error {np.abs(out - ref).max():.3e}"
+
+
+# Chunks decoded several at a time (a unit: as many as 64 lanes hold runs of): one to 64 chunks per unit, chunks of whole
+# and of broken runs, 33 runs (one chunk per unit again), a last unit of one chunk and a chunk of one pixel; narrow and
+# wide kernels, with and without 4-byte rows; the first chunks so busy that their unit does not fit the LDS copy.
+UNIT_CASES = [  # C, chunk, P
+    (64, 64, 1000), (3, 65, 4000), (100, 2048, 2101), (24, 330, 3003), (32, 1056, 4000), (128, 2176, 1200), (144, 288, 1001),
+    (160, 1000, 700), (50, 800, 1601), (200, 64, 777), (313, 1024, 430), (576, 1024, 641), (1000, 64, 150), (257, 600, 509),
+    (960, 2048, 131),
+]
+
+
+@pytest.mark.parametrize("C,chunk,P", UNIT_CASES, ids=[f"C{c[0]}k{c[1]}P{c[2]}" for c in UNIT_CASES])
+def test_decoder_of_small_chunks(fmtc, oracle, C, chunk, P):
+    from paper_1905_10830_amd import synth
+
+    bits, A = 8, np.float32(4.0)
+    rng = np.random.default_rng(C + chunk)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    mu = rng.standard_normal(C).astype(np.float32)
+    d = oracle.delta(A, bits)
+    level = np.clip(np.rint(rng.laplace(0.0, 1.0, (P, C))), -128, 127)
+    busy = min(P // 8, max(1, 4096 // C))
+    level[:busy] = rng.integers(-128, 128, (busy, C))
+    sym = (level + 128).astype(np.uint8)
+    stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, float(d), chunk)
+    basis = fmtc.basis_import(T, mu, A)
+    torch.cuda.synchronize()
+    n = int(nbytes.item())
+    back, err = fmtc.decode_symbols(stream, P, C, bits, nbytes=n)
+    torch.cuda.synchronize()
+    assert int(err.item()) == 0 and np.array_equal(back.cpu().numpy().reshape(P, C), sym)
+    ref = (level * float(d)) @ T.astype(np.float64) + mu
+    # as in test_planar_decoder
+    tol = (2.0 ** -22 + C * 2.0 ** -24) * ((np.abs(level) * float(d)) @ np.abs(T.astype(np.float64)) + np.abs(mu)) + 1e-7
+    for tag in (synth.NHWC, synth.NCHW):
+        shape = (1, 1, P, C) if tag == synth.NHWC else (1, C, 1, P)
+        out, err = fmtc.decode(basis, stream, shape, bits, tag, nbytes=n)
+        torch.cuda.synchronize()
+        assert int(err.item()) == 0
+        out = out.cpu().numpy().reshape((P, C) if tag == synth.NHWC else (C, P))
+        assert (np.abs((out if tag == synth.NHWC else out.T) - ref) <= tol).all()
+    # 8-bit activations: the same values whatever the chunk size
+    basis8 = fmtc.Basis8(basis, 0.05)
+    plain, plain_bytes = fmtc.code_symbols(dev(sym), C, bits, float(d))
+    outs = []
+    for s, b in ((stream, nbytes), (plain, plain_bytes)):
+        out, err = fmtc.decode_u8(basis8, s, (1, 1, P, C), bits, synth.NHWC, nbytes=int(b.item()))
+        torch.cuda.synchronize()
+        assert int(err.item()) == 0
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+    # two neighbouring chunk offsets exchanged
+    bad = stream[:n].clone()
+    co = bad[320:320 + 16].view(torch.int32)
+    co[[1, 2]] = co[[2, 1]]
+    for decode in (lambda: fmtc.decode(basis, bad, (1, 1, P, C), bits, synth.NHWC), lambda: fmtc.decode_symbols(bad, P, C, bits)):
+        _, err = decode()
+        torch.cuda.synchronize()
+        assert int(err.item()) & fmtc.ERR_OFFSETS
