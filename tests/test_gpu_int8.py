@@ -94,6 +94,38 @@ def test_u8_path_is_bit_exact(fmtc, oracle, case, layout):
     assert np.array_equal(out.cpu().numpy(), oracle.reconstruct_u8(want, xs.shape, Tq, sT, mf, sx, d, bits, layout))
 
 
+# The kernels of more than 128 channels: a single pixel, ragged last tiles of 64 pixels, images that end inside a group of
+# four pixels, channel counts that are no multiple of 4, 8 or 16, rows split over workgroups (few pixels) and not, more
+# tiles than workgroups, half a pair of contraction steps at the end.
+WIDE_CASES = [  # C, H, W, images, bits
+    (129, 3, 3, 8, 8), (136, 1, 1, 1, 4), (130, 5, 13, 1030, 3), (313, 7, 7, 3, 7), (512, 4, 16, 2, 6), (1000, 1, 65, 1, 5),
+    (1024, 9, 12, 1, 2), (272, 14, 14, 40, 6),
+]
+
+
+@pytest.mark.parametrize("layout", [synth.NHWC, synth.NCHW], ids=["nhwc", "nchw"])
+@pytest.mark.parametrize("C,H,W,N,bits", WIDE_CASES, ids=[f"C{c[0]}P{c[1] * c[2] * c[3]}b{c[4]}" for c in WIDE_CASES])
+def test_u8_path_of_wide_tensors(fmtc, oracle, C, H, W, N, bits, layout):
+    rng = np.random.default_rng(C)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    mu = rng.uniform(0.0, 6.0, C).astype(np.float32)
+    xs = synth.to_layout(rng.integers(0, 256, (N, H, W, C)).astype(np.uint8), layout)
+    sx, A = np.float32(6.0 / 255.0), np.float32(8.0)
+    d = oracle.delta(A, bits)
+    Tq, sT, mf = oracle.basis8(T, mu, sx)
+    b8 = fmtc.Basis8(fmtc.basis_import(T, mu, A), sx)
+    want = oracle.quantize_u8(xs, Tq, sT, mf, sx, d, bits, layout)
+    sym = fmtc.quantize_u8(b8, dev(xs), bits, layout)
+    out = fmtc.reconstruct_u8(b8, dev(want), xs.shape, bits, layout)
+    stream, nbytes = fmtc.encode_u8(b8, dev(xs), bits, layout)
+    torch.cuda.synchronize()
+    assert np.array_equal(sym.cpu().numpy(), want)
+    assert np.array_equal(out.cpu().numpy(), oracle.reconstruct_u8(want, xs.shape, Tq, sT, mf, sx, d, bits, layout))
+    ln = oracle.huffman_lengths(oracle.histogram(want, bits)[: 1 << bits])
+    ref = oracle.pack(want, C, bits, d, ln, oracle.canonical_codes(ln))
+    assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
 def test_u8_codec_quality_and_errors(fmtc, oracle):
     """The 8-bit path is a usable codec (error of the order of the quantizer's plus the grids'), and the entry
     points refuse what does not fit."""
