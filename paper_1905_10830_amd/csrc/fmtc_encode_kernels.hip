@@ -6,9 +6,11 @@
 // runs on the f16 matrix cores (v_mfma_f32_32x32x16_f16) with every fp32 operand
 // split into two f16 parts, which is as accurate as the fp32 matrix instruction
 // and several times as fast; values that land too close to a rounding boundary
-// for the fast pass to decide are recomputed in fp64 by the wavefront.  Two
-// kernels: one wavefront per 32 pixels with the basis in LDS (up to 160
-// channels), and a workgroup tile in LDS with the basis streamed from L2 (wider).
+// for the fast pass to decide are recomputed in fp64 by the wavefront.  Three
+// forms: one wavefront per 32 pixels with the basis in LDS (up to 160 channels),
+// a 128 x 128 tile per workgroup (wider), and a small tile whose contraction the
+// workgroup's wavefronts share out (few pixels; channel counts that are no
+// multiple of 16).
 #include <atomic>
 #include <type_traits>
 
@@ -19,398 +21,8 @@
 namespace fmtc {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-// ---------------------------------------------------------------------------
-// Wide tensors (more than 160 channels after padding to 32).  The contraction is the same f16
-// split as in the narrow-tensor kernel below (three v_mfma_f32_32x32x16_f16 per 16 channels,
-// see there), but a pixel's channels no longer fit a wavefront's registers: the workgroup
-// (8 wavefronts) first brings a tile of PT pixels, all channels, into LDS -- coalesced global
-// reads, mean removed and split into the two f16 parts on the way, rows padded by 16 bytes so
-// that the 16-byte operand reads of 8 neighbouring pixels cover all banks -- then its
-// wavefronts share out the work units (coefficient tile, 32-pixel group) of the workgroup's
-// coefficient range [kt0, kt0 + ktg) without further barriers, the four wavefronts of a round
-// taking the pixel groups of one coefficient tile so that they read the same part of the
-// basis, which streams from L2 in operand order one step ahead of its use.  Values too close
-// to a rounding boundary are recomputed in fp64; the quantized tile is staged in LDS and
-// leaves as whole rows of symbols.
-// PT: pixels per workgroup; LAYOUT: FMTC_NHWC / FMTC_NCHW; VEC: C % 4 == 0 (16-byte loads of
-// channels-last rows and 4-byte symbol stores are aligned).
-// ---------------------------------------------------------------------------
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
-
-struct WideParams {
-    const float* x;
-    const uint16_t* basis16;  // fwd16 packing
-    const float* mu;          // [Cpad]
-    const float* Trow;        // [C][C] row major, for the exact decisions
-    int64_t P, HW;
-    int C, ncs, kt_per_group, bits;
-    float inv_delta, delta, kappa, tau_min;
-    int64_t px_tiles;
-    uint8_t* syms;
-    uint32_t* hist_parts;
-    CoderCtrl* ctrl;
-    unsigned long long* lookback;
-    uint32_t n_groups;
-};
-
-constexpr int kWideThreads = 512;
-
-template <int PT, int LAYOUT, bool VEC>
-__global__ __launch_bounds__(kWideThreads) void k_project_quantize_wide(WideParams p) {
-    extern __shared__ __align__(16) uint8_t dyn_lds[];
-    __shared__ uint32_t lhist[256];
-    __shared__ float s_n2[PT];  // |x - mu|^2 of every pixel of the tile
-    zero_coder_scratch(p.ctrl, p.lookback, p.n_groups);
-
-    const int C = p.C, ncs = p.ncs;
-    const int Cpad = ncs * 32, NJ = ncs * 2;
-    const int RSH = Cpad + 8;  // pixel row stride in halves
-    const int kt0 = blockIdx.y * p.kt_per_group;
-    const int ktg = (ncs - kt0 < p.kt_per_group) ? ncs - kt0 : p.kt_per_group;
-    const int RSW = p.kt_per_group * 8 + 1;  // staging row stride in words
-    _Float16* xh = reinterpret_cast<_Float16*>(dyn_lds);
-    _Float16* xl = xh + (size_t)PT * RSH;
-    uint32_t* st = reinterpret_cast<uint32_t*>(xl + (size_t)PT * RSH);
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5, l32 = lane & 31;
-
-    if (tid < 256) lhist[tid] = 0u;
-    const int zero_sym = 1 << (p.bits - 1);
-    const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1);
-    const float inv_delta = p.inv_delta, inv_delta_lo = p.inv_delta * (1.f / 2048.f);
-
-    // the two f16 parts of one value (clamped to what f16 holds: a pixel with such a value is decided exactly)
-    auto split = [](float v, _Float16& vh, _Float16& vl) {
-        v = __builtin_amdgcn_fmed3f(v, -60000.f, 60000.f);
-        vh = (_Float16)v;
-        vl = (_Float16)((v - (float)vh) * 2048.f);
-    };
-
-    // the workgroup walks over pixel tiles; its histogram accumulates in LDS and leaves once at the end
-    for (int64_t tile = blockIdx.x; tile < p.px_tiles; tile += gridDim.x) {
-        const int64_t px0 = tile * PT;
-        if (tid < PT) s_n2[tid] = 0.f;
-        __syncthreads();  // also: the previous tile's staging rows have left
-
-        // ---- the pixel tile, mean removed, split, as xh / xl [pixel][channel] ----
-        if constexpr (LAYOUT == FMTC_NHWC && VEC) {
-            const int n4 = PT * (C / 4);  // the tile is one contiguous run of PT*C floats
-            const float* src = p.x + px0 * C;
-            const int64_t lim = (p.P - px0) * C;  // floats of the tile that exist
-            constexpr int B = 8;  // loads in flight per thread
-            for (int idx0 = tid; idx0 < n4; idx0 += B * kWideThreads) {
-                float4 v[B];
-#pragma unroll
-                for (int b = 0; b < B; b++) {
-                    const int f = 4 * (idx0 + b * kWideThreads);
-                    v[b] = (idx0 + b * kWideThreads < n4 && f < lim) ? *reinterpret_cast<const float4*>(src + f)
-                                                                     : make_float4(0, 0, 0, 0);
-                }
-#pragma unroll
-                for (int b = 0; b < B; b++) {
-                    const int idx = idx0 + b * kWideThreads;
-                    if (idx < n4) {
-                        const int f = 4 * idx;
-                        const int pxl = f / C, c = f - pxl * C;
-                        const float4 m = *reinterpret_cast<const float4*>(p.mu + c);
-                        const float d[4] = {v[b].x - m.x, v[b].y - m.y, v[b].z - m.z, v[b].w - m.w};
-                        halfx4 vh, vl;
-                        float n2 = 0.f;
-#pragma unroll
-                        for (int i = 0; i < 4; i++) {
-                            _Float16 a, bb;
-                            split(d[i], a, bb);
-                            vh[i] = a;
-                            vl[i] = bb;
-                            n2 = __builtin_fmaf(d[i], d[i], n2);
-                        }
-                        *reinterpret_cast<halfx4*>(xh + pxl * RSH + c) = vh;
-                        *reinterpret_cast<halfx4*>(xl + pxl * RSH + c) = vl;
-                        atomicAdd(&s_n2[pxl], n2);
-                    }
-                }
-            }
-        } else if constexpr (LAYOUT == FMTC_NHWC) {
-            const int n1 = PT * C;
-            const float* src = p.x + px0 * C;
-            for (int idx = tid; idx < n1; idx += kWideThreads) {
-                const int pxl = idx / C, c = idx - pxl * C;
-                const float d = ((px0 + pxl < p.P) ? src[idx] : 0.f) - p.mu[c];
-                _Float16 a, b;
-                split(d, a, b);
-                xh[pxl * RSH + c] = a;
-                xl[pxl * RSH + c] = b;
-                atomicAdd(&s_n2[pxl], d * d);
-            }
-        } else {
-            const int pxl = tid % PT;
-            const int64_t px = px0 + pxl;
-            const bool ok = px < p.P;
-            int64_t base = 0;
-            if (ok) {
-                const int64_t n = px / p.HW;
-                base = n * (int64_t)C * p.HW + (px - n * p.HW);
-            }
-            float n2 = 0.f;
-            for (int c = tid / PT; c < C; c += kWideThreads / PT) {
-                const float d = (ok ? p.x[base + (int64_t)c * p.HW] : 0.f) - p.mu[c];
-                _Float16 a, b;
-                split(d, a, b);
-                xh[pxl * RSH + c] = a;
-                xl[pxl * RSH + c] = b;
-                n2 = __builtin_fmaf(d, d, n2);
-            }
-            atomicAdd(&s_n2[pxl], n2);
-        }
-        if (Cpad > C) {  // padding channels meet zero basis entries; they must still be finite
-            const int padw = Cpad - C;
-            for (int idx = tid; idx < PT * padw; idx += kWideThreads) {
-                const int pxl = idx / padw, c = C + (idx - pxl * padw);
-                xh[pxl * RSH + c] = (_Float16)0.f;
-                xl[pxl * RSH + c] = (_Float16)0.f;
-            }
-        }
-        __syncthreads();
-
-        constexpr int PG = PT / 32;  // pixel groups per workgroup
-        const int nunits = ktg * PG;
-        for (int u = wave; u < nunits; u += kWideThreads / 64) {
-            const int pg = u % PG, ktl = u / PG;
-            const int kt = kt0 + ktl;
-            const int pxl = pg * 32 + l32;
-            const bool px_ok = px0 + pxl < p.P;
-            floatx16 am, ac;
-#pragma unroll
-            for (int r = 0; r < 16; r++) { am[r] = 0.f; ac[r] = 0.f; }
-
-            // (kt, j): the 64 lanes' hi parts, then their lo parts, 16 bytes per lane each; the basis comes from L2
-            // (the wavefronts of a round read the same part of it), one step ahead of its use
-            const uint4* asrc = reinterpret_cast<const uint4*>(p.basis16) + (size_t)kt * NJ * 2 * 64 + lane;
-            uint4 th4 = asrc[0], tl4 = asrc[64];
-            const _Float16* bh = xh + pxl * RSH + 8 * half;
-            const _Float16* bl = xl + pxl * RSH + 8 * half;
-            for (int jj = 0; jj < NJ; jj++) {
-                uint4 nh4 = th4, nl4 = tl4;
-                if (jj + 1 < NJ) {
-                    nh4 = asrc[(size_t)(2 * jj + 2) * 64];
-                    nl4 = asrc[(size_t)(2 * jj + 3) * 64];
-                }
-                const halfx8 th = __builtin_bit_cast(halfx8, th4), tl = __builtin_bit_cast(halfx8, tl4);
-                const halfx8 xh8 = *reinterpret_cast<const halfx8*>(bh + 16 * jj);
-                const halfx8 xl8 = *reinterpret_cast<const halfx8*>(bl + 16 * jj);
-                am = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, xh8, am, 0, 0, 0);
-                ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, xl8, ac, 0, 0, 0);
-                ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl, xh8, ac, 0, 0, 0);
-                th4 = nh4;
-                tl4 = nl4;
-            }
-
-            // ---- quantize ----
-            // accumulator r = 4g + i of lane (pixel, h) is coefficient kt*32 + 16h + 4g + i of the pixel
-            const float n2 = s_n2[pxl];
-            const bool force = !(n2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
-            const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
-            const float near_limit = force ? -1.f : 0.5f - tau;
-            const int k0 = kt * 32 + 16 * half;
-            uint32_t words[4];
-            uint32_t near_mask = 0;  // bit r: the fast value is too close to a rounding boundary to be trusted
-#pragma unroll
-            for (int g = 0; g < 4; g++) {
-                uint32_t word = 0;
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const float t = __builtin_fmaf(ac[4 * g + i], inv_delta_lo, am[4 * g + i] * inv_delta);
-                    float q = __builtin_rintf(t);  // round half to even
-                    const bool near = !(fabsf(t - q) <= near_limit);
-                    q = __builtin_amdgcn_fmed3f(q, lo, hi);
-                    word |= (uint32_t)((int)q + zero_sym) << (8 * i);
-                    if (near && px_ok && (k0 + 4 * g + i) < C) near_mask |= 1u << (4 * g + i);
-                }
-                words[g] = word;
-            }
-            // ---- exact decision for the flagged values: fp64 recomputation, four values per round ----
-            // (same arithmetic as the definition: sum of T[k][c] * (x[c] - mu[c]), divided by the step).
-            // Each 16-lane group of the wavefront takes one flagged value, so the loads of four values overlap.
-            unsigned long long pending = __ballot(near_mask != 0);
-            while (pending) {
-                int Ls[4];
-                unsigned long long pm = pending;
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    Ls[q] = pm ? (__ffsll((long long)pm) - 1) : -1;
-                    pm &= pm - 1;
-                }
-                const int grp = lane >> 4;
-                const int Lq = grp == 0 ? Ls[0] : (grp == 1 ? Ls[1] : (grp == 2 ? Ls[2] : Ls[3]));
-                const bool active = Lq >= 0;
-                const uint32_t fm = (uint32_t)__shfl((int)near_mask, active ? Lq : 0, 64);
-                const int r = active ? (__ffs((int)fm) - 1) : 0;
-                const int k = kt * 32 + 16 * (Lq >> 5) + r;
-                const int64_t px = px0 + pg * 32 + (Lq & 31);
-                double part = 0.0;
-                if (active) {
-                    int64_t xbase, xstride;
-                    if constexpr (LAYOUT == FMTC_NHWC) {
-                        xbase = px * C;
-                        xstride = 1;
-                    } else {
-                        const int64_t n = px / p.HW;
-                        xbase = n * (int64_t)C * p.HW + (px - n * p.HW);
-                        xstride = p.HW;
-                    }
-#pragma unroll 8  // independent loads of eight terms in flight together: the loop is all latency
-                    for (int c = lane & 15; c < C; c += 16)
-                        part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)p.mu[c]);
-                }
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the 16-lane group
-                double qd = rint(part / (double)p.delta);
-                qd = fmin(fmax(qd, (double)lo), (double)hi);
-                const int sfix = (int)qd + zero_sym;
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const int rq = __shfl(r, 16 * q, 64);
-                    const int sq = __shfl(sfix, 16 * q, 64);
-                    if (lane == Ls[q]) {
-#pragma unroll
-                        for (int g = 0; g < 4; g++)
-                            if (g == (rq >> 2))
-                                words[g] = (words[g] & ~(0xffu << (8 * (rq & 3)))) | ((uint32_t)sq << (8 * (rq & 3)));
-                        near_mask &= ~(1u << rq);
-                    }
-                }
-                pending = __ballot(near_mask != 0);
-            }
-            // ---- count and stage ----
-            // zero-level symbols (the bulk) are counted with byte arithmetic, the others with LDS atomics
-            uint32_t zero_count = 0;
-            const uint32_t zero4 = (uint32_t)zero_sym * 0x01010101u;
-#pragma unroll
-            for (int g = 0; g < 4; g++) {
-                const int k = k0 + 4 * g;
-                const uint32_t word = words[g];
-                // 0x80 in every byte of the word that is a valid coefficient
-                const int nvalid = !px_ok ? 0 : (C - k >= 4 ? 4 : (C - k > 0 ? C - k : 0));
-                const uint32_t vmask = nvalid == 4 ? 0x80808080u : (0x80808080u >> (8 * (4 - nvalid))) * (nvalid != 0);
-                const uint32_t xz = word ^ zero4;
-                uint32_t t = (xz & 0x7f7f7f7fu) + 0x7f7f7f7fu;
-                t = ~(t | xz | 0x7f7f7f7fu);  // 0x80 where the byte equals the zero level
-                zero_count += (uint32_t)__popc(t & vmask);
-                uint32_t nz = ~t & vmask;
-                while (nz) {
-                    const int bit = __ffs((int)nz) - 1;  // 8*i + 7
-                    atomicAdd(&lhist[(word >> (bit - 7)) & 255u], 1u);
-                    nz &= nz - 1;
-                }
-                st[pxl * RSW + ktl * 8 + 4 * half + g] = word;
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) zero_count += __shfl_xor(zero_count, o, 64);
-            if (lane == 0 && zero_count) atomicAdd(&lhist[zero_sym], zero_count);
-        }
-        __syncthreads();
-
-        // ---- symbols leave as rows of ktg*32 bytes per pixel ----
-        const int kbase = kt0 * 32;
-        const int row_words = ktg * 8;
-        for (int idx = tid; idx < PT * row_words; idx += kWideThreads) {
-            const int row = idx / row_words, col = idx - row * row_words;
-            const int64_t px = px0 + row;
-            const int k = kbase + 4 * col;
-            if (px < p.P && k < C) {
-                const uint32_t word = st[row * RSW + col];
-                uint8_t* dst = p.syms + px * C + k;
-                if constexpr (VEC) {
-                    *reinterpret_cast<uint32_t*>(dst) = word;
-                } else {
-                    for (int i = 0; i < 4 && k + i < C; i++) dst[i] = (uint8_t)(word >> (8 * i));
-                }
-            }
-        }
-    }
-    __syncthreads();
-    // one row of partial counts per workgroup: nothing to clear beforehand, no global atomics
-    const int K = 1 << p.bits;
-    if (tid < K) p.hist_parts[(size_t)(blockIdx.x + blockIdx.y * gridDim.x) * K + tid] = lhist[tid];
-}
-
-static hipError_t launch_wide(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
-                              int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
-    WideParams p{};
-    p.x = d_x;
-    p.basis16 = b.fwd16;
-    p.mu = b.mu;
-    p.Trow = b.T;
-    p.P = P;
-    p.HW = HW;
-    p.C = b.C;
-    p.ncs = b.Cpad / 32;
-    p.bits = bits;
-    p.inv_delta = (float)(1.0 / (double)delta);
-    p.delta = delta;
-    // see launch_rows for the bound behind these two
-    p.kappa = 1.9073486e-6f /* 2^-19 */ * b.row_norm * p.inv_delta;
-    p.tau_min = 4.7683716e-7f /* 2^-21 */ * (float)(1 << (bits - 1));
-    p.syms = d_syms;
-    p.hist_parts = cs.hist_parts;
-    p.ctrl = cs.ctrl;
-    p.lookback = cs.lookback;
-    p.n_groups = cs.n_groups;
-    if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback)
-        return hipErrorInvalidValue;  // (a field left out would be a wild pointer on the device)
-    const int ncs = p.ncs;
-    // Pixel tile: the larger it is the fewer times the basis streams through; the tile (both f16 parts) and the
-    // staging rows have to fit LDS, and a small tensor is better off with more, smaller workgroups.
-    const size_t lds_cap = 150 * 1024;
-    int PT = 0, ktg = 0, kgroups = 1;
-    int64_t px_tiles = 0;
-    size_t lds = 0;
-    for (int cand = 128; cand >= 32; cand /= 2) {
-        px_tiles = (P + cand - 1) / cand;
-        // split the coefficient range over workgroup rows only when the pixel tiles alone leave the chip idle
-        kgroups = (int)((256 + px_tiles - 1) / px_tiles);
-        if (kgroups < 1) kgroups = 1;
-        ktg = (ncs + kgroups - 1) / kgroups;
-        if (ktg > 16) ktg = 16;  // bounds the staging rows
-        if (ktg > ncs) ktg = ncs;
-        kgroups = (ncs + ktg - 1) / ktg;
-        lds = (size_t)cand * (b.Cpad + 8) * 4 + sizeof(uint32_t) * (size_t)cand * (ktg * 8 + 1);
-        PT = cand;
-        if (lds <= lds_cap && (px_tiles >= 256 || cand == 32)) break;
-    }
-    if (lds > 158 * 1024) return hipErrorInvalidValue;  // not reachable for C <= 1024
-    p.kt_per_group = ktg;
-    p.px_tiles = px_tiles;
-    int64_t gx = px_tiles;
-    if (gx * kgroups > kMaxHistParts) gx = kMaxHistParts / kgroups;
-    dim3 grid((unsigned)gx, (unsigned)kgroups);
-    *n_parts = (int)(gx * kgroups);
-    const bool vec = (b.C % 4) == 0;
-    hipError_t el = hipSuccess;
-#define FMTC_WIDE(PTV, LAY, VEC)                                                                                 \
-    do {                                                                                                         \
-        hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_project_quantize_wide<PTV, LAY, VEC>), \
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
-        if (ea != hipSuccess) return ea;                                                                         \
-        el = launch(K_PROJECT, k_project_quantize_wide<PTV, LAY, VEC>, grid, dim3(kWideThreads), lds, s, p);     \
-    } while (0)
-#define FMTC_WIDE_PT(LAY, VEC)                                                                                   \
-    do {                                                                                                         \
-        if (PT == 128) FMTC_WIDE(128, LAY, VEC);                                                                 \
-        else if (PT == 64) FMTC_WIDE(64, LAY, VEC);                                                              \
-        else FMTC_WIDE(32, LAY, VEC);                                                                            \
-    } while (0)
-    if (layout == FMTC_NHWC) { if (vec) FMTC_WIDE_PT(FMTC_NHWC, true); else FMTC_WIDE_PT(FMTC_NHWC, false); }
-    else                     { if (vec) FMTC_WIDE_PT(FMTC_NCHW, true); else FMTC_WIDE_PT(FMTC_NCHW, false); }
-#undef FMTC_WIDE_PT
-#undef FMTC_WIDE
-    return el;
-}
 
 // ---------------------------------------------------------------------------
 // Narrow tensors (at most 160 channels after padding to 32).  One wavefront owns 32 pixels
@@ -2207,6 +1819,370 @@ static hipError_t launch_gemm(const BasisDevice& b, const float* d_x, int64_t P,
                                : launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NCHW>, grid, dim3(256), lds, s, p);
 }
 
+// ---------------------------------------------------------------------------
+// Few pixels, and channel counts that are no multiple of 16.  The kernels above walk all C / 16 dependent steps of a tile
+// in one wavefront or behind barriers, and with few tiles most of the device idles meanwhile; here a tile is 32 PT pixels x 32 KT
+// coefficients and its W wavefronts share out the contraction instead: each takes a run of the 16-channel steps, its
+// operands straight from memory in registers several steps ahead (the basis in operand order, a lane's eight channels of
+// its pixel as they lie), with no barrier in the loop.  The partial sums meet once in LDS, and every wavefront quantizes
+// a part of the tile.  What bounds it: the latency of the loads (few tiles), then the caches' rate: a tile's operands are
+// read by all tiles of its row and column.  Coefficient tiles are the fastest block index, padded to the eight dies, so
+// that a die's L2 holds its share of the basis.  Measured, us (a pixel tile with all channels in LDS, the 128 x 128 tiles or the
+// narrow kernel before): 314 channels, 20 x 20 25.6 -> 7.8; 768, N = 4, 7 x 6 32 -> 13.6; 1024, N = 8, 11 x 11 43 -> 29,
+// planar 79 -> 31; 619, N = 20, 9 x 9 53 -> 23; 1001, N = 64, 7 x 7 186 -> 80; 169, N = 9, 80 x 80 122 -> 65; 124, N = 1,
+// 20 x 20 12.9 -> 4.8; 64, 56 x 56 7.7 -> 5.3.
+// ---------------------------------------------------------------------------
+struct SplitParams {
+    const float* x;
+    const uint4* basis16;  // fwd16 packing: [ncs][NJ][2][64]
+    const float* mu;       // [Cpad]
+    const float* Trow;
+    int64_t P, HW, n_pg;   // groups of 32 PT pixels
+    int C, ncs, NJ, bits;
+    int active_kt;         // coefficient tiles from here on are left out: their rows of the basis are all zero
+    int n_kg, n_kg_pad;    // groups of KT coefficient tiles; as block indices
+    int hist_shift;
+    float inv_delta, delta, kappa, tau_min;
+    uint8_t* syms;
+    uint32_t* hist_parts;
+    CoderCtrl* ctrl;
+    unsigned long long* lookback;
+    uint32_t n_groups;
+};
+
+struct __attribute__((packed, aligned(4))) Float4u { float v[4]; };  // four floats at any float's address
+
+template <int PT, int KT, int W, int D, int E, int LAYOUT>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(E, E))) void k_project_quantize_split(SplitParams p) {
+    constexpr int TILES = PT * KT;
+    constexpr int QW = TILES * 4 > W ? TILES * 4 / W : 1;  // quads of accumulators that a wavefront quantizes
+    static_assert(QW <= 4 && (QW * W == TILES * 4 || QW == 1), "quads of one tile per wavefront");
+    extern __shared__ __align__(16) uint8_t dyn_lds[];
+    // partial sums [W][TILES][4][64] (four per lane), mean [Cpad], histogram copies [K << hist_shift]
+    float4* s_part = reinterpret_cast<float4*>(dyn_lds);
+    float* s_mu = reinterpret_cast<float*>(s_part + W * TILES * 4 * 64);
+    uint32_t* s_hist = reinterpret_cast<uint32_t*>(s_mu + 16 * p.NJ);
+    __shared__ float s_n2[W][PT * 32];
+
+    zero_coder_scratch(p.ctrl, p.lookback, p.n_groups);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int C = p.C, NJ = p.NJ, K = 1 << p.bits, HS = p.hist_shift, HC = 1 << HS;
+    const int kg = (int)(blockIdx.x % (unsigned)p.n_kg_pad);
+    if (kg >= p.n_kg) return;
+    const int64_t pg0 = blockIdx.x / (unsigned)p.n_kg_pad, pg_step = gridDim.x / (unsigned)p.n_kg_pad;
+    const int kt0 = kg * KT;
+    // this wavefront's steps (none where the basis' rows are all zero: every sum is then exactly zero)
+    const bool computed = kt0 < p.active_kt;
+    const int s_begin = computed ? wave * NJ / W : 0, s_end = computed ? (wave + 1) * NJ / W : 0;
+
+    const uint4* a_src[KT];
+#pragma unroll
+    for (int a = 0; a < KT; a++) {
+        int kt = kt0 + a;
+        kt = kt < p.ncs ? kt : p.ncs - 1;  // a tile past the end repeats the last one; its results are dropped
+        a_src[a] = p.basis16 + (size_t)kt * NJ * 128 + lane;
+    }
+    struct Step {
+        uint4 th[KT], tl[KT];
+        float v[PT][8];
+    };
+    Step buf[D];
+    const float* xsrc[PT];
+    auto locate = [&](int64_t pg) {  // past the end of the tensor the last pixel is loaded; its results are dropped
+#pragma unroll
+        for (int b = 0; b < PT; b++) {
+            int64_t q = (pg * PT + b) * 32 + l32;
+            q = q < p.P ? q : p.P - 1;
+            if constexpr (LAYOUT == FMTC_NHWC) {
+                xsrc[b] = p.x + q * C + 8 * half;
+            } else {
+                const int64_t n_img = q / p.HW;
+                xsrc[b] = p.x + n_img * (int64_t)C * p.HW + (q - n_img * p.HW) + (int64_t)(8 * half) * p.HW;
+            }
+        }
+    };
+    auto load = [&](Step& t, int s) {
+#pragma unroll
+        for (int a = 0; a < KT; a++) {
+            t.th[a] = a_src[a][(size_t)s * 128];
+            t.tl[a] = a_src[a][(size_t)s * 128 + 64];
+        }
+        if (16 * s + 16 <= C) {
+#pragma unroll
+            for (int b = 0; b < PT; b++) {
+                if constexpr (LAYOUT == FMTC_NHWC) {
+                    const Float4u u0 = *reinterpret_cast<const Float4u*>(xsrc[b] + 16 * s);
+                    const Float4u u1 = *reinterpret_cast<const Float4u*>(xsrc[b] + 16 * s + 4);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) { t.v[b][e] = u0.v[e]; t.v[b][4 + e] = u1.v[e]; }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) t.v[b][e] = xsrc[b][(int64_t)(16 * s + e) * p.HW];
+                }
+            }
+        } else {  // the channels that are missing from the last step meet a zero basis and a zero mean
+            const int left = C - 16 * s - 8 * half;
+#pragma unroll
+            for (int b = 0; b < PT; b++)
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    t.v[b][e] = e < left ? xsrc[b][(int64_t)(16 * s + e) * (LAYOUT == FMTC_NHWC ? 1 : p.HW)] : 0.f;
+        }
+    };
+    locate(pg0);
+    if (pg0 < p.n_pg) {
+#pragma unroll
+        for (int d = 0; d < D; d++)
+            if (s_begin + d < s_end) load(buf[d], s_begin + d);
+    }
+    for (int i = tid; i < 16 * NJ; i += 64 * W) s_mu[i] = p.mu[i];
+    for (int i = tid; i < K << HS; i += 64 * W) s_hist[i] = 0u;
+    __syncthreads();
+
+    const int zero_sym = 1 << (p.bits - 1);
+    const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1);
+    const float magic = 12582912.f + (float)zero_sym;  // rounding, offset and conversion in one addition: see k_project_quantize_rows
+    const float magic_lo = 12582912.f, magic_hi = 12582912.f + (float)(2 * zero_sym - 1);
+
+    for (int64_t pg = pg0; pg < p.n_pg; pg += pg_step) {
+        if (pg != pg0) {
+            locate(pg);
+#pragma unroll
+            for (int d = 0; d < D; d++)
+                if (s_begin + d < s_end) load(buf[d], s_begin + d);
+        }
+        floatx16 am[PT][KT], ac[PT][KT];
+        float n2[PT];
+#pragma unroll
+        for (int b = 0; b < PT; b++) {
+            n2[b] = 0.f;
+#pragma unroll
+            for (int a = 0; a < KT; a++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) { am[b][a][r] = 0.f; ac[b][a][r] = 0.f; }
+        }
+        for (int s0 = s_begin; s0 < s_end; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; d++) {
+                const int s = s0 + d;
+                if (s >= s_end) break;  // wavefront-uniform
+                Step& t = buf[d];
+                const float4 m0 = *reinterpret_cast<const float4*>(&s_mu[16 * s + 8 * half]);
+                const float4 m1 = *reinterpret_cast<const float4*>(&s_mu[16 * s + 8 * half + 4]);
+                const float m[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+                halfx8 xh[PT], xl[PT];
+#pragma unroll
+                for (int b = 0; b < PT; b++)
+#pragma unroll
+                    for (int e = 0; e < 8; e++) {
+                        // (no clamp of values beyond f16: what their infinities make of the products stays in the pixel's own
+                        // column of outputs, and such a pixel is decided exactly in all coefficients, see n2)
+                        const float dv = t.v[b][e] - m[e];
+                        n2[b] = __builtin_fmaf(dv, dv, n2[b]);
+                        const _Float16 h = (_Float16)dv;
+                        xh[b][e] = h;
+                        xl[b][e] = (_Float16)__builtin_fmaf((float)h, -2048.f, dv * 2048.f);  // 2^11 (d - h), exact, one mixed multiply-add
+                    }
+                halfx8 th[KT], tl[KT];
+#pragma unroll
+                for (int a = 0; a < KT; a++) {
+                    th[a] = __builtin_bit_cast(halfx8, t.th[a]);
+                    tl[a] = __builtin_bit_cast(halfx8, t.tl[a]);
+                }
+#pragma unroll
+                for (int b = 0; b < PT; b++)
+#pragma unroll
+                    for (int a = 0; a < KT; a++) {
+                        am[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th[a], xh[b], am[b][a], 0, 0, 0);
+                        ac[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th[a], xl[b], ac[b][a], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int b = 0; b < PT; b++)
+#pragma unroll
+                    for (int a = 0; a < KT; a++)
+                        ac[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl[a], xh[b], ac[b][a], 0, 0, 0);
+                if (s + D < s_end) load(t, s + D);
+            }
+        }
+        // ---- the partial sums meet ----
+#pragma unroll
+        for (int b = 0; b < PT; b++) {
+            n2[b] += __shfl_xor(n2[b], 32, 64);  // the other half of the pixel
+            if (half == 0) s_n2[wave][b * 32 + l32] = n2[b];
+#pragma unroll
+            for (int a = 0; a < KT; a++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) {
+                    float y[4];
+#pragma unroll
+                    for (int i = 0; i < 4; i++) y[i] = __builtin_fmaf(ac[b][a][4 * g + i], 1.f / 2048.f, am[b][a][4 * g + i]);
+                    s_part[((wave * TILES + b * KT + a) * 4 + g) * 64 + lane] = make_float4(y[0], y[1], y[2], y[3]);
+                }
+        }
+        __syncthreads();
+        if (QW * W == TILES * 4 || wave < TILES * 4) {
+            const int unit = wave * QW, tile = unit >> 2, q0 = unit & 3;
+            const int pt = tile / KT, kt = kt0 + tile % KT;
+            const int64_t px = (pg * PT + pt) * 32 + l32;
+            const int k0 = kt * 32 + 16 * half + 4 * q0;
+            int valid = px < p.P ? C - k0 : 0;  // coefficients of this lane that exist
+            valid = valid < 0 ? 0 : (valid > 4 * QW ? 4 * QW : valid);
+            float pn2 = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; w++) pn2 += s_n2[w][pt * 32 + l32];
+            const bool force = !(pn2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
+            const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(pn2), p.tau_min), 0.125f);
+            const float near_limit = force ? -1.f : 0.5f - tau;
+            uint32_t word[QW], near_mask = 0;
+#pragma unroll
+            for (int g = 0; g < QW; g++) {
+                float4 y = s_part[unit * 64 + g * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < W; w++) {
+                    const float4 o = s_part[(w * TILES * 4 + unit + g) * 64 + lane];
+                    y.x += o.x; y.y += o.y; y.z += o.z; y.w += o.w;
+                }
+                const float ys[4] = {y.x, y.y, y.z, y.w};
+                uint32_t ub[4];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const float t = ys[i] * p.inv_delta;
+                    const float u = t + magic;  // round half to even
+                    if (!(fabsf(t - (u - magic)) <= near_limit) && 4 * g + i < valid) near_mask |= 1u << (4 * g + i);
+                    ub[i] = clamp_pattern(u, magic_lo, magic_hi);  // (its lowest byte is the symbol: in range whatever u is)
+                }
+                word[g] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(ub[3], ub[2], 0x0c0c0400u),
+                                                __builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u), 0x05040100u);
+            }
+            // ---- exact fp64 decision of the flagged values, two per round (one per half of the wavefront) ----
+            unsigned long long pending = __ballot(near_mask != 0);
+            while (__builtin_expect(pending != 0, 0)) {
+                const int L0 = __ffsll((long long)pending) - 1;
+                const unsigned long long rest = pending & (pending - 1);
+                const int L1 = rest ? __ffsll((long long)rest) - 1 : -1;
+                const int Lq = half ? L1 : L0;
+                const bool active = Lq >= 0;
+                const uint32_t fm = (uint32_t)__shfl((int)near_mask, active ? Lq : 0, 64);
+                const int r = active ? __ffs((int)fm) - 1 : 0;
+                double part = 0.0;
+                if (active) {
+                    const int k = kt * 32 + 16 * (Lq >> 5) + 4 * q0 + r;
+                    const int64_t qpx = (pg * PT + pt) * 32 + (Lq & 31);
+                    int64_t xbase = qpx * C, xstride = 1;
+                    if constexpr (LAYOUT != FMTC_NHWC) {
+                        const int64_t n_img = qpx / p.HW;
+                        xbase = n_img * (int64_t)C * p.HW + (qpx - n_img * p.HW);
+                        xstride = p.HW;
+                    }
+#pragma unroll 16  // independent loads in flight together: the loop is all latency
+                    for (int c = l32; c < C; c += 32)
+                        part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)s_mu[c]);
+                }
+#pragma unroll
+                for (int o = 16; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the half
+                double qd = rint(part / (double)p.delta);
+                qd = fmin(fmax(qd, (double)lo), (double)hi);
+                const int sfix = (int)qd + zero_sym;
+                const int r0 = __shfl(r, 0, 64), r1 = __shfl(r, 32, 64), f0 = __shfl(sfix, 0, 64), f1 = __shfl(sfix, 32, 64);
+                if (lane == L0 || lane == L1) {
+                    const int rq = lane == L0 ? r0 : r1;
+                    const uint32_t sq = (uint32_t)(lane == L0 ? f0 : f1);
+#pragma unroll
+                    for (int g = 0; g < QW; g++)
+                        if (g == (rq >> 2)) word[g] = (word[g] & ~(0xffu << (8 * (rq & 3)))) | (sq << (8 * (rq & 3)));
+                    near_mask &= ~(1u << rq);
+                }
+                pending = __ballot(near_mask != 0);
+            }
+            // ---- count and store ----
+#pragma unroll
+            for (int g = 0; g < QW; g++)
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (4 * g + i < valid) atomicAdd(&s_hist[(((word[g] >> (8 * i)) & 255u) << HS) + (lane & (HC - 1))], 1u);
+            uint8_t* dst = p.syms + px * C + k0;
+            if ((C & 15) == 0) {  // all of a lane's coefficients or none, aligned
+                if (valid) {
+                    if constexpr (QW == 4) *reinterpret_cast<uint4*>(dst) = make_uint4(word[0], word[1], word[2], word[3]);
+                    else if constexpr (QW == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(word[0], word[1]);
+                    else *reinterpret_cast<uint32_t*>(dst) = word[0];
+                }
+            } else {
+#pragma unroll
+                for (int g = 0; g < QW; g++) {
+                    if ((C & 3) == 0) {
+                        if (4 * g < valid) *reinterpret_cast<uint32_t*>(dst + 4 * g) = word[g];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; i++)
+                            if (4 * g + i < valid) dst[4 * g + i] = (uint8_t)(word[g] >> (8 * i));
+                    }
+                }
+            }
+        }
+        __syncthreads();  // the partial sums have been read
+    }
+    // one row of partial counts per workgroup (see the narrow-tensor kernel)
+    for (int row = tid; row < K; row += 64 * W) {
+        uint32_t total = 0;
+        for (int q = 0; q < HC; q++) total += s_hist[(row << HS) + ((q + row) & (HC - 1))];
+        p.hist_parts[(size_t)(pg0 * p.n_kg + kg) * K + row] = total;
+    }
+}
+
+template <int PT, int KT, int W, int D, int E>
+static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
+                               int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
+    SplitParams p{};
+    p.x = d_x;
+    p.basis16 = reinterpret_cast<const uint4*>(b.fwd16);
+    p.mu = b.mu;
+    p.Trow = b.T;
+    p.P = P;
+    p.HW = HW;
+    p.C = b.C;
+    p.ncs = b.Cpad / 32;
+    p.NJ = b.Cpad / 16;
+    p.bits = bits;
+    p.n_pg = (P + 32 * PT - 1) / (32 * PT);
+    p.n_kg = (p.ncs + KT - 1) / KT;
+    // (a block beyond the last coefficient group ends at once)
+    const int padded = (p.n_kg + 7) / 8 * 8;
+    p.n_kg_pad = 4 * (padded - p.n_kg) <= p.n_kg ? padded : p.n_kg;
+    // groups of four coefficient tiles whose rows of the basis are all zero (truncation) are not computed
+    p.active_kt = b.C % 16 == 0 ? (b.active_rows + 127) / 128 * 4 : p.ncs;
+    if (p.active_kt < 4) p.active_kt = 4;
+    p.inv_delta = (float)(1.0 / (double)delta);
+    p.delta = delta;
+    // see launch_rows for the bound behind these two (the W partial sums and the two roundings after them add at most
+    // (W + 2) 2^-24 |T_k|_2 |x - mu|_2: 2^-20.7 at W = 8)
+    p.kappa = 1.9073486e-6f /* 2^-19 */ * b.row_norm * p.inv_delta;
+    p.tau_min = 4.7683716e-7f /* 2^-21 */ * (float)(1 << (bits - 1));
+    p.syms = d_syms;
+    p.hist_parts = cs.hist_parts;
+    p.ctrl = cs.ctrl;
+    p.lookback = cs.lookback;
+    p.n_groups = cs.n_groups;
+    // every pointer the kernel follows is set (a field left out here would be a wild pointer on the device)
+    if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback)
+        return hipErrorInvalidValue;
+    int64_t gx = p.n_pg;
+    if (gx * p.n_kg > kMaxHistParts) gx = kMaxHistParts / p.n_kg;
+    *n_parts = (int)(gx * p.n_kg);
+    // histogram copies: 8 KB at most, so that two workgroups with 64 KB of partial sums share a compute unit
+    p.hist_shift = bits <= 7 ? 4 : 3;
+    const size_t lds = sizeof(float4) * W * PT * KT * 4 * 64 + sizeof(float) * b.Cpad + (sizeof(uint32_t) << (bits + p.hist_shift));
+    const void* fn = layout == FMTC_NHWC ? reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, W, D, E, FMTC_NHWC>)
+                                         : reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>);
+    hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (ea != hipSuccess) return ea;
+    const dim3 grid((unsigned)(gx * p.n_kg_pad));
+    return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NHWC>, grid, dim3(64 * W), lds, s, p)
+                               : launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>, grid, dim3(64 * W), lds, s, p);
+}
+
 hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64_t N, int64_t HW, int layout,
                                    float delta, int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts,
                                    hipStream_t s) {
@@ -2215,11 +2191,30 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
     // in LDS beside the basis: 100 + 64 KB); for planar tensors only the streaming form, with 32-bit offsets and whole groups
     // of 16 channels
     const bool fits160 = b.Cpad == 160 && bits < 8 && (layout == FMTC_NHWC || (b.C % 16 == 0 && planar_offsets_fit(b.C, P, HW)));
-    if (b.Cpad <= 128 || fits160)
-        return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    // wide: the tiled matrix product needs whole groups of 16 channels; other channel counts keep the pixel-tile kernel
-    if (b.C % 16 == 0) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    return launch_wide(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    const bool narrow = b.Cpad <= 128 || fits160, whole16 = b.C % 16 == 0;
+    const int ncs = b.Cpad / 32;
+    const int64_t tiles = (P + 31) / 32 * ncs;  // of 32 pixels x 32 coefficients
+    // Up to 32 channels the narrow kernel has no contraction to split (5.4 to 6.4 us against 6.0 at 16 and 32 channels).
+    if (narrow && ncs == 1) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    // The split contraction's tile grows with their number.  One or two coefficient tiles per workgroup while that leaves
+    // compute units idle otherwise (us, 1 : 2 : 4 of them: 512 channels, 64 tiles 10.5 : 11.2 : 12.8; 768 channels, 312 tiles
+    // 17.3 : 14.6 : 17.2; 512 channels, 720 tiles 21.5 : 16.9 : 15.0).
+    if (tiles <= 256) return launch_split<1, 1, 4, 4, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (tiles <= 640 || (tiles <= 1024 && ncs == 2))
+        return launch_split<1, 2, 4, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    // Four of them: up to 1024 tiles instead of the narrow kernels (us, theirs first: 96 channels, 999 tiles 11.9 : 8.4; 128
+    // 10.9 : 8.5; 160 13.8 : 10.4; at 144 channels and 2330 tiles 13.9 : 17.8), and of 100 to 127 channels that are no multiple
+    // of 16, which those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 12800 57.2 : 55.6); instead
+    // of the tiled product, whose steps are a chain of barriers, up to 1536 tiles (512, 1456 25.6 : 23.1; 256, 1600 16.9 :
+    // 12.6; 1024, 1568 43.5 : 46.6; 512, 2304 26.8 : 33.4), up to 4096 where it fetches planar pixels four bytes at a time
+    // (512, 2304 46.3 : 31.6; 960, 2940 88 : 63; 256, 4096 28.0 : 24.8; 384, 4464 39.7 : 38.5, 192, 9900 45 : 51).
+    const int64_t four = narrow ? (ncs == 4 && !whole16 ? 16384 : 1024) : (whole16 && layout == FMTC_NHWC ? 1536 : 4096);
+    if (tiles <= four) return launch_split<1, 4, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (narrow) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    // The tiled product needs whole groups of 16 channels.  Other channel counts take two by two tiles (us, 1 x 4 : 2 x 2:
+    // 169 channels, 10800 tiles 77 : 65; 180, 19200 99 : 83; 300, 7520 60.5 : 58.8; 1001, 3136 80 : 80).
+    if (whole16) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    return launch_split<2, 2, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
 }
 
 // Histogram of given symbols (staged coder entry point): one row of partial counts per workgroup.

@@ -367,7 +367,7 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None):
 
 
 # Rows of a basis with entries that f16 does not hold (not orthonormal, but accepted): every kernel family decides their
-# coefficients exactly.  Tiled product with four and eight wavefronts, streaming and rows form, pixel-tile kernel.
+# coefficients exactly.  Tiled product with four and eight wavefronts, streaming and rows form, split form.
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
 @pytest.mark.parametrize("C,P", [(32, 500), (64, 3000), (100, 700), (128, 40000), (144, 5000), (176, 16411), (256, 2000), (250, 900)])
 def test_projection_with_basis_entries_beyond_f16(fmtc, oracle, C, P, layout):
@@ -379,6 +379,20 @@ def test_projection_with_basis_entries_beyond_f16(fmtc, oracle, C, P, layout):
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
 @pytest.mark.parametrize("C,P,bits", WIDE_CASES, ids=[f"C{c[0]}P{c[1]}b{c[2]}" for c in WIDE_CASES])
 def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
+    H = next(h for h in (10, 7, 5, 3, 2, 1) if P % h == 0)
+    check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
+
+
+# The split contraction: one, two and four coefficient tiles per workgroup (up to 256, 640 and 4096 tiles of 32 x 32) and two by
+# two tiles beyond; wavefronts without a step (2 to 5 of them at 33 to 80 channels), last steps of 1 to 15 channels, ragged
+# last pixel and coefficient tiles, more pixel groups than workgroups; a pixel beyond f16, decided exactly in all coefficients.
+SPLIT_CASES = [(33, 1, 2), (48, 8192, 8), (80, 3333, 5), (99, 9000, 6), (128, 5000, 3), (161, 40, 4), (250, 1300, 8), (255, 2600, 5),
+               (316, 20000, 6), (353, 13000, 7), (1023, 70, 4), (1024, 33, 8), (1024, 1400, 5), (701, 6100, 2)]
+
+
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("C,P,bits", SPLIT_CASES, ids=[f"C{c[0]}P{c[1]}b{c[2]}" for c in SPLIT_CASES])
+def test_split_projection(fmtc, oracle, C, P, bits, layout):
     H = next(h for h in (10, 7, 5, 3, 2, 1) if P % h == 0)
     check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
 
