@@ -25,6 +25,22 @@ typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 // pad bytes so that the 64 lanes of a decoding wavefront hit different banks
 __device__ __forceinline__ uint32_t sym_addr(uint32_t n) { return n + 4u * (n >> 6); }
 
+// Symbols n .. n + 7 of a tile (which starts on a word), four to a word.  ALIGNED4: n is a multiple of 4.  Otherwise the
+// three words around them (eight byte reads instead, and their joining, took two thirds of the wide decoder's time at 293
+// channels).
+template <bool ALIGNED4>
+__device__ __forceinline__ void read_octet(const uint8_t* tile, uint32_t n, uint32_t& w0, uint32_t& w1) {
+    auto word = [&](uint32_t m) { return *reinterpret_cast<const uint32_t*>(tile + sym_addr(m)); };
+    if constexpr (ALIGNED4) {
+        w0 = word(n);
+        w1 = word(n + 4u);
+    } else {
+        const uint32_t n0 = n & ~3u;
+        const uint32_t a = word(n0), b = word(n0 + 4u), c = word(n0 + 8u);
+        w0 = __builtin_amdgcn_alignbyte(b, a, n & 3u);
+        w1 = __builtin_amdgcn_alignbyte(c, b, n & 3u);
+    }
+}
 
 constexpr int kLut2Bits = 10;  // second table: codes longer than kLutBits bits
 
@@ -509,7 +525,7 @@ struct DecodeParams {
     uint32_t* err;
     // where the side information and the payload start if the stream was made with the nominal chunk size
     size_t g_off_chunk_off, g_off_sub_bits, g_off_payload;
-    uint32_t g_n_chunks, g_spc;
+    uint32_t g_n_chunks, g_spc, g_tile_chunks;
     const void* prebuilt;  // PrebuiltTables of a code table fixed beforehand, or NULL: build them from the stream
     // chunk decoder: bytes of the basis operand at the start of its dynamic LDS, and the words of payload the LDS
     // copy of a chunk holds (larger chunks are read in place); a multiple of 64
@@ -626,40 +642,61 @@ __device__ __forceinline__ UnitBits open_unit(const StreamView& v, const Unit& u
     return b;
 }
 
-constexpr int kPayWords = 1216;  // LDS copy of a unit's payload: up to 9 bits a symbol; larger units read global memory
-
 // Wide tensors and the symbols-only mode: a tile of G chunks per workgroup is decoded into an LDS tile of symbol
 // bytes, one chunk per wavefront and round; the inverse transform of the tile's pixels then runs on the f16 matrix
 // cores with the arithmetic of the narrow-tensor kernel below (levels exact in f16, basis entries split in two f16
-// parts, two matrix instructions per 16 coefficients), as a matrix product tiled over the workgroup: the basis
-// blocks of a contraction step are brought into LDS once for all the tile's pixels (see the loop).
-template <int MT, int LAYOUT, bool ALIGNED4>
-__global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
+// parts, two matrix instructions per 16 coefficients), shared out over the wavefronts (see the loop).
+// MT: pixel tiles of 32 per workgroup; KS: wavefronts that share a channel tile's contraction (MT = 1).
+template <int MT, int KS, int LAYOUT, bool ALIGNED4>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : 2, MT == 1 ? 4 : 2))) void k_decode_tiles(DecodeParams p) {
+    static_assert(KS == 1 || MT == 1, "the partial sums of one pixel tile fit the payload buffers");
     __shared__ __align__(16) DecTables T;
-    // 8 wavefronts.  Workgroup tile in units of 32: 4 pixel tiles x 8 channel tiles (128 pixels x 256 channels, a
-    // wavefront 2 x 2 of them), or 2 x 8 (64 pixels, a wavefront 1 x 2) where 128 pixels of symbols do not fit LDS.
-    constexpr int PTW = MT, CTW = 8, PPW = MT / 2;  // PPW: pixel tiles per wavefront
-    // the chunks' payload words (one buffer per wavefront) while decoding, the basis blocks of three contraction
-    // steps afterwards: the two uses are a workgroup barrier apart
-    // (a payload buffer: the unit's words and the room a corrupt stream's cursor may run into)
-    constexpr int kPayStride = kPayWords + kPayOverrun;
-    constexpr size_t kPayBytes = sizeof(uint32_t) * 8 * kPayStride, kRingBytes = sizeof(uint4) * 3 * CTW * 2 * 64;
-    __shared__ __align__(16) uint8_t s_shared[kPayBytes > kRingBytes ? kPayBytes : kRingBytes];
-    uint32_t(*pay)[kPayStride] = reinterpret_cast<uint32_t(*)[kPayStride]>(s_shared);
-    uint4(*s_ring)[CTW * 2][64] = reinterpret_cast<uint4(*)[CTW * 2][64]>(s_shared);
-    extern __shared__ __align__(16) uint8_t symtile[];
+    constexpr int CTW = 8 / KS;  // channel tiles of a workgroup: a wavefront (or KS of them) each
+    // dynamic LDS: the chunks' payload words (a buffer per wavefront: the unit's words and the room a corrupt stream's
+    // cursor may run into) while decoding, the partial sums [KS][CTW][4][64] afterwards (the two uses are a workgroup
+    // barrier apart), then the symbol tile
+    extern __shared__ __align__(16) uint8_t dyn_lds[];
+    float4* s_part = reinterpret_cast<float4*>(dyn_lds);
+    uint8_t* symtile = dyn_lds + p.lds_basis_bytes;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront-uniform by construction
     const int half = lane >> 5, l32 = lane & 31;
     const int C = p.C;
 
+    // What does not depend on the header goes out first: the code lengths, and (see the chunk decoder) offsets, run sizes
+    // and payload of the wavefront's first chunk, where the nominal chunk size puts them.  The guess is checked against the
+    // header below.  Nothing outside [stream, stream + bytes) is touched either way.
+    const int my_len = tid < 256 && p.bytes >= (size_t)(kHeaderBytes + kLenTableBytes) ? (int)p.stream[kHeaderBytes + tid] : 0;
+    uint32_t* pw = reinterpret_cast<uint32_t*>(dyn_lds) + (size_t)wave * (p.pay_words + (uint32_t)kPayOverrun);
+    const uint32_t ch_first = blockIdx.x * p.g_tile_chunks + (uint32_t)wave;
+    const bool guess = p.g_off_payload <= p.bytes && (uint32_t)wave < p.g_tile_chunks && ch_first < p.g_n_chunks && p.g_spc > 32u;  // (a chunk is a unit)
+    UnitInfo first{0u, 0u, 0u};
+    uint32_t first_w0 = 0u, first_w1 = 0u;
+    bool first_in_lds = false;
+    if (guess) {
+        const uint32_t* co = reinterpret_cast<const uint32_t*>(p.stream + p.g_off_chunk_off);
+        const uint16_t* sb = reinterpret_cast<const uint16_t*>(p.stream + p.g_off_sub_bits);
+        first.off = co[ch_first];
+        first.end = co[ch_first + 1];
+        first.run = ((uint32_t)lane < p.g_spc) ? sb[(size_t)ch_first * p.g_spc + lane] : 0u;
+        const size_t cap_words = (p.bytes - p.g_off_payload) / 4;
+        first_w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)first.off);
+        first_w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)first.end);
+        first_in_lds = first_w0 <= first_w1 && (size_t)first_w1 <= cap_words && first_w1 - first_w0 <= p.pay_words;
+        if (first_in_lds) {
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(p.stream + p.g_off_payload) + first_w0;
+            for (uint32_t k = 0; 64u * k < first_w1 - first_w0; k++) {  // wavefront-uniform trip count
+                const uint32_t i = (uint32_t)lane + 64u * k;
+                if (i < first_w1 - first_w0) load_to_lds<4>(src + i, pw + 64u * k);
+            }
+        }
+    }
     StreamView sv;
     if (!open_stream(p, &sv)) {
         if (tid == 0) atomicOr(p.err, FMTC_ERR_HEADER);
         return;
     }
-    const int my_len = tid < 256 ? (int)p.stream[kHeaderBytes + tid] : 0;
     if (!(p.prebuilt ? load_decode_tables<512>(T, my_len, static_cast<const PrebuiltTables*>(p.prebuilt))
                      : build_decode_tables<512>(T, my_len, p.bits))) {
         if (tid == 0) atomicOr(p.err, FMTC_ERR_TABLE);
@@ -678,6 +715,7 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
     uint32_t G = p.syms_out ? 8u * un.m : (uint32_t)p.tile_px / ppc;
     const uint32_t fits = p.tile_bytes / slot_bytes;
     G = G < 1u ? 1u : (G > fits ? fits : G);
+    bool guessed = guess && sv.n_chunks == p.g_n_chunks && sv.spc == p.g_spc && G == p.g_tile_chunks;  // of the first unit
     const uint32_t n_tiles = (n_chunks + G - 1) / G;
     // 0x6400 | s is the f16 number 1024 + s: the level s - 2^(b-1) is that minus (1024 + 2^(b-1)), exactly
     const _Float16 level_off = (_Float16)(float)(1024 + (1 << (p.bits - 1)));
@@ -686,35 +724,34 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
     // ... of which the first NJA meet basis rows that are not all zero (fewer than NJ for a truncated basis)
     const int NJA = p.active_steps < 1 ? 1 : (p.active_steps > NJ ? NJ : p.active_steps);
 
-    // x_hat = Delta (sum q T_hi + 2^-11 sum q T_lo) + mu for one 32 x 32 tile (channel tile ct, pixel tile pt of a
-    // workgroup tile of TP pixels starting at pixel px_tile0).  Accumulator r of lane l is element
-    // (8*(r/4) + 4*(l/32) + r%4, l%32) of the tile: rows = pixels for NHWC, channels for NCHW.  Whole tiles are
+    // x_hat = Delta (sum q T_hi + 2^-11 sum q T_lo) + mu for quads g0 .. g0 + NQ - 1 of one 32 x 32 tile (channel tile ct, pixel
+    // tile pt of a workgroup tile of TP pixels starting at pixel px_tile0), y the sums.  Element 4 g + i of lane l is element
+    // (8 g + 4*(l/32) + i, l%32) of the tile: rows = pixels for NHWC, channels for NCHW.  Whole tiles are
     // stored without per-element predicates (one straight run of stores).
-    auto store_tile = [&](int ct, int pt, int TP, int64_t px_tile0, floatx16& acc, const floatx16& acl) {
-#pragma unroll
-        for (int r = 0; r < 16; r++) acc[r] = __builtin_fmaf(acl[r], 1.f / 2048.f, acc[r]) * delta;
+    auto store_quads = [&](int ct, int pt, int TP, int64_t px_tile0, auto& y, int g0) {
+        constexpr int NR = sizeof(y) / sizeof(float);
         if constexpr (LAYOUT == FMTC_NHWC) {
             const int c = ct * 32 + l32;
             if (c < C) {
                 const float m_c = p.mu[c];
-                const int px_first = pt * 32;
+                const int px_first = pt * 32 + 8 * g0;
                 float* dst = p.xhat + (px_tile0 + px_first + 4 * half) * C + c;
-                if (px_first + 32 <= TP) {
+                if (pt * 32 + 32 <= TP) {
 #pragma unroll
-                    for (int r = 0; r < 16; r++) dst[(size_t)(8 * (r >> 2) + (r & 3)) * C] = acc[r] + m_c;
+                    for (int r = 0; r < NR; r++) dst[(size_t)(8 * (r >> 2) + (r & 3)) * C] = y[r] * delta + m_c;
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; r++) {
+                    for (int r = 0; r < NR; r++) {
                         int pxl = px_first + 8 * (r >> 2) + 4 * half + (r & 3);
-                        if (pxl < TP) dst[(size_t)(8 * (r >> 2) + (r & 3)) * C] = acc[r] + m_c;
+                        if (pxl < TP) dst[(size_t)(8 * (r >> 2) + (r & 3)) * C] = y[r] * delta + m_c;
                     }
                 }
             }
         } else {
-            float m_r[16];
-            const int cb = ct * 32 + 4 * half;
+            float m_r[NR];
+            const int cb = ct * 32 + 8 * g0 + 4 * half;
 #pragma unroll
-            for (int r = 0; r < 16; r++) m_r[r] = p.mu[cb + 8 * (r >> 2) + (r & 3)];  // mu is padded to a multiple of 32
+            for (int r = 0; r < NR; r++) m_r[r] = p.mu[cb + 8 * (r >> 2) + (r & 3)];  // mu is padded to a multiple of 32
             const int pxl = pt * 32 + l32;
             if (pxl < TP) {
                 const int64_t px = px_tile0 + pxl;
@@ -722,12 +759,12 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
                 float* dst = p.xhat + (n * (int64_t)C + cb) * p.HW + hw;
                 if (ct * 32 + 32 <= C) {
 #pragma unroll
-                    for (int r = 0; r < 16; r++) dst[(int64_t)(8 * (r >> 2) + (r & 3)) * p.HW] = acc[r] + m_r[r];
+                    for (int r = 0; r < NR; r++) dst[(int64_t)(8 * (r >> 2) + (r & 3)) * p.HW] = y[r] * delta + m_r[r];
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; r++) {
+                    for (int r = 0; r < NR; r++) {
                         int c = cb + 8 * (r >> 2) + (r & 3);
-                        if (c < C) dst[(int64_t)(8 * (r >> 2) + (r & 3)) * p.HW] = acc[r] + m_r[r];
+                        if (c < C) dst[(int64_t)(8 * (r >> 2) + (r & 3)) * p.HW] = y[r] * delta + m_r[r];
                     }
                 }
             }
@@ -740,22 +777,26 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
         // ---- variable length decoding into the LDS tile, a unit per wavefront and round ----
         for (uint32_t k0 = (uint32_t)wave * un.m; k0 < tile_chunks; k0 += 8u * un.m) {
             const uint32_t count = tile_chunks - k0 < un.m ? tile_chunks - k0 : un.m;
-            UnitInfo info;
-            info.load(sv, un, first_ch + k0, count, lane);
+            UnitInfo info = first;
+            if (!guessed) info.load(sv, un, first_ch + k0, count, lane);
             const UnitBits ub = open_unit(sv, un, info, first_ch + k0, count, last_syms, lane);
             if (ub.bad && lane == 0) atomicOr(p.err, FMTC_ERR_OFFSETS);
             uint8_t* slots = symtile + slot_bytes * k0;
             bool ok_run = true;
-            if (ub.n_words <= (uint32_t)kPayWords) {
+            if (ub.n_words <= p.pay_words) {
                 // the unit's payload goes to LDS with full-width loads (what lies behind it there is never taken for a
                 // symbol of a run)
-                uint32_t* pw = pay[wave];
-                const uint32_t* src = sv.payload + ub.w0;
-                for (uint32_t i = lane; i < ub.n_words; i += 64) pw[i] = src[i];
+                if (guessed && first_in_lds && ub.w0 == first_w0 && ub.w0 + ub.n_words == first_w1) {
+                    wait_loads<0>();
+                } else {
+                    wait_loads<0>();  // (a guess that was wrong must not land later)
+                    const uint32_t* src = sv.payload + ub.w0;
+                    for (uint32_t i = lane; i < ub.n_words; i += 64) pw[i] = src[i];
+                }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 if (ub.cnt) ok_run = decode_run_bytes(pw, ub.n_words, ub.start + 32u * ub.rel, ub.cnt, T, slots + 68u * (uint32_t)lane);
-                // the next unit of this wavefront overwrites pay[]: all lanes are done reading here
+                // the next unit of this wavefront overwrites the copy: all lanes are done reading here
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             } else if (ub.cnt) {
@@ -763,7 +804,10 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
                 ok_run = decode_run(sv.payload + ub.w0 + ub.rel, ub.n_words - ub.rel, ub.start, ub.cnt, T, ByteOut(slots, 64u * (uint32_t)lane));
             }
             if (!ok_run) atomicOr(p.err, FMTC_ERR_CODE);
+            guessed = false;
         }
+        guessed = false;
+        wait_loads<0>();  // (of a wavefront without a unit: the room is used again below)
         __syncthreads();
 
         if (p.syms_out) {
@@ -781,110 +825,119 @@ __global__ __launch_bounds__(512) void k_decode_tiles(DecodeParams p) {
             }
         } else {
             // ---- inverse quantizer + inverse transform: a tiled matrix product over the workgroup's pixels ----
-            // The tile of PTW x 32 pixels times CTW x 32 output channels is shared out 2 x 2 per wavefront; the
-            // contraction runs over the coefficients 16 at a time.  The basis (both f16 parts of CTW tiles, 16 bytes
-            // per lane and block, operand order) goes from L2 straight into a ring of three LDS slots two steps
-            // ahead -- once per workgroup and step, for all its pixels; the loads are counted by hand (see
-            // load_to_lds).  The other operand is read from the symbol tile: lane (pixel, h) takes the eight symbols
-            // 16 ks + 8 h .. + 7 of its pixel and turns them into f16 levels with two byte permutes each.
+            // A wavefront takes one channel tile for all MT pixel tiles (KS of them share its contraction).  The basis (both
+            // f16 parts, 16 bytes per lane each, operand order) comes straight into registers D steps ahead, every block
+            // once per workgroup; no barrier until the sums are made.  The other operand is read from the symbol tile: lane
+            // (pixel, h) takes the eight symbols 16 ks + 8 h .. + 7 of its pixel and turns them into f16 levels with two
+            // byte permutes each.
             const int64_t px_tile0 = (int64_t)first_ch * (int64_t)ppc;
             int TP = p.P - px_tile0 < (int64_t)(tile_chunks * ppc) ? (int)(p.P - px_tile0) : (int)(tile_chunks * ppc);  // pixels in this tile
-            if (TP > PTW * 32) TP = PTW * 32;  // (not so: a chunk of a wide tensor has fewer pixels than a tile)
+            if (TP > MT * 32) TP = MT * 32;  // (not so: a chunk of a wide tensor has fewer pixels than a tile)
             const int n_cg = (p.ncs + CTW - 1) / CTW;
-            const int ctp = wave & 3;   // this wavefront's pair of channel tiles ...
-            const int ptp = wave >> 2;  // ... and its PPW pixel tiles
-            constexpr int BPW = CTW * 2 / 8;  // basis blocks a wavefront brings per step
+            const int slice = wave / CTW;
+            const int s_begin = slice * NJA / KS, s_end = (slice + 1) * NJA / KS;
+            uint32_t rowbase[MT];       // this lane's first symbol of a pixel in its chunk ...
+            const uint8_t* rows[MT];    // ... which starts here
+#pragma unroll
+            for (int b = 0; b < MT; b++) {
+                int pxl = b * 32 + l32;
+                if (pxl > TP - 1) pxl = TP - 1;  // rows past the tile repeat the last pixel; never stored
+                if (pxl < 0) pxl = 0;
+                const uint32_t k = (uint32_t)pxl / ppc;
+                rows[b] = symtile + slot_bytes * k;
+                rowbase[b] = ((uint32_t)pxl - k * ppc) * (uint32_t)C + 8u * half;
+            }
+            constexpr int D = MT == 4 ? 2 : 3;
             for (int cg = blockIdx.y; cg < n_cg; cg += gridDim.y) {
-                const int ct_base = cg * CTW;
-                floatx16 acc[2][PPW], acl[2][PPW];
+                const int ct = cg * CTW + wave % CTW;
+                const bool mine = ct < p.ncs;  // wavefront-uniform
+                floatx16 acc[MT], acl[MT];
 #pragma unroll
-                for (int a = 0; a < 2; a++)
+                for (int b = 0; b < MT; b++)
 #pragma unroll
-                    for (int b = 0; b < PPW; b++)
+                    for (int r = 0; r < 16; r++) { acc[b][r] = 0.f; acl[b][r] = 0.f; }
+                if (mine) {
+                    const uint4* src = reinterpret_cast<const uint4*>(p.Bp16) + (size_t)ct * NJ * 128 + lane;
+                    uint4 bufh[D], bufl[D];
 #pragma unroll
-                        for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acl[a][b][r] = 0.f; }
-                uint32_t rowbase[PPW];       // this lane's first symbol of a pixel in its chunk ...
-                const uint8_t* rows[PPW];    // ... which starts here
-#pragma unroll
-                for (int b = 0; b < PPW; b++) {
-                    int pxl = (PPW * ptp + b) * 32 + l32;
-                    if (pxl > TP - 1) pxl = TP - 1;  // rows past the tile repeat the last pixel; never stored
-                    if (pxl < 0) pxl = 0;
-                    const uint32_t k = (uint32_t)pxl / ppc;
-                    rows[b] = symtile + slot_bytes * k;
-                    rowbase[b] = ((uint32_t)pxl - k * ppc) * (uint32_t)C + 8u * half;
-                }
-                // steps past the end repeat the last one: the number of loads in flight is the same in every step
-                auto issue = [&](int ks) {
-                    const int slot = ks % 3;
-                    ks = ks < NJA ? ks : NJA - 1;
-#pragma unroll
-                    for (int q = 0; q < BPW; q++) {
-                        const int blk = wave * BPW + q;  // (channel tile blk / 2, part blk % 2)
-                        int ct = ct_base + (blk >> 1);
-                        ct = ct < p.ncs ? ct : p.ncs - 1;  // tiles past the end repeat the last; never stored
-                        load_to_lds<16>(reinterpret_cast<const uint4*>(p.Bp16) + (((size_t)ct * NJ + ks) * 2 + (blk & 1)) * 64 + lane,
-                                        &s_ring[slot][blk][0]);
-                    }
-                };
-                issue(0);
-                issue(1);
-                for (int ks = 0; ks < NJA; ks++) {
-                    wait_loads<BPW>();  // this wavefront's blocks of step ks have landed
-                    __syncthreads();    // everybody's have, and everybody is done with the slot of step ks - 1
-                    issue(ks + 2);
-                    halfx8 bh[2], bl[2], q[PPW];
-#pragma unroll
-                    for (int a = 0; a < 2; a++) {
-                        bh[a] = __builtin_bit_cast(halfx8, s_ring[ks % 3][(2 * ctp + a) * 2][lane]);
-                        bl[a] = __builtin_bit_cast(halfx8, s_ring[ks % 3][(2 * ctp + a) * 2 + 1][lane]);
-                    }
-#pragma unroll
-                    for (int b = 0; b < PPW; b++) {
-                        // (coefficients past C meet zero basis entries; whatever level the tile's bytes give there
-                        // does not count)
-                        const uint32_t n = rowbase[b] + 16u * (uint32_t)ks;
-                        uint32_t w0, w1;
-                        if constexpr (ALIGNED4) {
-                            w0 = *reinterpret_cast<const uint32_t*>(rows[b] + sym_addr(n));
-                            w1 = *reinterpret_cast<const uint32_t*>(rows[b] + sym_addr(n + 4));
-                        } else {
-                            w0 = (uint32_t)rows[b][sym_addr(n)] | ((uint32_t)rows[b][sym_addr(n + 1)] << 8) |
-                                 ((uint32_t)rows[b][sym_addr(n + 2)] << 16) | ((uint32_t)rows[b][sym_addr(n + 3)] << 24);
-                            w1 = (uint32_t)rows[b][sym_addr(n + 4)] | ((uint32_t)rows[b][sym_addr(n + 5)] << 8) |
-                                 ((uint32_t)rows[b][sym_addr(n + 6)] << 16) | ((uint32_t)rows[b][sym_addr(n + 7)] << 24);
+                    for (int d = 0; d < D; d++)
+                        if (s_begin + d < s_end) {
+                            bufh[d] = src[(size_t)(s_begin + d) * 128];
+                            bufl[d] = src[(size_t)(s_begin + d) * 128 + 64];
                         }
-                        const halfx2 q01 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x05010400u)) - level_off2;
-                        const halfx2 q23 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x07030602u)) - level_off2;
-                        const halfx2 q45 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w1, 0x05010400u)) - level_off2;
-                        const halfx2 q67 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w1, 0x07030602u)) - level_off2;
-                        q[b] = halfx8{q01[0], q01[1], q23[0], q23[1], q45[0], q45[1], q67[0], q67[1]};
-                    }
+                    for (int k0 = s_begin; k0 < s_end; k0 += D) {
 #pragma unroll
-                    for (int a = 0; a < 2; a++)
+                        for (int d = 0; d < D; d++) {
+                            const int ks = k0 + d;
+                            if (ks >= s_end) break;  // wavefront-uniform
+                            halfx8 q[MT];
 #pragma unroll
-                        for (int b = 0; b < PPW; b++) {
-                            if constexpr (LAYOUT == FMTC_NHWC) {
-                                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(q[b], bh[a], acc[a][b], 0, 0, 0);
-                                acl[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(q[b], bl[a], acl[a][b], 0, 0, 0);
-                            } else {
-                                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[a], q[b], acc[a][b], 0, 0, 0);
-                                acl[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl[a], q[b], acl[a][b], 0, 0, 0);
+                            for (int b = 0; b < MT; b++) {
+                                // (coefficients past C meet zero basis entries; whatever level the tile's bytes give there
+                                // does not count)
+                                const uint32_t n = rowbase[b] + 16u * (uint32_t)ks;
+                                uint32_t w0, w1;
+                                read_octet<ALIGNED4>(rows[b], n, w0, w1);
+                                const halfx2 q01 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x05010400u)) - level_off2;
+                                const halfx2 q23 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x07030602u)) - level_off2;
+                                const halfx2 q45 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w1, 0x05010400u)) - level_off2;
+                                const halfx2 q67 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w1, 0x07030602u)) - level_off2;
+                                q[b] = halfx8{q01[0], q01[1], q23[0], q23[1], q45[0], q45[1], q67[0], q67[1]};
+                            }
+                            const halfx8 bh = __builtin_bit_cast(halfx8, bufh[d]), bl = __builtin_bit_cast(halfx8, bufl[d]);
+#pragma unroll
+                            for (int b = 0; b < MT; b++) {
+                                if constexpr (LAYOUT == FMTC_NHWC) {
+                                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(q[b], bh, acc[b], 0, 0, 0);
+                                    acl[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(q[b], bl, acl[b], 0, 0, 0);
+                                } else {
+                                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh, q[b], acc[b], 0, 0, 0);
+                                    acl[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl, q[b], acl[b], 0, 0, 0);
+                                }
+                            }
+                            if (ks + D < s_end) {
+                                bufh[d] = src[(size_t)(ks + D) * 128];
+                                bufl[d] = src[(size_t)(ks + D) * 128 + 64];
                             }
                         }
+                    }
                 }
-                wait_loads<0>();  // the repeated loads of the last steps
-                __syncthreads();  // nobody reads the ring any more: the next channel group may refill it
-
+                if constexpr (KS == 1) {
+                    if (mine) {
 #pragma unroll
-                for (int a = 0; a < 2; a++) {
-                    const int ct = ct_base + 2 * ctp + a;
-                    if (ct >= p.ncs) continue;  // wavefront-uniform
+                        for (int b = 0; b < MT; b++) {
+                            if (b * 32 >= TP) break;  // wavefront-uniform
+                            float y[16];
 #pragma unroll
-                    for (int b = 0; b < PPW; b++) {
-                        const int pt = PPW * ptp + b;
-                        if (pt * 32 >= TP) continue;  // wavefront-uniform
-                        store_tile(ct, pt, TP, px_tile0, acc[a][b], acl[a][b]);
+                            for (int r = 0; r < 16; r++) y[r] = __builtin_fmaf(acl[b][r], 1.f / 2048.f, acc[b][r]);
+                            store_quads(ct, b, TP, px_tile0, y, 0);
+                        }
+                    }
+                } else {
+                    // the partial sums meet; each of the KS wavefronts finishes its share of the tile
+                    __syncthreads();  // the payload (the previous group's sums) has been read
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        float y[4];
+#pragma unroll
+                        for (int i = 0; i < 4; i++) y[i] = __builtin_fmaf(acl[0][4 * g + i], 1.f / 2048.f, acc[0][4 * g + i]);
+                        s_part[(wave * 4 + g) * 64 + lane] = make_float4(y[0], y[1], y[2], y[3]);
+                    }
+                    __syncthreads();
+                    if (mine) {
+                        constexpr int NQ = 4 / KS;
+                        float y[4 * NQ];
+#pragma unroll
+                        for (int g = 0; g < NQ; g++) {
+                            float4 t = s_part[((wave % CTW) * 4 + slice * NQ + g) * 64 + lane];
+#pragma unroll
+                            for (int w = 1; w < KS; w++) {
+                                const float4 o = s_part[((wave % CTW + w * CTW) * 4 + slice * NQ + g) * 64 + lane];
+                                t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+                            }
+                            y[4 * g] = t.x; y[4 * g + 1] = t.y; y[4 * g + 2] = t.z; y[4 * g + 3] = t.w;
+                        }
+                        store_quads(ct, 0, TP, px_tile0, y, slice * NQ);
                     }
                 }
             }
@@ -1121,17 +1174,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
                 for (int j = 0; j < NJ; j++) {
                     const uint32_t n = rowbase + 16u * (uint32_t)j;
                     uint32_t w0 = 0, w1 = 0;
-                    if (j < NS) {
-                        if constexpr (ALIGNED4) {
-                            w0 = *reinterpret_cast<const uint32_t*>(tile + sym_addr(n));
-                            w1 = *reinterpret_cast<const uint32_t*>(tile + sym_addr(n + 4));
-                        } else {
-                            w0 = (uint32_t)tile[sym_addr(n)] | ((uint32_t)tile[sym_addr(n + 1)] << 8) |
-                                 ((uint32_t)tile[sym_addr(n + 2)] << 16) | ((uint32_t)tile[sym_addr(n + 3)] << 24);
-                            w1 = (uint32_t)tile[sym_addr(n + 4)] | ((uint32_t)tile[sym_addr(n + 5)] << 8) |
-                                 ((uint32_t)tile[sym_addr(n + 6)] << 16) | ((uint32_t)tile[sym_addr(n + 7)] << 24);
-                        }
-                    }
+                    if (j < NS) read_octet<ALIGNED4>(tile, n, w0, w1);
                     b[j] = (long)((((unsigned long long)w1 << 32) | w0) ^ 0x8080808080808080ull);
                 }
                 const int my_px = pt * 32 + l32;
@@ -1197,15 +1240,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
             for (int j = 0; j < NJ; j++) {
                 const uint32_t n = rowbase + 16u * (uint32_t)j;
                 uint32_t w0, w1;
-                if constexpr (ALIGNED4) {
-                    w0 = *reinterpret_cast<const uint32_t*>(tile + sym_addr(n));
-                    w1 = *reinterpret_cast<const uint32_t*>(tile + sym_addr(n + 4));
-                } else {
-                    w0 = (uint32_t)tile[sym_addr(n)] | ((uint32_t)tile[sym_addr(n + 1)] << 8) |
-                         ((uint32_t)tile[sym_addr(n + 2)] << 16) | ((uint32_t)tile[sym_addr(n + 3)] << 24);
-                    w1 = (uint32_t)tile[sym_addr(n + 4)] | ((uint32_t)tile[sym_addr(n + 5)] << 8) |
-                         ((uint32_t)tile[sym_addr(n + 6)] << 16) | ((uint32_t)tile[sym_addr(n + 7)] << 24);
-                }
+                read_octet<ALIGNED4>(tile, n, w0, w1);
                 const halfx2 q01 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x05010400u)) - level_off2;
                 const halfx2 q23 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w0, 0x07030602u)) - level_off2;
                 const halfx2 q45 = __builtin_bit_cast(halfx2, __builtin_amdgcn_perm(0x64646464u, w1, 0x05010400u)) - level_off2;
@@ -1481,22 +1516,41 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
     }
 
     // ---- tiles of several chunks per workgroup ----
-    // A workgroup tile is 128 pixels x 256 output channels (4 x 8 matrix tiles), or 64 x 256 for more than 512
-    // channels (the symbols of 128 such pixels would not fit LDS): as many chunks as give that many pixels at the
-    // nominal chunk size, 16 at most.
-    const int n_cg = (ncs + 7) / 8;
-    auto chunks_for = [&](int px) {
-        int n = (int)(px / (int64_t)g.px_per_chunk);
-        return n < 1 ? 1 : (n > 16 ? 16 : n);
+    // the LDS copy of a unit's payload: see above
+    p.pay_words = 128u * (uint32_t)bits + 64u;
+    const uint32_t pay_bytes = 8u * 4u * (p.pay_words + (uint32_t)kPayOverrun);
+    const uint32_t slot_bytes = d_syms ? 4352u : 68u * g.subs_per_chunk;  // of a chunk in the symbol tile
+    const int max_chunks = (int)((159u * 1024u - sizeof(DecTables) - pay_bytes - 128u) / slot_bytes);
+    // The tile: 32, 64 or 128 pixels (as many chunks as give them at the nominal chunk size), 32 of them with one, two or four
+    // wavefronts per channel tile.  The channel groups (256 channels, fewer where wavefronts share a tile) of a tile go to
+    // workgroups of their own (each decodes the tile's symbols again) while that still fills the device; otherwise a
+    // workgroup walks them in turn.
+    int mt = 0, ks = 0, G = 0, n_cg = 0;
+    uint32_t n_tiles = 0;
+    uint64_t blocks = 0;
+    auto choose = [&](int m, int k) {
+        mt = m;
+        ks = k;
+        G = (int)(32 * m / (int64_t)g.px_per_chunk);
+        G = G < 1 ? 1 : (G > max_chunks ? max_chunks : G);
+        if (d_syms) G = 8;  // symbols only: no projection to feed, one chunk per wavefront and as many workgroups as that gives
+        n_tiles = (g.n_chunks + G - 1) / G;
+        n_cg = (ncs * k + 7) / 8;
+        return blocks = (uint64_t)n_tiles * (uint64_t)n_cg;
     };
-    // ... and 64 pixels also where 128 would leave most of the device without a workgroup
-    const bool wide = C > 512 || (uint64_t)((g.n_chunks + chunks_for(128) - 1) / chunks_for(128)) * n_cg < 128;
-    int G = chunks_for(wide ? 64 : 128);
-    if (d_syms) G = 8;  // symbols only: no projection to feed, one chunk per wavefront and as many workgroups as that gives
+    // The finest split whose workgroups run at the same time: one per compute unit (two of 32 pixels and one wavefront per
+    // channel tile: 128 registers, and LDS for two at up to 512 channels).  Beyond that the largest tile, and from 513
+    // channels, whose symbols take the LDS, the smallest.  Kernel times, us, for 1 x 4 : 1 x 2 : 1 x 1 : 2 x 1 : 4 x 1 (32-pixel
+    // tiles x wavefronts per channel tile): 512 channels, 121 pixels 15 : 17 : 20 : 24 : 37; 1024, 968 35 : 24 : 30 : 50 : 50; 512,
+    // 3146 35 : 22 : 21 : 25 : 38; 384, 5670 34 : 33 : 23 : 27 : 38; 304, 7220 34 : 35 : 34 : 36 : 31; 256, 50176 64 : 58 : 53 :
+    // 56 : 45; 640, 11760 68 : 63 : 62 : 92 : 87; 960, 12544 158 : 156 : 101 : 150 : 132.
+    if (d_syms) choose(1, 1);
+    else if (choose(1, 4) > 256u && choose(1, 2) > 256u && choose(1, 1) > 256u) {
+        // (up to 256 channels: 64 pixels while those workgroups have a compute unit each; 256, 9792 pixels 19.8 : 18.9)
+        if (C > 256 || choose(2, 1) > 256u)
+            if (choose(1, 1) > 512u && C <= 512) choose(4, 1);
+    }
     // the grid is sized from the nominal geometry; the kernel takes the real one from the header
-    const uint32_t n_tiles = (g.n_chunks + G - 1) / G;
-    // the channel groups (256 channels) of a tile go to workgroups of their own (each decodes the tile's
-    // symbols again) while that still fills the device; otherwise a workgroup walks them in turn
     int groups = 1;
     if (!d_syms) {
         groups = (int)(1024 / (n_tiles < 1024u ? n_tiles : 1024u));
@@ -1506,30 +1560,37 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
         // tiles than the device holds)
         if (test_option(kTestDecodeOneRow)) groups = 1;
     }
-    unsigned gx = n_tiles < 1024u ? n_tiles : 1024u;
-    dim3 grid(gx, (unsigned)groups);
-    // (chunks of another size, whose last runs may be nearly empty, take more room for the same pixels: there is some to
-    // spare where a tile holds few pixels, and otherwise their tiles get smaller)
-    p.tile_px = wide ? 64 : 128;
-    p.tile_bytes = (uint32_t)G * 4352u;
-    const size_t lds = (size_t)p.tile_bytes + 128;
+    // More tiles than run at the same time are walked by the workgroups that do, which build their tables once (256
+    // channels, 392 tiles 51 -> 45 us; 169, 470 tiles 49 -> 43).
+    const uint32_t most = d_syms || blocks <= 512u ? 512u : 256u;
+    dim3 grid(n_tiles < most ? n_tiles : most, (unsigned)groups);
+    p.g_tile_chunks = (uint32_t)G;
+    // (chunks of another size than the nominal may take more room for the same pixels: their tiles get smaller)
+    p.tile_px = 32 * mt;
+    p.tile_bytes = (uint32_t)G * slot_bytes < 4352u ? 4352u : (uint32_t)G * slot_bytes;  // (any chunk fits)
+    p.lds_basis_bytes = ks > 1 && pay_bytes < 32u * 1024u ? 32u * 1024u : pay_bytes;
+    const size_t lds = (size_t)p.lds_basis_bytes + p.tile_bytes + 128;
     // more than 64 KB of dynamic LDS has to be requested per kernel (the CU has 160 KB)
-#define FMTC_DEC(MT, LAY, AL)                                                                                \
+#define FMTC_DEC_L(MT, KS, LAY, AL)                                                                          \
     do {                                                                                                     \
-        if (lds > 32 * 1024) {                                                                               \
-            hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_tiles<MT, LAY, AL>), \
+        if (lds > 8 * 1024) {                                                                                \
+            hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_decode_tiles<MT, KS, LAY, AL>), \
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);      \
             if (ea != hipSuccess) return ea;                                                                 \
         }                                                                                                    \
-        el = launch(K_DECODE, k_decode_tiles<MT, LAY, AL>, grid, dim3(512), lds, s, p);                      \
+        el = launch(K_DECODE, k_decode_tiles<MT, KS, LAY, AL>, grid, dim3(512), lds, s, p);                  \
     } while (0)
-    if (layout == FMTC_NHWC) {
-        if (al) { if (wide) FMTC_DEC(2, FMTC_NHWC, true); else FMTC_DEC(4, FMTC_NHWC, true); }
-        else    { if (wide) FMTC_DEC(2, FMTC_NHWC, false); else FMTC_DEC(4, FMTC_NHWC, false); }
-    } else {
-        if (al) { if (wide) FMTC_DEC(2, FMTC_NCHW, true); else FMTC_DEC(4, FMTC_NCHW, true); }
-        else    { if (wide) FMTC_DEC(2, FMTC_NCHW, false); else FMTC_DEC(4, FMTC_NCHW, false); }
-    }
+#define FMTC_DEC(MT, KS)                                                                                     \
+    do {                                                                                                     \
+        if (layout == FMTC_NHWC) { if (al) FMTC_DEC_L(MT, KS, FMTC_NHWC, true); else FMTC_DEC_L(MT, KS, FMTC_NHWC, false); } \
+        else                     { if (al) FMTC_DEC_L(MT, KS, FMTC_NCHW, true); else FMTC_DEC_L(MT, KS, FMTC_NCHW, false); } \
+    } while (0)
+    if (mt == 4) FMTC_DEC(4, 1);
+    else if (mt == 2) FMTC_DEC(2, 1);
+    else if (ks == 1) FMTC_DEC(1, 1);
+    else if (ks == 2) FMTC_DEC(1, 2);
+    else FMTC_DEC(1, 4);
+#undef FMTC_DEC_L
 #undef FMTC_DEC
     return el;
 }

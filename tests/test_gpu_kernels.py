@@ -484,6 +484,10 @@ UNIT_CASES = [  # C, chunk, P
     (64, 64, 1000), (3, 65, 4000), (100, 2048, 2101), (24, 330, 3003), (32, 1056, 4000), (128, 2176, 1200), (144, 288, 1001),
     (160, 1000, 700), (50, 800, 1601), (200, 64, 777), (313, 1024, 430), (576, 1024, 641), (1000, 64, 150), (257, 600, 509),
     (960, 2048, 131),
+    # a chunk per unit, by the wide decoder's tiles: 32 pixels and four, two or one wavefronts per channel tile, 64 and 128
+    # pixels, workgroups that walk several tiles; the last pixel tile and the last channel group ragged
+    (512, 4096, 121), (1023, 4096, 203), (500, 4096, 1728), (1000, 4096, 3001), (250, 4096, 9500), (170, 4096, 13001),
+    (300, 4096, 12001), (640, 4096, 9001), (256, 4096, 33000),
 ]
 
 
