@@ -322,7 +322,7 @@ __device__ __forceinline__ void canonical_entries(const uint32_t (&len)[NVS], in
     // count(j) * 2^(48-j) shifted down to l bits
     const bool in = lane >= 1 && lane <= kMaxLen;
     const unsigned long long w = (unsigned long long)my_count << (in ? kMaxLen - lane : 0);
-    const unsigned long long incl = wave_inclusive_scan64(w, lane);
+    const unsigned long long incl = wave_inclusive_scan64(w);
     const unsigned long long first_code = in ? ((incl - w) >> (kMaxLen - lane)) : 0ull;
 #pragma unroll
     for (int j = 0; j < NVS; j++) {
@@ -1205,7 +1205,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 const int ready = missing ? __ffsll((long long)missing) - 1 : 64;
                 const unsigned long long size = lane < ready ? e[j] & 0xffffffffull : 0ull;
                 if constexpr (STATIC) my_bits += lane < ready ? (e[j] & (kKnown - 1ull)) >> 32 : 0ull;
-                const unsigned long long incl = wave_inclusive_scan64(size, lane);
+                const unsigned long long incl = wave_inclusive_scan64(size);
                 if (lane < ready) publish64(&places[added + (uint32_t)lane], kKnown | (total_words + incl - size));
                 total_words += __shfl(incl, 63, 64);
                 added += (uint32_t)ready;

@@ -57,7 +57,7 @@ __device__ __forceinline__ uint32_t first_slot(uint32_t v) { return v ^ (v >> 5)
 // Decode tables, in LDS, built by every workgroup from the code length table of the stream.
 struct DecTables {
     uint32_t cnt_len[64];     // number of codes of each length
-    uint32_t first_rank[64];  // rank (in (length, symbol) order) of the first code of each length
+    uint32_t rank_of_code[64];  // plus a code of the length: its rank (in (length, symbol) order), modulo 2^32
     uint64_t first_code[64];  // first canonical code of each length
     uint64_t limit[64];       // (first_code + count) << (32 - length) for length <= 32: first left-aligned 32-bit
                               // value that is NOT a code of this length or shorter
@@ -79,10 +79,13 @@ struct DecTables {
     };
     uint32_t wave_len_count[4][64];
     uint32_t lut_limit[kLutBits + 1];  // limit[] in a kLutBits-bit frame
-    uint32_t n_used, bad_len, ok, max_len;
+    uint32_t n_used, ok, max_len, pad;
     uint32_t long_base, long_shift, pad0, pad1;
 };
 
+// A cold run of dependent LDS round trips and of instructions that are fetched for the first time: what counts is the number
+// of barriers, of LDS operations in a row and the size of the code.  Counts by ballot instead of LDS additions, 64-bit sums
+// without shuffles, the second table's limits out of one register: 6.3 -> 4.1 us at four wavefronts.
 // All THREADS threads of the workgroup call this (THREADS a multiple of 256); my_len is the code length of symbol
 // threadIdx.x from the stream (threads past 255: anything).  Returns false (for every thread)
 // unless the lengths form a complete prefix code (Kraft sum exactly 1), or the single one-bit code of a
@@ -91,48 +94,10 @@ template <int THREADS>
 __device__ __forceinline__ bool build_decode_tables(DecTables& T, int my_len, int bits) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int K = 1 << bits;
-    if (tid < 64) T.cnt_len[tid] = 0u;
-    if (tid < 256) T.wave_len_count[tid >> 6][tid & 63] = 0u;
-    if (tid == 0) { T.n_used = 0u; T.bad_len = 0u; }
-    __syncthreads();
+    uint32_t before = 0;  // symbols of this one's length before it
     if (tid < 256) {
-        if (my_len > kMaxLen || (tid >= K && my_len != 0)) {
-            atomicAdd(&T.bad_len, 1u);
-            my_len = 0;
-        } else if (my_len) {
-            atomicAdd(&T.cnt_len[my_len], 1u);
-            atomicAdd(&T.n_used, 1u);
-        }
-    }
-    __syncthreads();
-    if (tid < 64) {
-        // running sums over the lengths: count(j) * 2^(48-j) gives the first code of each length (shifted down to
-        // its own width), the Kraft sum and the "first value that is no code of this length" limits
-        const bool in = tid >= 1 && tid <= kMaxLen;
-        const uint32_t c = in ? T.cnt_len[tid] : 0u;
-        const unsigned long long w = (unsigned long long)c << (in ? kMaxLen - tid : 0);
-        const unsigned long long incl = wave_inclusive_scan64(w, lane);
-        const uint32_t rank = wave_exclusive_scan(c);
-        const unsigned long long kraft = __shfl(incl, 63, 64);
-        T.first_code[tid] = in ? ((incl - w) >> (kMaxLen - tid)) : 0ull;
-        T.first_rank[tid] = in ? rank : 0u;
-        const unsigned long long lim32 = (in && tid <= 32) ? (incl >> (kMaxLen - 32)) : ~0ull;
-        T.limit[tid] = lim32;
-        T.limit32[tid] = lim32 > 0xffffffffull ? 0xffffffffu : (uint32_t)lim32;
-        if (tid >= 1 && tid <= kLutBits) T.lut_limit[tid] = (uint32_t)(incl >> (kMaxLen - kLutBits));
-        if (!in) T.cnt_len[tid] = 0u;
-        const unsigned long long used = __ballot(c != 0);
-        if (tid == 0) {
-            const uint32_t n = T.n_used;
-            T.max_len = used ? (uint32_t)(63 - __clzll((long long)used)) : 0u;
-            T.ok = (T.bad_len == 0 && n >= 1 && (n == 1 ? T.cnt_len[1] == 1 : kraft == (1ull << kMaxLen))) ? 1u : 0u;
-        }
-    }
-    __syncthreads();
-    if (!T.ok) return false;
-    // symbols of equal length are numbered in symbol order
-    uint32_t before = 0;
-    if (tid < 256) {
+        const bool bad = my_len > kMaxLen || (tid >= K && my_len != 0);
+        if (bad) my_len = 0;
         // the lanes of this wavefront with the same length as this one: six ballots, one per bit of the length
         unsigned long long same = ~0ull;
 #pragma unroll
@@ -141,25 +106,61 @@ __device__ __forceinline__ bool build_decode_tables(DecTables& T, int my_len, in
             same &= ((my_len >> bit) & 1) ? m : ~m;
         }
         before = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-        if (my_len && before == 0) T.wave_len_count[tid >> 6][my_len] = (uint32_t)__popcll(same);  // the first of them
+        // (the wavefront's own row: cleared, then the first lane of every length leaves the length's count)
+        const uint32_t n_bad = (uint32_t)__popcll(__ballot(bad)), n_used = (uint32_t)__popcll(__ballot(my_len != 0));
+        T.wave_len_count[tid >> 6][lane] = 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (my_len && before == 0) T.wave_len_count[tid >> 6][my_len] = (uint32_t)__popcll(same);
+        if (lane == 0) T.wave_len_count[tid >> 6][0] = n_used | (n_bad << 16);  // (no code has length 0)
     }
     __syncthreads();
+    if (tid < 64) {
+        // running sums over the lengths: count(j) * 2^(48-j) gives the first code of each length (shifted down to
+        // its own width), the Kraft sum and the "first value that is no code of this length" limits
+        const bool in = tid >= 1 && tid <= kMaxLen;
+        const uint32_t all = T.wave_len_count[0][tid] + T.wave_len_count[1][tid] + T.wave_len_count[2][tid] + T.wave_len_count[3][tid];
+        const uint32_t c = in ? all : 0u, totals = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+        const unsigned long long w = (unsigned long long)c << (in ? kMaxLen - tid : 0);
+        const unsigned long long incl = wave_inclusive_scan64(w);
+        const uint32_t rank = wave_exclusive_scan(c);
+        const unsigned long long kraft = __shfl(incl, 63, 64);
+        const unsigned long long first = in ? ((incl - w) >> (kMaxLen - tid)) : 0ull;
+        T.cnt_len[tid] = c;
+        T.first_code[tid] = first;
+        T.rank_of_code[tid] = in ? rank - (uint32_t)first : 0u;
+        const unsigned long long lim32 = (in && tid <= 32) ? (incl >> (kMaxLen - 32)) : ~0ull;
+        T.limit[tid] = lim32;
+        T.limit32[tid] = lim32 > 0xffffffffull ? 0xffffffffu : (uint32_t)lim32;
+        if (tid >= 1 && tid <= kLutBits) T.lut_limit[tid] = (uint32_t)(incl >> (kMaxLen - kLutBits));
+        const unsigned long long used = __ballot(c != 0);
+        const uint32_t n = totals & 0xffffu, c1 = (uint32_t)__builtin_amdgcn_readlane((int)c, 1);
+        if (tid == 0) {
+            T.n_used = n;
+            T.max_len = used ? (uint32_t)(63 - __clzll((long long)used)) : 0u;
+            T.ok = ((totals >> 16) == 0 && n >= 1 && (n == 1 ? c1 == 1 : kraft == (1ull << kMaxLen))) ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+    if (!T.ok) return false;
+    // symbols of equal length are numbered in symbol order
     if (tid < 256) {
         if (my_len) {
             for (int q = 0; q < (tid >> 6); q++) before += T.wave_len_count[q][my_len];
-            T.sorted_sym[T.first_rank[my_len] + before] = (uint16_t)tid;
+            T.sorted_sym[(T.rank_of_code[my_len] + (uint32_t)T.first_code[my_len] + before) & 255u] = (uint16_t)tid;
         }
         if ((uint32_t)tid >= T.n_used) T.sorted_sym[tid] = 0;  // ranks past the last code stay harmless
     }
     __syncthreads();
     {
         // Step 1: the first code in every kLutBits-bit value.  Canonical codes, left-aligned, grow with their
-        // length, so the length is 1 + the number of per-length limits the value reaches.  Fixed trip count,
-        // unrolled: the searches of several values are independent and interleave.
+        // length, so the length is 1 + the number of per-length limits the value reaches.  Four values at a time: their
+        // searches are independent and interleave (all of a thread's in one straight run waits for more instructions,
+        // fetched for the first and only time, than it saves).
         uint32_t lim[kLutBits + 1];
 #pragma unroll
         for (int l = 1; l <= kLutBits; l++) lim[l] = T.lut_limit[l];
-#pragma unroll
+#pragma unroll 4
         for (int it = 0; it < ((1 << kLutBits) + THREADS - 1) / THREADS; it++) {
             const uint32_t v = (uint32_t)(tid + it * THREADS);
             // (only workgroup sizes that do not divide the table need the test: without it the turns are one
@@ -170,12 +171,9 @@ __device__ __forceinline__ bool build_decode_tables(DecTables& T, int my_len, in
             uint32_t len = 1;
 #pragma unroll
             for (int l = 1; l < kLutBits; l++) len += (v >= lim[l]) ? 1u : 0u;
-            uint32_t entry = 0;
-            if (v < lim[kLutBits]) {
-                const uint32_t off = (v >> (kLutBits - len)) - (uint32_t)T.first_code[len];
-                entry = (uint32_t)T.sorted_sym[(T.first_rank[len] + off) & 255u] | (len << 8);
-            }
-            T.first[first_slot(v)] = (uint16_t)entry;
+            const uint32_t at = (v >> (kLutBits - len)) + T.rank_of_code[len];
+            const uint32_t entry = (uint32_t)T.sorted_sym[at & 255u] | (len << 8);
+            T.first[first_slot(v)] = (uint16_t)(v < lim[kLutBits] ? entry : 0u);
         }
     }
     __syncthreads();
@@ -183,7 +181,7 @@ __device__ __forceinline__ bool build_decode_tables(DecTables& T, int my_len, in
         // Step 2: chain up to three codes per table entry (the index of an entry is in stream order, least
         // significant bit first).  A later code counts only if all its bits are inside the kLutBits bits.
         constexpr uint32_t kMask = (1u << kLutBits) - 1u;
-#pragma unroll
+#pragma unroll 4
         for (int it = 0; it < ((1 << kLutBits) + THREADS - 1) / THREADS; it++) {
             if constexpr (((1 << kLutBits) % THREADS) != 0) {
                 if ((uint32_t)(tid + it * THREADS) >= (1u << kLutBits)) break;
@@ -234,28 +232,30 @@ __device__ __forceinline__ bool build_decode_tables(DecTables& T, int my_len, in
             T.pad0 = 0u;
             T.pad1 = 0u;
         }
-        // (worth its construction only where long codes are frequent: their share of the code space, about their
-        // share of the symbols, is span / 2^32; below 2^-11 a chunk meets a handful of them)
-        if (have_long && span >= (1ull << 21)) {
-            const uint32_t top = max_len < 33u ? max_len : 33u;
-            uint32_t lim32[33 - (kLutBits + 1)];  // the limits, read once
+        constexpr int IT = ((1 << kLut2Bits) + THREADS - 1) / THREADS;
+        if (have_long) {
+            // the limits of the lengths in use, out of one register (lane l holds that of length l)
+            const uint32_t top = (uint32_t)__builtin_amdgcn_readfirstlane((int)(max_len < 33u ? max_len : 33u));
+            const uint32_t limits = T.limit32[lane];
+            uint32_t v[IT], len[IT];
 #pragma unroll
-            for (uint32_t l = kLutBits + 1; l < 33u; l++) lim32[l - (kLutBits + 1)] = T.limit32[l];
+            for (int it = 0; it < IT; it++) {
+                v[it] = base + ((uint32_t)(tid + it * THREADS) << shift);  // (wraps past the table's last value: left out below)
+                len[it] = kLutBits + 1;
+            }
+            for (uint32_t l = kLutBits + 1; l < top; l++) {
+                const uint32_t lim_l = (uint32_t)__builtin_amdgcn_readlane((int)limits, (int)l);
 #pragma unroll
-            for (int it = 0; it < ((1 << kLut2Bits) + THREADS - 1) / THREADS; it++) {
-                const uint32_t idx = (uint32_t)tid + (uint32_t)(it * THREADS);
+                for (int it = 0; it < IT; it++) len[it] += v[it] >= lim_l ? 1u : 0u;
+            }
+#pragma unroll
+            for (int it = 0; it < IT; it++) {
+                const uint32_t idx = (uint32_t)(tid + it * THREADS), n = len[it];
                 if (idx >= (1u << kLut2Bits)) break;
-                const uint64_t v64 = (uint64_t)base + ((uint64_t)idx << shift);
-                const uint32_t v = (uint32_t)v64;
-                uint32_t len = kLutBits + 1;
-#pragma unroll
-                for (uint32_t l = kLutBits + 1; l < 33u; l++) {
-                    len += (l < top && v >= lim32[l - (kLutBits + 1)]) ? 1u : 0u;
-                }
                 uint32_t entry = 0;
-                if (v64 <= 0xffffffffull && len <= 32u - shift && len <= 31u) {
-                    const uint32_t off = (v >> (32 - len)) - (uint32_t)T.first_code[len];
-                    if (off < T.cnt_len[len]) entry = (uint32_t)T.sorted_sym[(T.first_rank[len] + off) & 255u] | (len << 8);
+                if (((uint64_t)idx << shift) < span && n <= 32u - shift && n <= 31u) {
+                    const uint32_t code = v[it] >> (32 - n), off = code - (uint32_t)T.first_code[n];
+                    if (off < T.cnt_len[n]) entry = (uint32_t)T.sorted_sym[(code + T.rank_of_code[n]) & 255u] | (n << 8);
                 }
                 T.lut2[idx] = (uint16_t)entry;
             }
@@ -356,7 +356,7 @@ __device__ __forceinline__ bool decode_run(const uint32_t* __restrict__ gw, uint
             if (len <= 32) {
                 const uint32_t off = (v >> (32 - len)) - (uint32_t)T.first_code[len];
                 if (off >= T.cnt_len[len]) ok = false;
-                sym0 = T.sorted_sym[(T.first_rank[len] + off) & 255u];
+                sym0 = T.sorted_sym[((v >> (32 - len)) + T.rank_of_code[len]) & 255u];
                 len0 = len;
                 n = 1;
             } else {
@@ -371,7 +371,7 @@ __device__ __forceinline__ bool decode_run(const uint32_t* __restrict__ gw, uint
                     const uint64_t f = T.first_code[l];
                     const uint32_t c = T.cnt_len[l];
                     if (c && code >= f && code - f < c) {
-                        sym = T.sorted_sym[T.first_rank[l] + (uint32_t)(code - f)];
+                        sym = T.sorted_sym[((uint32_t)code + T.rank_of_code[l]) & 255u];
                         found = true;
                         break;
                     }
@@ -475,7 +475,7 @@ __device__ __forceinline__ bool decode_run_bytes(const uint32_t* pw, uint32_t nw
                     if (len <= 32) {
                         const uint32_t off = (v >> (32 - len)) - (uint32_t)T.first_code[len];
                         if (off >= T.cnt_len[len]) ok = false;
-                        sym = T.sorted_sym[(T.first_rank[len] + off) & 255u];
+                        sym = T.sorted_sym[((v >> (32 - len)) + T.rank_of_code[len]) & 255u];
                     } else {
                         // longer than 32 bits (needs a histogram as skewed as the Fibonacci numbers): bit by bit
                         unsigned long long code = 0;
@@ -488,7 +488,7 @@ __device__ __forceinline__ bool decode_run_bytes(const uint32_t* pw, uint32_t nw
                             const unsigned long long f = T.first_code[len];
                             const uint32_t c = T.cnt_len[len];
                             if (c && code >= f && code - f < c) {
-                                sym = T.sorted_sym[T.first_rank[len] + (uint32_t)(code - f)];
+                                sym = T.sorted_sym[((uint32_t)code + T.rank_of_code[len]) & 255u];
                                 found = true;
                                 break;
                             }
@@ -551,9 +551,12 @@ struct StreamView {
     const uint32_t* payload;
     float delta;
 };
-__device__ __forceinline__ bool open_stream(const DecodeParams& p, StreamView* v) {
+// (requested before anything else of the stream: see the kernels)
+__device__ __forceinline__ Header load_header(const DecodeParams& p) {
+    return p.bytes < (size_t)(kHeaderBytes + kLenTableBytes) ? Header{} : *reinterpret_cast<const Header*>(p.stream);
+}
+__device__ __forceinline__ bool open_stream(const DecodeParams& p, const Header& hd, StreamView* v) {
     if (p.bytes < (size_t)(kHeaderBytes + kLenTableBytes)) return false;
-    const Header hd = *reinterpret_cast<const Header*>(p.stream);
     const uint64_t ppc = hd.px_per_chunk;
     const uint64_t chunk_syms64 = ppc * (uint64_t)p.C;
     bool ok = hd.magic == kMagic && hd.version == 1 && hd.bits == p.bits && hd.C == (uint32_t)p.C &&
@@ -667,9 +670,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
     // What does not depend on the header goes out first: the code lengths, and (see the chunk decoder) offsets, run sizes
     // and payload of the wavefront's first chunk, where the nominal chunk size puts them.  The guess is checked against the
     // header below.  Nothing outside [stream, stream + bytes) is touched either way.
+    const Header hd = load_header(p);
     const int my_len = tid < 256 && p.bytes >= (size_t)(kHeaderBytes + kLenTableBytes) ? (int)p.stream[kHeaderBytes + tid] : 0;
     uint32_t* pw = reinterpret_cast<uint32_t*>(dyn_lds) + (size_t)wave * (p.pay_words + (uint32_t)kPayOverrun);
-    const uint32_t ch_first = blockIdx.x * p.g_tile_chunks + (uint32_t)wave;
+    const uint32_t ch_first = blockIdx.y * p.g_tile_chunks + (uint32_t)wave;
     const bool guess = p.g_off_payload <= p.bytes && (uint32_t)wave < p.g_tile_chunks && ch_first < p.g_n_chunks && p.g_spc > 32u;  // (a chunk is a unit)
     UnitInfo first{0u, 0u, 0u};
     uint32_t first_w0 = 0u, first_w1 = 0u;
@@ -693,13 +697,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
         }
     }
     StreamView sv;
-    if (!open_stream(p, &sv)) {
+    if (!open_stream(p, hd, &sv)) {
         if (tid == 0) atomicOr(p.err, FMTC_ERR_HEADER);
-        return;
-    }
-    if (!(p.prebuilt ? load_decode_tables<512>(T, my_len, static_cast<const PrebuiltTables*>(p.prebuilt))
-                     : build_decode_tables<512>(T, my_len, p.bits))) {
-        if (tid == 0) atomicOr(p.err, FMTC_ERR_TABLE);
         return;
     }
     const uint32_t n_chunks = sv.n_chunks, spc = sv.spc, chunk_syms = sv.chunk_syms, ppc = (uint32_t)sv.ppc;
@@ -707,8 +706,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
     const uint64_t V = (uint64_t)p.P * (uint64_t)C;
     const uint32_t last_syms = (uint32_t)(V - (uint64_t)(n_chunks - 1u) * chunk_syms);
     const Unit un(sv, lane);
-    __syncthreads();
-
     const float delta = sv.delta;
     // Chunks of a tile: what the stream's chunk size makes of the tile's pixels (symbols only: of a unit per wavefront), and
     // what its LDS holds.
@@ -717,6 +714,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
     G = G < 1u ? 1u : (G > fits ? fits : G);
     bool guessed = guess && sv.n_chunks == p.g_n_chunks && sv.spc == p.g_spc && G == p.g_tile_chunks;  // of the first unit
     const uint32_t n_tiles = (n_chunks + G - 1) / G;
+    if (blockIdx.y >= n_tiles) {  // (the grid is made for any chunk size)
+        wait_loads<0>();  // (nothing is on its way into LDS any more)
+        return;
+    }
+    if (!(p.prebuilt ? load_decode_tables<512>(T, my_len, static_cast<const PrebuiltTables*>(p.prebuilt))
+                     : build_decode_tables<512>(T, my_len, p.bits))) {
+        if (tid == 0) atomicOr(p.err, FMTC_ERR_TABLE);
+        return;
+    }
+    __syncthreads();
+
     // 0x6400 | s is the f16 number 1024 + s: the level s - 2^(b-1) is that minus (1024 + 2^(b-1)), exactly
     const _Float16 level_off = (_Float16)(float)(1024 + (1 << (p.bits - 1)));
     const halfx2 level_off2 = {level_off, level_off};
@@ -771,7 +779,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
         }
     };
 
-    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    for (uint32_t tile = blockIdx.y; tile < n_tiles; tile += gridDim.y) {
         const uint32_t first_ch = tile * G;
         const uint32_t tile_chunks = n_chunks - first_ch < G ? n_chunks - first_ch : G;
         // ---- variable length decoding into the LDS tile, a unit per wavefront and round ----
@@ -848,7 +856,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
                 rowbase[b] = ((uint32_t)pxl - k * ppc) * (uint32_t)C + 8u * half;
             }
             constexpr int D = MT == 4 ? 2 : 3;
-            for (int cg = blockIdx.y; cg < n_cg; cg += gridDim.y) {
+            for (int cg = blockIdx.x; cg < n_cg; cg += gridDim.x) {
                 const int ct = cg * CTW + wave % CTW;
                 const bool mine = ct < p.ncs;  // wavefront-uniform
                 floatx16 acc[MT], acl[MT];
@@ -999,7 +1007,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     // the projection after it, which no longer shares the memory with that write-back, 14 us less.)
     constexpr bool kStreamOut = !U8 && (WAVES >= 12 || LOG);
 
-    // loads that do not depend on the header go out first: the code length table and the basis
+    // the header, and the loads that do not depend on it, go out first: the code length table and the basis
+    const Header hd = load_header(p);
     int my_len = 0;
     if (tid < 256 && p.bytes >= (size_t)(kHeaderBytes + kLenTableBytes)) my_len = p.stream[kHeaderBytes + tid];
     // the basis goes from global memory straight into LDS (no registers in between), 16 bytes per lane and
@@ -1064,7 +1073,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
         if (pay_pre) request_payload(reinterpret_cast<const uint32_t*>(p.stream + p.g_off_payload), gw0, gw1 - gw0);
     }
     StreamView sv;
-    if (!open_stream(p, &sv)) {
+    if (!open_stream(p, hd, &sv)) {
         if (tid == 0 && blockIdx.x == 0) atomicOr(p.err, FMTC_ERR_HEADER);
         return;
     }
@@ -1072,6 +1081,10 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     const uint32_t guess_w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.off);
     const uint32_t guess_w1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)cur.end);
     const Unit un(sv, lane);
+    if (blockIdx.x >= un.n_units) {  // (the grid is made for any chunk size)
+        wait_loads<0>();  // (nothing is on its way into LDS any more)
+        return;
+    }
     auto chunks_of = [&](uint32_t u) { return sv.n_chunks - u * un.m < un.m ? sv.n_chunks - u * un.m : un.m; };
     if (!guess_valid && ch_first < un.n_units) cur.load(sv, un, ch_first * un.m, chunks_of(ch_first), lane);
     if constexpr (!U8) {
@@ -1473,11 +1486,13 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
             p.lds_basis_bytes = (uint32_t)lds_basis_log;
         }
         const size_t lds = log12 ? lds_dyn(waves) - lds_basis + lds_basis_log : lds_dyn(waves);
-        const unsigned per_cu = log12 ? 1u : (unsigned)((160 * 1024) / lds_all(waves));
-        unsigned gx = (g.n_chunks + waves - 1) / waves;
-        const unsigned most = waves >= 8 ? 1u : 2u;
-        const unsigned cap = 256u * (per_cu < 1 ? 1u : (per_cu > most ? most : per_cu));
-        if (gx > cap) gx = cap;
+        // A unit of chunks of another size than the nominal may hold half its symbols: workgroups for twice the chunks.  The
+        // units are dealt to the workgroups first and to their wavefronts then, so a small tensor's have a compute unit
+        // each; a workgroup without one ends when it has read the header.
+        // (As many wavefronts as nominal chunks before: chunks of 2210 symbols, 24 channels, 6510 pixels 18.0 -> 11.2 us; of
+        // 1024, 80 channels, 2187 pixels, planar 34 -> 21.)
+        // (One workgroup per compute unit: the registers allow no second.)
+        const unsigned gx = g.n_chunks < 128u ? 2u * g.n_chunks : 256u;
 #define FMTC_DECC_L(NCT, LAY, AL, WV, CF, LG, NL)                                                                \
     do {                                                                                                         \
         if (lds > 16 * 1024) {                                                                                   \
@@ -1563,11 +1578,19 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
     // More tiles than run at the same time are walked by the workgroups that do, which build their tables once (256
     // channels, 392 tiles 51 -> 45 us; 169, 470 tiles 49 -> 43).
     const uint32_t most = d_syms || blocks <= 512u ? 512u : 256u;
-    dim3 grid(n_tiles < most ? n_tiles : most, (unsigned)groups);
+    // (Chunks of another size than the nominal may give a tile fewer pixels: workgroups for twice the tiles where they run at
+    // the same time; one without a tile ends when it has read the header.)
+    const uint32_t resident = 256u / (uint32_t)groups;
+    uint32_t gx = 2u * n_tiles < resident ? 2u * n_tiles : resident;
+    if (gx < n_tiles) gx = n_tiles < most ? n_tiles : most;
+    dim3 grid((unsigned)groups, gx);  // (a tile's channel groups side by side, spread over the dies; workgroups without a tile last)
     p.g_tile_chunks = (uint32_t)G;
     // (chunks of another size than the nominal may take more room for the same pixels: their tiles get smaller)
     p.tile_px = 32 * mt;
-    p.tile_bytes = (uint32_t)G * slot_bytes < 4352u ? 4352u : (uint32_t)G * slot_bytes;  // (any chunk fits)
+    uint32_t tile_bytes = (uint32_t)G * slot_bytes;
+    const uint32_t singly = 32u * (uint32_t)mt * 68u * (uint32_t)((C + kSubSyms - 1) / kSubSyms);  // every pixel a chunk of its own
+    if (!d_syms && tile_bytes < singly && (mt == 1 || C <= 512)) tile_bytes = singly;
+    p.tile_bytes = tile_bytes < 4352u ? 4352u : tile_bytes;  // (any chunk fits)
     p.lds_basis_bytes = ks > 1 && pay_bytes < 32u * 1024u ? 32u * 1024u : pay_bytes;
     const size_t lds = (size_t)p.lds_basis_bytes + p.tile_bytes + 128;
     // more than 64 KB of dynamic LDS has to be requested per kernel (the CU has 160 KB)
@@ -1642,9 +1665,7 @@ hipError_t launch_decode_u8(const Basis8Device& b, const uint8_t* d_stream, size
                          lds_dyn(16) + sizeof(DecTables) + 16 * (size_t)kChunkTileBytes + 64 <= 160 * 1024;
     const int waves = sixteen ? 16 : (eight ? 8 : 4);
     const size_t lds = lds_dyn(waves);
-    unsigned gx = (g.n_chunks + waves - 1) / waves;
-    const unsigned cap = 256u * (waves >= 8 ? 1u : 2u);
-    if (gx > cap) gx = cap;
+    const unsigned gx = g.n_chunks < 128u ? 2u * g.n_chunks : 256u;  // see launch_decode
     hipError_t el = hipSuccess;
 #define FMTC_DECU_F(NCT, LAY, AL, WV, CF) \
     do {                                                                                                         \
