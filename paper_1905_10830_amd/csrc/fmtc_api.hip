@@ -830,7 +830,7 @@ fmtc_status fmtc_encode_static(const fmtc_basis* basis, const fmtc_table* t, con
         PackParams pk = pack_params(nullptr, pl.g, bits, delta, cs, 0, t->d_enc_table, static_cast<uint8_t*>(d_stream_out),
                                     cap_words, d_out_bytes);
         pk.static_max_len = t->max_len;
-        if (!test_option(kTestStaticTwoKernels) && encode_static_fused_applies(C, layout, (uint32_t)chunk_syms, cs.n_groups)) {
+        if (!test_option(kTestStaticTwoKernels) && encode_static_fused_applies(C, layout, bits, (uint32_t)chunk_syms, cs.n_groups)) {
             static_assert(sizeof(CoderCtrl) % 4 == 0, "control block is cleared as words");
             const size_t clear_bytes = pl.ws.off_lookback + sizeof(uint64_t) * (size_t)cs.n_groups - pl.ws.off_ctrl;
             if ((e = launch_fill_zero(reinterpret_cast<uint32_t*>(w + pl.ws.off_ctrl), clear_bytes / 4, s)) != hipSuccess)

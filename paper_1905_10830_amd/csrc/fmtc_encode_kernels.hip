@@ -1062,21 +1062,16 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
 // The fused kernel for a channel count and layout, its LDS size, and how many of its workgroups the device
 // holds at once (0: shape not supported or the query failed).
 static int fused_kernel_for(int C, int layout, const void** fn_out, size_t* lds_out) {
-    if (!(C == 32 || C == 64 || C == 128)) return 0;
+    if (!(C == 64 || (C == 32 && layout == FMTC_NHWC))) return 0;
     const int nct = C / 32;
     const size_t lds = sizeof(float) * (size_t)C * C + 4 * 4096 + sizeof(PackShared);
-    const void* fn = nullptr;
-#define FMTC_FUSED(NCT, LAY) fn = reinterpret_cast<const void*>(&k_project_quantize_rows<NCT, LAY, true, true>)
-    if (layout == FMTC_NHWC) {
-        if (nct == 1) FMTC_FUSED(1, FMTC_NHWC); else if (nct == 2) FMTC_FUSED(2, FMTC_NHWC); else FMTC_FUSED(4, FMTC_NHWC);
-    } else {
-        if (nct == 1) FMTC_FUSED(1, FMTC_NCHW); else if (nct == 2) FMTC_FUSED(2, FMTC_NCHW); else FMTC_FUSED(4, FMTC_NCHW);
-    }
-#undef FMTC_FUSED
+    const void* fn = nct == 1 ? reinterpret_cast<const void*>(&k_project_quantize_rows<1, FMTC_NHWC, true, true>)
+                     : layout == FMTC_NHWC ? reinterpret_cast<const void*>(&k_project_quantize_rows<2, FMTC_NHWC, true, true>)
+                                           : reinterpret_cast<const void*>(&k_project_quantize_rows<2, FMTC_NCHW, true, true>);
     *fn_out = fn;
     *lds_out = lds;
-    static std::atomic<int> resident[2][3];  // (zero-initialised; every thread computes the same values)
-    std::atomic<int>& slot = resident[layout == FMTC_NHWC][nct == 4 ? 2 : nct - 1];
+    static std::atomic<int> resident[2][2];  // (zero-initialised; every thread computes the same values)
+    std::atomic<int>& slot = resident[layout == FMTC_NHWC][nct - 1];
     int cap = slot.load(std::memory_order_relaxed);
     if (!cap) {
         int dev = 0, cus = 0, per_cu = 0;
@@ -1093,16 +1088,17 @@ static int fused_kernel_for(int C, int layout, const void** fn_out, size_t* lds_
 
 // The one-kernel encoder is used where every chunk group gets a workgroup of its own: its workgroups work through
 // their groups in lock step (project, pack, wait for the position, store), which loses to two specialised kernels for
-// tensors that the device does not hold at once (135 us against 60 + 40 us at 1568 groups).  Below that the line is due to
-// be drawn anew: it dates from a projection of 17 us at 128 channels and 196 groups, which takes 12 to 13.5 us now.
-// Measured with the present kernels, whole calls, one kernel against two, us: 64 channels, channels last, 6 bits 20.3
-// and 18.8 (13 groups), 22.7 and 23.4 (197), at 8 bits 25.2 and 29.3 (197); planar 26.2 and 23.6 (197), at 8 bits 28.7
-// and 30.0; 128 channels 23.9 and 21.6 (7), 26.4 and 26.1 (197), planar 30.6 and 25.9; 32 channels 20.3 and 17.1 (50),
-// 21.6 and 21.1 (184).  So one kernel is ahead at 64 channels and some 200 groups only.
-bool encode_static_fused_applies(int C, int layout, uint32_t chunk_syms, uint32_t n_groups) {
+// tensors that the device does not hold at once (135 us against 60 + 40 us at 1568 groups); below, where few groups leave most
+// of the device idle while each walks its three phases, and wherever the projection is quicker in another form.  What is
+// left, whole calls, one kernel against two, us: 64 channels, channels last, 4 / 6 / 8 bits 20.4 : 19.0 / 21.5 : 20.3 /
+// 23.6 : 23.1 (128 groups), 20.2 : 20.6 / 21.3 : 22.1 / 23.8 : 27.2 (160), 22.0 : 22.4 / 22.8 : 23.5 / 25.1 : 28.8 (256);
+// planar 24.7 : 21.9 (160, 6 bits), 27.3 : 24.0 and 27.3 : 28.4 (128 and 160, 8 bits); 32 channels, channels last, 160 groups
+// 19.4 : 18.4 / 21.2 : 19.9 / 22.5 : 22.8, 256 at 8 bits 23.5 : 25.1, planar 26.4 : 25.0; 128 channels, 13 groups 24.5 :
+// 16.9, 256 26.9 : 26.2, planar 28.9 : 24.7.
+bool encode_static_fused_applies(int C, int layout, int bits, uint32_t chunk_syms, uint32_t n_groups) {
     const void* fn;
     size_t lds;
-    if (chunk_syms != 4096u) return false;
+    if (chunk_syms != 4096u || n_groups <= 144u || (bits < 8 && !(C == 64 && layout == FMTC_NHWC))) return false;
     const int cap = fused_kernel_for(C, layout, &fn, &lds);
     return cap > 0 && n_groups <= (uint32_t)cap;
 }

@@ -129,6 +129,30 @@ def test_single_kernel_and_two_kernel_paths_agree(fmtc, oracle, case, monkeypatc
     assert int(nb.item()) == n and (a[:n] == b[:n]).all()
 
 
+# Around the number of chunk groups from which one kernel is used (four chunks a group: 145 of them), a last group of one
+# chunk, and the largest number (one group per compute unit)
+@pytest.mark.parametrize("C,bits,layout", [(64, 5, synth.NHWC), (64, 8, synth.NHWC), (64, 8, synth.NCHW), (32, 8, synth.NHWC)])
+@pytest.mark.parametrize("groups", [144.0, 144.25, 160.5, 256.0])
+def test_one_kernel_and_two_agree_on_larger_tensors(fmtc, C, bits, layout, groups):
+    P = int(groups * 4 * 4096) // C
+    rng = np.random.default_rng(C + bits)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C)).astype(np.float32)
+    basis = fmtc.basis_import(T, np.zeros(C, np.float32), np.float32(8.0))
+    xs = dev(x.reshape(1, P // 32, 32, C) if layout == synth.NHWC else x.T.reshape(1, C, P // 32, 32))
+    table = fmtc.fit_table(basis, xs, bits, layout)
+    a, na = fmtc.encode_static(basis, table, xs, layout)
+    torch.cuda.synchronize()
+    fmtc.test_option(fmtc.TEST_STATIC_TWO_KERNELS, 1)
+    try:
+        b, nb = fmtc.encode_static(basis, table, xs, layout)
+        torch.cuda.synchronize()
+    finally:
+        fmtc.test_option(fmtc.TEST_STATIC_TWO_KERNELS, 0)
+    n = int(na.item())
+    assert int(nb.item()) == n and (a[:n] == b[:n]).all()
+
+
 def test_table_import_export_and_bad_tables(fmtc, oracle):
     case = CASES[1]
     C, H, W, ncal, ndat, rank, act, bits, cs = case
