@@ -53,7 +53,8 @@ __device__ __forceinline__ void wave_sync() {
 // scalar registers: node k of the queue stands behind k others and the leaves not heavier than it.  A lane then finds
 // its node by counting mask bits below it, and a pair's sum is its neighbour's weight away.
 // 15 to 25 rounds for the 130 to 250 symbols of 7 and 8 bits, where one merge after the other in one lane took
-// 0.11 us each: 168 symbols 19.4 -> 11.2 us, issue-bound in one wavefront at about 100 instructions a round.  (Up to
+// 0.11 us each: 168 symbols 19.4 -> 8 us, bound by one wavefront's issue and LDS latencies (11.2 us where the waiting
+// internal nodes' places were found one node at a time, up to 30 of them a round).  (Up to
 // 64 symbols the loop below stays: 70 ns a merge, and the small alphabets' steep counts need as many rounds.)
 // Leaves parents in leaf_parent and node (see TableLds).  Internal node weights go where the ranks were (the caller
 // holds those in registers by now).  One wavefront.
@@ -74,20 +75,33 @@ __device__ __forceinline__ void huffman_merge_rounds(TableLds& L, int lane, int 
         const uint32_t s0 = add(l0, l1), s1 = add(l0, i0), s2 = add(i0, i1);
         const uint32_t t01 = s0 < s1 ? s0 : s1, t = t01 < s2 ? t01 : s2;
         const int wait = made - ni;
-        // Places of internal nodes among the first 62 of the order (a place past them sets bit 63, which nobody looks
-        // at): four nodes per turn, their chains side by side.  Past the queue's end the weight is infinite, the place too.
+        // Places of internal nodes among the first 62 of the order (a place past them sets bit 63, which nobody looks at).
         unsigned long long places = 0;
-        int last = 0;
-        for (int k = 0; k < wait && last < 62; k += 4) {
+        if (wait <= 4) {
+            // their chains side by side; past the queue's end the weight is infinite, the place too
             int at[4];
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)iv, k + u);
-                at[u] = k + u + __popcll(__ballot(lw <= w));  // (leaves not heavier than an internal node: at most t)
+                const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)iv, u);
+                at[u] = u + __popcll(__ballot(lw <= w));  // (leaves not heavier than an internal node: at most t)
             }
 #pragma unroll
             for (int u = 0; u < 4; u++) places |= 1ull << (at[u] < 63 ? at[u] : 63);
-            last = at[3];
+        } else {
+            // a node per lane: the block of eight leaves that its weight falls into, by the blocks' last leaves in scalar
+            // registers, and its place in the block, by the others, fetched all at once
+            uint32_t block = 0;
+#pragma unroll
+            for (int q = 0; q < 7; q++) block += (uint32_t)__builtin_amdgcn_readlane((int)lw, 8 * q + 7) <= iv ? 1u : 0u;
+            uint32_t leaf[7];
+#pragma unroll
+            for (int q = 0; q < 7; q++) leaf[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(32u * block + 4u * q), (int)lw);
+            uint32_t at = (uint32_t)lane + 8u * block;
+#pragma unroll
+            for (int q = 0; q < 7; q++) at += leaf[q] <= iv ? 1u : 0u;
+            at = lane < wait && at < 63u ? at : 63u;
+            // (a lane that nobody writes to receives 0)
+            places = __ballot(__builtin_amdgcn_ds_permute((int)(4u * at), at < 63u ? 1 : 0) != 0);
         }
         const int all = __popcll(__ballot(lw <= t && nl + lane < n)) + wait;
         const int count = all < 62 ? all & ~1 : 62;
