@@ -2130,7 +2130,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(E, E))) 
 
 template <int PT, int KT, int W, int D, int E>
 static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
-                               int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
+                               int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s,
+                               bool skip_zero_rows) {
     SplitParams p{};
     p.x = d_x;
     p.basis16 = reinterpret_cast<const uint4*>(b.fwd16);
@@ -2147,8 +2148,10 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
     // (a block beyond the last coefficient group ends at once)
     const int padded = (p.n_kg + 7) / 8 * 8;
     p.n_kg_pad = 4 * (padded - p.n_kg) <= p.n_kg ? padded : p.n_kg;
-    // groups of four coefficient tiles whose rows of the basis are all zero (truncation) are not computed
-    p.active_kt = b.C % 16 == 0 ? (b.active_rows + 127) / 128 * 4 : p.ncs;
+    // Groups of four coefficient tiles whose rows of the basis are all zero (truncation) are not computed where the tiled
+    // product leaves them out too.  The narrow kernels decide every coefficient of a pixel beyond f16 exactly, those of
+    // zero rows too, and what a pixel that is not finite gives there must not depend on the tensor's size.
+    p.active_kt = skip_zero_rows ? (b.active_rows + 127) / 128 * 4 : p.ncs;
     if (p.active_kt < 4) p.active_kt = 4;
     p.inv_delta = (float)(1.0 / (double)delta);
     p.delta = delta;
@@ -2192,12 +2195,13 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
     const int64_t tiles = (P + 31) / 32 * ncs;  // of 32 pixels x 32 coefficients
     // Up to 32 channels the narrow kernel has no contraction to split (5.4 to 6.4 us against 6.0 at 16 and 32 channels).
     if (narrow && ncs == 1) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    const bool skip = !narrow && whole16;
     // The split contraction's tile grows with their number.  One or two coefficient tiles per workgroup while that leaves
     // compute units idle otherwise (us, 1 : 2 : 4 of them: 512 channels, 64 tiles 10.5 : 11.2 : 12.8; 768 channels, 312 tiles
     // 17.3 : 14.6 : 17.2; 512 channels, 720 tiles 21.5 : 16.9 : 15.0).
-    if (tiles <= 256) return launch_split<1, 1, 4, 4, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (tiles <= 256) return launch_split<1, 1, 4, 4, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
     if (tiles <= 640 || (tiles <= 1024 && ncs == 2))
-        return launch_split<1, 2, 4, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+        return launch_split<1, 2, 4, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
     // Four of them: up to 1024 tiles instead of the narrow kernels (us, theirs first: 96 channels, 999 tiles 11.9 : 8.4; 128
     // 10.9 : 8.5; 160 13.8 : 10.4; at 144 channels and 2330 tiles 13.9 : 17.8), and of 100 to 127 channels that are no multiple
     // of 16, which those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 12800 57.2 : 55.6); instead
@@ -2205,12 +2209,12 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
     // 12.6; 1024, 1568 43.5 : 46.6; 512, 2304 26.8 : 33.4), up to 4096 where it fetches planar pixels four bytes at a time
     // (512, 2304 46.3 : 31.6; 960, 2940 88 : 63; 256, 4096 28.0 : 24.8; 384, 4464 39.7 : 38.5, 192, 9900 45 : 51).
     const int64_t four = narrow ? (ncs == 4 && !whole16 ? 16384 : 1024) : (whole16 && layout == FMTC_NHWC ? 1536 : 4096);
-    if (tiles <= four) return launch_split<1, 4, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (tiles <= four) return launch_split<1, 4, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
     if (narrow) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     // The tiled product needs whole groups of 16 channels.  Other channel counts take two by two tiles (us, 1 x 4 : 2 x 2:
     // 169 channels, 10800 tiles 77 : 65; 180, 19200 99 : 83; 300, 7520 60.5 : 58.8; 1001, 3136 80 : 80).
     if (whole16) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    return launch_split<2, 2, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    return launch_split<2, 2, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
 }
 
 // Histogram of given symbols (staged coder entry point): one row of partial counts per workgroup.

@@ -89,6 +89,27 @@ def test_truncated_decode_matches_oracle(fmtc, oracle, case, layout):
     assert np.abs(xhat2.cpu().numpy().astype(np.float64) - want).max() <= RECON_TOL
 
 
+@pytest.mark.parametrize("layout", [synth.NHWC, synth.NCHW], ids=["nhwc", "nchw"])
+@pytest.mark.parametrize("C,keep,bits", [(64, 9, 5), (96, 40, 5), (128, 100, 4), (144, 100, 5), (160, 16, 6), (144, 100, 8), (200, 17, 5),
+                                         (256, 40, 4), (512, 130, 5)])
+def test_truncated_pixels_do_not_depend_on_the_tensor(fmtc, C, keep, bits, layout):
+    """The symbols of a pixel are the same whichever kernel its tensor's size selects, those of dropped coefficients and
+    of pixels that are not finite among them."""
+    rng = np.random.default_rng(C + keep)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    basis = fmtc.basis_import(T, rng.standard_normal(C).astype(np.float32), np.float32(4.0)).truncate(keep)
+    P, few = 32 * (20000 // (C // 32 + 1)), 150
+    x = rng.standard_normal((P, C)).astype(np.float32)
+    x[7, 3], x[8, C - 1], x[40, 0], x[99, 1], x[100] = np.inf, -np.inf, np.nan, 1.0e25, 7.0e4
+    syms = []
+    for n in (P, few):
+        xs = x[:n].reshape(1, n, 1, C) if layout == synth.NHWC else np.ascontiguousarray(x[:n].T).reshape(1, C, n, 1)
+        s, _ = fmtc.quantize(basis, dev(xs), bits, layout)
+        torch.cuda.synchronize()
+        syms.append(s.cpu().numpy().reshape(n, C))
+    assert np.array_equal(syms[0][:few], syms[1])
+
+
 def test_truncated_handle(fmtc, oracle):
     s = synth.FeatureMapStream(C=24, H=8, W=8, rank=6, act="relu", seed=12)
     x = s.images(2)
