@@ -324,6 +324,11 @@ fmtc_status fmtc_profile_copy(void *d_dst, const void *d_src, size_t bytes, void
  * value 1: the packer of large tensors gives up its waits at once (the stream
  * is left invalid).  Value 0 restores the library's own choice.  Process-wide. */
 fmtc_status fmtc_test_option(int option, int value);
+/* Test support: the form of the projection kernel that fmtc_quantize (and fmtc_encode, and fmtc_encode_static's
+ * two kernels) use for such a tensor and a basis of which `keep` rows are not all zero, as a short text, so that a
+ * test can state which kernel its case is meant for.  Host only. */
+fmtc_status fmtc_test_projection(int64_t N, int C, int H, int W, fmtc_layout layout, int bits, int keep, char *text,
+                                 size_t size);
 
 /* Text of the last error on the calling thread ("" if none). */
 const char *fmtc_last_error(void);

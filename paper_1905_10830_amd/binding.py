@@ -27,7 +27,7 @@ EXPORTS = [
     "fmtc_basis8_create", "fmtc_basis8_export", "fmtc_basis8_destroy", "fmtc_quantize_u8", "fmtc_reconstruct_u8",
     "fmtc_encode_u8", "fmtc_decode_u8",
     "fmtc_profile_enable", "fmtc_profile_kernels", "fmtc_profile_name", "fmtc_profile_read", "fmtc_profile_copy",
-    "fmtc_test_option",
+    "fmtc_test_option", "fmtc_test_projection",
 ]
 
 _lib = None
@@ -104,6 +104,7 @@ def load_library():
                                       ctypes.POINTER(i32)]
     lib.fmtc_profile_copy.argtypes = [vp, vp, sz, vp]
     lib.fmtc_test_option.argtypes = [i32, i32]
+    lib.fmtc_test_projection.argtypes = [i64, i32, i32, i32, i32, i32, i32, ctypes.c_char_p, sz]
     _lib = lib
     return lib
 
@@ -559,6 +560,17 @@ def test_option(option, value):
 
 
 test_option.__test__ = False  # (not a test, whatever a collector makes of the name)
+
+
+def test_projection(shape, layout=NHWC, bits=4, keep=None):
+    """-> the form of the projection kernel that a tensor of the 4-d `shape` takes, as a text (tests only)."""
+    n, h, w, c = shape if layout == NHWC else (shape[0], shape[2], shape[3], shape[1])
+    text = ctypes.create_string_buffer(64)
+    _check(load_library().fmtc_test_projection(n, c, h, w, layout, bits, c if keep is None else keep, text, len(text)))
+    return text.value.decode()
+
+
+test_projection.__test__ = False
 
 
 def profile_enable(max_launches_per_kernel):

@@ -12,6 +12,7 @@
 // workgroup's wavefronts share out (few pixels; channel counts that are no
 // multiple of 16).
 #include <atomic>
+#include <cstdio>
 #include <type_traits>
 
 #include "fmtc_device.h"
@@ -938,6 +939,40 @@ static bool planar_offsets_fit(int C, int64_t P, int64_t HW) {
     return (uint64_t)C * ((uint64_t)HW + 32u) + 9u * (uint64_t)HW < (1ull << 30) && (uint64_t)P + 64u < (1ull << 31);
 }
 
+// Which of the narrow kernels takes a tensor.
+struct RowsPlan {
+    int nct, waves;
+    bool stream;  // k_project_quantize_stream
+    bool vec;     // k_project_quantize_rows: loads of four channels (planar: uniform plane addresses) without masks
+};
+static size_t rows_lds(int nct, int bits, int waves) {
+    return sizeof(float) * (size_t)(32 * nct) * (32 * nct) + sizeof(uint32_t) * waves * kHistLanes * ((size_t)1 << bits);
+}
+static RowsPlan plan_rows(int C, int64_t P, int64_t HW, int layout, int bits) {
+    RowsPlan r{};
+    r.nct = (C + 31) / 32;
+    // 128 channels: eight wavefronts on one copy of the basis, two per SIMD, each working tile by tile with one pair
+    // of accumulators (two four-wavefront workgroups with a copy each would not fit a compute unit's LDS).  Measured
+    // at 25.7 M values: 57 us against 63 us with four wavefronts, one per SIMD.  (The same form for 144 channels
+    // spills registers: 119 us against 80 us.)
+    // (planar tensors: the loads' addresses do not fit the registers either; 8 bits: eight wavefronts' histograms do
+    // not fit LDS beside the basis)
+    const bool eight = r.nct == 4 && layout == FMTC_NHWC && (P + 31) / 32 > 1024 && rows_lds(r.nct, bits, 8) <= 144 * 1024;
+    r.waves = eight ? 8 : 4;
+    const bool offsets_fit = layout == FMTC_NHWC || planar_offsets_fit(C, P, HW);
+    // planar: vec = a multiple of 16 channels and offsets within the images of a pixel tile that fit 32 bits
+    r.vec = layout == FMTC_NHWC ? C % 4 == 0 : C % 16 == 0 && offsets_fit;
+    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, four wavefronts.
+    // (Measured: 144 channels, 28.9 M values, 79 -> 62 us; 128 channels, 3.2 M values, 15.9 -> 13.6 us.  With more
+    // tiles than SIMDs at four coefficient tiles the eight-wavefront form of k_project_quantize_rows stays: 50 us
+    // at 25.7 M values against 53 us for this kernel with four wavefronts and 48 to 58 us with eight, whose registers
+    // fit or spill with the compiler's schedule.  Planar: 128 channels, N = 256, 28 x 28 75 us in
+    // k_project_quantize_rows, 55.7 here; N = 32 16.7 and 11.7; 144 channels, N = 64, 28 x 28 42.9 in the tiled product,
+    // 26.1 here, with half of the basis truncated 28.1 and 23.8.)
+    r.stream = (r.nct == 5 || (r.nct == 4 && !eight)) && C % 16 == 0 && offsets_fit;
+    return r;
+}
+
 static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
                               int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
     RowParams p{};
@@ -967,24 +1002,10 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     p.pk = PackParams{};
     if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback)
         return hipErrorInvalidValue;  // (a field left out would be a wild pointer on the device)
-    const int nct = b.Cpad / 32;
-    // eight wavefronts on one copy of the basis where two four-wavefront workgroups (each with its own copy) do not
-    // fit a compute unit's LDS and there are tiles enough for them
-    // (measured at 128 channels, 25.7 M values: 67 us against 62 us with four wavefronts, one per SIMD -- the second
-    // wavefront's registers do not fit without spills -- so the eight-wavefront form stays off)
-    const bool vec0 = (b.C % 4) == 0;
-    // 128 channels: eight wavefronts on one copy of the basis, two per SIMD, each working tile by tile with one pair
-    // of accumulators (two four-wavefront workgroups with a copy each would not fit a compute unit's LDS).  Measured
-    // at 25.7 M values: 57 us against 63 us with four wavefronts, one per SIMD.  (The same form for 144 channels
-    // spills registers: 119 us against 80 us.)
-    // (planar tensors: the loads' addresses do not fit the registers either; 8 bits: eight wavefronts' histograms do
-    // not fit LDS beside the basis)
-    auto lds_for = [&](int wv) {
-        return sizeof(float) * (size_t)b.Cpad * b.Cpad + sizeof(uint32_t) * wv * kHistLanes * ((size_t)1 << bits);
-    };
-    const bool eight = nct == 4 && layout == FMTC_NHWC && p.n_tiles > 1024 && lds_for(8) <= 144 * 1024;
-    const int waves = eight ? 8 : 4;
-    const size_t lds = lds_for(waves);
+    const RowsPlan pl = plan_rows(b.C, P, HW, layout, bits);
+    const int nct = pl.nct, waves = pl.waves;
+    const bool eight = waves == 8, vec = pl.vec;
+    const size_t lds = rows_lds(nct, bits, waves);
     // workgroups a compute unit holds at once: by registers (rows_waves_per_simd) and by LDS
     const size_t lds_static = (size_t)waves * (2 * kFixList + 1 + 256) * 4 + (size_t)nct * 128 + 512;
     int per_cu = eight ? 1 : rows_waves_per_simd(nct, false, 4);
@@ -994,20 +1015,11 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     const int64_t cap = 256 * (int64_t)per_cu;
     if (gx > cap) gx = cap;
     *n_parts = (int)gx;
-    // planar: vec = a multiple of 16 channels and offsets within the images of a pixel tile that fit 32 bits
-    const bool vec = layout == FMTC_NHWC ? vec0 : b.C % 16 == 0 && planar_offsets_fit(b.C, P, HW);
     hipError_t el = hipSuccess;
-    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, four wavefronts.
-    // (Measured: 144 channels, 28.9 M values, 79 -> 62 us; 128 channels, 3.2 M values, 15.9 -> 13.6 us.  With more
-    // tiles than SIMDs at four coefficient tiles the eight-wavefront form of k_project_quantize_rows below stays: 50 us
-    // at 25.7 M values against 53 us for this kernel with four wavefronts and 48 to 58 us with eight, whose registers
-    // fit or spill with the compiler's schedule.  Planar: 128 channels, N = 256, 28 x 28 75 us in
-    // k_project_quantize_rows, 55.7 here; N = 32 16.7 and 11.7; 144 channels, N = 64, 28 x 28 42.9 in the tiled product,
-    // 26.1 here, with half of the basis truncated 28.1 and 23.8.)
-    if ((nct == 5 || (nct == 4 && !eight)) && (b.C % 16) == 0 && (layout == FMTC_NHWC || planar_offsets_fit(b.C, P, HW))) {
+    if (pl.stream) {
         const int swaves = 4;
         const bool whole = b.C == nct * 32;  // else 16 channels less
-        const size_t slds = lds_for(swaves);
+        const size_t slds = rows_lds(nct, bits, swaves);
         int64_t sgx = (p.n_tiles + swaves - 1) / swaves;
         if (sgx > 256) sgx = 256;  // one workgroup per compute unit (the basis takes 64 to 100 KB of its LDS)
         *n_parts = (int)sgx;
@@ -1746,6 +1758,22 @@ __global__ __launch_bounds__(256) void k_fill_symbol_columns(uint8_t* __restrict
         hist_row[threadIdx.x] = threadIdx.x == value ? (uint32_t)(P * (int64_t)(C - c0)) : 0u;
 }
 
+// Workgroups of the tiled product over pixel groups and coefficient groups (gy_all; gy of them are computed: the others' rows
+// of the basis are all zero), and whether those have eight wavefronts: while every tile has a compute unit of its own, four
+// (two workgroups per compute unit) beyond.
+struct GemmPlan {
+    int gy, gy_all;
+    bool eight;
+};
+static GemmPlan plan_gemm(int C, int64_t P, int active_rows) {
+    GemmPlan g{};
+    g.gy_all = ((C + 31) / 32 + 3) / 4;
+    g.gy = ((active_rows + 31) / 32 + 3) / 4;
+    g.gy = g.gy < 1 ? 1 : (g.gy > g.gy_all ? g.gy_all : g.gy);
+    g.eight = ((P + 31) / 32 + 3) / 4 * g.gy <= 256;
+    return g;
+}
+
 static hipError_t launch_gemm(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
                               int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
     const int ncs = b.Cpad / 32, NJ = b.Cpad / 16;
@@ -1777,9 +1805,8 @@ static hipError_t launch_gemm(const BasisDevice& b, const float* d_x, int64_t P,
         return hipErrorInvalidValue;
     // groups of four coefficient tiles; those whose rows of the basis are all zero (truncation) are not computed:
     // k_fill_symbol_columns writes their symbols and counts
-    const int gy_all = (ncs + 3) / 4;
-    int gy = ((b.active_rows + 31) / 32 + 3) / 4;
-    gy = gy < 1 ? 1 : (gy > gy_all ? gy_all : gy);
+    const GemmPlan pl = plan_gemm(b.C, P, b.active_rows);
+    const int gy_all = pl.gy_all, gy = pl.gy;
     int64_t gx = p.n_ptg;
     if (gx * gy_all > kMaxHistParts) gx = kMaxHistParts / gy_all;
     *n_parts = (int)(gx * gy) + (gy < gy_all ? 1 : 0);
@@ -1793,8 +1820,7 @@ static hipError_t launch_gemm(const BasisDevice& b, const float* d_x, int64_t P,
         hipError_t ef = hipGetLastError();
         if (ef != hipSuccess) return ef;
     }
-    // 8 wavefronts per tile while every tile has a compute unit of its own, 4 (two workgroups per compute unit) beyond
-    const bool eight = p.n_ptg * gy <= 256;
+    const bool eight = pl.eight;
     const int waves = eight ? 8 : 4;
     // histogram copies per wavefront: as many as 2 KB of LDS hold, 16 at most, 2 at least
     int copies = 512 >> bits;
@@ -1813,6 +1839,369 @@ static hipError_t launch_gemm(const BasisDevice& b, const float* d_x, int64_t P,
     if (ea != hipSuccess) return ea;
     return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NHWC>, grid, dim3(256), lds, s, p)
                                : launch(K_PROJECT, k_project_quantize_gemm4<FMTC_NCHW>, grid, dim3(256), lds, s, p);
+}
+
+// ---------------------------------------------------------------------------
+// Channel counts that are no multiple of 16, many pixels.  The contraction is the same f16 split as in the
+// narrow-tensor kernel above (three v_mfma_f32_32x32x16_f16 per 16 channels, see there), but a pixel's channels do
+// not fit a wavefront's registers: the workgroup (8 wavefronts) first brings a tile of 32 pixels, all channels,
+// into LDS -- coalesced global reads, mean removed and split into the two f16 parts on the way, rows padded by 16
+// bytes so that the 16-byte operand reads of 8 neighbouring pixels cover all banks -- then its wavefronts share out
+// the coefficient tiles of the workgroup's range [kt0, kt0 + ktg) without further barriers; the basis streams from
+// L2 in operand order one step ahead of its use.  Values too close to a rounding boundary are recomputed in fp64;
+// the quantized tile is staged in LDS and leaves as whole rows of symbols.
+// What bounds it: one workgroup per compute unit (LDS) from 480 channels on, so a tile's loads are not covered and a
+// last round of few workgroups costs as much as a full one.  Its gain over the split form below: no wavefront waits for
+// another one's exact decisions, and the pixels are read and converted once per 512 coefficients instead of once per 128.
+// (Which of the two is used: see wide_form_is_ahead.)
+// LAYOUT: FMTC_NHWC (C % 4 == 0: 16-byte loads of channels-last rows and 4-byte symbol stores are aligned) / FMTC_NCHW.
+// ---------------------------------------------------------------------------
+struct WideParams {
+    const float* x;
+    const uint16_t* basis16;  // fwd16 packing
+    const float* mu;          // [Cpad]
+    const float* Trow;        // [C][C] row major, for the exact decisions
+    int64_t P, HW;
+    int C, ncs, kt_per_group, bits;
+    float inv_delta, delta, kappa, tau_min;
+    int64_t px_tiles;
+    uint8_t* syms;
+    uint32_t* hist_parts;
+    CoderCtrl* ctrl;
+    unsigned long long* lookback;
+    uint32_t n_groups;
+};
+
+constexpr int kWideThreads = 512, kWidePixels = 32;
+
+// Workgroups of the kernel below for a tensor: the coefficient range is split over them only when the pixel tiles alone
+// leave compute units idle, and to bound the staging rows (16 tiles).
+struct WidePlan {
+    int ktg, kgroups;
+    int64_t px_tiles;
+    size_t lds;
+};
+static WidePlan plan_wide(int C, int64_t P) {
+    const int ncs = (C + 31) / 32;
+    WidePlan w{};
+    w.px_tiles = (P + kWidePixels - 1) / kWidePixels;
+    w.kgroups = (int)((256 + w.px_tiles - 1) / w.px_tiles);
+    w.ktg = (ncs + w.kgroups - 1) / w.kgroups;
+    if (w.ktg > 16) w.ktg = 16;
+    w.kgroups = (ncs + w.ktg - 1) / w.ktg;
+    w.lds = sizeof(_Float16) * 2 * (size_t)kWidePixels * (32 * ncs + 8) + sizeof(uint32_t) * (size_t)kWidePixels * (w.ktg * 8 + 1);
+    return w;
+}
+
+template <int LAYOUT>
+__global__ __launch_bounds__(kWideThreads) void k_project_quantize_wide(WideParams p) {
+    constexpr int PT = kWidePixels;
+    extern __shared__ __align__(16) uint8_t dyn_lds[];
+    __shared__ uint32_t lhist[256];
+    __shared__ float s_n2[PT];  // |x - mu|^2 of every pixel of the tile
+    zero_coder_scratch(p.ctrl, p.lookback, p.n_groups);
+
+    const int C = p.C, ncs = p.ncs;
+    const int Cpad = ncs * 32, NJ = ncs * 2;
+    const int RSH = Cpad + 8;  // pixel row stride in halves
+    const int kt0 = blockIdx.y * p.kt_per_group;
+    const int ktg = (ncs - kt0 < p.kt_per_group) ? ncs - kt0 : p.kt_per_group;
+    const int RSW = p.kt_per_group * 8 + 1;  // staging row stride in words
+    _Float16* xh = reinterpret_cast<_Float16*>(dyn_lds);
+    _Float16* xl = xh + (size_t)PT * RSH;
+    uint32_t* st = reinterpret_cast<uint32_t*>(xl + (size_t)PT * RSH);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+
+    if (tid < 256) lhist[tid] = 0u;
+    const int zero_sym = 1 << (p.bits - 1);
+    const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1);
+    const float inv_delta = p.inv_delta, inv_delta_lo = p.inv_delta * (1.f / 2048.f);
+
+    // the two f16 parts of one value (clamped to what f16 holds: a pixel with such a value is decided exactly)
+    auto split = [](float v, _Float16& vh, _Float16& vl) {
+        v = __builtin_amdgcn_fmed3f(v, -60000.f, 60000.f);
+        vh = (_Float16)v;
+        vl = (_Float16)((v - (float)vh) * 2048.f);
+    };
+
+    // the workgroup walks over pixel tiles; its histogram accumulates in LDS and leaves once at the end
+    for (int64_t tile = blockIdx.x; tile < p.px_tiles; tile += gridDim.x) {
+        const int64_t px0 = tile * PT;
+        if (tid < PT) s_n2[tid] = 0.f;
+        __syncthreads();  // also: the previous tile's staging rows have left
+
+        // ---- the pixel tile, mean removed, split, as xh / xl [pixel][channel] ----
+        if constexpr (LAYOUT == FMTC_NHWC) {
+            const int n4 = PT * (C / 4);  // the tile is one contiguous run of PT*C floats
+            const float* src = p.x + px0 * C;
+            const int64_t lim = (p.P - px0) * C;  // floats of the tile that exist
+            constexpr int B = 8;  // loads in flight per thread
+            for (int idx0 = tid; idx0 < n4; idx0 += B * kWideThreads) {
+                float4 v[B];
+#pragma unroll
+                for (int b = 0; b < B; b++) {
+                    const int f = 4 * (idx0 + b * kWideThreads);
+                    v[b] = (idx0 + b * kWideThreads < n4 && f < lim) ? *reinterpret_cast<const float4*>(src + f)
+                                                                     : make_float4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < B; b++) {
+                    const int idx = idx0 + b * kWideThreads;
+                    if (idx < n4) {
+                        const int f = 4 * idx;
+                        const int pxl = f / C, c = f - pxl * C;
+                        const float4 m = *reinterpret_cast<const float4*>(p.mu + c);
+                        const float d[4] = {v[b].x - m.x, v[b].y - m.y, v[b].z - m.z, v[b].w - m.w};
+                        halfx4 vh, vl;
+                        float n2 = 0.f;
+#pragma unroll
+                        for (int i = 0; i < 4; i++) {
+                            _Float16 a, bb;
+                            split(d[i], a, bb);
+                            vh[i] = a;
+                            vl[i] = bb;
+                            n2 = __builtin_fmaf(d[i], d[i], n2);
+                        }
+                        *reinterpret_cast<halfx4*>(xh + pxl * RSH + c) = vh;
+                        *reinterpret_cast<halfx4*>(xl + pxl * RSH + c) = vl;
+                        atomicAdd(&s_n2[pxl], n2);
+                    }
+                }
+            }
+        } else {
+            const int pxl = tid % PT;
+            const int64_t px = px0 + pxl;
+            const bool ok = px < p.P;
+            int64_t base = 0;
+            if (ok) {
+                const int64_t n = px / p.HW;
+                base = n * (int64_t)C * p.HW + (px - n * p.HW);
+            }
+            float n2 = 0.f;
+            for (int c = tid / PT; c < C; c += kWideThreads / PT) {
+                const float d = (ok ? p.x[base + (int64_t)c * p.HW] : 0.f) - p.mu[c];
+                _Float16 a, b;
+                split(d, a, b);
+                xh[pxl * RSH + c] = a;
+                xl[pxl * RSH + c] = b;
+                n2 = __builtin_fmaf(d, d, n2);
+            }
+            atomicAdd(&s_n2[pxl], n2);
+        }
+        if (Cpad > C) {  // padding channels meet zero basis entries; they must still be finite
+            const int padw = Cpad - C;
+            for (int idx = tid; idx < PT * padw; idx += kWideThreads) {
+                const int pxl = idx / padw, c = C + (idx - pxl * padw);
+                xh[pxl * RSH + c] = (_Float16)0.f;
+                xl[pxl * RSH + c] = (_Float16)0.f;
+            }
+        }
+        __syncthreads();
+
+        constexpr int PG = PT / 32;  // pixel groups per workgroup
+        const int nunits = ktg * PG;
+        for (int u = wave; u < nunits; u += kWideThreads / 64) {
+            const int pg = u % PG, ktl = u / PG;
+            const int kt = kt0 + ktl;
+            const int pxl = pg * 32 + l32;
+            const bool px_ok = px0 + pxl < p.P;
+            floatx16 am, ac;
+#pragma unroll
+            for (int r = 0; r < 16; r++) { am[r] = 0.f; ac[r] = 0.f; }
+
+            // (kt, j): the 64 lanes' hi parts, then their lo parts, 16 bytes per lane each; the basis comes from L2
+            // (the wavefronts of a round read the same part of it), one step ahead of its use
+            const uint4* asrc = reinterpret_cast<const uint4*>(p.basis16) + (size_t)kt * NJ * 2 * 64 + lane;
+            uint4 th4 = asrc[0], tl4 = asrc[64];
+            const _Float16* bh = xh + pxl * RSH + 8 * half;
+            const _Float16* bl = xl + pxl * RSH + 8 * half;
+            for (int jj = 0; jj < NJ; jj++) {
+                uint4 nh4 = th4, nl4 = tl4;
+                if (jj + 1 < NJ) {
+                    nh4 = asrc[(size_t)(2 * jj + 2) * 64];
+                    nl4 = asrc[(size_t)(2 * jj + 3) * 64];
+                }
+                const halfx8 th = __builtin_bit_cast(halfx8, th4), tl = __builtin_bit_cast(halfx8, tl4);
+                const halfx8 xh8 = *reinterpret_cast<const halfx8*>(bh + 16 * jj);
+                const halfx8 xl8 = *reinterpret_cast<const halfx8*>(bl + 16 * jj);
+                am = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, xh8, am, 0, 0, 0);
+                ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, xl8, ac, 0, 0, 0);
+                ac = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl, xh8, ac, 0, 0, 0);
+                th4 = nh4;
+                tl4 = nl4;
+            }
+
+            // ---- quantize ----
+            // accumulator r = 4g + i of lane (pixel, h) is coefficient kt*32 + 16h + 4g + i of the pixel
+            const float n2 = s_n2[pxl];
+            const bool force = !(n2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
+            const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
+            const float near_limit = force ? -1.f : 0.5f - tau;
+            const int k0 = kt * 32 + 16 * half;
+            uint32_t words[4];
+            uint32_t near_mask = 0;  // bit r: the fast value is too close to a rounding boundary to be trusted
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const float t = __builtin_fmaf(ac[4 * g + i], inv_delta_lo, am[4 * g + i] * inv_delta);
+                    float q = __builtin_rintf(t);  // round half to even
+                    const bool near = !(fabsf(t - q) <= near_limit);
+                    q = __builtin_amdgcn_fmed3f(q, lo, hi);
+                    word |= (uint32_t)((int)q + zero_sym) << (8 * i);
+                    if (near && px_ok && (k0 + 4 * g + i) < C) near_mask |= 1u << (4 * g + i);
+                }
+                words[g] = word;
+            }
+            // ---- exact decision for the flagged values: fp64 recomputation, four values per round ----
+            // (same arithmetic as the definition: sum of T[k][c] * (x[c] - mu[c]), divided by the step).
+            // Each 16-lane group of the wavefront takes one flagged value, so the loads of four values overlap.
+            unsigned long long pending = __ballot(near_mask != 0);
+            while (pending) {
+                int Ls[4];
+                unsigned long long pm = pending;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    Ls[q] = pm ? (__ffsll((long long)pm) - 1) : -1;
+                    pm &= pm - 1;
+                }
+                const int grp = lane >> 4;
+                const int Lq = grp == 0 ? Ls[0] : (grp == 1 ? Ls[1] : (grp == 2 ? Ls[2] : Ls[3]));
+                const bool active = Lq >= 0;
+                const uint32_t fm = (uint32_t)__shfl((int)near_mask, active ? Lq : 0, 64);
+                const int r = active ? (__ffs((int)fm) - 1) : 0;
+                const int k = kt * 32 + 16 * (Lq >> 5) + r;
+                const int64_t px = px0 + pg * 32 + (Lq & 31);
+                double part = 0.0;
+                if (active) {
+                    int64_t xbase, xstride;
+                    if constexpr (LAYOUT == FMTC_NHWC) {
+                        xbase = px * C;
+                        xstride = 1;
+                    } else {
+                        const int64_t n = px / p.HW;
+                        xbase = n * (int64_t)C * p.HW + (px - n * p.HW);
+                        xstride = p.HW;
+                    }
+#pragma unroll 8  // independent loads of eight terms in flight together: the loop is all latency
+                    for (int c = lane & 15; c < C; c += 16)
+                        part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)p.mu[c]);
+                }
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the 16-lane group
+                double qd = rint(part / (double)p.delta);
+                qd = fmin(fmax(qd, (double)lo), (double)hi);
+                const int sfix = (int)qd + zero_sym;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const int rq = __shfl(r, 16 * q, 64);
+                    const int sq = __shfl(sfix, 16 * q, 64);
+                    if (lane == Ls[q]) {
+#pragma unroll
+                        for (int g = 0; g < 4; g++)
+                            if (g == (rq >> 2))
+                                words[g] = (words[g] & ~(0xffu << (8 * (rq & 3)))) | ((uint32_t)sq << (8 * (rq & 3)));
+                        near_mask &= ~(1u << rq);
+                    }
+                }
+                pending = __ballot(near_mask != 0);
+            }
+            // ---- count and stage ----
+            // zero-level symbols (the bulk) are counted with byte arithmetic, the others with LDS atomics
+            uint32_t zero_count = 0;
+            const uint32_t zero4 = (uint32_t)zero_sym * 0x01010101u;
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const int k = k0 + 4 * g;
+                const uint32_t word = words[g];
+                // 0x80 in every byte of the word that is a valid coefficient
+                const int nvalid = !px_ok ? 0 : (C - k >= 4 ? 4 : (C - k > 0 ? C - k : 0));
+                const uint32_t vmask = nvalid == 4 ? 0x80808080u : (0x80808080u >> (8 * (4 - nvalid))) * (nvalid != 0);
+                const uint32_t xz = word ^ zero4;
+                uint32_t t = (xz & 0x7f7f7f7fu) + 0x7f7f7f7fu;
+                t = ~(t | xz | 0x7f7f7f7fu);  // 0x80 where the byte equals the zero level
+                zero_count += (uint32_t)__popc(t & vmask);
+                uint32_t nz = ~t & vmask;
+                while (nz) {
+                    const int bit = __ffs((int)nz) - 1;  // 8*i + 7
+                    atomicAdd(&lhist[(word >> (bit - 7)) & 255u], 1u);
+                    nz &= nz - 1;
+                }
+                st[pxl * RSW + ktl * 8 + 4 * half + g] = word;
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) zero_count += __shfl_xor(zero_count, o, 64);
+            if (lane == 0 && zero_count) atomicAdd(&lhist[zero_sym], zero_count);
+        }
+        __syncthreads();
+
+        // ---- symbols leave as rows of ktg*32 bytes per pixel ----
+        const int kbase = kt0 * 32;
+        const int row_words = ktg * 8;
+        for (int idx = tid; idx < PT * row_words; idx += kWideThreads) {
+            const int row = idx / row_words, col = idx - row * row_words;
+            const int64_t px = px0 + row;
+            const int k = kbase + 4 * col;
+            if (px < p.P && k < C) {
+                const uint32_t word = st[row * RSW + col];
+                uint8_t* dst = p.syms + px * C + k;
+                if constexpr (LAYOUT == FMTC_NHWC) {
+                    *reinterpret_cast<uint32_t*>(dst) = word;
+                } else {
+                    for (int i = 0; i < 4 && k + i < C; i++) dst[i] = (uint8_t)(word >> (8 * i));
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // one row of partial counts per workgroup: nothing to clear beforehand, no global atomics
+    const int K = 1 << p.bits;
+    if (tid < K) p.hist_parts[(size_t)(blockIdx.x + blockIdx.y * gridDim.x) * K + tid] = lhist[tid];
+}
+
+static hipError_t launch_wide(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
+                              int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s) {
+    WideParams p{};
+    p.x = d_x;
+    p.basis16 = b.fwd16;
+    p.mu = b.mu;
+    p.Trow = b.T;
+    p.P = P;
+    p.HW = HW;
+    p.C = b.C;
+    p.ncs = b.Cpad / 32;
+    p.bits = bits;
+    p.inv_delta = (float)(1.0 / (double)delta);
+    p.delta = delta;
+    // see launch_rows for the bound behind these two
+    p.kappa = 1.9073486e-6f /* 2^-19 */ * b.row_norm * p.inv_delta;
+    p.tau_min = 4.7683716e-7f /* 2^-21 */ * (float)(1 << (bits - 1));
+    p.syms = d_syms;
+    p.hist_parts = cs.hist_parts;
+    p.ctrl = cs.ctrl;
+    p.lookback = cs.lookback;
+    p.n_groups = cs.n_groups;
+    if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback ||
+        (layout == FMTC_NHWC && b.C % 4 != 0))
+        return hipErrorInvalidValue;  // (a field left out would be a wild pointer on the device)
+    const WidePlan pl = plan_wide(b.C, P);
+    p.kt_per_group = pl.ktg;
+    p.px_tiles = pl.px_tiles;
+    int64_t gx = p.px_tiles;
+    if (gx * pl.kgroups > kMaxHistParts) gx = kMaxHistParts / pl.kgroups;
+    const dim3 grid((unsigned)gx, (unsigned)pl.kgroups);
+    *n_parts = (int)(gx * pl.kgroups);
+    const void* fn = layout == FMTC_NHWC ? reinterpret_cast<const void*>(&k_project_quantize_wide<FMTC_NHWC>)
+                                         : reinterpret_cast<const void*>(&k_project_quantize_wide<FMTC_NCHW>);
+    hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds);
+    if (ea != hipSuccess) return ea;
+    return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_wide<FMTC_NHWC>, grid, dim3(kWideThreads), pl.lds, s, p)
+                               : launch(K_PROJECT, k_project_quantize_wide<FMTC_NCHW>, grid, dim3(kWideThreads), pl.lds, s, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -2182,39 +2571,105 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
                                : launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>, grid, dim3(64 * W), lds, s, p);
 }
 
+// Which of the forms above projects a tensor.
+struct ProjectionForm {
+    enum Kernel { kRows, kGemm, kWide, kSplit } kernel;
+    int px_tiles, coef_tiles;  // kSplit: of a workgroup
+    bool skip_zero_rows;       // kSplit
+};
+
+// Channel counts that are no multiple of 16, more than 128 channels: whether the workgroups with all channels in LDS
+// (k_project_quantize_wide) are ahead of the split form.  us, theirs : split, at 4 / 6 / 8 bits:
+//   - Two of them share a compute unit up to 448 channels, and 12000 to 16320 pixels are one round of 376 to 510: planar
+//     185 channels, 16000 pixels 21.3 : 27.4 / 22.7 : 28.9 / 24.3 : 30.8; 265, 12800 31 : 39 / 33 : 41 / 36 : 45; channels last,
+//     404, 16000 46 : 54 / 55 : 66 / 59 : 73.
+//   - Beyond that one per compute unit, and a round costs the same however many are in it.  One full round: 1000 channels,
+//     channels last, 4096 pixels 59 : 78 (3 bits) / 70 : 96 / 72 : 145; planar 510, 8192 31 : 53 / 38 : 60 / 44 : 76.
+//   - With the bits more values are close to a rounding boundary, and in the split form three wavefronts wait while one
+//     decides its own exactly, so rounds less full are worth it: channels last, 1000, 20000 (1250 workgroups in five rounds)
+//     305 : 369 at 6 bits, 6496 (406 in two) 132 : 161 at 7, 14000 260 : 369 and 1024 48 : 67 at 8; but 5184 (324 in two) 125 : 115
+//     at 6; 900, 5728 (358 in two) 112 : 104 at 6, 121 : 130 at 8.
+//   - From 17 to 22 coefficient tiles the second workgroup of a pixel tile is given one to six of them: 580, 18496 147 : 115
+//     at 6 bits, 644, 13696 132 : 151 at 7; planar, where the pixels' loads take longer, 570, 11552 113 : 94 at 6, 153 : 133 at 8.
+// (Planar channel counts that are a multiple of 4 are slower there in every case: 500, 17984 150 : 115, 1000, 8992 316 : 198;
+// channels last, others are: 333, 26176 145 : 78, 1001, 8992 303 : 195; 300, 28800, of a shorter contraction, 106 : 77.)
+static bool wide_form_is_ahead(int C, int64_t P, int layout, int bits) {
+    if ((layout == FMTC_NHWC) != (C % 4 == 0)) return false;
+    const int ncs = (C + 31) / 32;
+    const bool nhwc = layout == FMTC_NHWC;
+    if (P > 12000 && P <= 16320 && ncs <= 16 && (ncs >= 13 || !nhwc)) return true;
+    const WidePlan w = plan_wide(C, P);
+    if (ncs < 15 || w.px_tiles * ncs <= (bits <= 7 ? 3500 : 640)) return false;
+    if (nhwc && bits <= 6 && ncs > 16 && ncs < 23) return false;
+    // percent of the rounds' workgroups (planar: of their coefficient tiles) that there are
+    const int64_t slots = (w.px_tiles * w.kgroups + 255) / 256 * 256;
+    const int64_t share = nhwc ? 100 * w.px_tiles * w.kgroups / slots : 100 * w.px_tiles * ncs / (slots * w.ktg);
+    if (bits <= 5) return slots == 256 && share >= 97;
+    return share >= (bits == 6 ? (nhwc ? 80 : 95) : bits == 7 ? (nhwc ? 75 : 85) : (nhwc ? 70 : 75));
+}
+
+static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout, int bits) {
+    const int ncs = (C + 31) / 32;
+    // 160 padded channels still fit the one-wavefront-per-32-pixels kernels (not at 8 bits, where the histograms find no room
+    // in LDS beside the basis: 100 + 64 KB); for planar tensors only the streaming form, with 32-bit offsets and whole groups
+    // of 16 channels
+    const bool fits160 = ncs == 5 && bits < 8 && (layout == FMTC_NHWC || (C % 16 == 0 && planar_offsets_fit(C, P, HW)));
+    const bool narrow = ncs <= 4 || fits160, whole16 = C % 16 == 0;
+    const int64_t tiles = (P + 31) / 32 * ncs;  // of 32 pixels x 32 coefficients
+    auto split = [&](int pt, int kt) { return ProjectionForm{ProjectionForm::kSplit, pt, kt, !narrow && whole16}; };
+    const ProjectionForm rows{ProjectionForm::kRows, 0, 0, false}, gemm{ProjectionForm::kGemm, 0, 0, false};
+    // Up to 32 channels the narrow kernel has no contraction to split (5.4 to 6.4 us against 6.0 at 16 and 32 channels).
+    if (ncs == 1) return rows;
+    // The split contraction's tile grows with their number.  One or two coefficient tiles per workgroup while that leaves
+    // compute units idle otherwise (us, 1 : 2 : 4 of them: 512 channels, 64 tiles 10.5 : 11.2 : 12.8; 768 channels, 312 tiles
+    // 17.3 : 14.6 : 17.2; 512 channels, 720 tiles 21.5 : 16.9 : 15.0).
+    if (tiles <= 256) return split(1, 1);
+    if (tiles <= 640 || (tiles <= 1024 && ncs == 2)) return split(1, 2);
+    // Four of them, or two by two where the last four would be half empty (five and six coefficient tiles; us, 1 x 4 : 2 x 2:
+    // 144 channels, 1300 tiles 15.5 : 11, 129, 6500 57 : 45, 161, 9000 67 : 59, 20000 133 : 109; but 200 channels, 9000 tiles
+    // 54 : 60, 300 66 : 74, 500 100 : 117, 1000 182 : 198):
+    const ProjectionForm large = tiles > 1200 && (ncs == 5 || ncs == 6) ? split(2, 2) : split(1, 4);
+    // up to 1024 tiles instead of the narrow kernels (us, theirs first: 96 channels, 999 tiles 11.9 : 8.4; 128 10.9 : 8.5; 160
+    // 13.8 : 10.4; at 144 channels and 2330 tiles 13.9 : 17.8), and of 97 to 127 channels that are no multiple of 16, which
+    // those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 12800 57.2 : 55.6);
+    if (narrow) return tiles <= (ncs == 4 && !whole16 ? 16384 : 1024) ? large : rows;
+    // instead of the tiled product, whose steps are a chain of barriers, up to 1536 tiles (512, 1456 25.6 : 23.1; 256, 1600 16.9 :
+    // 12.6; 1024, 1568 43.5 : 46.6; 512, 2304 26.8 : 33.4), up to 4096 where it fetches planar pixels four bytes at a time
+    // (512, 2304 46.3 : 31.6; 960, 2940 88 : 63; 256, 4096 28.0 : 24.8; 384, 4464 39.7 : 38.5, 192, 9900 45 : 51);
+    if (whole16) return tiles <= (layout == FMTC_NHWC ? 1536 : 4096) ? large : gemm;
+    // the tiled product needs whole groups of 16 channels.
+    return tiles > 640 && wide_form_is_ahead(C, P, layout, bits) ? ProjectionForm{ProjectionForm::kWide, 0, 0, false} : large;
+}
+
+// The same in words, for tests: "rows 2 vec", "stream 5 half", "gemm8 fill", "split 1x4", ... and the layout.
+int describe_projection(int C, int64_t P, int64_t HW, int layout, int bits, int active_rows, char* text, size_t size) {
+    const ProjectionForm f = choose_projection(C, P, HW, layout, bits);
+    const char* lay = layout == FMTC_NHWC ? "nhwc" : "nchw";
+    if (f.kernel == ProjectionForm::kRows) {
+        const RowsPlan r = plan_rows(C, P, HW, layout, bits);
+        if (r.stream) return snprintf(text, size, "stream %d%s %s", r.nct, C == 32 * r.nct ? "" : " half", lay);
+        return snprintf(text, size, "rows %d%s%s %s", r.nct, r.waves == 8 ? "x8" : "", r.vec ? " vec" : "", lay);
+    }
+    if (f.kernel == ProjectionForm::kGemm) {
+        const GemmPlan g = plan_gemm(C, P, active_rows);
+        return snprintf(text, size, "gemm%d%s %s", g.eight ? 8 : 4, g.gy < g.gy_all ? " fill" : "", lay);
+    }
+    if (f.kernel == ProjectionForm::kWide) return snprintf(text, size, "wide %s", lay);
+    return snprintf(text, size, "split %dx%d %s", f.px_tiles, f.coef_tiles, lay);
+}
+
 hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64_t N, int64_t HW, int layout,
                                    float delta, int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts,
                                    hipStream_t s) {
     const int64_t P = N * HW;
-    // 160 padded channels still fit the one-wavefront-per-32-pixels kernels (not at 8 bits, where the histograms find no room
-    // in LDS beside the basis: 100 + 64 KB); for planar tensors only the streaming form, with 32-bit offsets and whole groups
-    // of 16 channels
-    const bool fits160 = b.Cpad == 160 && bits < 8 && (layout == FMTC_NHWC || (b.C % 16 == 0 && planar_offsets_fit(b.C, P, HW)));
-    const bool narrow = b.Cpad <= 128 || fits160, whole16 = b.C % 16 == 0;
-    const int ncs = b.Cpad / 32;
-    const int64_t tiles = (P + 31) / 32 * ncs;  // of 32 pixels x 32 coefficients
-    // Up to 32 channels the narrow kernel has no contraction to split (5.4 to 6.4 us against 6.0 at 16 and 32 channels).
-    if (narrow && ncs == 1) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    const bool skip = !narrow && whole16;
-    // The split contraction's tile grows with their number.  One or two coefficient tiles per workgroup while that leaves
-    // compute units idle otherwise (us, 1 : 2 : 4 of them: 512 channels, 64 tiles 10.5 : 11.2 : 12.8; 768 channels, 312 tiles
-    // 17.3 : 14.6 : 17.2; 512 channels, 720 tiles 21.5 : 16.9 : 15.0).
-    if (tiles <= 256) return launch_split<1, 1, 4, 4, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
-    if (tiles <= 640 || (tiles <= 1024 && ncs == 2))
-        return launch_split<1, 2, 4, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
-    // Four of them: up to 1024 tiles instead of the narrow kernels (us, theirs first: 96 channels, 999 tiles 11.9 : 8.4; 128
-    // 10.9 : 8.5; 160 13.8 : 10.4; at 144 channels and 2330 tiles 13.9 : 17.8), and of 100 to 127 channels that are no multiple
-    // of 16, which those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 12800 57.2 : 55.6); instead
-    // of the tiled product, whose steps are a chain of barriers, up to 1536 tiles (512, 1456 25.6 : 23.1; 256, 1600 16.9 :
-    // 12.6; 1024, 1568 43.5 : 46.6; 512, 2304 26.8 : 33.4), up to 4096 where it fetches planar pixels four bytes at a time
-    // (512, 2304 46.3 : 31.6; 960, 2940 88 : 63; 256, 4096 28.0 : 24.8; 384, 4464 39.7 : 38.5, 192, 9900 45 : 51).
-    const int64_t four = narrow ? (ncs == 4 && !whole16 ? 16384 : 1024) : (whole16 && layout == FMTC_NHWC ? 1536 : 4096);
-    if (tiles <= four) return launch_split<1, 4, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
-    if (narrow) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    // The tiled product needs whole groups of 16 channels.  Other channel counts take two by two tiles (us, 1 x 4 : 2 x 2:
-    // 169 channels, 10800 tiles 77 : 65; 180, 19200 99 : 83; 300, 7520 60.5 : 58.8; 1001, 3136 80 : 80).
-    if (whole16) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    return launch_split<2, 2, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, skip);
+    const ProjectionForm f = choose_projection(b.C, P, HW, layout, bits);
+    if (f.kernel == ProjectionForm::kRows) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (f.kernel == ProjectionForm::kGemm) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (f.kernel == ProjectionForm::kWide) return launch_wide(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
+    if (f.px_tiles == 2) return launch_split<2, 2, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    if (f.coef_tiles == 4) return launch_split<1, 4, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    if (f.coef_tiles == 2) return launch_split<1, 2, 4, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    return launch_split<1, 1, 4, 4, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
 }
 
 // Histogram of given symbols (staged coder entry point): one row of partial counts per workgroup.

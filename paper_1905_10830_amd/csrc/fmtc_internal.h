@@ -190,6 +190,7 @@ __device__ __forceinline__ void zero_coder_scratch(CoderCtrl* ctrl, unsigned lon
 }
 
 // ---- kernel launchers (definitions in the *_kernels.hip files) ----
+int describe_projection(int C, int64_t P, int64_t HW, int layout, int bits, int active_rows, char* text, size_t size);
 hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64_t N, int64_t HW, int layout,
                                    float delta, int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts,
                                    hipStream_t s);

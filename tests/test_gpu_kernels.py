@@ -397,6 +397,23 @@ def test_split_projection(fmtc, oracle, C, P, bits, layout):
     check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
 
 
+# Channel counts that are no multiple of 16, a workgroup's pixels with all channels in LDS: one and many coefficient groups,
+# a group of fewer tiles than wavefronts, ragged last pixel and coefficient tiles, more pixel tiles than workgroups.
+WIDE_FORM_CASES = [(1000, 1021, 8, "nhwc"), (452, 12001, 6, "nhwc"), (516, 16500, 8, "nhwc"), (1020, 4090, 3, "nhwc"), (129, 12001, 5, "nchw"),
+                   (1001, 1021, 8, "nchw"), (250, 16320, 2, "nchw"), (502, 8161, 6, "nchw"), (510, 32800, 8, "nchw")]
+
+
+@pytest.mark.parametrize("C,P,bits,layout", WIDE_FORM_CASES, ids=[f"C{c[0]}P{c[1]}b{c[2]}{c[3]}" for c in WIDE_FORM_CASES])
+def test_projection_with_all_channels_in_lds(fmtc, oracle, C, P, bits, layout):
+    from paper_1905_10830_amd import synth
+
+    tag = synth.NHWC if layout == "nhwc" else synth.NCHW
+    H = next(h for h in (10, 7, 5, 3, 2, 1) if P % h == 0)
+    shape = (1, H, P // H, C) if layout == "nhwc" else (1, C, H, P // H)
+    assert fmtc.test_projection(shape, tag, bits) == "wide " + layout
+    check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
+
+
 # Planar projection of up to 160 channels: even and odd numbers of 32-channel pairs with and without a half step, tiles
 # across one and many images, ragged last tiles, fewer and more tiles than wavefronts; 8 bits (five coefficient tiles: the
 # tiled kernel, for LDS); a channel count that is no multiple of 16.
