@@ -2224,8 +2224,9 @@ struct SplitParams {
     const float* Trow;
     int64_t P, HW, n_pg;   // groups of 32 PT pixels
     int C, ncs, NJ, bits;
-    int active_kt;         // coefficient tiles from here on are left out: their rows of the basis are all zero
-    int n_kg, n_kg_pad;    // groups of KT coefficient tiles; as block indices
+    int n_kg;              // groups of KT coefficient tiles
+    int n_kc, n_kc_pad;    // those that are computed (the others' rows of the basis are all zero); as block indices
+    uint32_t computed_blocks;  // the blocks of the others follow
     int hist_shift;
     float inv_delta, delta, kappa, tau_min;
     uint8_t* syms;
@@ -2254,12 +2255,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(E, E))) 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int C = p.C, NJ = p.NJ, K = 1 << p.bits, HS = p.hist_shift, HC = 1 << HS;
-    const int kg = (int)(blockIdx.x % (unsigned)p.n_kg_pad);
-    if (kg >= p.n_kg) return;
-    const int64_t pg0 = blockIdx.x / (unsigned)p.n_kg_pad, pg_step = gridDim.x / (unsigned)p.n_kg_pad;
+    const bool computed = blockIdx.x < p.computed_blocks;
+    const uint32_t block = computed ? blockIdx.x : blockIdx.x - p.computed_blocks;
+    const uint32_t per_pg = (uint32_t)(computed ? p.n_kc_pad : p.n_kg - p.n_kc);
+    const int kg = (int)(block % per_pg) + (computed ? 0 : p.n_kc);
+    if (computed && kg >= p.n_kc) return;
+    const int64_t pg0 = block / per_pg, pg_step = p.computed_blocks / (unsigned)p.n_kc_pad;
     const int kt0 = kg * KT;
     // this wavefront's steps (none where the basis' rows are all zero: every sum is then exactly zero)
-    const bool computed = kt0 < p.active_kt;
     const int s_begin = computed ? wave * NJ / W : 0, s_end = computed ? (wave + 1) * NJ / W : 0;
 
     const uint4* a_src[KT];
@@ -2534,14 +2537,17 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
     p.bits = bits;
     p.n_pg = (P + 32 * PT - 1) / (32 * PT);
     p.n_kg = (p.ncs + KT - 1) / KT;
-    // (a block beyond the last coefficient group ends at once)
-    const int padded = (p.n_kg + 7) / 8 * 8;
-    p.n_kg_pad = 4 * (padded - p.n_kg) <= p.n_kg ? padded : p.n_kg;
     // Groups of four coefficient tiles whose rows of the basis are all zero (truncation) are not computed where the tiled
     // product leaves them out too.  The narrow kernels decide every coefficient of a pixel beyond f16 exactly, those of
     // zero rows too, and what a pixel that is not finite gives there must not depend on the tensor's size.
-    p.active_kt = skip_zero_rows ? (b.active_rows + 127) / 128 * 4 : p.ncs;
-    if (p.active_kt < 4) p.active_kt = 4;
+    static_assert(4 % KT == 0, "whole groups are left out");
+    p.n_kc = skip_zero_rows ? (b.active_rows + 127) / 128 * (4 / KT) : p.n_kg;
+    p.n_kc = p.n_kc < 4 / KT ? 4 / KT : p.n_kc;
+    p.n_kc = p.n_kc > p.n_kg ? p.n_kg : p.n_kc;
+    // (a block beyond the last group ends at once.  The groups that are not computed have blocks of their own behind the
+    // others: in one order with them they would be whole dies' share.)
+    const int padded = (p.n_kc + 7) / 8 * 8;
+    p.n_kc_pad = 4 * (padded - p.n_kc) <= p.n_kc ? padded : p.n_kc;
     p.inv_delta = (float)(1.0 / (double)delta);
     p.delta = delta;
     // see launch_rows for the bound behind these two (the W partial sums and the two roundings after them add at most
@@ -2566,7 +2572,8 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
                                          : reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>);
     hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (ea != hipSuccess) return ea;
-    const dim3 grid((unsigned)(gx * p.n_kg_pad));
+    p.computed_blocks = (uint32_t)(gx * p.n_kc_pad);
+    const dim3 grid(p.computed_blocks + (uint32_t)(gx * (p.n_kg - p.n_kc)));
     return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NHWC>, grid, dim3(64 * W), lds, s, p)
                                : launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>, grid, dim3(64 * W), lds, s, p);
 }
