@@ -2615,7 +2615,7 @@ static bool wide_form_is_ahead(int C, int64_t P, int layout, int bits) {
     return share >= (bits == 6 ? (nhwc ? 80 : 95) : bits == 7 ? (nhwc ? 75 : 85) : (nhwc ? 70 : 75));
 }
 
-static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout, int bits) {
+static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout, int bits, int active_rows) {
     const int ncs = (C + 31) / 32;
     // 160 padded channels still fit the one-wavefront-per-32-pixels kernels (not at 8 bits, where the histograms find no room
     // in LDS beside the basis: 100 + 64 KB); for planar tensors only the streaming form, with 32-bit offsets and whole groups
@@ -2640,17 +2640,27 @@ static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout
     // 13.8 : 10.4; at 144 channels and 2330 tiles 13.9 : 17.8), and of 97 to 127 channels that are no multiple of 16, which
     // those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 12800 57.2 : 55.6);
     if (narrow) return tiles <= (ncs == 4 && !whole16 ? 16384 : 1024) ? large : rows;
-    // instead of the tiled product, whose steps are a chain of barriers, up to 1536 tiles (512, 1456 25.6 : 23.1; 256, 1600 16.9 :
-    // 12.6; 1024, 1568 43.5 : 46.6; 512, 2304 26.8 : 33.4), up to 4096 where it fetches planar pixels four bytes at a time
-    // (512, 2304 46.3 : 31.6; 960, 2940 88 : 63; 256, 4096 28.0 : 24.8; 384, 4464 39.7 : 38.5, 192, 9900 45 : 51);
-    if (whole16) return tiles <= (layout == FMTC_NHWC ? 1536 : 4096) ? large : gemm;
+    // instead of the tiled product, whose steps are a chain of barriers: channels last up to 1536 tiles (us, theirs first: 512
+    // channels, 1456 25.6 : 23.1; 256, 1600 16.9 : 12.6; 512, 2304 26.8 : 33.4), but from 544 channels on, whose exact decisions are
+    // what a workgroup of the split form ends with, up to 1024 at 6 and 7 bits (1024 channels, 1024 tiles 42 : 40, 1184 42 : 50; 768,
+    // 1200 33 : 35; 640, 1200 28 : 32) and up to 800 at 8 (640, 900 32 : 37; 960, 1024 46 : 51; 896, 784 42 : 38).  Planar pixels are
+    // fetched four bytes at a time there: up to 4096 tiles from 512 channels on (512, 3888 64 : 50; 768, 3888 96 : 73; 1024,
+    // 4096 109 : 83), up to 3840 at 256, 384 and from 448 on (256, 3800 25 : 23, 4096 24 : 27; 448, 3290 40 : 33), up to 2800
+    // otherwise (192, 2598 22 : 21, 4092 25 : 29; 288, 2898 31 : 29, 3798 34 : 37; 400, 3497 35 : 37).  Both forms leave groups of
+    // zero rows out, and the closer lines count the other tiles only (768 channels of which 307 are kept, channels last, 1008
+    // tiles, 504 of them computed, 8 bits 37 : 25).
+    const int64_t computed = tiles / ncs * (active_rows >= C ? ncs : (active_rows + 127) / 128 * 4);
+    const int64_t nhwc_most = ncs <= 16 || bits <= 5 ? 1536 : (bits <= 7 ? 1024 : 800);
+    const int64_t nchw_most = ncs >= 16 ? 4096 : (ncs % 4 == 0 || ncs > 13 ? 3840 : 2800);
+    if (whole16)
+        return (layout == FMTC_NHWC ? tiles <= 1536 && computed <= nhwc_most : tiles <= 4096 && computed <= nchw_most) ? large : gemm;
     // the tiled product needs whole groups of 16 channels.
     return tiles > 640 && wide_form_is_ahead(C, P, layout, bits) ? ProjectionForm{ProjectionForm::kWide, 0, 0, false} : large;
 }
 
 // The same in words, for tests: "rows 2 vec", "stream 5 half", "gemm8 fill", "split 1x4", ... and the layout.
 int describe_projection(int C, int64_t P, int64_t HW, int layout, int bits, int active_rows, char* text, size_t size) {
-    const ProjectionForm f = choose_projection(C, P, HW, layout, bits);
+    const ProjectionForm f = choose_projection(C, P, HW, layout, bits, active_rows);
     const char* lay = layout == FMTC_NHWC ? "nhwc" : "nchw";
     if (f.kernel == ProjectionForm::kRows) {
         const RowsPlan r = plan_rows(C, P, HW, layout, bits);
@@ -2669,7 +2679,7 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
                                    float delta, int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts,
                                    hipStream_t s) {
     const int64_t P = N * HW;
-    const ProjectionForm f = choose_projection(b.C, P, HW, layout, bits);
+    const ProjectionForm f = choose_projection(b.C, P, HW, layout, bits, b.active_rows);
     if (f.kernel == ProjectionForm::kRows) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     if (f.kernel == ProjectionForm::kGemm) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     if (f.kernel == ProjectionForm::kWide) return launch_wide(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);

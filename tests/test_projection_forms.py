@@ -37,6 +37,25 @@ def test_channel_counts_that_are_no_multiple_of_16(C, P, layout, bits, want, ahe
     assert form(C, P, layout, bits) == want, f"{ahead} us, {behind} in the other form"
 
 
+@pytest.mark.parametrize("C,tiles,layout,bits,want,ahead,behind", [
+    (512, 1456, NHWC, 6, "split 1x4", 23, 26), (512, 2304, NHWC, 6, "gemm8", 27, 33), (768, 1200, NHWC, 6, "gemm8", 33, 35),
+    (1024, 1184, NHWC, 6, "gemm8", 42, 50), (1024, 1024, NHWC, 6, "split 1x4", 40, 42), (1024, 1024, NHWC, 8, "gemm8", 46, 51),
+    (640, 1200, NHWC, 3, "split 1x4", 23, 28), (640, 900, NHWC, 8, "gemm8", 32, 37), (896, 784, NHWC, 8, "split 1x4", 38, 42),
+    (144, 1535, NHWC, 8, "split 2x2", 12, 14), (192, 4092, NCHW, 6, "gemm4", 25, 29), (192, 2598, NCHW, 6, "split 2x2", 21, 22),
+    (256, 4096, NCHW, 6, "gemm8", 24, 27), (256, 3800, NCHW, 6, "split 1x4", 23, 25), (400, 3497, NCHW, 6, "gemm4", 35, 37),
+    (512, 3888, NCHW, 7, "split 1x4", 50, 64), (448, 3290, NCHW, 4, "split 1x4", 33, 40), (144, 4095, NCHW, 8, "gemm4", 27, 33), (640, 4080, NCHW, 6, "split 1x4", 70, 76),
+])
+def test_wide_tensors_of_whole_16_channels(C, tiles, layout, bits, want, ahead, behind):
+    assert form(C, 32 * (tiles // -(-C // 32)), layout, bits) == want, f"{ahead} us, {behind} in the other form"
+
+
+def test_truncated_wide_tensors():
+    assert form(768, 1344, NHWC, 8, 307) == "split 1x4"  # 25 us, 37 in the other form
+    assert form(768, 1344, NHWC, 8, 700) == "gemm8"
+    assert form(768, 4800, NCHW, 6, 40) == "split 1x4"
+    assert form(512, 3200, NHWC, 6, 130) == "gemm8 fill"
+
+
 def test_arguments():
     for shape in ((0, 1, 1, 64), (1, 1, 1, 1025)):
         with pytest.raises(fmtc.FmtcError):
