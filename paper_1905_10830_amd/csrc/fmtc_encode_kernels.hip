@@ -2520,6 +2520,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(E, E))) 
     }
 }
 
+// Workgroups per coefficient group: one row of counts each.  Up to 256 channels no more workgroups than run at once (two per
+// compute unit): what adds up their rows is one workgroup (97 channels, 20800 pixels, 8 bits 20.6 us and 42.2 after it with 1024
+// rows, 18.6 and 40.5 with 512).  The longer contraction of wider tensors leaves too much of a second round idle (1001
+// channels, planar, 6496 pixels, 8 bits 200 us with 1024, 227 with 512).
+static int64_t split_px_workgroups(int ncs, int n_kg, int64_t n_pg) {
+    const int most = ncs <= 8 ? 512 : kMaxHistParts;
+    return n_pg * n_kg > most ? most / n_kg : n_pg;
+}
+
 template <int PT, int KT, int W, int D, int E>
 static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
                                int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s,
@@ -2562,8 +2571,7 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
     // every pointer the kernel follows is set (a field left out here would be a wild pointer on the device)
     if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback)
         return hipErrorInvalidValue;
-    int64_t gx = p.n_pg;
-    if (gx * p.n_kg > kMaxHistParts) gx = kMaxHistParts / p.n_kg;
+    const int64_t gx = split_px_workgroups(p.ncs, p.n_kg, p.n_pg);
     *n_parts = (int)(gx * p.n_kg);
     // histogram copies: 8 KB at most, so that two workgroups with 64 KB of partial sums share a compute unit
     p.hist_shift = bits <= 7 ? 4 : 3;
@@ -2658,7 +2666,8 @@ static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout
     return tiles > 640 && wide_form_is_ahead(C, P, layout, bits) ? ProjectionForm{ProjectionForm::kWide, 0, 0, false} : large;
 }
 
-// The same in words, for tests: "rows 2 vec", "stream 5 half", "gemm8 fill", "split 1x4", ... and the layout.
+// The same in words, for tests: "rows 2 vec", "stream 5 half", "gemm8 fill", "split 1x4", ..., the layout, and of the split
+// form the rows of counts.
 int describe_projection(int C, int64_t P, int64_t HW, int layout, int bits, int active_rows, char* text, size_t size) {
     const ProjectionForm f = choose_projection(C, P, HW, layout, bits, active_rows);
     const char* lay = layout == FMTC_NHWC ? "nhwc" : "nchw";
@@ -2672,7 +2681,10 @@ int describe_projection(int C, int64_t P, int64_t HW, int layout, int bits, int 
         return snprintf(text, size, "gemm%d%s %s", g.eight ? 8 : 4, g.gy < g.gy_all ? " fill" : "", lay);
     }
     if (f.kernel == ProjectionForm::kWide) return snprintf(text, size, "wide %s", lay);
-    return snprintf(text, size, "split %dx%d %s", f.px_tiles, f.coef_tiles, lay);
+    const int ncs = (C + 31) / 32, n_kg = (ncs + f.coef_tiles - 1) / f.coef_tiles;
+    const int64_t px = 32 * f.px_tiles;
+    return snprintf(text, size, "split %dx%d %s %d", f.px_tiles, f.coef_tiles, lay,
+                    (int)(split_px_workgroups(ncs, n_kg, (P + px - 1) / px) * n_kg));
 }
 
 hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64_t N, int64_t HW, int layout,

@@ -18,7 +18,7 @@ def library():
 
 def form(C, P, layout, bits, keep=None):
     shape = (1, 1, P, C) if layout == NHWC else (1, C, 1, P)
-    return fmtc.test_projection(shape, layout, bits, keep).rsplit(" ", 1)[0]
+    return fmtc.test_projection(shape, layout, bits, keep).split(" nhwc" if layout == NHWC else " nchw")[0]
 
 
 # us of the kernel in the form named and in the other of the two, as measured
@@ -54,6 +54,12 @@ def test_truncated_wide_tensors():
     assert form(768, 1344, NHWC, 8, 700) == "gemm8"
     assert form(768, 4800, NCHW, 6, 40) == "split 1x4"
     assert form(512, 3200, NHWC, 6, 130) == "gemm8 fill"
+
+
+@pytest.mark.parametrize("C,P,rows", [(97, 20800, 512), (64, 12288, 384), (250, 16384, 512), (161, 48000, 510), (353, 20000, 1023), (64, 3136, 196)])
+def test_rows_of_counts_of_the_split_form(C, P, rows):
+    """The table kernel adds them up in one workgroup: no more than run at once, where that costs the projection nothing."""
+    assert fmtc.test_projection((1, 1, P, C), NHWC, 6).split(" nhwc ")[1] == str(rows)
 
 
 def test_arguments():
