@@ -1484,8 +1484,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // The same product with 8 wavefronts per 128 x 128 tile, two per SIMD, each 2 coefficient tiles x 1 pixel tile and a
 // quarter of the conversion work: while one wavefront of a SIMD converts, the other's matrix instructions run.  More
-// LDS operand reads per matrix instruction and one workgroup per compute unit: the faster form for tensors whose
-// tiles all fit the device at once (C = 960, N = 64, 7 x 7: 42.1 us; k_project_quantize_gemm4's steps of 32 channels
+// LDS operand reads per matrix instruction and one workgroup per compute unit: the faster of the two for tensors whose
+// tiles all fit the device at once (few of them take the split form: see choose_projection; C = 960, N = 64, 7 x 7: 42.1 us; k_project_quantize_gemm4's steps of 32 channels
 // with two wavefronts per pixel tile: 45.9, C = 1024, N = 8, 14 x 14: 46.9 and 49.2), the slower one beyond.
 template <int LAYOUT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_project_quantize_gemm8(GemmParams p) {
@@ -2208,7 +2208,7 @@ static hipError_t launch_wide(const BasisDevice& b, const float* d_x, int64_t P,
 // Few pixels, and channel counts that are no multiple of 16.  The kernels above walk all C / 16 dependent steps of a tile
 // in one wavefront or behind barriers, and with few tiles most of the device idles meanwhile; here a tile is 32 PT pixels x 32 KT
 // coefficients and its W wavefronts share out the contraction instead: each takes a run of the 16-channel steps, its
-// operands straight from memory in registers several steps ahead (the basis in operand order, a lane's eight channels of
+// operands straight from memory in registers one to four steps ahead (the basis in operand order, a lane's eight channels of
 // its pixel as they lie), with no barrier in the loop.  The partial sums meet once in LDS, and every wavefront quantizes
 // a part of the tile.  What bounds it: the latency of the loads (few tiles), then the caches' rate: a tile's operands are
 // read by all tiles of its row and column.  Coefficient tiles are the fastest block index, padded to the eight dies, so
@@ -2238,11 +2238,15 @@ struct SplitParams {
 
 struct __attribute__((packed, aligned(4))) Float4u { float v[4]; };  // four floats at any float's address
 
-template <int PT, int KT, int W, int D, int E, int LAYOUT>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(E, E))) void k_project_quantize_split(SplitParams p) {
+constexpr int kSplitWaves = 4;
+
+// PT x KT: pixel and coefficient tiles of a workgroup; D: steps that a wavefront's operands are requested ahead
+template <int PT, int KT, int D, int LAYOUT>
+__global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_project_quantize_split(SplitParams p) {
+    constexpr int W = kSplitWaves;
     constexpr int TILES = PT * KT;
-    constexpr int QW = TILES * 4 > W ? TILES * 4 / W : 1;  // quads of accumulators that a wavefront quantizes
-    static_assert(QW <= 4 && (QW * W == TILES * 4 || QW == 1), "quads of one tile per wavefront");
+    constexpr int QW = TILES * 4 / W;  // quads of accumulators that a wavefront quantizes
+    static_assert(QW <= 4 && QW * W == TILES * 4, "quads of one tile per wavefront");
     extern __shared__ __align__(16) uint8_t dyn_lds[];
     // partial sums [W][TILES][4][64] (four per lane), mean [Cpad], histogram copies [K << hist_shift]
     float4* s_part = reinterpret_cast<float4*>(dyn_lds);
@@ -2410,103 +2414,101 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(E, E))) 
                 }
         }
         __syncthreads();
-        if (QW * W == TILES * 4 || wave < TILES * 4) {
-            const int unit = wave * QW, tile = unit >> 2, q0 = unit & 3;
-            const int pt = tile / KT, kt = kt0 + tile % KT;
-            const int64_t px = (pg * PT + pt) * 32 + l32;
-            const int k0 = kt * 32 + 16 * half + 4 * q0;
-            int valid = px < p.P ? C - k0 : 0;  // coefficients of this lane that exist
-            valid = valid < 0 ? 0 : (valid > 4 * QW ? 4 * QW : valid);
-            float pn2 = 0.f;
+        const int unit = wave * QW, tile = unit >> 2, q0 = unit & 3;
+        const int pt = tile / KT, kt = kt0 + tile % KT;
+        const int64_t px = (pg * PT + pt) * 32 + l32;
+        const int k0 = kt * 32 + 16 * half + 4 * q0;
+        int valid = px < p.P ? C - k0 : 0;  // coefficients of this lane that exist
+        valid = valid < 0 ? 0 : (valid > 4 * QW ? 4 * QW : valid);
+        float pn2 = 0.f;
 #pragma unroll
-            for (int w = 0; w < W; w++) pn2 += s_n2[w][pt * 32 + l32];
-            const bool force = !(pn2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
-            const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(pn2), p.tau_min), 0.125f);
-            const float near_limit = force ? -1.f : 0.5f - tau;
-            uint32_t word[QW], near_mask = 0;
+        for (int w = 0; w < W; w++) pn2 += s_n2[w][pt * 32 + l32];
+        const bool force = !(pn2 < 1.0e9f);  // too large for f16, or not finite: every coefficient decided exactly
+        const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(pn2), p.tau_min), 0.125f);
+        const float near_limit = force ? -1.f : 0.5f - tau;
+        uint32_t word[QW], near_mask = 0;
+#pragma unroll
+        for (int g = 0; g < QW; g++) {
+            float4 y = s_part[unit * 64 + g * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < W; w++) {
+                const float4 o = s_part[(w * TILES * 4 + unit + g) * 64 + lane];
+                y.x += o.x; y.y += o.y; y.z += o.z; y.w += o.w;
+            }
+            const float ys[4] = {y.x, y.y, y.z, y.w};
+            uint32_t ub[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float t = ys[i] * p.inv_delta;
+                const float u = t + magic;  // round half to even
+                if (!(fabsf(t - (u - magic)) <= near_limit) && 4 * g + i < valid) near_mask |= 1u << (4 * g + i);
+                ub[i] = clamp_pattern(u, magic_lo, magic_hi);  // (its lowest byte is the symbol: in range whatever u is)
+            }
+            word[g] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(ub[3], ub[2], 0x0c0c0400u),
+                                            __builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u), 0x05040100u);
+        }
+        // ---- exact fp64 decision of the flagged values, two per round (one per half of the wavefront) ----
+        unsigned long long pending = __ballot(near_mask != 0);
+        while (__builtin_expect(pending != 0, 0)) {
+            const int L0 = __ffsll((long long)pending) - 1;
+            const unsigned long long rest = pending & (pending - 1);
+            const int L1 = rest ? __ffsll((long long)rest) - 1 : -1;
+            const int Lq = half ? L1 : L0;
+            const bool active = Lq >= 0;
+            const uint32_t fm = (uint32_t)__shfl((int)near_mask, active ? Lq : 0, 64);
+            const int r = active ? __ffs((int)fm) - 1 : 0;
+            double part = 0.0;
+            if (active) {
+                const int k = kt * 32 + 16 * (Lq >> 5) + 4 * q0 + r;
+                const int64_t qpx = (pg * PT + pt) * 32 + (Lq & 31);
+                int64_t xbase = qpx * C, xstride = 1;
+                if constexpr (LAYOUT != FMTC_NHWC) {
+                    const int64_t n_img = qpx / p.HW;
+                    xbase = n_img * (int64_t)C * p.HW + (qpx - n_img * p.HW);
+                    xstride = p.HW;
+                }
+#pragma unroll 16  // independent loads in flight together: the loop is all latency
+                for (int c = l32; c < C; c += 32)
+                    part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)s_mu[c]);
+            }
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the half
+            double qd = rint(part / (double)p.delta);
+            qd = fmin(fmax(qd, (double)lo), (double)hi);
+            const int sfix = (int)qd + zero_sym;
+            const int r0 = __shfl(r, 0, 64), r1 = __shfl(r, 32, 64), f0 = __shfl(sfix, 0, 64), f1 = __shfl(sfix, 32, 64);
+            if (lane == L0 || lane == L1) {
+                const int rq = lane == L0 ? r0 : r1;
+                const uint32_t sq = (uint32_t)(lane == L0 ? f0 : f1);
+#pragma unroll
+                for (int g = 0; g < QW; g++)
+                    if (g == (rq >> 2)) word[g] = (word[g] & ~(0xffu << (8 * (rq & 3)))) | (sq << (8 * (rq & 3)));
+                near_mask &= ~(1u << rq);
+            }
+            pending = __ballot(near_mask != 0);
+        }
+        // ---- count and store ----
+#pragma unroll
+        for (int g = 0; g < QW; g++)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                if (4 * g + i < valid) atomicAdd(&s_hist[(((word[g] >> (8 * i)) & 255u) << HS) + (lane & (HC - 1))], 1u);
+        uint8_t* dst = p.syms + px * C + k0;
+        if ((C & 15) == 0) {  // all of a lane's coefficients or none, aligned
+            if (valid) {
+                if constexpr (QW == 4) *reinterpret_cast<uint4*>(dst) = make_uint4(word[0], word[1], word[2], word[3]);
+                else if constexpr (QW == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(word[0], word[1]);
+                else *reinterpret_cast<uint32_t*>(dst) = word[0];
+            }
+        } else {
 #pragma unroll
             for (int g = 0; g < QW; g++) {
-                float4 y = s_part[unit * 64 + g * 64 + lane];
+                if ((C & 3) == 0) {
+                    if (4 * g < valid) *reinterpret_cast<uint32_t*>(dst + 4 * g) = word[g];
+                } else {
 #pragma unroll
-                for (int w = 1; w < W; w++) {
-                    const float4 o = s_part[(w * TILES * 4 + unit + g) * 64 + lane];
-                    y.x += o.x; y.y += o.y; y.z += o.z; y.w += o.w;
-                }
-                const float ys[4] = {y.x, y.y, y.z, y.w};
-                uint32_t ub[4];
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const float t = ys[i] * p.inv_delta;
-                    const float u = t + magic;  // round half to even
-                    if (!(fabsf(t - (u - magic)) <= near_limit) && 4 * g + i < valid) near_mask |= 1u << (4 * g + i);
-                    ub[i] = clamp_pattern(u, magic_lo, magic_hi);  // (its lowest byte is the symbol: in range whatever u is)
-                }
-                word[g] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(ub[3], ub[2], 0x0c0c0400u),
-                                                __builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u), 0x05040100u);
-            }
-            // ---- exact fp64 decision of the flagged values, two per round (one per half of the wavefront) ----
-            unsigned long long pending = __ballot(near_mask != 0);
-            while (__builtin_expect(pending != 0, 0)) {
-                const int L0 = __ffsll((long long)pending) - 1;
-                const unsigned long long rest = pending & (pending - 1);
-                const int L1 = rest ? __ffsll((long long)rest) - 1 : -1;
-                const int Lq = half ? L1 : L0;
-                const bool active = Lq >= 0;
-                const uint32_t fm = (uint32_t)__shfl((int)near_mask, active ? Lq : 0, 64);
-                const int r = active ? __ffs((int)fm) - 1 : 0;
-                double part = 0.0;
-                if (active) {
-                    const int k = kt * 32 + 16 * (Lq >> 5) + 4 * q0 + r;
-                    const int64_t qpx = (pg * PT + pt) * 32 + (Lq & 31);
-                    int64_t xbase = qpx * C, xstride = 1;
-                    if constexpr (LAYOUT != FMTC_NHWC) {
-                        const int64_t n_img = qpx / p.HW;
-                        xbase = n_img * (int64_t)C * p.HW + (qpx - n_img * p.HW);
-                        xstride = p.HW;
-                    }
-#pragma unroll 16  // independent loads in flight together: the loop is all latency
-                    for (int c = l32; c < C; c += 32)
-                        part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)s_mu[c]);
-                }
-#pragma unroll
-                for (int o = 16; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the half
-                double qd = rint(part / (double)p.delta);
-                qd = fmin(fmax(qd, (double)lo), (double)hi);
-                const int sfix = (int)qd + zero_sym;
-                const int r0 = __shfl(r, 0, 64), r1 = __shfl(r, 32, 64), f0 = __shfl(sfix, 0, 64), f1 = __shfl(sfix, 32, 64);
-                if (lane == L0 || lane == L1) {
-                    const int rq = lane == L0 ? r0 : r1;
-                    const uint32_t sq = (uint32_t)(lane == L0 ? f0 : f1);
-#pragma unroll
-                    for (int g = 0; g < QW; g++)
-                        if (g == (rq >> 2)) word[g] = (word[g] & ~(0xffu << (8 * (rq & 3)))) | (sq << (8 * (rq & 3)));
-                    near_mask &= ~(1u << rq);
-                }
-                pending = __ballot(near_mask != 0);
-            }
-            // ---- count and store ----
-#pragma unroll
-            for (int g = 0; g < QW; g++)
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-                    if (4 * g + i < valid) atomicAdd(&s_hist[(((word[g] >> (8 * i)) & 255u) << HS) + (lane & (HC - 1))], 1u);
-            uint8_t* dst = p.syms + px * C + k0;
-            if ((C & 15) == 0) {  // all of a lane's coefficients or none, aligned
-                if (valid) {
-                    if constexpr (QW == 4) *reinterpret_cast<uint4*>(dst) = make_uint4(word[0], word[1], word[2], word[3]);
-                    else if constexpr (QW == 2) *reinterpret_cast<uint2*>(dst) = make_uint2(word[0], word[1]);
-                    else *reinterpret_cast<uint32_t*>(dst) = word[0];
-                }
-            } else {
-#pragma unroll
-                for (int g = 0; g < QW; g++) {
-                    if ((C & 3) == 0) {
-                        if (4 * g < valid) *reinterpret_cast<uint32_t*>(dst + 4 * g) = word[g];
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; i++)
-                            if (4 * g + i < valid) dst[4 * g + i] = (uint8_t)(word[g] >> (8 * i));
-                    }
+                    for (int i = 0; i < 4; i++)
+                        if (4 * g + i < valid) dst[4 * g + i] = (uint8_t)(word[g] >> (8 * i));
                 }
             }
         }
@@ -2529,7 +2531,7 @@ static int64_t split_px_workgroups(int ncs, int n_kg, int64_t n_pg) {
     return n_pg * n_kg > most ? most / n_kg : n_pg;
 }
 
-template <int PT, int KT, int W, int D, int E>
+template <int PT, int KT, int D>
 static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P, int64_t HW, int layout, float delta,
                                int bits, uint8_t* d_syms, const CoderScratch& cs, int* n_parts, hipStream_t s,
                                bool skip_zero_rows) {
@@ -2559,8 +2561,8 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
     p.n_kc_pad = 4 * (padded - p.n_kc) <= p.n_kc ? padded : p.n_kc;
     p.inv_delta = (float)(1.0 / (double)delta);
     p.delta = delta;
-    // see launch_rows for the bound behind these two (the W partial sums and the two roundings after them add at most
-    // (W + 2) 2^-24 |T_k|_2 |x - mu|_2: 2^-20.7 at W = 8)
+    // see launch_rows for the bound behind these two (the four partial sums and the two roundings after them add at most
+    // 6 * 2^-24 |T_k|_2 |x - mu|_2 to the 2^-22 there: 2^-20.7 in all)
     p.kappa = 1.9073486e-6f /* 2^-19 */ * b.row_norm * p.inv_delta;
     p.tau_min = 4.7683716e-7f /* 2^-21 */ * (float)(1 << (bits - 1));
     p.syms = d_syms;
@@ -2575,15 +2577,15 @@ static hipError_t launch_split(const BasisDevice& b, const float* d_x, int64_t P
     *n_parts = (int)(gx * p.n_kg);
     // histogram copies: 8 KB at most, so that two workgroups with 64 KB of partial sums share a compute unit
     p.hist_shift = bits <= 7 ? 4 : 3;
-    const size_t lds = sizeof(float4) * W * PT * KT * 4 * 64 + sizeof(float) * b.Cpad + (sizeof(uint32_t) << (bits + p.hist_shift));
-    const void* fn = layout == FMTC_NHWC ? reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, W, D, E, FMTC_NHWC>)
-                                         : reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>);
+    const size_t lds = sizeof(float4) * kSplitWaves * PT * KT * 4 * 64 + sizeof(float) * b.Cpad + (sizeof(uint32_t) << (bits + p.hist_shift));
+    const void* fn = layout == FMTC_NHWC ? reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, D, FMTC_NHWC>)
+                                         : reinterpret_cast<const void*>(&k_project_quantize_split<PT, KT, D, FMTC_NCHW>);
     hipError_t ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (ea != hipSuccess) return ea;
     p.computed_blocks = (uint32_t)(gx * p.n_kc_pad);
     const dim3 grid(p.computed_blocks + (uint32_t)(gx * (p.n_kg - p.n_kc)));
-    return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NHWC>, grid, dim3(64 * W), lds, s, p)
-                               : launch(K_PROJECT, k_project_quantize_split<PT, KT, W, D, E, FMTC_NCHW>, grid, dim3(64 * W), lds, s, p);
+    return layout == FMTC_NHWC ? launch(K_PROJECT, k_project_quantize_split<PT, KT, D, FMTC_NHWC>, grid, dim3(64 * kSplitWaves), lds, s, p)
+                               : launch(K_PROJECT, k_project_quantize_split<PT, KT, D, FMTC_NCHW>, grid, dim3(64 * kSplitWaves), lds, s, p);
 }
 
 // Which of the forms above projects a tensor.
@@ -2695,10 +2697,10 @@ hipError_t launch_project_quantize(const BasisDevice& b, const float* d_x, int64
     if (f.kernel == ProjectionForm::kRows) return launch_rows(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     if (f.kernel == ProjectionForm::kGemm) return launch_gemm(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
     if (f.kernel == ProjectionForm::kWide) return launch_wide(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s);
-    if (f.px_tiles == 2) return launch_split<2, 2, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
-    if (f.coef_tiles == 4) return launch_split<1, 4, 4, 1, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
-    if (f.coef_tiles == 2) return launch_split<1, 2, 4, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
-    return launch_split<1, 1, 4, 4, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    if (f.px_tiles == 2) return launch_split<2, 2, 1>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    if (f.coef_tiles == 4) return launch_split<1, 4, 1>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    if (f.coef_tiles == 2) return launch_split<1, 2, 2>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
+    return launch_split<1, 1, 4>(b, d_x, P, HW, layout, delta, bits, d_syms, cs, n_parts, s, f.skip_zero_rows);
 }
 
 // Histogram of given symbols (staged coder entry point): one row of partial counts per workgroup.

@@ -383,9 +383,9 @@ def test_projection_of_wide_tensors(fmtc, oracle, C, P, bits, layout):
     check_projection(fmtc, oracle, C, 1, H, P // H, bits, layout)
 
 
-# The split contraction: one, two and four coefficient tiles per workgroup (up to 256, 640 and 4096 tiles of 32 x 32) and two by
-# two tiles beyond; wavefronts without a step (2 to 5 of them at 33 to 80 channels), last steps of 1 to 15 channels, ragged
-# last pixel and coefficient tiles, more pixel groups than workgroups; a pixel beyond f16, decided exactly in all coefficients.
+# The split contraction: one, two and four coefficient tiles per workgroup and two by two of them; one step per wavefront (33
+# channels), last steps of 1 to 15 channels, ragged last pixel and coefficient tiles, more pixel groups than workgroups; a
+# pixel beyond f16, decided exactly in all coefficients.  (Wavefronts without a step: truncated bases, test_gpu_truncation.)
 SPLIT_CASES = [(33, 1, 2), (48, 8192, 8), (80, 3333, 5), (99, 9000, 6), (128, 5000, 3), (161, 40, 4), (250, 1300, 8), (255, 2600, 5),
                (316, 20000, 6), (353, 13000, 7), (1023, 70, 4), (1024, 33, 8), (1024, 1400, 5), (701, 6100, 2)]
 
