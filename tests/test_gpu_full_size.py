@@ -116,8 +116,8 @@ def test_full_size_encode_decode(fmtc, oracle, name, bits):
     assert worst <= RECON_TOL, f"reconstruction off by {worst:.3e}"
 
 
-# the shapes the one-kernel encoder with a fixed table takes, at full size: one chunk group per workgroup
-# (stage 2), and many more groups than the device holds workgroups (N = 256)
+# the encoder with a fixed table at full size, in two kernels: few chunk groups, and many more than the device holds
+# workgroups (N = 256).  (The sizes of the one-kernel encoder: test_gpu_static_table.)
 STATIC = [
     ("resnet18_stage2_c128_28", 6),
     ("cfg0_c64_56", 8),

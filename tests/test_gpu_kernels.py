@@ -341,7 +341,7 @@ def test_packer_is_no_slower_with_a_fixed_table(fmtc, oracle, bits, chunk, C):
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
 
 
-def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None):
+def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None, keep=None):
     from paper_1905_10830_amd import synth
 
     P = N * H * W
@@ -354,10 +354,14 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None):
     x[P // 2] *= 1.0e5
     A = np.float32(4.0 if T_scale is None else 4.0 * np.max(T_scale))
     y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
+    basis = fmtc.basis_import(T, mu, A)
+    if keep is not None:
+        y[:, keep:] = 0.0
+        basis = basis.truncate(keep)
     sym, margin = oracle.quantize(y, oracle.delta(A, bits), bits, want_margin=True)
     xs = x.reshape(N, H, W, C)
     xs = xs if layout == "nhwc" else np.ascontiguousarray(xs.transpose(0, 3, 1, 2))
-    got, hist = fmtc.quantize(fmtc.basis_import(T, mu, A), dev(xs), bits, synth.NHWC if layout == "nhwc" else synth.NCHW)
+    got, hist = fmtc.quantize(basis, dev(xs), bits, synth.NHWC if layout == "nhwc" else synth.NCHW)
     torch.cuda.synchronize()
     got, hist = got.cpu().numpy().reshape(P, C), hist.cpu().numpy()
     diff = got != sym.reshape(P, C)
@@ -366,8 +370,57 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None):
     assert hist.tolist() == np.bincount(got.reshape(-1), minlength=256).tolist()
 
 
-# Rows of a basis with entries that f16 does not hold (not orthonormal, but accepted): every kernel family decides their
-# coefficients exactly.  Tiled product with four and eight wavefronts, streaming and rows form, split form.
+# Every form of the projection that a tensor can take (the rows' and the streaming kernel's coefficient tiles, loads with and
+# without masks, ...), at a size just beyond where it begins: three images of 7 x w pixels, ragged last tiles.
+FORM_CASES = [  # form, channels, w, bits, kept components (all of them if not given)
+    ("rows 1 nhwc", 5, 77, 4), ("rows 1 nchw", 30, 77, 8), ("rows 1 vec nhwc", 28, 1600, 8), ("rows 1 vec nchw", 32, 77, 3),
+    ("rows 2 nhwc", 33, 790, 6), ("rows 2 nchw", 63, 790, 5), ("rows 2 vec nhwc", 64, 790, 6), ("rows 2 vec nchw", 48, 790, 8),
+    ("rows 3 nhwc", 65, 530, 6), ("rows 3 nchw", 95, 530, 8), ("rows 3 vec nhwc", 96, 530, 5), ("rows 3 vec nchw", 80, 530, 6),
+    ("rows 4 nhwc", 97, 6250, 8), ("rows 4 nchw", 99, 6250, 4), ("rows 4 vec nhwc", 100, 6250, 8), ("rows 4x8 nhwc", 98, 6250, 5),
+    ("rows 4x8 vec nhwc", 128, 1570, 6), ("rows 5 nhwc", 129, 320, 6), ("rows 5 vec nhwc", 140, 320, 7),
+    ("stream 4 nhwc", 128, 400, 6), ("stream 4 nchw", 128, 400, 7), ("stream 4 half nhwc", 112, 400, 5), ("stream 4 half nchw", 112, 400, 6),
+    ("stream 5 nhwc", 160, 320, 6), ("stream 5 nchw", 160, 320, 5), ("stream 5 half nhwc", 144, 320, 5), ("stream 5 half nchw", 144, 320, 7),
+    ("split 1x1 nhwc", 64, 38, 6), ("split 1x1 nchw", 101, 38, 8), ("split 1x2 nhwc", 300, 70, 8), ("split 1x2 nchw", 64, 500, 6),
+    ("split 1x4 nhwc", 250, 390, 6), ("split 1x4 nchw", 256, 570, 5), ("split 2x2 nhwc", 161, 600, 7), ("split 2x2 nchw", 133, 1590, 6),
+    ("gemm8 nhwc", 256, 320, 6), ("gemm8 nchw", 176, 720, 4), ("gemm4 nhwc", 176, 785, 8), ("gemm4 nchw", 240, 785, 5),
+    ("gemm8 fill nhwc", 256, 320, 6, 40), ("gemm8 fill nchw", 256, 790, 5, 128), ("gemm4 fill nhwc", 256, 1570, 5, 100),
+    ("gemm4 fill nchw", 272, 1570, 4, 1), ("wide nhwc", 452, 600, 6), ("wide nchw", 161, 600, 4),
+]
+
+
+def form_of(fmtc, C, w, bits, layout, keep=None):
+    from paper_1905_10830_amd import synth
+
+    shape, tag = ((3, 7, w, C), synth.NHWC) if layout == "nhwc" else ((3, C, 7, w), synth.NCHW)
+    head, rest = fmtc.test_projection(shape, tag, bits, keep).split(layout)
+    return head + layout  # (without the rows of counts)
+
+
+@pytest.mark.parametrize("case", FORM_CASES, ids=[c[0].replace(" ", "-") for c in FORM_CASES])
+def test_every_form_of_the_projection(fmtc, oracle, case):
+    form, C, w, bits, *keep = case
+    layout, keep = form.rsplit(" ", 1)[1], keep[0] if keep else None
+    assert form_of(fmtc, C, w, bits, layout, keep) == form
+    check_projection(fmtc, oracle, C, 3, 7, w, bits, layout, keep=keep)
+
+
+@pytest.mark.parametrize("case", [c for c in FORM_CASES if len(c) == 4], ids=[c[0].replace(" ", "-") for c in FORM_CASES if len(c) == 4])
+def test_every_form_with_basis_entries_beyond_f16(fmtc, oracle, case):
+    form, C, w, bits = case
+    scale = np.ones(C)
+    scale[[0, C // 2, C - 1]] = 3.0e6
+    check_projection(fmtc, oracle, C, 3, 7, w, bits, form.rsplit(" ", 1)[1], scale)
+
+
+# ... with a truncated basis, whose zero rows the forms leave out in units of their own (see also test_gpu_truncation)
+@pytest.mark.parametrize("case", [c for c in FORM_CASES if len(c) == 4], ids=[c[0].replace(" ", "-") for c in FORM_CASES if len(c) == 4])
+def test_every_form_with_a_truncated_basis(fmtc, oracle, case):
+    form, C, w, bits = case
+    check_projection(fmtc, oracle, C, 3, 7, w, bits, form.rsplit(" ", 1)[1], keep=max(1, C // 3))
+
+
+# Rows of a basis with entries that f16 does not hold (not orthonormal, but accepted), of one image: their coefficients are
+# decided exactly.  (Every form: above.)
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])
 @pytest.mark.parametrize("C,P", [(32, 500), (64, 3000), (100, 700), (128, 40000), (144, 5000), (176, 16411), (256, 2000), (250, 900)])
 def test_projection_with_basis_entries_beyond_f16(fmtc, oracle, C, P, layout):

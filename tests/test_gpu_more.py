@@ -153,7 +153,8 @@ def test_wide_decoder_walking_its_channel_groups(fmtc, oracle, C, layout, monkey
 @pytest.mark.parametrize("layout", [synth.NHWC, synth.NCHW], ids=["nhwc", "nchw"])
 def test_wide_projection_with_more_tiles_than_compute_units(fmtc, oracle, layout):
     """256 channels, 18000 pixels: 141 x 2 workgroup tiles, which takes the 4-wavefront form of the tiled
-    projection (small tensors take the 8-wavefront form), including a ragged last pixel tile."""
+    projection (tensors of up to 256 such tiles take the 8-wavefront form, small ones the split form), including a ragged
+    last pixel tile."""
     C, bits = 256, 4
     s = synth.FeatureMapStream(C, 30, 30, 64, "relu", 1400)
     calib, data = s.images(2), s.images(20)

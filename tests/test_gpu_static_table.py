@@ -112,7 +112,7 @@ def test_static_table_encode_matches_oracle(fmtc, oracle, case, layout):
 
 @pytest.mark.parametrize("case", [CASES[0], CASES[2], CASES[3], CASES[4]], ids=[IDS[0], IDS[2], IDS[3], IDS[4]])
 def test_single_kernel_and_two_kernel_paths_agree(fmtc, oracle, case, monkeypatch):
-    """Shapes the one-kernel encoder takes: the same call with that kernel switched off gives the same bytes."""
+    """Small shapes, which take two kernels with and without that forced: the same call gives the same bytes."""
     C, H, W, ncal, ndat, rank, act, bits, cs = case
     cal, dat, T, mu, A = split_case(oracle, case, 750 + C, synth.NHWC)
     basis = fmtc.basis_import(T, mu, A)
@@ -129,8 +129,65 @@ def test_single_kernel_and_two_kernel_paths_agree(fmtc, oracle, case, monkeypatc
     assert int(nb.item()) == n and (a[:n] == b[:n]).all()
 
 
-# Around the number of chunk groups from which one kernel is used (four chunks a group: 145 of them), a last group of one
-# chunk, and the largest number (one group per compute unit)
+def one_kernel(fmtc, call):
+    """Whether `call` launched the one-kernel encoder (projection without a packing kernel after it)."""
+    fmtc.profile_enable(4)
+    try:
+        call()
+        torch.cuda.synchronize()
+        launches = {k: v[2] for k, v in fmtc.profile_read().items()}
+    finally:
+        fmtc.profile_enable(0)
+    assert launches["k_project_quantize"] == 1
+    return not launches.get("k_pack", 0)
+
+
+# The sizes of the one-kernel encoder (145 chunk groups of four chunks to one per compute unit) against the oracle: pixels
+# beyond f16, a truncated basis, a last group of one to four chunks and a last chunk that is not full, a buffer too small.
+@pytest.mark.parametrize("keep", [None, 9])
+@pytest.mark.parametrize("C,bits,layout,groups", [(64, 4, synth.NHWC, 144.3), (64, 6, synth.NHWC, 200.8), (64, 8, synth.NHWC, 256.0),
+                                                  (64, 8, synth.NCHW, 150.5), (32, 8, synth.NHWC, 145.7)])
+def test_one_kernel_encoder_matches_oracle(fmtc, oracle, C, bits, layout, groups, keep):
+    P, K = int(groups * 4 * 4096) // C // 2 * 2, 1 << bits
+    rng = np.random.default_rng(C + bits)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    mu = rng.standard_normal(C).astype(np.float32)
+    x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C) + mu).astype(np.float32)
+    x[5, 3], x[40, C - 1], x[100, 0], x[P - 1, 1] = 3.0e5, -7.0e6, 1.0e25, 7.0e4
+    x[41] *= 1.0e4
+    A = np.float32(6.0)
+    d = oracle.delta(A, bits)
+    y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
+    basis = fmtc.basis_import(T, mu, A)
+    if keep:
+        y[:, keep:] = 0.0
+        basis = basis.truncate(keep)
+    sym, margin = oracle.quantize(y, d, bits, want_margin=True)
+    ln = oracle.static_lengths(oracle.histogram(sym, bits)[:K])
+    table = fmtc.table_import(ln, bits)
+    xs = dev(x.reshape(1, 2, P // 2, C) if layout == synth.NHWC else np.ascontiguousarray(x.T).reshape(1, C, 2, P // 2))
+    stream, nbytes = fmtc.encode_static(basis, table, xs, layout)
+    assert one_kernel(fmtc, lambda: fmtc.encode_static(basis, table, xs, layout, stream_out=stream, out_bytes=nbytes))
+    n = int(nbytes.item())
+    got = stream[:n].cpu().numpy()
+    sym_gpu, _, pbits = oracle.unpack(got, P, C, bits)
+    diff = sym_gpu.reshape(P, C) != sym.reshape(P, C)
+    assert not diff.any() or margin.reshape(P, C)[diff].max() <= 1e-9  # (the order of an fp64 sum)
+    ref = oracle.pack(sym_gpu, C, bits, d, ln, oracle.canonical_codes(ln), cap=n + 4096)
+    assert n == len(ref) and np.array_equal(got, ref)
+    # a buffer that holds about half of the payload: nothing past it, and no valid stream
+    small = n - int(pbits) // 16
+    guard = torch.full((small + 8192,), 0xAB, dtype=torch.uint8, device="cuda")
+    fmtc.encode_static(basis, table, xs, layout, stream_out=guard[:small])
+    torch.cuda.synchronize()
+    assert (guard[small:] == 0xAB).all(), "wrote past the capacity it was given"
+    _, err = fmtc.decode_symbols(guard[:small], P, C, bits)
+    torch.cuda.synchronize()
+    assert int(err.item()) & fmtc.ERR_HEADER
+
+
+# Around the number of chunk groups from which one kernel is used (four chunks a group: two kernels at 144 of them, one at
+# 145), a last group of one chunk, and the largest number (one group per compute unit)
 @pytest.mark.parametrize("C,bits,layout", [(64, 5, synth.NHWC), (64, 8, synth.NHWC), (64, 8, synth.NCHW), (32, 8, synth.NHWC)])
 @pytest.mark.parametrize("groups", [144.0, 144.25, 160.5, 256.0])
 def test_one_kernel_and_two_agree_on_larger_tensors(fmtc, C, bits, layout, groups):
@@ -142,7 +199,8 @@ def test_one_kernel_and_two_agree_on_larger_tensors(fmtc, C, bits, layout, group
     xs = dev(x.reshape(1, P // 32, 32, C) if layout == synth.NHWC else x.T.reshape(1, C, P // 32, 32))
     table = fmtc.fit_table(basis, xs, bits, layout)
     a, na = fmtc.encode_static(basis, table, xs, layout)
-    torch.cuda.synchronize()
+    assert one_kernel(fmtc, lambda: fmtc.encode_static(basis, table, xs, layout, stream_out=a, out_bytes=na)) == (
+        groups > 144 and (C == 64 and layout == synth.NHWC or bits == 8))
     fmtc.test_option(fmtc.TEST_STATIC_TWO_KERNELS, 1)
     try:
         b, nb = fmtc.encode_static(basis, table, xs, layout)

@@ -21,14 +21,15 @@ def fmtc():
     return binding
 
 
-# (C, H, W, data images, rank, act, bits, keep): every projection / decoder kernel family, keep on and off tile edges
+# (C, H, W, data images, rank, act, bits, keep): small tensors, which take the split projection from 33 channels on, and every
+# decoder kernel family; keep on and off tile edges.  (The projection of larger tensors: test_gpu_kernels.FORM_CASES and below.)
 CASES = [
     (64, 20, 20, 2, 16, "relu", 6, 9),
     (128, 28, 28, 2, 32, "relu", 6, 32),
     (128, 14, 14, 3, 32, "relu", 4, 127),
-    (256, 14, 14, 5, 64, "relu", 4, 40),     # tiled matrix-product kernels, three coefficient tiles of zeros
+    (256, 14, 14, 5, 64, "relu", 4, 40),     # one of two groups of four coefficient tiles skipped
     (512, 7, 7, 9, 128, "relu", 5, 130),
-    (960, 7, 7, 2, 120, "relu6", 5, 200),    # 8 groups of coefficient tiles, 6 of them skipped and filled
+    (960, 7, 7, 2, 120, "relu6", 5, 200),    # 8 groups of coefficient tiles, 6 of them skipped
     (512, 7, 7, 3, 128, "relu", 4, 16),      # all but the first group skipped
     (200, 6, 7, 3, 25, "relu", 5, 17),       # channel count that is no multiple of 16
     (50, 10, 10, 2, 10, "relu", 5, 1),

@@ -62,6 +62,24 @@ def test_rows_of_counts_of_the_split_form(C, P, rows):
     assert fmtc.test_projection((1, 1, P, C), NHWC, 6).split(" nhwc ")[1] == str(rows)
 
 
+def test_every_form_has_a_case():
+    """The table of test_gpu_kernels holds every form that a tensor can take: a line that moves cannot leave a kernel untested."""
+    pytest.importorskip("torch")
+    from test_gpu_kernels import FORM_CASES, form_of
+
+    reached = set()
+    for C in range(1, 1025):
+        ncs = -(-C // 32)
+        for tiles in (50, 300, 1000, 1300, 1700, 2900, 3600, 4096, 4200, 17000):
+            w = 32 * (tiles // ncs) // 21
+            for layout in ("nhwc", "nchw"):
+                for bits in (5, 8):
+                    reached |= {form_of(fmtc, C, w, bits, layout, keep) for keep in (C, -(-C // 3))} if w else set()
+    assert reached == {c[0] for c in FORM_CASES}
+    for form, C, w, bits, *keep in FORM_CASES:
+        assert form_of(fmtc, C, w, bits, form.rsplit(" ", 1)[1], *keep) == form
+
+
 def test_arguments():
     for shape in ((0, 1, 1, 64), (1, 1, 1, 1025)):
         with pytest.raises(fmtc.FmtcError):
