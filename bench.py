@@ -40,7 +40,8 @@ SHAPES = [("resnet18_n256_c64_56", 6), ("resnet18_n256_c128_28", 6), ("resnet18_
 # rocprofv3 kernel names -> the names fmtc_profile_* reports
 KERNEL_FAMILIES = [("k_project_quantize", "k_project_quantize"), ("k_huffman_table", "k_huffman_table"),
                    ("k_pack", "k_pack"), ("k_decode", "k_decode"),
-                   ("k_quantize_u8", "k_quantize_u8"), ("k_int8_tiles", "k_quantize_u8"), ("k_copy", "k_copy")]
+                   ("k_quantize_u8", "k_quantize_u8"), ("k_int8_tiles", "k_quantize_u8"), ("k_int8_wide", "k_quantize_u8"),
+                   ("k_copy", "k_copy")]
 
 
 def family(kernel_name):

@@ -3,12 +3,13 @@
 // domain, then the inverse PCA).  One kernel per call:
 //   1. every workgroup checks the header and the code length table and builds the
 //      canonical decode tables and a 2^11-entry three-symbol lookup table in LDS;
-//   2. one wavefront per chunk, one lane per run of 64 symbols (bit offset = prefix
-//      sum of the stored run sizes) decodes into an LDS symbol tile;
+//   2. one wavefront per unit (a chunk, or as many small ones as it has lanes for),
+//      one lane per run of 64 symbols (bit offset = prefix sum of the stored run
+//      sizes) decodes into an LDS symbol tile;
 //   3. x_hat = T^T (Delta q) + mu on the f16 matrix cores
 //      (v_mfma_f32_32x32x16_f16; the levels are exact in f16, the basis entries are
 //      split in two f16 parts).  Narrow tensors (up to 160 channels): the wavefront
-//      that decoded a chunk also transforms it, the basis sits in LDS in operand
+//      that decoded a unit also transforms it, the basis sits in LDS in operand
 //      order and no workgroup barrier is needed after the tables.  Wide tensors: a
 //      tile of several chunks per workgroup, the basis streamed from L2.
 // Nothing outside [stream, stream + bytes) is read whatever the stream holds.
@@ -646,7 +647,7 @@ __device__ __forceinline__ UnitBits open_unit(const StreamView& v, const Unit& u
 }
 
 // Wide tensors and the symbols-only mode: a tile of G chunks per workgroup is decoded into an LDS tile of symbol
-// bytes, one chunk per wavefront and round; the inverse transform of the tile's pixels then runs on the f16 matrix
+// bytes, one unit per wavefront and round; the inverse transform of the tile's pixels then runs on the f16 matrix
 // cores with the arithmetic of the narrow-tensor kernel below (levels exact in f16, basis entries split in two f16
 // parts, two matrix instructions per 16 coefficients), shared out over the wavefronts (see the loop).
 // MT: pixel tiles of 32 per workgroup; KS: wavefronts that share a channel tile's contraction (MT = 1).

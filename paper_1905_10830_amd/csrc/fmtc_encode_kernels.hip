@@ -6,11 +6,11 @@
 // runs on the f16 matrix cores (v_mfma_f32_32x32x16_f16) with every fp32 operand
 // split into two f16 parts, which is as accurate as the fp32 matrix instruction
 // and several times as fast; values that land too close to a rounding boundary
-// for the fast pass to decide are recomputed in fp64 by the wavefront.  Three
+// for the fast pass to decide are recomputed in fp64 by the wavefront.  Four
 // forms: one wavefront per 32 pixels with the basis in LDS (up to 160 channels),
-// a 128 x 128 tile per workgroup (wider), and a small tile whose contraction the
-// workgroup's wavefronts share out (few pixels; channel counts that are no
-// multiple of 16).
+// a 128 x 128 tile per workgroup (wider, a multiple of 16 channels), a small tile
+// whose contraction the workgroup's wavefronts share out (few pixels, other channel
+// counts), and 32 pixels with all channels in LDS (many pixels of such counts).
 #include <atomic>
 #include <cstdio>
 #include <type_traits>
@@ -89,7 +89,7 @@ struct RowParams {
 
 // FUSED: the same projection and quantizer, but the symbols of a chunk stay in LDS and the wavefront packs them
 // with a code table fixed beforehand (no histogram, nothing but the container leaves the kernel).  Needs
-// C = 32 NCT in {32, 64, 128} and chunks of 4096 symbols, i.e. 4 / NCT whole pixel tiles; the grid must not exceed
+// C = 32 NCT in {32, 64} and chunks of 4096 symbols, i.e. 4 / NCT whole pixel tiles; the grid must not exceed
 // what the device holds at once (a chunk's position in the payload comes from the workgroups before it), and the
 // look-back words and the control block must be clear when the kernel starts.
 // WAVES wavefronts per workgroup (4, or 8 sharing one copy of a large basis); the register budget is set so that
@@ -2648,7 +2648,8 @@ static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout
     const ProjectionForm large = tiles > 1200 && (ncs == 5 || ncs == 6) ? split(2, 2) : split(1, 4);
     // up to 1024 tiles instead of the narrow kernels (us, theirs first: 96 channels, 999 tiles 11.9 : 8.4; 128 10.9 : 8.5; 160
     // 13.8 : 10.4; at 144 channels and 2330 tiles 13.9 : 17.8), and of 97 to 127 channels that are no multiple of 16, which
-    // those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 12800 57.2 : 55.6);
+    // those load with masks (100, 3456 tiles 19.4 : 15.9; 124, 4680 27.9 : 23.2; 97, 14000 62 : 58; of 65 to 95, channels last, 75,
+    // 1998 15.7 : 17.3, 95, 9999 53 : 55, planar 19.6 : 18.0 and 60.7 : 59.4);
     if (narrow) return tiles <= (ncs == 4 && !whole16 ? 16384 : 1024) ? large : rows;
     // instead of the tiled product, whose steps are a chain of barriers: channels last up to 1536 tiles (us, theirs first: 512
     // channels, 1456 25.6 : 23.1; 256, 1600 16.9 : 12.6; 512, 2304 26.8 : 33.4), but from 544 channels on, whose exact decisions are
