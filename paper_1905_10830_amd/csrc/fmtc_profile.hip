@@ -88,7 +88,7 @@ fmtc_status fmtc_test_option(int option, int value) {
 
 fmtc_status fmtc_test_projection(int64_t N, int C, int H, int W, fmtc_layout layout, int bits, int keep, char* text, size_t size) {
     if (!text || !size || N < 1 || C < 1 || C > 1024 || H < 1 || W < 1 || bits < 2 || bits > 8 || keep < 1 || keep > C ||
-        (layout != FMTC_NCHW && layout != FMTC_NHWC))
+        (layout != FMTC_NCHW && layout != FMTC_NHWC) || (double)N * C * H * W >= 4294967296.0)
         return FMTC_EINVAL;
     const int64_t HW = (int64_t)H * W;
     return fmtc::describe_projection(C, N * HW, HW, layout, bits, keep, text, size) < (int)size ? FMTC_OK : FMTC_EBUFSIZE;

@@ -81,7 +81,7 @@ def test_every_form_has_a_case():
 
 
 def test_arguments():
-    for shape in ((0, 1, 1, 64), (1, 1, 1, 1025)):
+    for shape in ((0, 1, 1, 64), (1, 1, 1, 1025), (1 << 62, 4, 4, 64), (1 << 20, 8, 8, 64)):
         with pytest.raises(fmtc.FmtcError):
             fmtc.test_projection(shape, NHWC, 4)
     for bits, keep in ((1, 64), (9, 64), (4, 0), (4, 65)):
