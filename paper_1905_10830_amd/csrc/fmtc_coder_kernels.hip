@@ -17,7 +17,6 @@
 #include "fmtc_device.h"
 #include "fmtc_internal.h"
 #include "fmtc_pack_device.h"
-#include "fmtc_pack_turns.h"
 
 namespace fmtc {
 
@@ -581,55 +580,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
 // ---------------------------------------------------------------------------
 // Large tensors (more chunk groups than the device holds pack workgroups): one pass over the symbols.
-// One workgroup of 16 wavefronts per compute unit: 15 pack, the 16th finds out where the chunks go.  A turn is a group of
-// 15 chunks; the packers take its chunks one by one (a fixed chunk per wavefront and turn left the wavefronts of a SIMD
-// up to three turns apart, and a turn waits for its last one), though of a turn no more than they have images for (see
-// deal).  Groups are claimed from a counter, so a group's predecessors have all been claimed by workgroups that run; a
-// group's size is published when its images are built, and its place is the sum of the sizes before it (added up by one
-// wavefront of the device).
-// A place is known 4 to 5 us after the group is packed, longer than a turn: a packer keeps up to three images waiting
-// in its part of the LDS (one or two where the code is longer, see images_for) and goes on with its next chunk, and the
-// 16th wavefront publishes a size as soon as it is there, between polls for the places of earlier groups.  The
-// wavefronts of a workgroup meet in LDS counters and not in barriers.  A size is published without waiting for any later
-// group, so whatever shares the device the lowest unpublished group can always go on.  The 16th wavefront's waits are
-// bounded all the same: it ends them in an invalid stream and sends its packers, which wait for nobody else, home.
-// Every workgroup builds the code table for itself (the first group's ticket and symbols arrive meanwhile).
-// (Before: a table kernel, a size pass over all chunks, a one-workgroup scan and a packing pass at known places.)
-//
-// Packing was bound by vector instructions and LDS operations per symbol (53 and 6 per 256 symbols).  A lane takes
-// eight neighbouring symbols per step, and up to 6 bits the table holds the joined code words of symbol pairs: four
-// lookups, one prefix sum over the lanes and two or three ORs into the image per 512 symbols.
+// One workgroup of 16 wavefronts per compute unit takes a range of neighbouring chunks, as many as its LDS holds packed
+// images of: all its wavefronts pack, one publishes the range's size, adds up the sizes of the ranges before it, and all
+// of them store.  A tensor with more chunks than that is packed in rounds, a range per workgroup and round, all ranges
+// of one size, so that every workgroup has the same number of chunks.  Ranges are claimed from a counter, so those before
+// a range have all been claimed by workgroups that run, and their sizes are published without waiting for any later one:
+// whatever shares the device, the lowest range without a size can always go on.  The wait is bounded all the same and
+// ends in an invalid stream.
+// Every workgroup builds the code table for itself (the range's ticket and the first symbols arrive meanwhile).
+// Chunks go to the wavefronts in a fixed order: dealt by a counter, the older wavefronts of a SIMD, which issue first, took
+// four each and the others two, which then had nobody to share the SIMD with (12544 chunks of 4096 symbols at 6 bits, whole
+// encoder 99.8 us, 97.9 this way).
+// (Before: 15 chunks at a time, claimed in turn, packed by 15 wavefronts while the 16th saw to places that one wavefront of
+// the device added up.  Of its 45 us for those chunks the packing took 8: the wavefronts spent 7 us waiting for their last
+// places, some compute units having four turns and others three, 4.6 on dealing chunks that must not get stuck, 4 on what a
+// turn leaves for its server.)
+// What bounds it, at those 33.8 us: 13 us before the first chunk (partial counts 4.3, table 7.4, pair table 1), 16 of packing,
+// two thirds of whose clocks issue vector instructions, 3 from the last size published to the places, 2 of stores.
+// A lane takes eight neighbouring symbols per step, and up to 6 bits the table holds the joined code words of symbol
+// pairs: four lookups, one prefix sum over the lanes and two or three ORs into the image per 512 symbols.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kStreamRoom = 2064;  // words a packer has for its images, each with 4 spare ones (see PackShared)
+constexpr uint32_t kStreamWaves = 16;
+constexpr uint32_t kStreamRoom = kStreamWaves * 2064;  // words for the images, each with 4 spare ones (see PackShared)
+constexpr uint32_t kMaxImages = 64;     // an image per lane of the wavefront that adds up
 constexpr uint32_t kShortCode = 26;     // a table entry holds up to 26 code bits below 6 bits of length ...
 constexpr uint32_t kNoCode = 63u << kShortCode;  // ... or says that the code word is longer: any eight symbols with
-                                        // such an entry come to more than 64 bits (less than eight: see look_up)
-// Marks a group's published size, and its place.  A size is the group's payload words; with a fixed table also its code
-// bits, from bit 32 on.  (Added up in memory before the size was published, a round trip per turn: 25088 chunks of 1024
-// symbols 55.5 -> 43.5 us without, the N = 256, C = 64 tensor at 6 bits 47.4 -> 42.5.)
+                                        // such an entry come to more than 64 bits (less than eight: see octet_of)
+// Marks a range's published size: its payload words; with a fixed table also its code bits, from bit 32 on.  (Added up in
+// memory before the size was published, a round trip per turn: 25088 chunks of 1024 symbols 55.5 -> 43.5 us without, the
+// N = 256, C = 64 tensor at 6 bits 47.4 -> 42.5.)
 constexpr unsigned long long kKnown = 1ull << 62;
 
 struct StreamShared {
-    unsigned long long tab[256];                                   // bit-reversed code | length << 56
-    uint32_t image[kStreamWaves][kStreamRoom];
+    unsigned long long tab[256];                 // bit-reversed code | length << 56
+    __align__(16) uint32_t image[kStreamRoom];
     uint16_t runs[kStreamWaves][64];
-    uint32_t words[kSlots][16], bits[kSlots][16];                  // payload words and code bits of the chunks of a turn
-    uint32_t done[kSlots];                                         // packers that have left theirs (counted over all turns)
-    unsigned long long place[kSlots];                              // first payload word of the group
-    uint32_t ticket[kSlots];                                       // the group
-    uint32_t placed, drawn;                                        // turns whose place / whose group is known, or kGone
-    uint32_t dealt;                                                // which chunk is next (see deal)
+    // of the chunks of the range: payload words, code bits, where the second window starts (see pack_window)
+    uint32_t words[kMaxImages], bits[kMaxImages], from[kMaxImages];
+    uint32_t range, next_range;
+    uint32_t images, image_words;
+    uint32_t gone;                               // the wait ran out
+    unsigned long long before;                   // payload words of the ranges before
     unsigned long long payload_bits;
-    uint32_t codes[1];                                             // [4096] (pairs) or [256]: code | length << 26
 };
-// A word of LDS that another wavefront of the workgroup advances.
-__device__ __forceinline__ uint32_t peek_lds(const uint32_t* q) {
-    return __hip_atomic_load(q, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void post_lds(uint32_t* q, uint32_t v) {
-    __hip_atomic_store(q, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
+// In front of it: code | length << 26 of symbol pairs, or of single ones.  (At the start of the LDS, where an entry's
+// address needs no base.)
+template <bool PAIRS>
+constexpr uint32_t kStreamCodes = PAIRS ? 4096u : 256u;
 // Eight symbols from any address (the compiler makes one 8-byte load of it: global memory takes them unaligned).
 __device__ __forceinline__ uint2 load_octet(const uint8_t* at) {
     uint2 v;
@@ -637,11 +634,11 @@ __device__ __forceinline__ uint2 load_octet(const uint8_t* at) {
     return v;
 }
 // The symbols of a chunk: register q of lane l holds symbols 512q + 8l .. + 7.  Past the chunk's end there is anything
-// (look_up takes none of it into account), so no load is masked: one address instruction each.  Nothing outside the tensor is read: where a piece would reach
+// (octet_of takes none of it into account), so no load is masked: one address instruction each.  Nothing outside the tensor is read: where a piece would reach
 // past its end, the tensor's last eight symbols are loaded (more than eight there are, in a tensor of this kernel), and
 // align_last_octet shifts them into place.
 // (Chunks that are no multiple of 8 symbols, fetched byte by byte and their last piece coded symbol by symbol: 8000 chunks
-// of 4092 symbols 68.8 us for the kernel, 31.6 this way; 100000 chunks of 66 474.8 and 184.)
+// of 4092 symbols 68.8 us for the kernel, 25.5 this way; 100000 chunks of 66 474.8 and 104.)
 __device__ __forceinline__ void load_chunk_octets(const PackParams& p, uint32_t ch, int lane, uint2 (&w)[8]) {
     const uint32_t clen = chunk_len_of(p, ch);
     const uint64_t at = (uint64_t)ch * p.chunk_syms;
@@ -670,16 +667,31 @@ __device__ __forceinline__ void align_chunk_octets(const PackParams& p, uint32_t
     for (int q = 0; q < 8; q++) w[q] = align_last_octet(w[q], 512 * q + 8 * lane, last);
 }
 
-// How many images a packer's room is divided into, and their words: as many as hold a chunk of the average size and a
+// How many images the room is divided into, and their words: as many as hold a chunk of the average size and a
 // third more.  (A larger chunk is finished window by window from its symbols in memory.)
 struct StreamImages {
     uint32_t count, words;
 };
 __device__ __forceinline__ StreamImages images_for(unsigned long long payload_bits, uint32_t n_chunks) {
     const unsigned long long need = payload_bits / 24u;  // words, and a third more
-    if (need <= 512ull * n_chunks) return {4u, 512u};
-    if (need <= 684ull * n_chunks) return {3u, 684u};
-    return {2u, 1024u};
+    if (need <= 512ull * n_chunks) return {64u, 512u};
+    if (need <= 684ull * n_chunks) return {48u, 684u};
+    return {32u, 1024u};
+}
+// The entropy of the symbol counts (`h`, 2^bits of them) and a little more, in bits, for images_for: the table's own bit
+// count is known only when the first symbols should already be on their way.  The same in every workgroup, which all
+// cut the tensor into the same ranges with it.  One wavefront.
+__device__ __forceinline__ unsigned long long bits_from_counts(const uint32_t* h, int bits, uint64_t V, int lane) {
+    const float log_v = __builtin_amdgcn_logf((float)V);
+    float sum = 0.f;
+    for (int s = lane; s < (1 << bits); s += 64) {
+        const uint32_t n = h[s];
+        const float l = log_v - __builtin_amdgcn_logf((float)(n ? n : 1u));  // (base 2)
+        sum += (float)n * (l > 1.f ? l : 1.f);  // (a code word has a bit at least)
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    return (unsigned long long)(uint32_t)(sum * (1.f / 64.f)) * 66ull;
 }
 
 // ORs the up to 64 bits of `c` into the image at bit `pos` of the chunk; what lies past the image's `words` goes to its
@@ -692,77 +704,143 @@ __device__ __forceinline__ void place_octet(unsigned long long c, uint32_t len, 
     if (__any(len + sh > 64u)) atomicOr(&img[at + 2u], sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
 }
 
+// The same for the usual step, without a test per lane.  Counted from the end of the word that the bits start in: k of them
+// (0 to 31) go there, 32 into the next word, the rest behind that; with k the shift of all three pieces, none of them needs
+// a case of its own for bits that start on a word (k = 0: nothing goes into the word before, which is there in any case).
+// The rest is left to the caller (none where past is not positive).
+struct Placed {
+    uint32_t* next;
+    uint32_t rest;
+    int past;
+};
+__device__ __forceinline__ Placed place_plain(unsigned long long c, uint32_t len, uint32_t pos, uint32_t* img, uint32_t words) {
+    const uint32_t p = pos < words * 32u ? pos : words * 32u, k = (0u - p) & 31u;
+    uint32_t* at = img + ((p + 31u) >> 5);
+    const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
+    atomicOr(at - 1, __builtin_amdgcn_alignbit(lo, 0u, k));
+    atomicOr(at, __builtin_amdgcn_alignbit(hi, lo, k));
+    return {at + 1, hi >> k, (int)(len - 32u - k)};
+}
+
 // A table entry of one symbol (see kShortCode).
 __device__ __forceinline__ uint32_t short_entry(unsigned long long e) {
     const uint32_t len = (uint32_t)(e >> 56);
     return len <= kShortCode ? (uint32_t)e | (len << kShortCode) : kNoCode;
 }
 
-// The code words of a lane's eight symbols.
-struct Octet {
-    unsigned long long lo, hi;  // of the first and of the last four
-    uint32_t l_lo, len;         // bits of the first four; of all
+// Where the table of pairs keeps the entry of symbols s0, s1.  The LDS bank of a word is its index modulo 64: with the plain
+// index s0 | s1 << 6 that is s0, the same few values for most lanes, whose pairs then wait for each other.
+__device__ __forceinline__ uint32_t pair_slot(uint32_t s0, uint32_t s1) { return (s0 ^ s1) | (s1 << 6); }
+
+// The code words of a lane's eight symbols, on their way into one value.
+constexpr uint32_t kCodeBits = (1u << kShortCode) - 1u;
+// N table entries joined, the first one lowest (at most 64 bits; of an entry without its code word: anything).
+template <int N>
+__device__ __forceinline__ unsigned long long join(const uint32_t* e) {
+    unsigned long long c = e[N - 1] & kCodeBits;
+#pragma unroll
+    for (int i = N - 2; i >= 0; i--) c = (c << ((e[i] >> kShortCode) & 63u)) | (e[i] & kCodeBits);
+    return c;
+}
+// The two halves of an octet.
+struct Halves {
+    unsigned long long lo, hi;
+    uint32_t l_lo;  // bits of the first
+};
+// len: all its bits (more than 64 where an entry is without its code word).
+// Of pairs the entries are kept, of which the usual octet, of up to 64 bits, is joined in one run; eight single ones would
+// be the registers of the kernel's third and fourth wavefront.
+template <bool PAIRS>
+struct Octet;
+template <>
+struct Octet<true> {
+    uint32_t e[4], len;
+    __device__ __forceinline__ unsigned long long whole() const { return join<4>(e); }
+    __device__ __forceinline__ Halves halves() const {
+        Halves h;
+        h.lo = join<2>(e);
+        h.hi = join<2>(e + 2);
+        h.l_lo = (e[0] >> kShortCode) + (e[1] >> kShortCode);
+        if (len - (e[2] >> kShortCode) - (e[3] >> kShortCode) != h.l_lo) h.l_lo = 127u;  // (without a code word, at a chunk's end)
+        return h;
+    }
+};
+template <>
+struct Octet<false> {
+    Halves h;
+    uint32_t len;
+    __device__ __forceinline__ unsigned long long whole() const { return h.lo | (h.hi << (h.l_lo & 63u)); }  // (64 bits in `lo` leave none in `hi`)
+    __device__ __forceinline__ Halves halves() const { return h; }
 };
 
-// PAIRS: `codes` holds the joined code words of symbol pairs s0 | s1 << 6; else of single symbols.
+// Table entries of eight symbols, in stream order.
+// PAIRS: the codes at the start of the LDS are the joined code words of symbol pairs (at pair_slot), else of single symbols.
+template <bool PAIRS>
+__device__ __forceinline__ void look_up(uint32_t x, uint32_t y, uint32_t (&e)[PAIRS ? 4 : 8]) {
+    // (an entry's offset is its address)
+    typedef const __attribute__((address_space(3))) uint32_t* lds_word;
+    if constexpr (PAIRS) {
+        // The byte address of a pair's entry is 4 (s0 ^ s1) | s1 << 8 (see pair_slot): with symbols of six bits the lower
+        // byte is one of (x << 2) ^ (x >> 6), and one byte permute takes the two from their places.  (Six bits whatever
+        // lies past a chunk's end.)
+        const uint32_t x1 = x & 0x3f3f3f3fu, y1 = y & 0x3f3f3f3fu;
+        const uint32_t x4 = (x1 << 2) ^ (x1 >> 6), y4 = (y1 << 2) ^ (y1 >> 6);
+        e[0] = *(lds_word)__builtin_amdgcn_perm(x1, x4, 0x0c0c0500u);
+        e[1] = *(lds_word)__builtin_amdgcn_perm(x1, x4, 0x0c0c0702u);
+        e[2] = *(lds_word)__builtin_amdgcn_perm(y1, y4, 0x0c0c0500u);
+        e[3] = *(lds_word)__builtin_amdgcn_perm(y1, y4, 0x0c0c0702u);
+    } else {
+        const uint32_t at[8] = {x << 2, x >> 6, x >> 14, x >> 22, y << 2, y >> 6, y >> 14, y >> 22};
+#pragma unroll
+        for (int i = 0; i < 8; i++) e[i] = *(lds_word)(at[i] & 0x3fcu);
+    }
+}
+// ... made an octet.
 // LAST: `left` is the number of the chunk's symbols from this lane's first one on (0 or less: none); those past the end
 // count no bits.
 template <bool PAIRS, bool LAST>
-__device__ __forceinline__ Octet look_up(uint32_t x, uint32_t y, int left, const uint32_t* codes, const unsigned long long* tab) {
-    const uint8_t* codes8 = reinterpret_cast<const uint8_t*>(codes);
-    constexpr uint32_t kCode = (1u << kShortCode) - 1u;
-    Octet o;
+__device__ __forceinline__ Octet<PAIRS> octet_of(uint32_t (&e)[PAIRS ? 4 : 8], uint32_t x, uint32_t y, int left, const unsigned long long* tab) {
+    Octet<PAIRS> o;
+    o.len = 0u;
+    bool none = false;
     if constexpr (PAIRS) {
-        auto entry = [&](uint32_t v) { return *reinterpret_cast<const uint32_t*>(codes8 + (((v << 2) & 0xfcu) | (v & 0x3f00u))); };
-        uint32_t e0 = entry(x), e1 = entry(x >> 16), e2 = entry(y), e3 = entry(y >> 16);
         if constexpr (LAST) {
             // (a pair of which the chunk has only the first symbol: that one's own code word)
             auto first_only = [&](uint32_t v) { return short_entry(tab[v & 255u]); };
             if (__any(left > 0 && left < 8 && (left & 1))) {
-                if (left == 1) e0 = first_only(x);
-                if (left == 3) e1 = first_only(x >> 16);
-                if (left == 5) e2 = first_only(y);
-                if (left == 7) e3 = first_only(y >> 16);
+                if (left == 1) e[0] = first_only(x);
+                if (left == 3) e[1] = first_only(x >> 16);
+                if (left == 5) e[2] = first_only(y);
+                if (left == 7) e[3] = first_only(y >> 16);
             }
-            e0 = left > 0 ? e0 : 0u;
-            e1 = left > 2 ? e1 : 0u;
-            e2 = left > 4 ? e2 : 0u;
-            e3 = left > 6 ? e3 : 0u;
         }
-        const uint32_t l0 = e0 >> kShortCode, l1 = e1 >> kShortCode, l2 = e2 >> kShortCode, l3 = e3 >> kShortCode;
-        o.lo = (unsigned long long)(e0 & kCode) | ((unsigned long long)(e1 & kCode) << l0);
-        o.hi = (unsigned long long)(e2 & kCode) | ((unsigned long long)(e3 & kCode) << l2);
-        o.l_lo = l0 + l1;
-        o.len = o.l_lo + l2 + l3;
-        if constexpr (LAST)
-            if (e0 >= kNoCode || e1 >= kNoCode || e2 >= kNoCode || e3 >= kNoCode) o.l_lo = o.len = 127u;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            if constexpr (LAST) {
+                e[i] = left > 2 * i ? e[i] : 0u;
+                none |= e[i] >= kNoCode;
+            }
+            o.e[i] = e[i];
+            o.len += e[i] >> kShortCode;
+        }
     } else {
-        auto entry = [&](uint32_t v4) { return *reinterpret_cast<const uint32_t*>(codes8 + (v4 & 0x3fcu)); };
-        uint32_t e[8] = {entry(x << 2), entry(x >> 6), entry(x >> 14), entry(x >> 22),
-                         entry(y << 2), entry(y >> 6), entry(y >> 14), entry(y >> 22)};
-        uint32_t l[8];
-        bool none = false;
+        o.h.l_lo = 0u;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
             if constexpr (LAST) {
-                if (i >= left) e[i] = 0u;
+                e[i] = i < left ? e[i] : 0u;
                 none |= e[i] >= kNoCode;
             }
-            l[i] = e[i] >> kShortCode;
-            e[i] &= kCode;
+            o.len += e[i] >> kShortCode;
+            if (i == 3) o.h.l_lo = o.len;
         }
-        const unsigned long long p0 = (unsigned long long)e[0] | ((unsigned long long)e[1] << l[0]);
-        const unsigned long long p1 = (unsigned long long)e[2] | ((unsigned long long)e[3] << l[2]);
-        const unsigned long long p2 = (unsigned long long)e[4] | ((unsigned long long)e[5] << l[4]);
-        const unsigned long long p3 = (unsigned long long)e[6] | ((unsigned long long)e[7] << l[6]);
-        const uint32_t l01 = l[0] + l[1], l45 = l[4] + l[5];
-        o.lo = p0 | (p1 << (l01 & 63u));
-        o.hi = p2 | (p3 << (l45 & 63u));
-        o.l_lo = l01 + l[2] + l[3];
-        o.len = o.l_lo + l45 + l[6] + l[7];
+        o.h.lo = join<4>(e);
+        o.h.hi = join<4>(e + 4);
         if constexpr (LAST)
-            if (none) o.l_lo = o.len = 127u;
+            if (none) o.h.l_lo = 127u;
     }
+    if constexpr (LAST)
+        if (none) o.len = 127u;
     return o;
 }
 
@@ -772,7 +850,7 @@ __device__ __forceinline__ Octet look_up(uint32_t x, uint32_t y, int left, const
 // symbol by symbol.
 __device__ __forceinline__ uint32_t octet_length(uint32_t x, uint32_t y, uint32_t first, uint32_t l_lo, uint32_t len,
                                                  uint32_t clen, const unsigned long long* tab) {
-    // (an entry without its code word says 63 bits, and any other symbol at least one; at the end of a chunk see look_up)
+    // (an entry without its code word says 63 bits, and any other symbol at least one; at the end of a chunk see octet_of)
     if (!__any(l_lo > 63u || len - l_lo > 63u)) return len;
     uint32_t n = 0u;
 #pragma unroll 1
@@ -819,65 +897,60 @@ __device__ __forceinline__ void place_long_octet(uint32_t x, uint32_t y, uint32_
 // serves both (16 bits each: a chunk has at most 64 x 8 x 48 bits in 512 symbols).
 template <bool PAIRS>
 __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t clen, const unsigned long long* tab,
-                                                const uint32_t* codes, uint32_t* img, uint32_t words, int lane,
-                                                uint16_t* run_bits, uint32_t& last_from) {
+                                                uint32_t* img, uint32_t words, int lane, uint16_t* run_bits, uint32_t& last_from) {
     uint32_t base = 0;
     auto step = [&](uint32_t q, uint32_t x0, uint32_t y0, uint32_t x1, uint32_t y1, auto some_c) __attribute__((always_inline)) -> uint32_t {
         constexpr bool some = decltype(some_c)::value;
         const uint32_t f0 = 512u * q + 8u * (uint32_t)lane, f1 = f0 + 512u;
         last_from = base < words * 32u ? (512u * q) | (base << 12) : last_from;
-        const Octet a = look_up<PAIRS, some>(x0, y0, (int)(clen - f0), codes, tab);
-        Octet b{0ull, 0ull, 0u, 0u};
         // (Wavefront-uniform.  Chunks of up to 512 symbols are one such octet per lane; with an empty second one 138660
         // chunks of 256 symbols took 266.7 us at 6 bits, 207.7 without, 249 in three kernels.)
         const bool two = !some || 512u * q + 512u < clen;
-        if (two) b = look_up<PAIRS, some>(x1, y1, (int)(clen - f1), codes, tab);
-        uint32_t len_a = a.len, len_b = b.len;
-        const uint32_t longer = a.len > b.len ? a.len : b.len;
-        const bool plain = !__any(longer > 64u);
-        bool single_a = false, single_b = false;
-        if (__builtin_expect(!plain, 0)) {
-            len_a = octet_length(x0, y0, f0, a.l_lo, a.len, clen, tab);
-            len_b = octet_length(x1, y1, f1, b.l_lo, b.len, clen, tab);
-            single_a = __any(len_a >> 31) != 0;
-            single_b = __any(len_b >> 31) != 0;
-            len_a &= 0x7fffffffu;
-            len_b &= 0x7fffffffu;
-        }
+        uint32_t ea[PAIRS ? 4 : 8], eb[PAIRS ? 4 : 8];
+        look_up<PAIRS>(x0, y0, ea);
+        if (two) look_up<PAIRS>(x1, y1, eb);
+        if constexpr (!some) __builtin_amdgcn_sched_barrier(0);  // (all of them on their way before the first is waited for)
+        const Octet<PAIRS> a = octet_of<PAIRS, some>(ea, x0, y0, (int)(clen - f0), tab);
+        Octet<PAIRS> b{};
+        if (two) b = octet_of<PAIRS, some>(eb, x1, y1, (int)(clen - f1), tab);
         // inclusive prefix sum over the lanes (see wave_inclusive_scan_rows; lanes 7 and 15 of a row of 16 hold
         // their eight lanes' sum after three steps: a run of 64 symbols)
-        uint32_t v = len_a | (len_b << 16);
-        v = dpp_add<0x111, 0xf>(v);
-        v = dpp_add<0x112, 0xf>(v);
-        v = dpp_add<0x114, 0xf>(v);
-        const uint32_t run = v;
-        v = dpp_add<0x118, 0xf>(v);
-        v = dpp_add<0x142, 0xa>(v);
-        v = dpp_add<0x143, 0xc>(v);
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-        const uint32_t pos_a = base + (v & 0xffffu) - len_a, pos_b = base + (total & 0xffffu) + (v >> 16) - len_b;
-        base += (total & 0xffffu) + (total >> 16);
-        if (__builtin_expect(plain, 1)) {
-            const unsigned long long ca = a.lo | (a.hi << (a.l_lo & 63u));  // (64 bits in `lo` leave none in `hi`)
-            const unsigned long long cb = b.lo | (b.hi << (b.l_lo & 63u));
-            const uint32_t limit = words * 32u;
-            const uint32_t at_a = (pos_a < limit ? pos_a : limit) >> 5, at_b = (pos_b < limit ? pos_b : limit) >> 5;
-            const uint32_t sh_a = pos_a & 31u, sh_b = pos_b & 31u;
-            const unsigned long long ta = ca << sh_a, tb = cb << sh_b;
-            atomicOr(&img[at_a], (uint32_t)ta);
-            atomicOr(&img[at_a + 1u], (uint32_t)(ta >> 32));
-            if (two) {
-                atomicOr(&img[at_b], (uint32_t)tb);
-                atomicOr(&img[at_b + 1u], (uint32_t)(tb >> 32));
-            }
-            const uint32_t reach_a = a.len + sh_a, reach_b = b.len + sh_b;
-            if (__any((reach_a > reach_b ? reach_a : reach_b) > 64u)) {
-                atomicOr(&img[at_a + 2u], sh_a ? (uint32_t)((ca >> 32) >> (32u - sh_a)) : 0u);
-                atomicOr(&img[at_b + 2u], sh_b ? (uint32_t)((cb >> 32) >> (32u - sh_b)) : 0u);
+        uint32_t run = 0u, pos_a = 0u, pos_b = 0u;
+        auto add_up = [&](uint32_t len_a, uint32_t len_b) __attribute__((always_inline)) {
+            uint32_t v = len_a | (len_b << 16);
+            v = dpp_add<0x111, 0xf>(v);
+            v = dpp_add<0x112, 0xf>(v);
+            v = dpp_add<0x114, 0xf>(v);
+            run = v;
+            v = dpp_add<0x118, 0xf>(v);
+            v = dpp_add<0x142, 0xa>(v);
+            v = dpp_add<0x143, 0xc>(v);
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+            pos_a = base + (v & 0xffffu) - len_a;
+            pos_b = base + (total & 0xffffu) + (v >> 16) - len_b;
+            base += (total & 0xffffu) + (total >> 16);
+        };
+        const uint32_t longer = a.len > b.len ? a.len : b.len;
+        if (__builtin_expect(!__any(longer > 64u), 1)) {
+            // (one straight run: what is joined fills the waits of the prefix sum)
+            add_up(a.len, b.len);
+            const Placed at_a = place_plain(a.whole(), a.len, pos_a, img, words);
+            Placed at_b{at_a.next, 0u, 0};
+            if (two) at_b = place_plain(b.whole(), b.len, pos_b, img, words);
+            if (__any((int)(at_a.past > at_b.past ? at_a.past : at_b.past) > 0)) {
+                atomicOr(at_a.next, at_a.rest);
+                atomicOr(at_b.next, at_b.rest);
             }
         } else {
-            place_long_octet(x0, y0, f0, a.lo, a.hi, a.l_lo, len_a, single_a, clen, tab, pos_a, img, words);
-            if (two) place_long_octet(x1, y1, f1, b.lo, b.hi, b.l_lo, len_b, single_b, clen, tab, pos_b, img, words);
+            const Halves ha = a.halves(), hb = b.halves();
+            uint32_t len_a = octet_length(x0, y0, f0, ha.l_lo, a.len, clen, tab);
+            uint32_t len_b = octet_length(x1, y1, f1, hb.l_lo, b.len, clen, tab);
+            const bool single_a = __any(len_a >> 31) != 0, single_b = __any(len_b >> 31) != 0;
+            len_a &= 0x7fffffffu;
+            len_b &= 0x7fffffffu;
+            add_up(len_a, len_b);
+            place_long_octet(x0, y0, f0, ha.lo, ha.hi, ha.l_lo, len_a, single_a, clen, tab, pos_a, img, words);
+            if (two) place_long_octet(x1, y1, f1, hb.lo, hb.hi, hb.l_lo, len_b, single_b, clen, tab, pos_b, img, words);
         }
         return run;
     };
@@ -918,7 +991,7 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
 // can have many such chunks.  Symbol by symbol, 64 per step, a window took some 50 us: 12544 chunks of which every tenth
 // is large, 118 us for the kernel, 61 this way, and 62 where every wavefront had one image of 2048 words.)
 template <bool PAIRS>
-__device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, const unsigned long long* tab, const uint32_t* codes,
+__device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, const unsigned long long* tab,
                                             uint32_t* img, uint32_t words, uint32_t win, int lane, uint32_t& from) {
     const uint32_t clen = chunk_len_of(p, ch);
     const uint64_t at = (uint64_t)ch * p.chunk_syms;
@@ -945,10 +1018,16 @@ __device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, co
         const uint2 xy = align_last_octet(next, (int)first, last);
         const uint32_t x = xy.x, y = xy.y;
         next = load(first + 512u);
-        const Octet o = look_up<PAIRS, true>(x, y, (int)(clen - first), codes, tab);
+        uint32_t e[PAIRS ? 4 : 8];
+        look_up<PAIRS>(x, y, e);
+        const Octet<PAIRS> o = octet_of<PAIRS, true>(e, x, y, (int)(clen - first), tab);
         const bool plain = !__any(o.len > 64u);
         uint32_t len = o.len;
-        if (__builtin_expect(!plain, 0)) len = octet_length(x, y, first, o.l_lo, o.len, clen, tab);
+        Halves h{};
+        if (__builtin_expect(!plain, 0)) {
+            h = o.halves();
+            len = octet_length(x, y, first, h.l_lo, o.len, clen, tab);
+        }
         const bool single = __any(len >> 31) != 0;
         len &= 0x7fffffffu;
         uint32_t row, half;
@@ -956,10 +1035,10 @@ __device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, co
         uint32_t pos = base + incl - len;
         base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         if (__builtin_expect(plain, 1)) {
-            put(o.lo | (o.hi << (o.l_lo & 63u)), pos);
+            put(o.whole(), pos);
         } else if (!single) {
-            put(o.lo, pos);
-            put(o.hi, pos + o.l_lo);
+            put(h.lo, pos);
+            put(h.hi, pos + h.l_lo);
         } else {
 #pragma unroll 1
             for (uint32_t i = 0; i < 8u; i++) {
@@ -977,11 +1056,11 @@ __device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, co
 template <bool STATIC, bool PAIRS>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_pack_stream(PackParams p) {
     extern __shared__ __align__(16) uint8_t dyn_lds[];
-    StreamShared& S = *reinterpret_cast<StreamShared*>(dyn_lds);
+    uint32_t* const codes = reinterpret_cast<uint32_t*>(dyn_lds);
+    StreamShared& S = *reinterpret_cast<StreamShared*>(dyn_lds + 4u * kStreamCodes<PAIRS>);
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool packer = wave < (int)kStreamWaves;  // wavefront-uniform
-    const uint32_t n_groups = (p.n_chunks + kStreamWaves - 1) / kStreamWaves;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr uint32_t kLast = kStreamWaves - 1u;  // the wavefront that draws the tickets
     auto claim = [&]() -> uint32_t {
         return __hip_atomic_fetch_add(&p.ctrl->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
@@ -989,250 +1068,200 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    if (tid < (int)kSlots) S.done[tid] = 0u;
-    if (tid == 0) {
-        S.dealt = 0u;
-        S.placed = 0u;
-        S.drawn = 0u;
-    }
-    TableLds& L = *reinterpret_cast<TableLds*>(&S.image[0][0]);  // shares LDS with the first wavefront's images
-    static_assert(sizeof(TableLds) <= sizeof(S.image[0]), "table scratch must fit a wavefront's images");
+    uint32_t ticket = 0;  // (on its way while the counts are added up)
+    if (wave == kLast && lane == 0) ticket = claim();
+    TableLds& L = *reinterpret_cast<TableLds*>(&S.image[0]);  // shares LDS with the first images
+    static_assert(sizeof(TableLds) <= 4u * kStreamRoom / kStreamWaves && kStreamRoom / kStreamWaves / 4u <= 1024u, "table scratch must fit the first wavefront's part of the images");
     if constexpr (!STATIC) {
         sum_partials<1024>(L, p.hist_parts, p.n_parts, p.bits, blockIdx.x);
+        if (wave == kLast && lane == 0) S.range = ticket;  // (a barrier follows)
         rank_symbols<1024>(L, p.bits);
     } else {
         if (tid < 256) S.tab[tid] = p.enc_table[tid];
+        if (wave == kLast && lane == 0) S.range = ticket;
         __syncthreads();
     }
-    // While the first wavefront builds the table, the others clear their images and request their first symbols.
-    // (A ticket takes up to 4 us with all workgroups drawing theirs.)
-    if (tid == 64 * (int)kStreamWaves) {
-        S.ticket[0] = claim();
-        post_lds(&S.drawn, 1u);
-        S.ticket[1] = claim();
-        post_lds(&S.drawn, 2u);
-    }
-    if (!STATIC && wave == 0) {
+    // While the first wavefront builds the table, the others clear the images and request their first symbols.
+    uint32_t images = 0, words = 0, per_range = 0, n_ranges = 0, c0 = 0, count = 0;
+    auto cut = [&]() {  // the tensor into ranges (see images_for)
+        const uint32_t rounds = (p.n_chunks + gridDim.x * images - 1u) / (gridDim.x * images);
+        per_range = (p.n_chunks + gridDim.x * rounds - 1u) / (gridDim.x * rounds);
+        n_ranges = (p.n_chunks + per_range - 1u) / per_range;
+    };
+    auto take_range = [&](uint32_t range) {  // (past the last one: no chunks)
+        c0 = range < n_ranges ? range * per_range : p.n_chunks;
+        count = p.n_chunks - c0 < per_range ? p.n_chunks - c0 : per_range;
+    };
+    uint2 w[8];
+    if (STATIC || wave != 0u) {
+        // (a fixed table says nothing of the tensor: room for 6 bits a symbol)
+        const StreamImages im = images_for(STATIC ? 6ull * p.V : bits_from_counts(L.h, p.bits, p.V, lane), p.n_chunks);
+        images = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.count);
+        words = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.words);
+        if (tid == 64 * (int)kLast) {
+            S.images = images;
+            S.image_words = words;
+            S.gone = 0u;
+        }
+        cut();
+        take_range((uint32_t)__builtin_amdgcn_readfirstlane((int)S.range));
+        if (wave < count) load_chunk_octets(p, c0 + wave, lane, w);
+    } else {
         TableOut out;
         out.entry = S.tab;
         table_from_hist_any(L, lane, p.bits, out);
         if (lane == 0) S.payload_bits = out.payload_bits;
     }
-    auto ticket_of = [&](uint32_t turn) {
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)S.ticket[turn % kSlots]);
-    };
-    // Until n turns are drawn / placed; false: they never will be.  (The 16th wavefront, which draws and places, waits
-    // for nothing without a limit, and ends these waits when it gives up.)
-    auto wait_for = [&](const uint32_t* count, uint32_t n) -> bool {
-        uint32_t v;
-        while ((v = peek_lds(count)) < n) __builtin_amdgcn_s_sleep(1);
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)v) != kGone;
-    };
-    // The next chunk for this wavefront, as its number among those of the workgroup.  (Never waits: the ticket of its
-    // turn may depend on the chunk the wavefront has at hand.)
-    uint32_t own_turn = 0, own = 0;  // the latest turn of which it has taken chunks, and how many
-    auto take = [&](uint32_t most) -> uint32_t {
-        // (in scalar registers: a dozen instructions, where one lane's branches took 2 us of the kernel at N = 256, C = 64)
-        uint32_t state = (uint32_t)__builtin_amdgcn_readfirstlane((int)peek_lds(&S.dealt));
-        Dealt d;
-        for (;;) {
-            d = deal(state, own_turn, own, most);
-            uint32_t was = state;
-            if (lane == 0) (void)__hip_atomic_compare_exchange_strong(&S.dealt, &was, d.state, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            was = (uint32_t)__builtin_amdgcn_readfirstlane((int)was);
-            if (was == state) break;
-            state = was;
-        }
-        const uint32_t n = d.n;
-        own = n / kStreamWaves == own_turn ? own + 1u : 1u;
-        own_turn = n / kStreamWaves;
-        return n;
-    };
-    // ... and its number among those of the tensor, once the ticket is known (past the last chunk: the chunk is empty;
-    // past the last group: no more chunks)
-    auto chunk_of = [&](uint32_t n) { return ticket_of(n / kStreamWaves) * kStreamWaves + n % kStreamWaves; };
-    auto have_group = [&](uint32_t n) { return ticket_of(n / kStreamWaves) < n_groups; };
-    uint32_t n = 0;
-    uint2 w[8];
-    if (packer) {
-        for (uint32_t i = lane; i < kStreamRoom; i += 64) S.image[wave][i] = 0u;
-        n = take(2u);  // (of turn 0)
-        (void)wait_for(&S.drawn, 1u);
-        if (have_group(n)) load_chunk_octets(p, chunk_of(n), lane, w);
-    }
+    constexpr uint32_t kPart = kStreamRoom / kStreamWaves;
+    if (wave != 0u)  // (the first wavefront's part holds the counts and the table's scratch)
+        for (uint32_t i = wave * kPart + 4u * (uint32_t)lane; i < (wave + 1u) * kPart; i += 256u)
+            *reinterpret_cast<uint4*>(&S.image[i]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
+    if (tid < (int)kPart / 4) *reinterpret_cast<uint4*>(&S.image[4 * tid]) = make_uint4(0u, 0u, 0u, 0u);
+    if (!STATIC && wave == 0u) {
+        images = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.images);
+        words = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.image_words);
+        cut();
+        take_range((uint32_t)__builtin_amdgcn_readfirstlane((int)S.range));
+        if (wave < count) load_chunk_octets(p, c0 + wave, lane, w);
+    }
+    uint32_t range = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.range);
     if (blockIdx.x == 0 && tid < 256) p.stream[kHeaderBytes + tid] = (uint8_t)(S.tab[tid] >> 56);  // the container's length table
-    for (int i = tid; i < (PAIRS ? 4096 : 256); i += 1024) {
+    for (int i = tid; i < (int)kStreamCodes<PAIRS>; i += 1024) {
         const unsigned long long e0 = S.tab[PAIRS ? i & 63 : i], e1 = PAIRS ? S.tab[i >> 6] : 0ull;
         const uint32_t l0 = (uint32_t)(e0 >> 56), l1 = (uint32_t)(e1 >> 56);
         const bool fits = l0 + l1 <= kShortCode;
-        S.codes[i] = fits ? (uint32_t)e0 | ((uint32_t)e1 << (l0 & 31u)) | ((l0 + l1) << kShortCode) : kNoCode;
+        codes[PAIRS ? pair_slot((uint32_t)i & 63u, (uint32_t)i >> 6) : (uint32_t)i] = fits ? (uint32_t)e0 | ((uint32_t)e1 << (l0 & 31u)) | ((l0 + l1) << kShortCode) : kNoCode;
     }
+    // (look_up reads them by their place in the LDS, which starts with them: no other shared memory in this kernel)
+    asm volatile("" : : "s"((uint32_t)(uintptr_t)(lds_void_t*)dyn_lds) : "memory");
     __syncthreads();
     uint32_t* chunk_off = reinterpret_cast<uint32_t*>(p.stream + kHeaderBytes + kLenTableBytes);
+    uint16_t* sub_bits = reinterpret_cast<uint16_t*>(p.stream + p.off_sub_bits);
+    uint32_t* payload = reinterpret_cast<uint32_t*>(p.stream + p.off_payload);
     const uint32_t n_runs = p.subs_per_chunk;  // at most 64
+    // First wavefront: what ranges [0, added) come to (bits: of the sizes this lane has read).
+    uint32_t added = 0;
+    unsigned long long added_words = 0, my_bits = 0;
 
-    if (packer) {
-        uint16_t* sub_bits = reinterpret_cast<uint16_t*>(p.stream + p.off_sub_bits);
-        uint32_t* payload = reinterpret_cast<uint32_t*>(p.stream + p.off_payload);
-        // (a fixed table says nothing of the tensor: room for 8 bits a symbol.  With two images of 1024 words whatever the
-        // chunk, 25088 chunks of 1024 symbols took 62.5 us, 55.5 with four of 512)
-        const StreamImages im = images_for(STATIC ? 6ull * p.V : S.payload_bits, p.n_chunks);
-        const uint32_t n_images = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.count);
-        const uint32_t words = (uint32_t)__builtin_amdgcn_readfirstlane((int)im.words);
-        // The images wait in a ring: `filled` chunks are packed, `stored` of them have left.  What is known of those
-        // waiting sits in the lanes of `held`: chunk number among the workgroup's, by image, and of `held_from`: where its
-        // second window starts.
-        uint32_t filled = 0, stored = 0, next_image = 0, next_stored = 0, held = 0, held_from = 0;
-        auto turn_of_oldest = [&]() { return (uint32_t)__builtin_amdgcn_readlane((int)held, (int)next_stored) / kStreamWaves; };
-        auto store = [&]() {  // (its place is known)
-            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)held, (int)next_stored);
-            uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)held_from, (int)next_stored);
-            const uint32_t turn = m / kStreamWaves, at = m % kStreamWaves, slot = turn % kSlots;
-            const uint32_t c = ticket_of(turn) * kStreamWaves + at;
-            uint32_t* img = S.image[wave] + next_stored * (words + 4u);
-            stored++;
-            next_stored = next_stored + 1u < n_images ? next_stored + 1u : 0u;
-            const uint32_t other = lane < (int)kStreamWaves ? S.words[slot][lane] : 0u;
-            const uint32_t n_words = (uint32_t)__builtin_amdgcn_readlane((int)other, (int)at);
-            const unsigned long long place = S.place[slot];
-            const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_sum((uint32_t)lane < at ? other : 0u));
-            const unsigned long long word0 =
-                before + ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)place) |
-                          ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(place >> 32)) << 32));
-            if (c >= p.n_chunks) return;  // (the last group's places past the last chunk: empty)
-            if (lane == 0) chunk_off[c] = (uint32_t)word0;
-            const bool fits = word0 + n_words <= p.cap_words;  // (else the header has been left invalid)
+    while (range < n_ranges) {
+        const bool more = n_ranges > gridDim.x;  // (otherwise every workgroup has one range)
+        if (more && wave == kLast && lane == 0) ticket = claim();
+        // ---- the chunks of the range into their images ----
+        uint32_t slot = wave;
+        while (slot < count) {
+            const uint32_t next = slot + kStreamWaves;
+            uint2 wn[8];
+            if (next < count) load_chunk_octets(p, c0 + next, lane, wn);  // they arrive while this chunk is packed
+            const uint32_t ch = c0 + slot;
+            uint32_t from = 0;
+            align_chunk_octets(p, ch, lane, w);
+            const uint32_t bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.image + slot * (words + 4u), words, lane, S.runs[wave], from);
+            if (lane == 0) {
+                S.words[slot] = (bits + 31u) >> 5;
+                if constexpr (STATIC) S.bits[slot] = bits;
+                S.from[slot] = from;
+            }
+            sync_wave();
+            if ((uint32_t)lane < n_runs) (sub_bits + (size_t)ch * n_runs)[lane] = S.runs[wave][lane];
+            sync_wave();
+            slot = next;
+#pragma unroll
+            for (int q = 0; q < 8; q++) w[q] = wn[q];
+        }
+        if (wave == kLast && lane == 0) S.next_range = more ? ticket : n_ranges;
+        __syncthreads();
+        // ---- the range's place: its size is published, and the sizes before it are added up ----
+        const uint32_t first_ch = c0, n_here = count, next_range = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.next_range);
+        const uint32_t my_words = (uint32_t)lane < n_here ? S.words[lane] : 0u;
+        const uint32_t my_end = wave_exclusive_scan(my_words) + my_words;  // (of the range's first lane + 1 chunks)
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)my_end, 63);
+        if (wave == 0u) {
+            unsigned long long size = total;
+            if constexpr (STATIC) size |= (unsigned long long)wave_sum((uint32_t)lane < n_here ? S.bits[lane] : 0u) << 32;
+            if (lane == 0) publish64(&p.lookback[range], kKnown | size);  // (at most 64 x 6144 words and 64 x 196608 bits)
+            // 256 sizes at a time, all loads in flight together; only those still missing are looked at again
+            bool gone = false;
+            for (; added < range && !gone; added += 256u) {
+                unsigned long long e[4] = {0ull, 0ull, 0ull, 0ull};
+                uint32_t tries = 0;
+                for (;;) {
+                    bool missing = false;
+                    if (tries < p.spin_limit) {
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            const uint32_t i = added + 64u * (uint32_t)j + (uint32_t)lane;
+                            if (i < range && e[j] == 0ull) e[j] = peek64(&p.lookback[i]);
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; j++) missing |= added + 64u * (uint32_t)j + (uint32_t)lane < range && e[j] == 0ull;
+                    if (!__any(missing)) break;
+                    gone = ++tries > p.spin_limit;  // (seconds: never reached)
+                    if (gone) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                uint32_t sum = 0;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    sum += (uint32_t)e[j];
+                    if constexpr (STATIC) my_bits += (e[j] & (kKnown - 1ull)) >> 32;
+                }
+                added_words += wave_sum(sum);
+            }
+            if (gone && lane == 0) {
+                const uint32_t was = __hip_atomic_fetch_or(&p.ctrl->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("" : : "v"(was) : "memory");  // (the returned value is waited for)
+                publish32(reinterpret_cast<uint32_t*>(p.stream), 0u);  // the header's magic
+                S.gone = 1u;
+            }
+            if (lane == 0) S.before = added_words;
+            added = range + 1u;
+            added_words += total;
+            if (STATIC && lane == 0) my_bits += size >> 32;
+        }
+        range = next_range;
+        take_range(range);
+        if (wave < count) load_chunk_octets(p, c0 + wave, lane, w);
+        __syncthreads();
+        if (S.gone) return;
+        // ---- the images leave ----
+        const unsigned long long before = S.before;
+        if (wave == 0u && (uint32_t)lane < n_here) chunk_off[first_ch + (uint32_t)lane] = (uint32_t)before + my_end - my_words;
+        for (slot = wave; slot < n_here; slot += kStreamWaves) {
+            const uint32_t n_words = (uint32_t)__builtin_amdgcn_readlane((int)my_words, (int)slot);
+            const unsigned long long word0 = before + ((uint32_t)__builtin_amdgcn_readlane((int)my_end, (int)slot) - n_words);
+            uint32_t* img = S.image + slot * (words + 4u);
+            uint32_t from = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.from[slot]);
+            const bool fits = word0 + n_words <= p.cap_words;  // (else the header is left invalid)
             for (uint32_t win = 0; win < n_words; win += words) {
                 const uint32_t win_words = n_words - win < words ? n_words - win : words;
                 if (win) {
-                    pack_window<PAIRS>(p, c, S.tab, S.codes, img, words, win, lane, from);
+                    pack_window<PAIRS>(p, first_ch + slot, S.tab, img, words, win, lane, from);
                     sync_wave();
                 }
-                for (uint32_t i = lane; i < win_words; i += 64) {
-                    if (fits) payload[(size_t)word0 + win + i] = img[i];
+                // four words per lane, to any word of the payload (images start on 16 bytes); then the last one to three
+                uint32_t* out = payload + (size_t)word0 + win;
+                for (uint32_t i = 4u * (uint32_t)lane; i + 4u <= win_words; i += 256u) {
+                    const uint4 v = *reinterpret_cast<const uint4*>(img + i);
+                    *reinterpret_cast<uint4*>(img + i) = make_uint4(0u, 0u, 0u, 0u);
+                    if (fits) __builtin_memcpy(out + i, &v, 16);
+                }
+                const uint32_t i = (win_words & ~3u) + (uint32_t)lane;
+                if (i < win_words) {
+                    if (fits) out[i] = img[i];
                     img[i] = 0u;
                 }
                 sync_wave();  // the image is read and clear before the next window or chunk writes it
             }
-        };
-        while (have_group(n)) {
-            const uint32_t n_next = take(n_images);
-            const uint32_t drawn = (uint32_t)__builtin_amdgcn_readfirstlane((int)peek_lds(&S.drawn));
-            if (drawn == kGone) return;
-            const bool early = drawn > n_next / kStreamWaves;  // its symbols arrive while this chunk is packed
-            uint2 wn[8];
-            if (early && have_group(n_next)) load_chunk_octets(p, chunk_of(n_next), lane, wn);
-            // images whose place is known leave, and one has to where all are waiting (its turn is before this chunk's)
-            while (stored < filled && stores_first(filled - stored, n_images, peek_lds(&S.placed), turn_of_oldest())) {
-                if (!wait_for(&S.placed, turn_of_oldest() + 1u)) return;
-                store();
-            }
-            const uint32_t ch = chunk_of(n);
-            uint32_t bits = 0, from = 0;
-            if (ch < p.n_chunks) {
-                align_chunk_octets(p, ch, lane, w);
-                bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.codes, S.image[wave] + next_image * (words + 4u), words, lane, S.runs[wave], from);
-            }
-            const uint32_t slot = n / kStreamWaves % kSlots;
-            if (lane == 0) {
-                S.words[slot][n % kStreamWaves] = (bits + 31u) >> 5;
-                S.bits[slot][n % kStreamWaves] = bits;
-                __hip_atomic_fetch_add(&S.done[slot], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            sync_wave();
-            if (ch < p.n_chunks && (uint32_t)lane < n_runs) (sub_bits + (size_t)ch * n_runs)[lane] = S.runs[wave][lane];
-            sync_wave();
-            held = (uint32_t)lane == next_image ? n : held;
-            held_from = (uint32_t)lane == next_image ? from : held_from;
-            filled++;
-            next_image = next_image + 1u < n_images ? next_image + 1u : 0u;
-            n = n_next;
-            if (!early) {
-                if (!wait_for(&S.drawn, n / kStreamWaves + 1u)) return;
-                if (have_group(n)) load_chunk_octets(p, chunk_of(n), lane, wn);
-            }
-#pragma unroll
-            for (int q = 0; q < 8; q++) w[q] = wn[q];
         }
-        while (stored < filled) {
-            if (!wait_for(&S.placed, turn_of_oldest() + 1u)) return;
-            store();
-        }
-        return;
-    }
-
-    // ---- the 16th wavefront: turns [0, published) have published their sizes, turns [0, placed) know their places ----
-    // A turn's size is published when at most two turns before it are waiting for their places.  The ticket of turn t is
-    // drawn behind the size of turn t - 2, so all turns up to t - 5 have their places by then, and a packer that starts
-    // on a chunk of turn t lets go of what it holds of those.  Its next chunk is of turn t + 2 at the latest (turn t + 2
-    // has no ticket before turn t is published, so at most the packers' next chunks are of that turn), and until that one
-    // is packed no ticket beyond turn t + 3 is drawn: never more than eight turns are in use.
-    // The sizes of all groups are added up by ONE wavefront, that of the workgroup which drew the first ticket (so it
-    // runs, and it stays until every group has its place): it reads the published sizes in order, 256 at a time, and
-    // writes the places, for which the others look at one word each.  (Every workgroup reading back over the sizes
-    // before its own group, 4 KB a look, all at the same few cache lines, took 7 to 10 us per turn.)
-    (void)wait_for(&S.drawn, 2u);
-    uint32_t published = 0, placed = 0;
-    uint32_t g = ticket_of(0);
-    unsigned long long* sizes = p.lookback;
-    unsigned long long* places = p.lookback + n_groups;
-    const bool adder = g == 0u;
-    uint32_t added = 0;                 // groups [0, added) have their places
-    unsigned long long total_words = 0;  // of those
-    unsigned long long my_bits = 0;      // STATIC: code bits of those whose size this lane has read
-    uint32_t tries = 0;                 // looks without anything new
-    while (g < n_groups || placed < published || (adder && added < n_groups)) {
-        bool news = false, draws = false;
-        uint32_t next_ticket = 0;
-        if (g < n_groups && may_publish(published, placed) && peek_lds(&S.done[published % kSlots]) == kStreamWaves * (published / kSlots + 1u)) {
-            const uint32_t slot = published % kSlots;
-            unsigned long long size = lane < (int)kStreamWaves ? S.words[slot][lane] : 0u;
-            // (at most 15 x 6144 words and 15 x 196608 bits)
-            if constexpr (STATIC) size |= (unsigned long long)(lane < (int)kStreamWaves ? S.bits[slot][lane] : 0u) << 32;
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) size += __shfl_xor(size, o, 64);
-            if (lane == 0) publish64(&sizes[g], kKnown | size);
-            published++;
-            g = ticket_of(published);
-            // (A ticket is drawn two turns ahead, so that the symbols of the group can be requested one turn ahead.  It is
-            // awaited below, together with the look at the places: 25088 chunks of 1024 symbols 80.0 -> 78.1 us.  Three or four
-            // turns ahead, with two to four images: 80.7 and 127, since every place then waits for groups that have been
-            // claimed longer.)
-            next_ticket = 0xffffffffu;
-            if (lane == 0 && g < n_groups) next_ticket = claim();
-            draws = true;
-            news = true;
-        }
-        if (adder && added < n_groups) {
-            unsigned long long e[4];
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const uint32_t i = added + 64u * (uint32_t)j + (uint32_t)lane;
-                e[j] = i < n_groups ? peek64(&sizes[i]) : 0ull;
-            }
-            bool more = true;
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                if (!more) break;
-                const unsigned long long missing = __ballot(e[j] == 0ull);
-                const int ready = missing ? __ffsll((long long)missing) - 1 : 64;
-                const unsigned long long size = lane < ready ? e[j] & 0xffffffffull : 0ull;
-                if constexpr (STATIC) my_bits += lane < ready ? (e[j] & (kKnown - 1ull)) >> 32 : 0ull;
-                const unsigned long long incl = wave_inclusive_scan64(size);
-                if (lane < ready) publish64(&places[added + (uint32_t)lane], kKnown | (total_words + incl - size));
-                total_words += __shfl(incl, 63, 64);
-                added += (uint32_t)ready;
-                more = ready == 64;
-                news |= ready != 0;
-            }
+        if (wave == 0u && added == n_ranges) {  // the last range: the header
             if constexpr (STATIC) {
-                if (added == n_groups)
 #pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) my_bits += __shfl_xor(my_bits, o, 64);
+                for (int o = 32; o > 0; o >>= 1) my_bits += __shfl_xor(my_bits, o, 64);
             }
-            if (added == n_groups && lane == 0) {
-                chunk_off[p.n_chunks] = (uint32_t)total_words;
+            if (lane == 0) {
+                chunk_off[p.n_chunks] = (uint32_t)added_words;
                 // (word by word: a copy of the header on the stack is one that every lane of the kernel would write)
                 Header* hdr = reinterpret_cast<Header*>(p.stream);
                 hdr->version = p.hdr.version;
@@ -1245,50 +1274,22 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 hdr->sub_syms = p.hdr.sub_syms;
                 hdr->delta = p.hdr.delta;
                 hdr->subs_per_chunk = p.hdr.subs_per_chunk;
-                hdr->payload_words = total_words;
+                hdr->payload_words = added_words;
                 hdr->payload_bits = STATIC ? my_bits : S.payload_bits;
                 hdr->reserved1 = p.hdr.reserved1;
                 // The magic last, past this part of the chip's cache: somebody who gives up waiting says so first and then
                 // clears the magic the same way, so one of the two sees it.
-                const bool fits = total_words <= p.cap_words && total_words <= 0xffffffffull;
+                const bool fits = added_words <= p.cap_words && added_words <= 0xffffffffull;
                 publish32(&hdr->magic, fits ? p.hdr.magic : 0u);
                 __builtin_amdgcn_s_waitcnt(0);
                 if (__hip_atomic_load(&p.ctrl->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) publish32(&hdr->magic, 0u);
-                if (p.out_bytes) *p.out_bytes = (uint64_t)p.off_payload + 4 * total_words;
+                if (p.out_bytes) *p.out_bytes = (uint64_t)p.off_payload + 4 * added_words;
                 // alignment gaps between the sections are part of the stream: keep them zero
                 for (size_t o = kHeaderBytes + kLenTableBytes + 4 * ((size_t)p.n_chunks + 1); o < p.off_sub_bits; o++) p.stream[o] = 0;
                 for (size_t o = p.off_sub_bits + 2 * (size_t)p.n_chunks * n_runs; o < p.off_payload; o++) p.stream[o] = 0;
             }
         }
-        unsigned long long e = 0;
-        if (placed < published) e = peek64(&places[ticket_of(placed)]);  // (one word, the same for all lanes)
-        if (draws && lane == 0) {
-            S.ticket[(published + 1u) % kSlots] = next_ticket;
-            post_lds(&S.drawn, published + 2u);
-        }
-        if (placed < published) {
-            if (e) {
-                if (lane == 0) {
-                    S.place[placed % kSlots] = e & (kKnown - 1ull);
-                    post_lds(&S.placed, placed + 1u);
-                }
-                placed++;
-                news = true;
-            }
-        }
-        tries = news ? 0u : tries + 1u;
-        // (a limit that is never reached: seconds.  The one that adds up gives up first where a size does not come.)
-        if (tries > (adder ? p.spin_limit : 2u * p.spin_limit)) {
-            if (lane == 0) {
-                const uint32_t was = __hip_atomic_fetch_or(&p.ctrl->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                asm volatile("" : : "v"(was) : "memory");  // (the returned value is waited for)
-                publish32(reinterpret_cast<uint32_t*>(p.stream), 0u);  // the header's magic
-                post_lds(&S.placed, kGone);
-                post_lds(&S.drawn, kGone);
-            }
-            break;
-        }
-        if (!news) __builtin_amdgcn_s_sleep(1);
+        if (more) __syncthreads();  // the images are clear, and what the range left in LDS has been read
     }
 }
 
@@ -1343,19 +1344,20 @@ PackParams pack_params(const uint8_t* d_syms, const Geometry& g, int bits, float
     p.stream = d_stream;
     p.out_bytes = d_out_bytes;
     p.static_max_len = 0;
-    p.spin_limit = test_option(kTestShortWaits) ? 1u : kSpinLimit;
+    p.spin_limit = test_option(kTestShortWaits) ? 0u : kSpinLimit;
     return p;
 }
 
 // Packing of a tensor with more chunk groups than the device holds pack workgroups.
 template <bool STATIC>
 static hipError_t launch_pack_large(const PackParams& p, hipStream_t s) {
-    const uint32_t n_groups = (p.n_chunks + kStreamWaves - 1) / kStreamWaves;
-    if (2u * n_groups > p.n_groups) return hipErrorInvalidValue;  // sizes and places would not fit the look-back words
-    const unsigned grid = n_groups < 256u ? n_groups : 256u;  // one workgroup per compute unit: its images take most of the LDS
+    // One workgroup per compute unit: its images take most of the LDS.  Ranges have four chunks at least, so their sizes
+    // fit the look-back words.
+    if (p.n_groups < pack_groups(p.n_chunks)) return hipErrorInvalidValue;
+    const unsigned grid = p.n_groups < 256u ? p.n_groups : 256u;
     // (7 and 8 bits: a table of pairs would not fit beside the images)
     const bool pairs = p.bits <= 6;
-    const size_t lds = sizeof(StreamShared) + sizeof(uint32_t) * (pairs ? 4096 : 256);
+    const size_t lds = sizeof(StreamShared) + sizeof(uint32_t) * (pairs ? kStreamCodes<true> : kStreamCodes<false>);
     const void* fn = pairs ? reinterpret_cast<const void*>(&k_pack_stream<STATIC, true>)
                            : reinterpret_cast<const void*>(&k_pack_stream<STATIC, false>);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

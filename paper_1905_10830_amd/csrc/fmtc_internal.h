@@ -66,7 +66,7 @@ inline bool make_geometry(int64_t P, int C, int chunk_syms, Geometry* g) {
 
 // Control words of one encoder call (in the workspace).  Zeroed by the first kernel of the call.
 struct alignas(64) CoderCtrl {
-    uint32_t ticket;                  // next chunk group to be packed (pack kernel of large tensors)
+    uint32_t ticket;                  // next range of chunks to be packed (pack kernel of large tensors)
     uint32_t max_len;                 // longest code length (table kernel)
     unsigned long long payload_bits;  // sum of count * length (table kernel)
     uint32_t error;                   // set if a bounded wait of the pack kernel ran out
@@ -83,8 +83,8 @@ struct Workspace {
     size_t off_hist;         // u32 [256] final histogram
     size_t off_enc_table;    // u64 [256]: bit-reversed code | length << 56
     // u64 [pack_groups(n_chunks)], cleared by the first kernel of the call.  Small tensors and the fused encoder: payload
-    // words, unused bits and a flag per group of kPackWaves chunks.  Large tensors: the sizes, then the places of their
-    // groups of kStreamWaves chunks (fewer than half as many; launch_pack_large checks it)
+    // words, unused bits and a flag per group of kPackWaves chunks.  Large tensors: the sizes of their ranges of chunks
+    // (fewer than the groups; launch_pack_large checks it)
     size_t off_lookback;
     size_t off_reserved;     // 4 bytes per chunk, not used: the total stays what buffers have been sized by
     size_t off_syms;         // u8 [V]

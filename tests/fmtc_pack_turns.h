@@ -1,5 +1,6 @@
-// Who packs what, and who waits for whom, in the packer of large tensors (k_pack_stream): the rules that decide whether
-// every wait of a workgroup ends.  Plain C++, so that a model of the protocol on the CPU runs the same rules.
+// Who packs what, and who waits for whom, in a packer whose workgroups take turns: the rules that decide whether every wait of
+// a workgroup ends.  Plain C++, for the model of the protocol on the CPU (pack_turns_model.cpp).  k_pack_stream followed these
+// rules until its workgroups took whole ranges of chunks, with workgroup barriers in place of these waits.
 //
 // A workgroup's turns are the groups of chunks that it claims, one after the other.  Packers keep images of packed chunks
 // until the place of the chunk's turn is known.  A turn's size is published when all its chunks are packed, and its place

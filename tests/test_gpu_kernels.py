@@ -126,6 +126,33 @@ def test_packer_of_many_turns(fmtc, oracle, n_chunks, chunk, C, bits, kind):
     assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
 
 
+# Ranges of chunks: (chunks, symbols a chunk, C, bits, counts) with as many chunks as 256 workgroups have images and one more, a
+# range per workgroup and three, the fewest chunks of that kernel; images of 1024 and of 684 words (code words of nearly 8 and
+# nearly 5 bits), the last of them one round and a chunk.
+RANGE_CASES = [(4097, 64, 16, 6, "gaps"), (256 * 64, 66, 33, 6, "steep"), (256 * 64 + 1, 64, 16, 6, "steep"),
+               (256 * 128 + 3, 99, 9, 4, "gaps"), (256 * 32 + 1, 3200, 32, 8, "flat"), (256 * 48 + 1, 4092, 33, 5, "flat")]
+
+
+@pytest.mark.parametrize("n_chunks,chunk,C,bits,kind", RANGE_CASES, ids=[f"n{c[0]}k{c[1]}b{c[3]}" for c in RANGE_CASES])
+def test_packer_of_chunk_ranges(fmtc, oracle, n_chunks, chunk, C, bits, kind):
+    V = n_chunks * chunk
+    rng = np.random.default_rng(n_chunks)
+    if kind == "flat":
+        sym = rng.integers(0, 1 << bits, V, dtype=np.uint8)
+    else:
+        counts = counts_of(kind, 1 << bits).astype(np.float64)
+        counts = np.where(counts > 0, np.maximum(1, counts * (V / counts.sum()) * 0.9), 0).astype(np.int64)
+        counts[counts.argmax()] += V - counts.sum()
+        sym = np.repeat(np.arange(1 << bits), counts).astype(np.uint8)
+        rng.shuffle(sym)
+    ln = oracle.huffman_lengths(oracle.histogram(sym, bits))
+    ref = oracle.pack(sym, C, bits, 0.5, ln, oracle.canonical_codes(ln), max(chunk, 64))
+    for _ in range(2):
+        stream, nbytes = fmtc.code_symbols(dev(sym), C, bits, 0.5, max(chunk, 64))
+        torch.cuda.synchronize()
+        assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
+
+
 def test_packer_of_large_tensors_gives_up_its_waits(fmtc, oracle):
     """With the limit of its waits at once reached the kernel ends, leaves an invalid stream and harms no later call."""
     C, bits, chunk, n_chunks = 16, 6, 64, 15 * 256 * 2
