@@ -12,6 +12,7 @@
 // whose contraction the workgroup's wavefronts share out (few pixels, other channel
 // counts), and 32 pixels with all channels in LDS (many pixels of such counts).
 #include <atomic>
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
@@ -84,6 +85,7 @@ struct RowParams {
     CoderCtrl* ctrl;
     unsigned long long* lookback;
     uint32_t n_groups;
+    float x_scale;            // k_project_quantize_stream: a power of two, 2^11 s (see there)
     PackParams pk;            // FUSED only: where the container goes
 };
 
@@ -619,18 +621,44 @@ void k_project_quantize_rows(RowParams p) {
 // 112 to 160 channels, a multiple of 16 of them: the same projection with the loops the other way
 // round.  k_project_quantize_rows holds a whole pixel tile twice (the fp32 values of the next tile on their way in, the
 // two f16 parts of this one) and one or two pairs of accumulators: 350 to 450 registers at four and five coefficient
-// tiles, one wavefront per SIMD -- where a vector instruction issues every 8 clocks instead of every 4 and nothing
-// covers a wait.  Here the channel steps are the outer loop: a step's eight channels per lane are converted when
-// their turn comes and go into the accumulators of ALL coefficient tiles at once (32 NCT accumulator registers), and
-// the pixels stream in through two small buffers of two steps each, across tile boundaries, so that between one and
-// two buffers (4 to 8 KB per wavefront) are in flight at any time.  130 registers less at four tiles: two wavefronts
-// per SIMD (eight on one copy of the basis) without spills.  A pixel too large for f16 needs no clamp here: what its
+// tiles, one wavefront per SIMD.  Here the channel steps are the outer loop: a step's eight channels per lane are
+// converted when their turn comes and go into the accumulators of ALL coefficient tiles at once, and the registers they
+// came in are requested again for the same step of the next tile, so that nearly a whole tile (14 to 20 KB per wavefront)
+// is in flight at any time.
+//
+// ONE accumulator per coefficient: with v = S (x - mu), S = 2^11 s a power of two,
+//   2^11 s y = sum T_hi v_hi + sum T_hi v_lo + sum (2^11 T_lo) (2^-11 v_hi)
+// where v_hi = v rounded to f16 and v_lo = v - v_hi rounded to f16, all three products at the same scale.  s brings the
+// range A = Delta 2^(b-1) of the leading coefficient to 1/16 .. 1/8, so that values up to 256 A fit f16 (a pixel beyond is
+// decided exactly in all coefficients) and what v_lo and 2^-11 v_hi lose in the subnormals is below 2^-30 A.  Half the
+// accumulator registers (80 of 160 at five coefficient tiles) are a second wavefront per SIMD, whose vector instructions
+// issue while the first one's matrix instructions run (measured: a 32x32x16 product takes 32 clocks, and five independent
+// vector instructions behind it none), and the quantizer takes one multiply-add where it joined two sums: u = acc g +
+// magic, and the distance to the level is acc g - (u - magic) in another.  (All products being added to the large sum, its
+// error is up to 1.8 times that of two sums: at 112 to 160 channels at most 2^-21.1 |x - mu|_2 against 2^-21.8 where a
+// leading component holds most of the pixel, 2^-22.9 against 2^-23.7 where none does, in random data.  The distance below
+// which a value is decided exactly is that much larger here.)
+//
+// A pixel too large for f16 needs no clamp here: what its
 // infinities make of the matrix product stays in its own column of outputs, all of which are decided exactly, and
 // the clamp of the quantizer keeps the histogram index in range whatever the value.
 // ---------------------------------------------------------------------------
+// x_scale of RowParams: 2^11 s for a step delta at a bit depth (kept within what fp32 and its reciprocal hold).
+static float stream_scale(float delta, int bits) {
+    int e = 0;
+    (void)std::frexp(std::ldexp(delta, bits - 1), &e);  // A in [2^(e-1), 2^e)
+    const int k = 11 - 3 - e;
+    return std::ldexp(1.f, k < -100 ? -100 : (k > 100 ? 100 : k));
+}
+// c clamped between lo and hi (lo <= hi), as signed integers.
+__device__ __forceinline__ uint32_t clamp_pattern3(float u, float lo, float hi) {
+    uint32_t c;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(c) : "v"(u), "s"(lo), "v"(hi));
+    return c;
+}
 // NJA: the tensor's channel count / 16 (the launcher checks it), 2 NCT - 1 or 2 NCT.
 // Planar tensors: a channel's plane starts at a wavefront-uniform address (image of the tile's first pixel) and a lane's
-// place in it is one 32-bit offset (the launcher checks that it fits), so the loads of 16 channels per lane and pair
+// place in it is one 32-bit offset (the launcher checks that it fits), so the loads of 16 channels per lane and step
 // take no 64-bit address each -- which is what the registers of k_project_quantize_rows go to there.
 template <int NCT, int WAVES, int NJA, int LAYOUT>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4)))
@@ -638,15 +666,13 @@ void k_project_quantize_stream(RowParams p) {
     constexpr int THREADS = WAVES * 64;
     constexpr int NJ = NCT * 2;        // steps of 16 channels in the basis operand (of which the first NJA hold channels)
     static_assert(NJA == NJ || NJA == NJ - 1, "channel count");
-    constexpr int NP = (NJ + 1) / 2;   // pairs of steps: the unit of the pixel buffers
+    constexpr int kSets = 4;           // histograms: wavefronts w and w + 4 share one
     extern __shared__ __align__(16) uint4 basis16[];  // [NCT][NJ][2][64], then the histograms
-    __shared__ __align__(16) float s_mu[NCT * 32];
+    __shared__ __align__(16) float s_mu[NCT * 32], s_mu_scaled[NCT * 32];  // mu, and -S mu
     __shared__ uint32_t s_fix_list[WAVES][kFixList];
     __shared__ uint32_t s_fix_tile[WAVES][kFixList];
-    __shared__ uint32_t s_fix_count[WAVES];
-    __shared__ uint32_t s_red[WAVES * 256];
     const int K = 1 << p.bits;
-    uint32_t* whist = reinterpret_cast<uint32_t*>(basis16 + NCT * NJ * 2 * 64);  // [WAVES][K * kHistLanes]
+    uint32_t* whist = reinterpret_cast<uint32_t*>(basis16 + NCT * NJ * 2 * 64);  // [kSets][K * kHistLanes]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -654,8 +680,9 @@ void k_project_quantize_stream(RowParams p) {
     constexpr int C = 16 * NJA;
     typedef float f4_t __attribute__((ext_vector_type(4)));
 
-    // where a tile's pixels lie: this lane's row, or (planar) channel 0 of the image that the tile starts in and this
-    // lane's offset from there (pixel and half)
+    // where a tile's pixels lie: the tile's first row, or (planar) channel 0 of the image that the tile starts in, the same
+    // for all lanes, and this lane's offset from there (pixel and half); rows past the tensor repeat its last pixel, and are
+    // never stored or counted
     struct Place {
         const char* base;
         uint32_t off;
@@ -663,9 +690,9 @@ void k_project_quantize_stream(RowParams p) {
     auto place_of = [&](int64_t tile) __attribute__((always_inline)) {
         Place at{};
         if constexpr (LAYOUT == FMTC_NHWC) {
-            int64_t px = tile * 32 + l32;
-            px = px < p.P ? px : p.P - 1;  // rows past the tensor repeat its last pixel; never stored or counted
-            at.base = reinterpret_cast<const char*>(p.x + px * C + 8 * half);
+            const int64_t left = p.P - 1 - tile * 32;
+            at.base = reinterpret_cast<const char*>(p.x) + (uint64_t)tile * (uint64_t)(32 * 4 * C);
+            at.off = (uint32_t)(left < l32 ? (int)left : l32) * (uint32_t)(4 * C) + 32u * (uint32_t)half;
         } else {
             const uint32_t HW = (uint32_t)p.HW, P = (uint32_t)p.P, px0 = (uint32_t)tile * 32u;
             const uint32_t px = px0 + (uint32_t)l32 < P ? px0 + (uint32_t)l32 : P - 1u;
@@ -675,33 +702,28 @@ void k_project_quantize_stream(RowParams p) {
         }
         return at;
     };
-    // this lane's channels [16 j + 8 half, + 8) of its pixel, steps 2 pr and 2 pr + 1
-    auto load_pair = [&](const Place& at, int pr, f4_t (&buf)[2][2]) __attribute__((always_inline)) {
+    // this lane's channels [16 j + 8 half, + 8) of its pixel
+    auto load_step = [&](const Place& at, int j, f4_t (&raw)[2]) __attribute__((always_inline)) {
+        if constexpr (LAYOUT == FMTC_NHWC) {
+            raw[0] = *reinterpret_cast<const f4_t*>(at.base + 64 * j + at.off);
+            raw[1] = *reinterpret_cast<const f4_t*>(at.base + 64 * j + 16 + at.off);
+        } else {
+            const uint64_t plane_bytes = 4u * (uint64_t)(uint32_t)p.HW;
+            const char* plane = at.base + (uint64_t)(16 * j) * plane_bytes;
 #pragma unroll
-        for (int u = 0; u < 2; u++) {
-            const int j = 2 * pr + u;
-            if (j < NJ && j < NJA) {  // wavefront-uniform
-                if constexpr (LAYOUT == FMTC_NHWC) {
-                    const f4_t* row = reinterpret_cast<const f4_t*>(at.base);
-                    buf[u][0] = row[4 * j];
-                    buf[u][1] = row[4 * j + 1];
-                } else {
-                    const uint64_t plane_bytes = 4u * (uint64_t)(uint32_t)p.HW;
-                    const char* plane = at.base + (uint64_t)(16 * j) * plane_bytes;
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        buf[u][e >> 2][e & 3] = *reinterpret_cast<const float*>(plane + (uint64_t)e * plane_bytes + at.off);
-                }
-            }
+            for (int e = 0; e < 8; e++)
+                raw[e >> 2][e & 3] = *reinterpret_cast<const float*>(plane + (uint64_t)e * plane_bytes + at.off);
         }
     };
+    f4_t raw[NJA][2];
     const int64_t stride = (int64_t)gridDim.x * WAVES;
+    // (neighbouring tiles to one workgroup: dealt to the workgroups first, planar tiles lose the lines that they share, 144
+    // channels, 50176 pixels 19.1 -> 21.2 us)
     int64_t tile = (int64_t)blockIdx.x * WAVES + wave;
-    f4_t bufA[2][2], bufB[2][2];
-    Place here = place_of(tile < p.n_tiles ? tile : 0);
-    if (tile < p.n_tiles) {
-        load_pair(here, 0, bufA);
-        if (NP > 1) load_pair(here, 1, bufB);
+    {
+        const Place here = place_of(tile < p.n_tiles ? tile : 0);
+#pragma unroll
+        for (int j = 0; j < NJA; j++) load_step(here, j, raw[j]);
     }
     zero_coder_scratch(p.ctrl, p.lookback, p.n_groups);
     {
@@ -711,37 +733,50 @@ void k_project_quantize_stream(RowParams p) {
             if (THREADS * i + 64 * wave < NCT * NCT * 256)  // whole wavefronts
                 __builtin_amdgcn_global_load_lds(src + tid + THREADS * i, &basis16[THREADS * i + 64 * wave], 16, 0, 0);
     }
-    if (tid < NCT * 32) s_mu[tid] = p.mu[tid];
-    for (int i = tid; i < WAVES * K * kHistLanes; i += THREADS) whist[i] = 0u;
+    const float S = p.x_scale;
+    if (tid < NCT * 32) {
+        const float m = p.mu[tid];
+        s_mu[tid] = m;
+        s_mu_scaled[tid] = -S * m;
+    }
+    for (int i = tid; i < kSets * K * kHistLanes; i += THREADS) whist[i] = 0u;
 
     const int zero_sym = 1 << (p.bits - 1);
     const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1);
-    const float inv_delta = p.inv_delta;
-    const float inv_delta_lo = p.inv_delta * (1.f / 2048.f);
+    const float per_step = p.inv_delta / S;  // (exact: S is a power of two)
+    const float kappa = 1.75f * p.kappa / S;  // (see above)
+    float minus_one = -1.f;  // (unknown to the compiler, which then takes the multiply-add on the f16 part as it is)
+    asm("" : "+s"(minus_one));
     constexpr uint32_t kMagicBits = 0x4B400000u;  // 1.5 * 2^23: see k_project_quantize_rows
     const float magic = 12582912.f + (float)zero_sym;
     const float magic_lo = 12582912.f, magic_hi = 12582912.f + (float)(2 * zero_sym - 1);
-    uint32_t* wh0 = whist + wave * K * kHistLanes;
+    uint32_t* wh0 = whist + (wave % kSets) * K * kHistLanes;
     uint32_t* wh = wh0 + (lane & (kHistLanes - 1));
     static_assert(kHistLanes * sizeof(uint32_t) == 64, "shift of the histogram address");
     typedef __attribute__((address_space(3))) uint32_t lds_u32;
     const uint32_t wh_magic = (uint32_t)(uintptr_t)(lds_u32*)wh - (kMagicBits << 6);
-    auto hist_add = [&](uint32_t ub) {
-        __hip_atomic_fetch_add((lds_u32*)(uintptr_t)((ub << 6) + wh_magic), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    auto hist_add = [&](uint32_t ub, uint32_t one) {
+        __hip_atomic_fetch_add((lds_u32*)(uintptr_t)((ub << 6) + wh_magic), one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     uint32_t* fix_list = s_fix_list[wave];
     uint32_t* fix_tile = s_fix_tile[wave];
-    uint32_t* fix_count = &s_fix_count[wave];
-    if (lane == 0) *fix_count = 0u;
+    uint32_t n_fix = 0;  // values listed, the same in all lanes
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's part of the basis has landed in LDS
     __syncthreads();
 
     // exact decision of the listed values (as in k_project_quantize_rows)
     auto resolve_list = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_waitcnt(0x0F70);
-        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)*fix_count);
+        // (None of this rare path's addresses is to be kept in registers over the loop outside: where it starts from is made
+        // unknown here.)
+        int ln = lane;
+        const float *x = p.x, *Trow = p.Trow;
+        uint8_t* syms = p.syms;
+        asm volatile("" : "+v"(ln), "+s"(x), "+s"(Trow), "+s"(syms));
+        const uint32_t n = n_fix;
+        wave_sync_lds();
         for (uint32_t base = 0; base < n; base += 4) {
-            const uint32_t idx = base + (uint32_t)(lane >> 4);
+            const uint32_t idx = base + (uint32_t)(ln >> 4);
             const bool active = idx < n;
             const uint32_t e = active ? fix_list[idx] : 0u;
             const int k = (int)(e & 255u), pl = (int)((e >> 8) & 31u);
@@ -756,165 +791,144 @@ void k_project_quantize_stream(RowParams p) {
             double part = 0.0;
             if (active)
 #pragma unroll 5
-                for (int c = lane & 15; c < C; c += 16)
-                    part += (double)p.Trow[(size_t)k * C + c] * ((double)p.x[xbase + c * xstride] - (double)s_mu[c]);
+                for (int c = ln & 15; c < C; c += 16)
+                    part += (double)Trow[(size_t)k * C + c] * ((double)x[xbase + c * xstride] - (double)s_mu[c]);
 #pragma unroll
             for (int o = 8; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the 16-lane group
             double qd = rint(part / (double)p.delta);
             qd = fmin(fmax(qd, (double)lo), (double)hi);
             const uint32_t sfix = (uint32_t)((int)qd + zero_sym);
-            if (active && (lane & 15) == 0 && sfix != old) {
+            if (active && (ln & 15) == 0 && sfix != old) {
                 atomicSub(&wh0[old * kHistLanes], 1u);
                 atomicAdd(&wh0[sfix * kHistLanes], 1u);
-                p.syms[qpx * C + k] = (uint8_t)sfix;
+                syms[qpx * C + k] = (uint8_t)sfix;
             }
         }
         wave_sync_lds();
-        if (lane == 0) *fix_count = 0u;
-        wave_sync_lds();
+        n_fix = 0u;
     };
 
-    // One pixel tile.  SWAP (a compile-time flag): the roles of the two buffers are exchanged (see the loop below).
-    auto tile_body = [&](auto swap_c, const int64_t tile) __attribute__((always_inline)) {
-        constexpr bool SWAP = decltype(swap_c)::value;
+    for (; tile < p.n_tiles; tile += stride) {
         const int64_t next_tile = tile + stride;
-        const Place next = place_of(next_tile < p.n_tiles ? next_tile : 0);
-        const int64_t px = tile * 32 + l32;
-        const bool px_ok = px < p.P;
-        floatx16 am[NCT], ac[NCT];
+        const bool more = next_tile < p.n_tiles;
+        const Place next = place_of(more ? next_tile : 0);
+        const bool px_ok = l32 < p.P - tile * 32;
+        f4_t coming[NJA][2];  // (in the registers of `raw`: see below)
+        floatx16 acc[NCT];
         float n2 = 0.f;
         const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        // one step: this lane's eight channels converted, then into every coefficient tile's accumulators
-        auto step = [&](int j, const f4_t (&raw)[2]) __attribute__((always_inline)) {
-            halfx8 xh, xl;
+#pragma unroll
+        for (int j = 0; j < NJA; j++) {
+            // one step: this lane's eight channels converted, then into every coefficient tile's accumulators
+            halfx8 vh, vl, vt;
 #pragma unroll
             for (int q = 0; q < 2; q++) {
-                const float4 m = *reinterpret_cast<const float4*>(&s_mu[16 * j + 8 * half + 4 * q]);
+                const float4 m = *reinterpret_cast<const float4*>(&s_mu_scaled[16 * j + 8 * half + 4 * q]);
                 const float mv[4] = {m.x, m.y, m.z, m.w};
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const float v = raw[q][i] - mv[i];
+                    const float v = __builtin_fmaf(raw[j][q][i], S, mv[i]);  // S (x - mu) as if rounded before the scaling
                     n2 = __builtin_fmaf(v, v, n2);
-                    const _Float16 vh = (_Float16)v;
-                    xh[4 * q + i] = vh;
-                    xl[4 * q + i] = (_Float16)__builtin_fmaf((float)vh, -2048.f, v * 2048.f);  // 2^11 (v - vh), exact
+                    const _Float16 h = (_Float16)v;
+                    vh[4 * q + i] = h;
+                    vl[4 * q + i] = (_Float16)__builtin_fmaf((float)h, minus_one, v);  // v - h, exact
                 }
             }
+            // (converted, and their squares added up, before their registers are requested again: the compiler would rather do
+            // that behind the branch, with a second set of registers for the loads)
+            asm volatile("" : "+v"(vh), "+v"(vl), "+v"(n2));
+            if (more) load_step(next, j, coming[j]);
+            vt = vh * (_Float16)(1.f / 2048.f);
 #pragma unroll
             for (int kt = 0; kt < NCT; kt++) {
                 // (a truncated basis' zero rows are multiplied like any others: their coefficients come out zero)
                 const halfx8 th = __builtin_bit_cast(halfx8, basis16[((kt * NJ + j) * 2) * 64 + lane]);
                 const halfx8 tl = __builtin_bit_cast(halfx8, basis16[((kt * NJ + j) * 2 + 1) * 64 + lane]);
-                am[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, xh, j ? am[kt] : zero, 0, 0, 0);
-                ac[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, xl, j ? ac[kt] : zero, 0, 0, 0);
-                ac[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl, xh, ac[kt], 0, 0, 0);
+                acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, vl, j ? acc[kt] : zero, 0, 0, 0);
+                acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(tl, vt, acc[kt], 0, 0, 0);
+                acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(th, vh, acc[kt], 0, 0, 0);
             }
-            // (steps stay apart in the schedule: merged, their operands would not fit the registers of two wavefronts
-            // per SIMD)
+            // (The basis of two coefficient tiles is read ahead of its products, not of all five: their operands would not fit
+            // the registers of two wavefronts per SIMD.  Nor would those of two steps.)
+            __builtin_amdgcn_sched_group_barrier(0x100, 2 + 4, 0);  // LDS reads: the means, two coefficient tiles
+#pragma unroll
+            for (int kt = 0; kt < NCT; kt++) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);  // matrix products
+                if (kt + 2 < NCT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
-        };
-        // Pair pr of this tile sits in buffer A or B as (pr odd) != SWAP says; a buffer is requested again as soon as
-        // its steps are converted: for the pair two further on, which past this tile's end is pair 0 or 1 of the next
-        // tile (whose SWAP is this one's for an even number of pairs and the opposite for an odd one, so that pair
-        // finds its data where it looks for it).
-#pragma unroll
-        for (int pr = 0; pr < NP; pr++) {
-            const bool in_b = ((pr & 1) != 0) != SWAP;
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-                const int j = 2 * pr + u;
-                if (j < NJ && j < NJA) {  // wavefront-uniform
-                    if (in_b) step(j, bufB[u]); else step(j, bufA[u]);
-                }
-            }
-            const int npr = pr + 2;
-            if (npr < NP) {
-                if (in_b) load_pair(here, npr, bufB); else load_pair(here, npr, bufA);
-            } else if (next_tile < p.n_tiles && npr - NP < NP) {
-                if (in_b) load_pair(next, npr - NP, bufB); else load_pair(next, npr - NP, bufA);
-            }
         }
-        here = next;
         n2 += __shfl_xor(n2, 32, 64);  // the other half of the pixel
-        const bool force = !(n2 < 1.0e9f);  // too large for f16 (or not finite): every coefficient decided exactly
-        const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
+        const bool force = !(n2 < 3.6e9f);  // too large for f16 (or not finite): every coefficient decided exactly
+        const float tau = fminf(fmaxf(kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
         const float near_limit = force ? -1.f : 0.5f - tau;
 
 #pragma unroll
         for (int kt = 0; kt < NCT; kt++) {
             const bool k_ok = kt * 32 + 16 * half < C && px_ok;  // (C a multiple of 16: a lane's 16 coefficients all in or all out)
+            const uint32_t one = k_ok ? 1u : 0u;  // (what does not count adds nothing: no branch per value)
             uint32_t word[4], ub[16];
             float maxd = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r++) {
-                const float t = __builtin_fmaf(ac[kt][r], inv_delta_lo, am[kt][r] * inv_delta);
-                const float u = t + magic;  // round half to even
-                maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
-                ub[r] = clamp_pattern(u, magic_lo, magic_hi);
-                if (k_ok) hist_add(ub[r]);
+                const float u = __builtin_fmaf(acc[kt][r], per_step, magic);  // round half to even
+                maxd = max_or_nan(maxd, fabsf(__builtin_fmaf(acc[kt][r], per_step, magic - u)));
+                ub[r] = clamp_pattern3(u, magic_lo, magic_hi);
+                hist_add(ub[r], one);
             }
 #pragma unroll
             for (int g = 0; g < 4; g++)
                 word[g] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(ub[4 * g + 3], ub[4 * g + 2], 0x0c0c0400u),
                                                 __builtin_amdgcn_perm(ub[4 * g + 1], ub[4 * g], 0x0c0c0400u), 0x05040100u);
             if (k_ok)
-                *reinterpret_cast<uint4*>(p.syms + px * C + kt * 32 + 16 * half) = make_uint4(word[0], word[1], word[2], word[3]);
+                *reinterpret_cast<uint4*>(p.syms + (uint64_t)tile * (uint64_t)(32 * C) + kt * 32 + (uint32_t)(l32 * C + 16 * half)) =
+                    make_uint4(word[0], word[1], word[2], word[3]);
             if (__builtin_expect(__any(!(maxd <= near_limit) && k_ok), 0)) {
                 // the values too close to a rounding boundary go to the wavefront's list (resolved when it is full
                 // and after the last tile)
                 uint32_t near_mask = 0;
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
-                    const float t = __builtin_fmaf(ac[kt][r], inv_delta_lo, am[kt][r] * inv_delta);
-                    if (!(fabsf(t - __builtin_rintf(t)) <= near_limit) && k_ok) near_mask |= 1u << r;
+                    const float u = __builtin_fmaf(acc[kt][r], per_step, magic);
+                    if (!(fabsf(__builtin_fmaf(acc[kt][r], per_step, magic - u)) <= near_limit) && k_ok) near_mask |= 1u << r;
                 }
-                const int k0 = kt * 32 + 16 * half;
-                const uint32_t incoming = wave_sum((uint32_t)__popc(near_mask));
-                if (*fix_count + incoming > (uint32_t)kFixList) resolve_list();
-                if (incoming > (uint32_t)kFixList) {
+                // (one after the other in scalar registers: mostly it is one value.  Counted by shuffles, and placed by LDS
+                // additions, they held the wavefront up for 0.7 us each time.)
+                unsigned long long lanes = __ballot(near_mask != 0u);
 #pragma unroll 1
-                    for (int r = 0; r < 16; r++) {
-                        if ((near_mask >> r) & 1u) {
-                            const uint32_t slot = atomicAdd(fix_count, 1u);
-                            fix_list[slot] = (uint32_t)(k0 + r) | ((uint32_t)l32 << 8) |
-                                             (((word[r >> 2] >> (8 * (r & 3))) & 255u) << 13);
-                            fix_tile[slot] = (uint32_t)tile;
-                        }
-                        wave_sync_lds();
-                        resolve_list();
-                    }
-                } else {
-                    while (near_mask) {
-                        const int r = __ffs((int)near_mask) - 1;
-                        near_mask &= near_mask - 1;
-                        uint32_t sy = 0;
+                while (lanes) {
+                    const int from = __ffsll((long long)lanes) - 1;
+                    lanes &= lanes - 1ull;
+                    uint32_t mask = (uint32_t)__builtin_amdgcn_readlane((int)near_mask, from);
+                    uint32_t w[4];
 #pragma unroll
-                        for (int g = 0; g < 4; g++)
-                            if (g == (r >> 2)) sy = (word[g] >> (8 * (r & 3))) & 255u;
-                        const uint32_t slot = atomicAdd(fix_count, 1u);
-                        fix_list[slot] = (uint32_t)(k0 + r) | ((uint32_t)l32 << 8) | (sy << 13);
-                        fix_tile[slot] = (uint32_t)tile;
+                    for (int g = 0; g < 4; g++) w[g] = (uint32_t)__builtin_amdgcn_readlane((int)word[g], from);
+#pragma unroll 1
+                    while (mask) {
+                        const int r = __ffs((int)mask) - 1;
+                        mask &= mask - 1u;
+                        const uint32_t of4 = r < 8 ? (r < 4 ? w[0] : w[1]) : (r < 12 ? w[2] : w[3]);
+                        if (lane == 0) {
+                            fix_list[n_fix] = (uint32_t)(kt * 32 + 16 * (from >> 5) + r) | ((uint32_t)(from & 31) << 8) |
+                                              (((of4 >> (8 * (r & 3))) & 255u) << 13);
+                            fix_tile[n_fix] = (uint32_t)tile;
+                        }
+                        n_fix++;
+                        if (n_fix == (uint32_t)kFixList) resolve_list();
                     }
-                    wave_sync_lds();
                 }
             }
         }
-    };
-    if constexpr ((NP & 1) != 0) {
-        for (;;) {
-            if (tile >= p.n_tiles) break;
-            tile_body(std::false_type{}, tile);
-            tile += stride;
-            if (tile >= p.n_tiles) break;
-            tile_body(std::true_type{}, tile);
-            tile += stride;
+#pragma unroll
+        for (int j = 0; j < NJA; j++) {
+            raw[j][0] = coming[j][0];
+            raw[j][1] = coming[j][1];
         }
-    } else {
-        for (; tile < p.n_tiles; tile += stride) tile_body(std::false_type{}, tile);
     }
-    if (*fix_count) resolve_list();
+    if (n_fix) resolve_list();
     __syncthreads();
-    for (int row = tid; row < WAVES * K; row += THREADS) {
+    uint32_t* s_red = reinterpret_cast<uint32_t*>(basis16);  // (not read any more)
+    for (int row = tid; row < kSets * K; row += THREADS) {
         const uint4* r4 = reinterpret_cast<const uint4*>(whist + (size_t)row * kHistLanes);
         uint32_t total = 0;
 #pragma unroll
@@ -928,7 +942,7 @@ void k_project_quantize_stream(RowParams p) {
     if (tid < K) {
         uint32_t total = 0;
 #pragma unroll
-        for (int q = 0; q < WAVES; q++) total += s_red[q * K + tid];
+        for (int q = 0; q < kSets; q++) total += s_red[q * K + tid];
         p.hist_parts[(size_t)blockIdx.x * K + tid] = total;
     }
 }
@@ -951,25 +965,25 @@ static size_t rows_lds(int nct, int bits, int waves) {
 static RowsPlan plan_rows(int C, int64_t P, int64_t HW, int layout, int bits) {
     RowsPlan r{};
     r.nct = (C + 31) / 32;
-    // 128 channels: eight wavefronts on one copy of the basis, two per SIMD, each working tile by tile with one pair
-    // of accumulators (two four-wavefront workgroups with a copy each would not fit a compute unit's LDS).  Measured
-    // at 25.7 M values: 57 us against 63 us with four wavefronts, one per SIMD.  (The same form for 144 channels
-    // spills registers: 119 us against 80 us.)
-    // (planar tensors: the loads' addresses do not fit the registers either; 8 bits: eight wavefronts' histograms do
-    // not fit LDS beside the basis)
-    const bool eight = r.nct == 4 && layout == FMTC_NHWC && (P + 31) / 32 > 1024 && rows_lds(r.nct, bits, 8) <= 144 * 1024;
-    r.waves = eight ? 8 : 4;
     const bool offsets_fit = layout == FMTC_NHWC || planar_offsets_fit(C, P, HW);
+    const int64_t tiles = (P + 31) / 32;
+    // 97 to 128 channels, channels last: eight wavefronts on one copy of the basis, two per SIMD, each working tile by
+    // tile with one pair of accumulators (two four-wavefront workgroups with a copy each would not fit a compute unit's
+    // LDS).  (Planar tensors: the loads' addresses do not fit the registers; 8 bits: eight wavefronts' histograms do not
+    // fit LDS beside the basis.)
+    bool eight = r.nct == 4 && layout == FMTC_NHWC && tiles > 1024 && rows_lds(r.nct, bits, 8) <= 144 * 1024;
+    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, with eight wavefronts on one copy of
+    // the basis where there are more tiles than SIMDs.  Kernel times, us, the other forms of this file before : now: 128
+    // channels, channels last, 200704 pixels 51.5 : 39.4 (8 bits 67 : 46, 4 bits 47 : 37), 100352 33.0 : 25.1, 65568 26.2 :
+    // 19.5; planar 57.3 : 42.6 and 50176 pixels 22.3 : 15.7; 112 channels, 100352 31.0 : 22.1; 144, 200704 67.7 : 50.3 (7 bits
+    // 75 : 53, planar 71 : 53), 33000 22.2 : 16.8; 160, 100352 43.2 : 32.4.  Up to 1024 tiles four wavefronts: 128 channels,
+    // 25088 pixels 12.7, 13.7 with eight.  (The first few tiles beyond 1024, channels last, are left to the eight-wavefront
+    // form above.)
+    r.stream = r.nct >= 4 && C % 16 == 0 && offsets_fit && !(eight && tiles <= 1056);
+    if (r.stream) eight = tiles > 1024;
+    r.waves = eight ? 8 : 4;
     // planar: vec = a multiple of 16 channels and offsets within the images of a pixel tile that fit 32 bits
     r.vec = layout == FMTC_NHWC ? C % 4 == 0 : C % 16 == 0 && offsets_fit;
-    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, four wavefronts.
-    // (Measured: 144 channels, 28.9 M values, 79 -> 62 us; 128 channels, 3.2 M values, 15.9 -> 13.6 us.  With more
-    // tiles than SIMDs at four coefficient tiles the eight-wavefront form of k_project_quantize_rows stays: 50 us
-    // at 25.7 M values against 53 us for this kernel with four wavefronts and 48 to 58 us with eight, whose registers
-    // fit or spill with the compiler's schedule.  Planar: 128 channels, N = 256, 28 x 28 75 us in
-    // k_project_quantize_rows, 55.7 here; N = 32 16.7 and 11.7; 144 channels, N = 64, 28 x 28 42.9 in the tiled product,
-    // 26.1 here, with half of the basis truncated 28.1 and 23.8.)
-    r.stream = (r.nct == 5 || (r.nct == 4 && !eight)) && C % 16 == 0 && offsets_fit;
     return r;
 }
 
@@ -999,6 +1013,7 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     p.ctrl = cs.ctrl;
     p.lookback = cs.lookback;
     p.n_groups = cs.n_groups;
+    p.x_scale = stream_scale(delta, bits);
     p.pk = PackParams{};
     if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback)
         return hipErrorInvalidValue;  // (a field left out would be a wild pointer on the device)
@@ -1017,10 +1032,9 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     *n_parts = (int)gx;
     hipError_t el = hipSuccess;
     if (pl.stream) {
-        const int swaves = 4;
         const bool whole = b.C == nct * 32;  // else 16 channels less
-        const size_t slds = rows_lds(nct, bits, swaves);
-        int64_t sgx = (p.n_tiles + swaves - 1) / swaves;
+        const size_t slds = rows_lds(nct, bits, 4);  // (four histograms whatever the wavefronts)
+        int64_t sgx = (p.n_tiles + waves - 1) / waves;
         if (sgx > 256) sgx = 256;  // one workgroup per compute unit (the basis takes 64 to 100 KB of its LDS)
         *n_parts = (int)sgx;
 #define FMTC_STREAM_J(NCT, WV, NJA, LAY)                                                                         \
@@ -1034,8 +1048,13 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     do {                                                                                                         \
         if (whole) FMTC_STREAM_J(NCT, WV, 2 * NCT, LAY); else FMTC_STREAM_J(NCT, WV, 2 * NCT - 1, LAY);          \
     } while (0)
-        if (layout == FMTC_NHWC) { if (nct == 5) FMTC_STREAM(5, 4, FMTC_NHWC); else FMTC_STREAM(4, 4, FMTC_NHWC); }
-        else                     { if (nct == 5) FMTC_STREAM(5, 4, FMTC_NCHW); else FMTC_STREAM(4, 4, FMTC_NCHW); }
+#define FMTC_STREAM_W(NCT, LAY)                                                                                  \
+    do {                                                                                                         \
+        if (eight) FMTC_STREAM(NCT, 8, LAY); else FMTC_STREAM(NCT, 4, LAY);                                      \
+    } while (0)
+        if (layout == FMTC_NHWC) { if (nct == 5) FMTC_STREAM_W(5, FMTC_NHWC); else FMTC_STREAM_W(4, FMTC_NHWC); }
+        else                     { if (nct == 5) FMTC_STREAM_W(5, FMTC_NCHW); else FMTC_STREAM_W(4, FMTC_NCHW); }
+#undef FMTC_STREAM_W
 #undef FMTC_STREAM_J
 #undef FMTC_STREAM
         return el;
