@@ -716,10 +716,14 @@ void k_project_quantize_stream(RowParams p) {
         }
     };
     f4_t raw[NJA][2];
-    const int64_t stride = (int64_t)gridDim.x * WAVES;
-    // (neighbouring tiles to one workgroup: dealt to the workgroups first, planar tiles lose the lines that they share, 144
-    // channels, 50176 pixels 19.1 -> 21.2 us)
+    // Whole rounds of tiles go to the wavefronts of the grid in order (neighbouring tiles to one workgroup: dealt to the
+    // workgroups first, planar tiles lose the lines that they share, 144 channels, 50176 pixels 19.1 -> 21.2 us), the tiles
+    // of the last one to the workgroups first: a few of them have a compute unit each.
+    const int64_t stride = (int64_t)gridDim.x * WAVES, whole = p.n_tiles - (int64_t)((uint32_t)p.n_tiles % (uint32_t)stride);
+    const int64_t last = whole + (int64_t)wave * gridDim.x + blockIdx.x;
+    auto tile_after = [&](int64_t t) { return t + stride < whole ? t + stride : (t < whole ? last : p.n_tiles); };
     int64_t tile = (int64_t)blockIdx.x * WAVES + wave;
+    if (tile >= whole) tile = last;
     {
         const Place here = place_of(tile < p.n_tiles ? tile : 0);
 #pragma unroll
@@ -765,7 +769,9 @@ void k_project_quantize_stream(RowParams p) {
     __syncthreads();
 
     // exact decision of the listed values (as in k_project_quantize_rows)
-    auto resolve_list = [&]() __attribute__((always_inline)) {
+    // ALL: a value's channels all in flight together (after the last tile, where nothing else needs the registers)
+    auto resolve_list = [&](auto all_c) __attribute__((always_inline)) {
+        constexpr int kFlight = decltype(all_c)::value ? NJA : 2;
         __builtin_amdgcn_s_waitcnt(0x0F70);
         // (None of this rare path's addresses is to be kept in registers over the loop outside: where it starts from is made
         // unknown here.)
@@ -789,10 +795,21 @@ void k_project_quantize_stream(RowParams p) {
                 xstride = p.HW;
             }
             double part = 0.0;
-            if (active)
-#pragma unroll 5
-                for (int c = ln & 15; c < C; c += 16)
-                    part += (double)Trow[(size_t)k * C + c] * ((double)x[xbase + c * xstride] - (double)s_mu[c]);
+            const int k_in = active ? k : 0;
+            if (!active) xbase = 0;  // (lanes without a value add up something that nobody looks at)
+#pragma unroll 1
+            for (int c0 = 0; c0 < NJA; c0 += kFlight) {
+                float tv[kFlight], xv[kFlight];
+#pragma unroll
+                for (int q = 0; q < kFlight; q++) {
+                    const int c = 16 * (c0 + q < NJA ? c0 + q : NJA - 1) + (ln & 15);
+                    tv[q] = Trow[(size_t)k_in * C + c];
+                    xv[q] = x[xbase + c * xstride];
+                }
+#pragma unroll
+                for (int q = 0; q < kFlight; q++)
+                    if (c0 + q < NJA) part += (double)tv[q] * ((double)xv[q] - (double)s_mu[16 * (c0 + q) + (ln & 15)]);
+            }
 #pragma unroll
             for (int o = 8; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);  // stays inside the 16-lane group
             double qd = rint(part / (double)p.delta);
@@ -808,8 +825,8 @@ void k_project_quantize_stream(RowParams p) {
         n_fix = 0u;
     };
 
-    for (; tile < p.n_tiles; tile += stride) {
-        const int64_t next_tile = tile + stride;
+    for (; tile < p.n_tiles; tile = tile_after(tile)) {
+        const int64_t next_tile = tile_after(tile);
         const bool more = next_tile < p.n_tiles;
         const Place next = place_of(more ? next_tile : 0);
         const bool px_ok = l32 < p.P - tile * 32;
@@ -914,7 +931,7 @@ void k_project_quantize_stream(RowParams p) {
                             fix_tile[n_fix] = (uint32_t)tile;
                         }
                         n_fix++;
-                        if (n_fix == (uint32_t)kFixList) resolve_list();
+                        if (n_fix == (uint32_t)kFixList) resolve_list(std::false_type{});
                     }
                 }
             }
@@ -925,7 +942,7 @@ void k_project_quantize_stream(RowParams p) {
             raw[j][1] = coming[j][1];
         }
     }
-    if (n_fix) resolve_list();
+    if (n_fix) resolve_list(std::true_type{});
     __syncthreads();
     uint32_t* s_red = reinterpret_cast<uint32_t*>(basis16);  // (not read any more)
     for (int row = tid; row < kSets * K; row += THREADS) {
