@@ -422,36 +422,37 @@ __device__ __forceinline__ bool decode_run_bytes(const uint32_t* pw, uint32_t nw
                                                  const DecTables& T, uint8_t* out) {
     constexpr uint32_t kMask = (1u << kLutBits) - 1u;
     uint32_t bit = start < 32u * nwords ? start : 32u * nwords;  // (side information of a corrupt stream)
-    bool ok = true;
-    uint32_t i = 0;
+    uint32_t bad = 0u, i = 0u;
+    // An entry's symbols, at the current position; the next entry is requested before they are stored (the LDS serves a
+    // wavefront in order: behind the three stores the chain of entries waits for them too).
+    auto put = [&](uint32_t e, uint32_t at) {
+        out[at] = (uint8_t)e;
+        out[at + 1] = (uint8_t)(e >> 8);
+        out[at + 2] = (uint8_t)(e >> 16);
+    };
+    uint32_t lo = pw[bit >> 5], hi = pw[(bit >> 5) + 1u];
     while (i < cnt) {
-        const uint32_t* pp = pw + (bit >> 5);
-        const uint32_t lo = pp[0], hi = pp[1];
         const unsigned long long win = ((unsigned long long)hi << 32) | lo;
         uint32_t sh = bit & 31u;
-        // first entry: i < 64, the store stays inside the run's 64 + 4 bytes
-        uint32_t e = T.lut[lut_slot(__builtin_amdgcn_alignbit(hi, lo, sh) & kMask)];
-        out[i] = (uint8_t)e;
-        out[i + 1] = (uint8_t)(e >> 8);
-        out[i + 2] = (uint8_t)(e >> 16);
-        i += e >> 29;
-        uint32_t l = (e >> 24) & 31u;
-        sh += l;
-        bit += l;
-#pragma unroll
-        for (int step = 1; step < 3; step++) {
-            e = T.lut[lut_slot((uint32_t)(win >> sh) & kMask)];
-            const uint32_t io = i < 64u ? i : 64u;
-            out[io] = (uint8_t)e;
-            out[io + 1] = (uint8_t)(e >> 8);
-            out[io + 2] = (uint8_t)(e >> 16);
-            i += e >> 29;
-            l = (e >> 24) & 31u;
-            sh += l;
-            bit += l;
-        }
-        if (__builtin_expect(__any((e >> 29) == 0 && i < cnt), 0)) {
-            if ((e >> 29) == 0 && i < cnt) {
+        const uint32_t e0 = T.lut[lut_slot(__builtin_amdgcn_alignbit(hi, lo, sh) & kMask)];
+        const uint32_t l0 = (e0 >> 24) & 31u;
+        sh += l0;
+        const uint32_t e1 = T.lut[lut_slot((uint32_t)(win >> sh) & kMask)];
+        put(e0, i);  // i < 64: the store stays inside the run's 64 + 4 bytes
+        i += e0 >> 29;
+        const uint32_t l1 = (e1 >> 24) & 31u;
+        sh += l1;
+        const uint32_t e2 = T.lut[lut_slot((uint32_t)(win >> sh) & kMask)];
+        put(e1, i < 64u ? i : 64u);
+        i += e1 >> 29;
+        bit += l0 + l1 + ((e2 >> 24) & 31u);
+        lo = pw[bit >> 5];
+        hi = pw[(bit >> 5) + 1u];
+        put(e2, i < 64u ? i : 64u);
+        i += e2 >> 29;
+        const bool is_long = (e2 >> 29) == 0 && i < cnt;
+        if (__builtin_expect(__any(is_long), 0)) {
+            if (is_long) {
                 // A code longer than the table starts at the cursor.  The next 32 bits, first stream bit on top:
                 const uint32_t* qq = pw + (bit >> 5);
                 const uint32_t v = __brev(__builtin_amdgcn_alignbit(qq[1], qq[0], bit & 31u));
@@ -475,7 +476,7 @@ __device__ __forceinline__ bool decode_run_bytes(const uint32_t* pw, uint32_t nw
                     }
                     if (len <= 32) {
                         const uint32_t off = (v >> (32 - len)) - (uint32_t)T.first_code[len];
-                        if (off >= T.cnt_len[len]) ok = false;
+                        if (off >= T.cnt_len[len]) bad = 1u;
                         sym = T.sorted_sym[((v >> (32 - len)) + T.rank_of_code[len]) & 255u];
                     } else {
                         // longer than 32 bits (needs a histogram as skewed as the Fibonacci numbers): bit by bit
@@ -495,7 +496,7 @@ __device__ __forceinline__ bool decode_run_bytes(const uint32_t* pw, uint32_t nw
                             }
                         }
                         if (!found) {
-                            ok = false;
+                            bad = 1u;
                             len = kMaxLen;
                         }
                     }
@@ -503,10 +504,12 @@ __device__ __forceinline__ bool decode_run_bytes(const uint32_t* pw, uint32_t nw
                 out[i] = (uint8_t)sym;
                 i++;
                 bit += len;
+                lo = pw[bit >> 5];
+                hi = pw[(bit >> 5) + 1u];
             }
         }
     }
-    return ok;
+    return bad == 0u;
 }
 
 struct DecodeParams {
@@ -1121,6 +1124,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     bool pay_ok = guess_valid && pay_pre;
     uint32_t pay_w0 = guess_w0, pay_w1 = guess_w1;
     const uint32_t u_step = gridDim.x * WAVES;
+    // The wavefronts with a unit more than the others are the last to end: theirs go first.
+    if (ch_first < un.n_units % u_step && un.n_units > u_step) __builtin_amdgcn_s_setprio(2);
     for (uint32_t u = ch_first; u < un.n_units; u += u_step) {
         // ---- variable length decoding of the unit into the wavefront's tile ----
         const UnitBits ub = open_unit(sv, un, cur, u * un.m, chunks_of(u), last_syms, lane);
