@@ -1465,12 +1465,12 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
         p.pay_words = 128u * (uint32_t)bits + 64u;
         auto lds_dyn = [&](int wv) { return lds_basis + (size_t)wv * (p.pay_words + kPayOverrun) * 4; };
         auto lds_all = [&](int wv) { return lds_dyn(wv) + sizeof(DecTables) + (size_t)wv * kChunkTileBytes + (size_t)ncs * 128 + 64; };
-        // One, two or four wavefronts per SIMD as the chunks outnumber the SIMDs of the device: the variable length
-        // decoding is a chain of dependent LDS reads, and the other wavefronts' work fills its waits.  (Three channel
-        // tiles need more registers, five more LDS, than two wavefronts per SIMD leave; four per SIMD fit up to two
-        // channel tiles.)
-        int waves = 4;
-        if (g.n_chunks > 1024 && ncs != 3 && ncs != 5) waves = 8;
+        // Two or four wavefronts per SIMD: the variable length decoding is a chain of dependent LDS reads, and the other
+        // wavefronts' work fills its waits; where there are fewer units than wavefronts they still build the tables in half
+        // the time.  (Four wavefronts per workgroup up to 1024 chunks before, us: 64 channels, 3136 pixels, 8 bits 17.4 -> 15.8;
+        // 128, 25088 pixels, 6 bits 19.7 -> 17.1; 100, 27621, 7 bits 26.7 -> 23.7; 30, 5000 14.0 -> 12.4.  Five channel tiles
+        // need more LDS than two wavefronts per SIMD leave; four per SIMD fit up to two channel tiles.)
+        int waves = ncs == 5 ? 4 : 8;
         if (g.n_chunks > 3072 && ncs <= 2 && C == ncs * 32 && fixed_ok && lds_all(16) <= 160 * 1024) waves = 16;
         // 128 to 160 channels: three wavefronts per SIMD with the lower parts of the basis left in global memory
         // (k_decode_chunks<..., LOG>); built for the channel counts 128 and 144, channels last (with a channel count
@@ -1512,10 +1512,10 @@ hipError_t launch_decode(const BasisDevice* b, const uint8_t* d_stream, size_t b
 #define FMTC_DECC(NCT, LAY, AL, WV) FMTC_DECC_F(NCT, LAY, AL, WV, 0, false)
 #define FMTC_DECC_N(LAY, AL)                                                                                     \
     do {                                                                                                         \
-        if (ncs == 1) { if (waves == 8) FMTC_DECC(1, LAY, AL, 8); else FMTC_DECC(1, LAY, AL, 4); }               \
-        else if (ncs == 2) { if (waves == 8) FMTC_DECC(2, LAY, AL, 8); else FMTC_DECC(2, LAY, AL, 4); }          \
-        else if (ncs == 3) FMTC_DECC(3, LAY, AL, 4);                                                             \
-        else { if (waves == 8) FMTC_DECC(4, LAY, AL, 8); else FMTC_DECC(4, LAY, AL, 4); }                        \
+        if (ncs == 1) FMTC_DECC(1, LAY, AL, 8);                                                                  \
+        else if (ncs == 2) FMTC_DECC(2, LAY, AL, 8);                                                             \
+        else if (ncs == 3) FMTC_DECC(3, LAY, AL, 8);                                                             \
+        else FMTC_DECC(4, LAY, AL, 8);                                                                           \
     } while (0)
 #define FMTC_DECC_FIXED(LAY)                                                                                     \
     do {                                                                                                         \
@@ -1662,14 +1662,13 @@ hipError_t launch_decode_u8(const Basis8Device& b, const uint8_t* d_stream, size
     p.out8 = d_xq_hat;
     const bool al = (C % 4) == 0;
     const size_t lds_basis = (size_t)ncs * ((C + 15) / 16) * 64 * 8;  // the basis operand
-    const bool eight = g.n_chunks > 1024 && ncs != 3;
     p.lds_basis_bytes = (uint32_t)lds_basis;
     p.pay_words = 128u * (uint32_t)bits + 64u;
     auto lds_dyn = [&](int wv) { return lds_basis + (size_t)wv * (p.pay_words + kPayOverrun) * 4; };
     // four wavefronts per SIMD under the conditions of the fp32 decoder (see launch_decode)
     const bool sixteen = g.n_chunks > 3072 && ncs <= 2 && C == ncs * 32 && layout == FMTC_NHWC &&
                          lds_dyn(16) + sizeof(DecTables) + 16 * (size_t)kChunkTileBytes + 64 <= 160 * 1024;
-    const int waves = sixteen ? 16 : (eight ? 8 : 4);
+    const int waves = sixteen ? 16 : 8;
     const size_t lds = lds_dyn(waves);
     const unsigned gx = g.n_chunks < 128u ? 2u * g.n_chunks : 256u;  // see launch_decode
     hipError_t el = hipSuccess;
@@ -1683,10 +1682,10 @@ hipError_t launch_decode_u8(const Basis8Device& b, const uint8_t* d_stream, size
 #define FMTC_DECU(NCT, LAY, AL, WV) FMTC_DECU_F(NCT, LAY, AL, WV, 0)
 #define FMTC_DECU_N(LAY, AL)                                                                                     \
     do {                                                                                                         \
-        if (ncs == 1) { if (eight) FMTC_DECU(1, LAY, AL, 8); else FMTC_DECU(1, LAY, AL, 4); }                    \
-        else if (ncs == 2) { if (eight) FMTC_DECU(2, LAY, AL, 8); else FMTC_DECU(2, LAY, AL, 4); }               \
-        else if (ncs == 3) FMTC_DECU(3, LAY, AL, 4);                                                             \
-        else { if (eight) FMTC_DECU(4, LAY, AL, 8); else FMTC_DECU(4, LAY, AL, 4); }                             \
+        if (ncs == 1) FMTC_DECU(1, LAY, AL, 8);                                                                  \
+        else if (ncs == 2) FMTC_DECU(2, LAY, AL, 8);                                                             \
+        else if (ncs == 3) FMTC_DECU(3, LAY, AL, 8);                                                             \
+        else FMTC_DECU(4, LAY, AL, 8);                                                                           \
     } while (0)
     if (sixteen) { if (ncs == 1) FMTC_DECU_F(1, FMTC_NHWC, true, 16, 32); else FMTC_DECU_F(2, FMTC_NHWC, true, 16, 64); }
     else if (layout == FMTC_NHWC) { if (al) FMTC_DECU_N(FMTC_NHWC, true); else FMTC_DECU_N(FMTC_NHWC, false); }
