@@ -49,9 +49,9 @@ typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 // patterns as signed integers).  Compared as integers so that every input ends in range: a negative u (sign bit set)
 // below lo, a NaN at one end or the other -- the result indexes the histogram.
 __device__ __forceinline__ uint32_t clamp_pattern(float u, float lo, float hi) {
-    const int ui = __builtin_bit_cast(int, u), li = __builtin_bit_cast(int, lo), hi_i = __builtin_bit_cast(int, hi);
-    const int c = ui < li ? li : (ui > hi_i ? hi_i : ui);
-    return (uint32_t)c;
+    uint32_t c;  // (one instruction, where the compiler, which does not know lo <= hi, takes three)
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(c) : "v"(u), "s"(lo), "v"(hi));
+    return c;
 }
 
 // The larger of two values, NaN if either is: the largest distance of a tile's values to their levels must not pass over one
@@ -243,8 +243,9 @@ void k_project_quantize_rows(RowParams p) {
     static_assert(kHistLanes * sizeof(uint32_t) == 64, "shift of the histogram address");
     typedef __attribute__((address_space(3))) uint32_t lds_u32;
     const uint32_t wh_magic = (uint32_t)(uintptr_t)(lds_u32*)wh - (kMagicBits << 6);
-    auto hist_add = [&](uint32_t ub) {
-        __hip_atomic_fetch_add((lds_u32*)(uintptr_t)((ub << 6) + wh_magic), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    // (one: 1, or 0 for a value that does not count -- no branch per value)
+    auto hist_add = [&](uint32_t ub, uint32_t one) {
+        __hip_atomic_fetch_add((lds_u32*)(uintptr_t)((ub << 6) + wh_magic), one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     uint32_t* fix_list = s_fix_list[wave];
     uint32_t* fix_tile = s_fix_tile[wave];
@@ -466,8 +467,7 @@ void k_project_quantize_rows(RowParams p) {
                     const float u = t + magic;  // round half to even
                     maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                     ub[r] = clamp_pattern(u, magic_lo, magic_hi);
-                    if constexpr (!FUSED)
-                        if (k_ok) hist_add(ub[r]);
+                    if constexpr (!FUSED) hist_add(ub[r], k_ok ? 1u : 0u);
                 }
 #pragma unroll
                 for (int g = 0; g < 4; g++)
@@ -500,8 +500,7 @@ void k_project_quantize_rows(RowParams p) {
                     const float u = t + magic;  // round half to even
                     maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                     ub[r] = clamp_pattern(u, magic_lo, magic_hi);
-                    if constexpr (!FUSED)
-                        if (k_ok) hist_add(ub[r]);
+                    if constexpr (!FUSED) hist_add(ub[r], k_ok ? 1u : 0u);
                     if ((r & 3) == 3)
                         word[r >> 2] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(ub[r], ub[r - 1], 0x0c0c0400u),
                                                              __builtin_amdgcn_perm(ub[r - 2], ub[r - 3], 0x0c0c0400u), 0x05040100u);
@@ -649,12 +648,6 @@ static float stream_scale(float delta, int bits) {
     (void)std::frexp(std::ldexp(delta, bits - 1), &e);  // A in [2^(e-1), 2^e)
     const int k = 11 - 3 - e;
     return std::ldexp(1.f, k < -100 ? -100 : (k > 100 ? 100 : k));
-}
-// c clamped between lo and hi (lo <= hi), as signed integers.
-__device__ __forceinline__ uint32_t clamp_pattern3(float u, float lo, float hi) {
-    uint32_t c;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(c) : "v"(u), "s"(lo), "v"(hi));
-    return c;
 }
 // NJA: the tensor's channel count / 16 (the launcher checks it), 2 NCT - 1 or 2 NCT.
 // Planar tensors: a channel's plane starts at a wavefront-uniform address (image of the tile's first pixel) and a lane's
@@ -890,7 +883,7 @@ void k_project_quantize_stream(RowParams p) {
             for (int r = 0; r < 16; r++) {
                 const float u = __builtin_fmaf(acc[kt][r], per_step, magic);  // round half to even
                 maxd = max_or_nan(maxd, fabsf(__builtin_fmaf(acc[kt][r], per_step, magic - u)));
-                ub[r] = clamp_pattern3(u, magic_lo, magic_hi);
+                ub[r] = clamp_pattern(u, magic_lo, magic_hi);
                 hist_add(ub[r], one);
             }
 #pragma unroll
@@ -1468,7 +1461,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const float u = t + magic;  // round half to even
                 maxd = max_or_nan(maxd, fabsf(t - (u - magic)));
                 ub[r] = clamp_pattern(u, magic_lo, magic_hi);  // (its lowest byte is the symbol: in range whatever u is)
-                if (ok) atomicAdd(&wh[(ub[r] & 255u) << HS], 1u);
+                atomicAdd(&wh[(ub[r] & 255u) << HS], ok ? 1u : 0u);  // (no branch per value)
             }
 #pragma unroll
             for (int g = 0; g < 4; g++)
@@ -1737,7 +1730,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     if (!(fabsf(t - q) <= near_limit)) near_mask |= 1u << r;
                     const float qc = __builtin_amdgcn_fmed3f(q, lo, hi) + zero_f;  // clamped level, as a symbol
                     word[r >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(qc, r & 3, word[r >> 2]);
-                    if (ok) atomicAdd(&wh[((uint32_t)qc < (uint32_t)K ? (uint32_t)qc : (uint32_t)(K - 1)) << HS], 1u);  // (in range whatever qc is)
+                    atomicAdd(&wh[((uint32_t)qc < (uint32_t)K ? (uint32_t)qc : (uint32_t)(K - 1)) << HS], ok ? 1u : 0u);  // (in range whatever qc is; no branch per value)
                 }
                 if (ok)
                     *reinterpret_cast<uint4*>(p.syms + px * C + k0) = make_uint4(word[0], word[1], word[2], word[3]);
