@@ -112,7 +112,6 @@ void k_project_quantize_rows(RowParams p) {
     __shared__ __align__(16) float s_mu[NCT * 32];
     __shared__ uint32_t s_fix_list[WAVES][kFixList];
     __shared__ uint32_t s_fix_tile[WAVES][kFixList];
-    __shared__ uint32_t s_fix_count[WAVES];
     __shared__ uint32_t s_red[WAVES * 256];  // per (wavefront, bin) sums of the histogram copies
     // Histogram: kHistLanes interleaved copies per wavefront (bin s of copy q at word s * kHistLanes + q), lane l
     // counts in copy l % kHistLanes.  Most symbols of a tile are the same few values: with one copy the LDS
@@ -249,8 +248,7 @@ void k_project_quantize_rows(RowParams p) {
     };
     uint32_t* fix_list = s_fix_list[wave];
     uint32_t* fix_tile = s_fix_tile[wave];
-    uint32_t* fix_count = &s_fix_count[wave];
-    if (lane == 0) *fix_count = 0u;
+    uint32_t n_fix = 0;  // values listed, the same in all lanes
 
     // the first tile's pixels are on their way while the basis lands; every wavefront of the workgroup takes
     // part in the barrier, with or without a tile
@@ -268,7 +266,8 @@ void k_project_quantize_rows(RowParams p) {
         // the symbols that get patched were stored by other lanes of this wavefront: those stores are
         // acknowledged before the patches go out (this also waits for the next tile's loads; rare)
         __builtin_amdgcn_s_waitcnt(0x0F70);
-        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)*fix_count);
+        const uint32_t n = n_fix;
+        wave_sync_lds();
         for (uint32_t base = 0; base < n; base += 4) {
             const uint32_t idx = base + (uint32_t)(lane >> 4);
             const bool active = idx < n;
@@ -314,8 +313,7 @@ void k_project_quantize_rows(RowParams p) {
             }
         }
         wave_sync_lds();
-        if (lane == 0) *fix_count = 0u;
-        wave_sync_lds();
+        n_fix = 0u;
     };
     auto process_tile = [&](const int64_t tile, const int64_t next_tile) {
         const int64_t px = tile * 32 + l32;
@@ -414,36 +412,29 @@ void k_project_quantize_rows(RowParams p) {
                 const float t = __builtin_fmaf(ac[r], inv_delta_lo, am[r] * inv_delta);
                 if (!(fabsf(t - __builtin_rintf(t)) <= near_limit) && px_ok && k0 + r < C) near_mask |= 1u << r;
             }
-            // at most 64 * 16 new entries would not fit: resolve what is there first if this tile could overflow
-            const uint32_t incoming = wave_sum((uint32_t)__popc(near_mask));
-            if (*fix_count + incoming > (uint32_t)kFixList) resolve_list();
-            if (incoming > (uint32_t)kFixList) {
-                // more flagged values than the list holds (a step so fine that the fast pass decides almost
-                // nothing, or pixels out of its range): 16 passes, one accumulator each, at most 64 entries per pass
+            // (one after the other in scalar registers: mostly it is one value)
+            unsigned long long lanes = __ballot(near_mask != 0u);
 #pragma unroll 1
-                for (int r = 0; r < 16; r++) {
-                    if ((near_mask >> r) & 1u) {
-                        const uint32_t slot = atomicAdd(fix_count, 1u);
-                        fix_list[slot] = (uint32_t)(k0 + r) | ((uint32_t)l32 << 8) |
-                                         (((word[r >> 2] >> (8 * (r & 3))) & 255u) << 13);
-                        fix_tile[slot] = (uint32_t)tile;
-                    }
-                    wave_sync_lds();
-                    resolve_list();
-                }
-            } else {
-                while (near_mask) {
-                    const int r = __ffs((int)near_mask) - 1;
-                    near_mask &= near_mask - 1;
-                    uint32_t sy = 0;
+            while (lanes) {
+                const int from = __ffsll((long long)lanes) - 1;
+                lanes &= lanes - 1ull;
+                uint32_t mask = (uint32_t)__builtin_amdgcn_readlane((int)near_mask, from);
+                uint32_t w[4];
 #pragma unroll
-                    for (int g = 0; g < 4; g++)
-                        if (g == (r >> 2)) sy = (word[g] >> (8 * (r & 3))) & 255u;
-                    const uint32_t slot = atomicAdd(fix_count, 1u);
-                    fix_list[slot] = (uint32_t)(k0 + r) | ((uint32_t)l32 << 8) | (sy << 13);
-                    fix_tile[slot] = (uint32_t)tile;
+                for (int g = 0; g < 4; g++) w[g] = (uint32_t)__builtin_amdgcn_readlane((int)word[g], from);
+#pragma unroll 1
+                while (mask) {
+                    const int r = __ffs((int)mask) - 1;
+                    mask &= mask - 1u;
+                    const uint32_t of4 = r < 8 ? (r < 4 ? w[0] : w[1]) : (r < 12 ? w[2] : w[3]);
+                    if (lane == 0) {
+                        fix_list[n_fix] = (uint32_t)(kt * 32 + 16 * (from >> 5) + r) | ((uint32_t)(from & 31) << 8) |
+                                          (((of4 >> (8 * (r & 3))) & 255u) << 13);
+                        fix_tile[n_fix] = (uint32_t)tile;
+                    }
+                    n_fix++;
+                    if (n_fix == (uint32_t)kFixList) resolve_list();
                 }
-                wave_sync_lds();
             }
         };
 
@@ -572,7 +563,7 @@ void k_project_quantize_rows(RowParams p) {
                         process_tile(tl, (t + 1 < TPC && tl + 1 < p.n_tiles) ? tl + 1
                                          : (group + gridDim.x < p.pk.n_groups ? next_chunk_tile : p.n_tiles));
                 }
-                if (*fix_count) resolve_list();
+                if (n_fix) resolve_list();
             }
             wave_sync_lds();  // the symbols other lanes wrote precede the reads below
             // register q of lane l: symbols 256q + 4l .. + 3 of the chunk (C is a multiple of 32: clen one of 4)
@@ -592,7 +583,7 @@ void k_project_quantize_rows(RowParams p) {
             if (WPS >= 3 && next_tile < p.n_tiles) load_pixels(next_tile);
         }
     }
-    if (*fix_count) resolve_list();
+    if (n_fix) resolve_list();
     __syncthreads();
     // One row of partial counts per workgroup: nothing to clear beforehand, no global atomics.  Every thread sums
     // the 16 copies of some (wavefront, bin) rows with 16-byte reads (a row is contiguous; reading one copy of
