@@ -10,7 +10,7 @@
 //   k_pack           one wavefront per chunk: run sizes, the chunk's place in the payload
 //                    (a running sum over the chunk groups handed from workgroup to
 //                    workgroup), then the code bits;
-//   k_pack_stream    the same for large tensors, the groups claimed in turn.
+//   k_pack_stream    the same for large tensors, a range of chunks per workgroup.
 #include <atomic>
 #include <type_traits>
 

@@ -974,8 +974,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4
 typedef int intx16 __attribute__((ext_vector_type(16)));
 constexpr int kChunkTileBytes = 4096 + 4096 / 16 + 64;  // symbols, 4 pad bytes per run, slack for padded reads
 
-// WAVES wavefronts per workgroup (4 or 8): one per SIMD where the chunks do not outnumber the SIMDs, two where
-// they do (the second hides the latencies of the first; the workgroup still holds one copy of the basis).
+// WAVES wavefronts per workgroup: two per SIMD (the second hides the latencies of the first; the workgroup holds one copy of
+// the basis), up to four where registers and LDS allow, one for five channel tiles of a count left open (see launch_decode).
 // U8: the tile's symbols go through the 8-bit basis on the integer matrix cores instead (v_mfma_i32_32x32x16_i8;
 // exact sums, one fused fp64 multiply-add and one rounding per value, 8-bit activations out); the 8-bit basis
 // takes the f16 basis' place in LDS.
@@ -1124,7 +1124,8 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVE
     bool pay_ok = guess_valid && pay_pre;
     uint32_t pay_w0 = guess_w0, pay_w1 = guess_w1;
     const uint32_t u_step = gridDim.x * WAVES;
-    // The wavefronts with a unit more than the others are the last to end: theirs go first.
+    // The wavefronts with a unit more than the others are the last to end: theirs go first.  (64 channels, 12544 chunks: 256 of
+    // 4096 wavefronts have a fourth; they ended 9 us after the others, of 51.)
     if (ch_first < un.n_units % u_step && un.n_units > u_step) __builtin_amdgcn_s_setprio(2);
     for (uint32_t u = ch_first; u < un.n_units; u += u_step) {
         // ---- variable length decoding of the unit into the wavefront's tile ----
