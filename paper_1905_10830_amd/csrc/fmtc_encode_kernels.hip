@@ -12,13 +12,13 @@
 // whose contraction the workgroup's wavefronts share out (few pixels, other channel
 // counts), and 32 pixels with all channels in LDS (many pixels of such counts).
 #include <atomic>
-#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
 #include "fmtc_device.h"
 #include "fmtc_internal.h"
 #include "fmtc_pack_device.h"
+#include "fmtc_stream_scale.h"
 
 namespace fmtc {
 
@@ -85,7 +85,7 @@ struct RowParams {
     CoderCtrl* ctrl;
     unsigned long long* lookback;
     uint32_t n_groups;
-    float x_scale;            // k_project_quantize_stream: a power of two, 2^11 s (see there)
+    float x_scale;            // k_project_quantize_stream: S, a power of two (see there)
     PackParams pk;            // FUSED only: where the container goes
 };
 
@@ -616,11 +616,10 @@ void k_project_quantize_rows(RowParams p) {
 // came in are requested again for the same step of the next tile, so that nearly a whole tile (14 to 20 KB per wavefront)
 // is in flight at any time.
 //
-// ONE accumulator per coefficient: with v = S (x - mu), S = 2^11 s a power of two,
-//   2^11 s y = sum T_hi v_hi + sum T_hi v_lo + sum (2^11 T_lo) (2^-11 v_hi)
-// where v_hi = v rounded to f16 and v_lo = v - v_hi rounded to f16, all three products at the same scale.  s brings the
-// range A = Delta 2^(b-1) of the leading coefficient to 1/16 .. 1/8, so that values up to 256 A fit f16 (a pixel beyond is
-// decided exactly in all coefficients) and what v_lo and 2^-11 v_hi lose in the subnormals is below 2^-30 A.  Half the
+// ONE accumulator per coefficient: with v = S (x - mu), S a power of two,
+//   S y = sum T_hi v_hi + sum T_hi v_lo + sum (2^11 T_lo) (2^-11 v_hi)
+// where v_hi = v rounded to f16 and v_lo = v - v_hi rounded to f16, all three products at the same scale.  S follows from the
+// quantizer's range and the norm of the basis' rows (see stream_scale).  Half the
 // accumulator registers (80 of 160 at five coefficient tiles) are a second wavefront per SIMD, whose vector instructions
 // issue while the first one's matrix instructions run (measured: a 32x32x16 product takes 32 clocks, and five independent
 // vector instructions behind it none), and the quantizer takes one multiply-add where it joined two sums: u = acc g +
@@ -633,13 +632,6 @@ void k_project_quantize_rows(RowParams p) {
 // infinities make of the matrix product stays in its own column of outputs, all of which are decided exactly, and
 // the clamp of the quantizer keeps the histogram index in range whatever the value.
 // ---------------------------------------------------------------------------
-// x_scale of RowParams: 2^11 s for a step delta at a bit depth (kept within what fp32 and its reciprocal hold).
-static float stream_scale(float delta, int bits) {
-    int e = 0;
-    (void)std::frexp(std::ldexp(delta, bits - 1), &e);  // A in [2^(e-1), 2^e)
-    const int k = 11 - 3 - e;
-    return std::ldexp(1.f, k < -100 ? -100 : (k > 100 ? 100 : k));
-}
 // NJA: the tensor's channel count / 16 (the launcher checks it), 2 NCT - 1 or 2 NCT.
 // Planar tensors: a channel's plane starts at a wavefront-uniform address (image of the tile's first pixel) and a lane's
 // place in it is one 32-bit offset (the launcher checks that it fits), so the loads of 16 channels per lane and step
@@ -1014,7 +1006,7 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     p.ctrl = cs.ctrl;
     p.lookback = cs.lookback;
     p.n_groups = cs.n_groups;
-    p.x_scale = stream_scale(delta, bits);
+    p.x_scale = stream_scale(delta, bits, b.row_norm);
     p.pk = PackParams{};
     if (!p.x || !p.basis16 || !p.mu || !p.Trow || !p.syms || !p.hist_parts || !p.ctrl || !p.lookback)
         return hipErrorInvalidValue;  // (a field left out would be a wild pointer on the device)

@@ -368,7 +368,7 @@ def test_packer_is_no_slower_with_a_fixed_table(fmtc, oracle, bits, chunk, C):
 WIDE_CASES = [(176, 16411, 4), (192, 16388, 6), (240, 16500, 8), (256, 16385, 3), (272, 11000, 5), (528, 6700, 4)]
 
 
-def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None, keep=None):
+def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None, keep=None, reach=4.0):
     from paper_1905_10830_amd import synth
 
     P = N * H * W
@@ -379,7 +379,7 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None, keep=
     mu = rng.standard_normal(C).astype(np.float32)
     x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C) + mu).astype(np.float32)
     x[P // 2] *= 1.0e5
-    A = np.float32(4.0 if T_scale is None else 4.0 * np.max(T_scale))
+    A = np.float32(reach if T_scale is None else reach * np.max(T_scale))
     y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
     basis = fmtc.basis_import(T, mu, A)
     if keep is not None:
@@ -454,6 +454,46 @@ def test_projection_with_basis_entries_beyond_f16(fmtc, oracle, C, P, layout):
     scale = np.ones(C)
     scale[[0, C // 2, C - 1]] = 3.0e6
     check_projection(fmtc, oracle, C, 1, 1, P, 5, layout, scale)
+
+
+# Rows of any norm, pixels that fill the quantizer's range and a tenth of it: the streaming form, whose operands are scaled by
+# the two, with fewer and with more pixel tiles than SIMDs.  (Every norm, against a model of the sums: test_projection_band.)
+LONG_ROWS = [(c, layout, reach) for c in ((128, 400, 8), (160, 320, 7), (128, 1800, 8)) for layout in ("nhwc", "nchw") for reach in (4.0, 40.0)]
+
+
+@pytest.mark.parametrize("case,layout,reach", LONG_ROWS, ids=[f"C{c[0]}w{c[1]}{l}{int(r)}" for c, l, r in LONG_ROWS])
+def test_streaming_projection_with_long_rows(fmtc, oracle, case, layout, reach):
+    C, w, bits = case
+    assert form_of(fmtc, C, w, bits, layout).startswith("stream")
+    check_projection(fmtc, oracle, C, 3, 7, w, bits, layout, np.full(C, 32768.0), reach=reach)
+
+
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("C,w", [(128, 400), (144, 1800)])
+def test_streaming_projection_with_short_rows(fmtc, oracle, C, w, layout):
+    """... and no more values decided exactly because of the rows' norm, which is most of the kernel's time then (some 30 times
+    as long where all of them were).  The limit leaves room for what timings differ by."""
+    from paper_1905_10830_amd import synth
+
+    bits, P, norm = 6, 21 * w, 2.0 ** -9
+    check_projection(fmtc, oracle, C, 3, 7, w, bits, layout, np.full(C, norm))
+    rng = np.random.default_rng(C)
+    T = np.linalg.qr(rng.standard_normal((C, C)))[0].astype(np.float32)
+    x = rng.standard_normal((P, C)).astype(np.float32)
+    xs, tag = (dev(x.reshape(3, 7, w, C)), synth.NHWC) if layout == "nhwc" else (dev(x.reshape(3, 7, w, C).transpose(0, 3, 1, 2)), synth.NCHW)
+    us = []
+    for scale in (1.0, norm):
+        basis = fmtc.basis_import(T * np.float32(scale), np.zeros(C, np.float32), np.float32(4.0 * scale))
+        fmtc.quantize(basis, xs, bits, tag)
+        fmtc.profile_enable(20)
+        try:
+            for _ in range(20):
+                fmtc.quantize(basis, xs, bits, tag)
+            torch.cuda.synchronize()
+            us.append(1e3 * next(v[1] for k, v in fmtc.profile_read().items() if "project" in k))
+        finally:
+            fmtc.profile_enable(0)
+    assert us[1] < 1.5 * us[0] + 2.0, f"{us[1]:.1f} us with short rows, {us[0]:.1f} us with unit rows"
 
 
 @pytest.mark.parametrize("layout", ["nhwc", "nchw"])

@@ -1,0 +1,82 @@
+"""The streaming projection's sums, modelled on the CPU: whatever the norm of the basis' rows, a value that they decide is
+decided as in 64 bits."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1905_10830_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    """The library's own scale, compiled for the host."""
+    tmp = tmp_path_factory.mktemp("rules")
+    src, lib = str(tmp / "rules.cpp"), str(tmp / "rules.so")
+    with open(src, "w") as f:
+        f.write('#include "fmtc_stream_scale.h"\n'
+                'extern "C" float scale(float delta, int bits, float row_norm) { return fmtc::stream_scale(delta, bits, row_norm); }\n')
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
+    so = ctypes.CDLL(lib)
+    so.scale.restype, so.scale.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_int, ctypes.c_float]
+    return so
+
+
+def f16(a):
+    return np.asarray(a).astype(np.float16).astype(np.float64)
+
+
+def f32(a):
+    return np.asarray(a).astype(np.float32).astype(np.float64)
+
+
+def fast_sums(T, v, scale):
+    """What the matrix instructions make of the f16 parts: exact products, the sum of every eight of them rounded once."""
+    t_hi = f16(T)
+    t_lo = f16((T - t_hi) * 2048.0)
+    s = f32(v * scale)
+    s_hi = f16(s)
+    s_lo, s_hi_low = f16(s - s_hi), f16(s_hi / 2048.0)
+    acc = np.zeros((len(v), len(T)))
+    for j in range(0, T.shape[1], 16):
+        for a, b in ((s_lo, t_hi), (s_hi_low, t_lo), (s_hi, t_hi)):
+            for i in (j, j + 8):
+                acc = f32(acc + a[:, i:i + 8] @ b[:, i:i + 8].T)
+    return acc, np.sqrt((s * s).sum(axis=1))
+
+
+def pixels(rng, T, P, kind):
+    C = len(T)
+    x = rng.standard_normal((P, C)) * (np.linspace(2.0, 0.1, C) if kind == "flat" else 2.0 * 0.9 ** np.arange(C))
+    return f32(x if kind == "flat" else x @ (T / np.linalg.norm(T[0])))
+
+
+@pytest.mark.parametrize("kind", ["flat", "steep"])
+@pytest.mark.parametrize("C,bits", [(112, 4), (128, 8), (160, 7)])
+@pytest.mark.parametrize("norm", [2.0 ** -9, 1.0, 4096.0, 32768.0])
+def test_values_that_the_sums_decide(rules, norm, C, bits, kind):
+    """norm: of the basis' rows.  The pixels fill the quantizer's range, a tenth and a hundredth of it."""
+    rng = np.random.default_rng(C)
+    T = f32(np.linalg.qr(rng.standard_normal((C, C)))[0] * norm)
+    row_norm = np.float32(np.linalg.norm(T, axis=1).max())
+    x = pixels(rng, T, 4000, kind)
+    y = x @ T.T
+    half = 1 << (bits - 1)
+    for part in (1.0, 0.1, 0.01):
+        delta = float(np.float32(np.abs(y[:, 0]).max() / part / (half - 1)))
+        S = rules.scale(delta, bits, row_norm)
+        acc, length = fast_sums(T, x, S)
+        inv_delta = np.float32(1.0 / delta)
+        tau = np.clip(1.75 * 2.0 ** -19 * float(row_norm) * float(inv_delta) / S * length, 2.0 ** -21 * half, 0.125)[:, None]
+        exact = length >= 60000.0
+        t = acc * float(inv_delta) / S
+        assert exact.mean() < 0.01, "pixels of the quantizer's range are too large for f16"
+        # the distance that the sums are trusted from covers their error ...
+        assert (np.abs(t - y / delta) <= tau)[~exact].all()
+        # ... so no symbol that they decide is another one in 64 bits
+        decided = (np.abs(t - np.rint(t)) <= 0.5 - tau) & ~exact[:, None]
+        symbol = np.clip(np.rint(t), -half, half - 1)
+        assert np.array_equal(symbol[decided], np.clip(np.rint(y / delta), -half, half - 1)[decided])
