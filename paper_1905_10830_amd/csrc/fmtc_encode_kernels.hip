@@ -624,9 +624,9 @@ void k_project_quantize_rows(RowParams p) {
 // issue while the first one's matrix instructions run (measured: a 32x32x16 product takes 32 clocks, and five independent
 // vector instructions behind it none), and the quantizer takes one multiply-add where it joined two sums: u = acc g +
 // magic, and the distance to the level is acc g - (u - magic) in another.  (All products being added to the large sum, its
-// error is up to 1.8 times that of two sums: at 112 to 160 channels at most 2^-21.1 |x - mu|_2 against 2^-21.8 where a
-// leading component holds most of the pixel, 2^-22.9 against 2^-23.7 where none does, in random data.  The distance below
-// which a value is decided exactly is that much larger here.)
+// error is larger than that of two sums: in random data of 112 to 160 channels 2^-21.1 |x - mu|_2 against 2^-21.8 was the
+// largest seen where a leading component holds most of the pixel, 2^-22.9 against 2^-23.7 where none does.  The distance
+// below which a value is decided exactly follows from a bound: see stream_band.)
 //
 // A pixel too large for f16 needs no clamp here: what its
 // infinities make of the matrix product stays in its own column of outputs, all of which are decided exactly, and
@@ -724,7 +724,6 @@ void k_project_quantize_stream(RowParams p) {
     const int zero_sym = 1 << (p.bits - 1);
     const float lo = (float)(-zero_sym), hi = (float)(zero_sym - 1);
     const float per_step = p.inv_delta / S;  // (exact: S is a power of two)
-    const float kappa = 1.75f * p.kappa / S;  // (see above)
     float minus_one = -1.f;  // (unknown to the compiler, which then takes the multiply-add on the f16 part as it is)
     asm("" : "+s"(minus_one));
     constexpr uint32_t kMagicBits = 0x4B400000u;  // 1.5 * 2^23: see k_project_quantize_rows
@@ -853,7 +852,7 @@ void k_project_quantize_stream(RowParams p) {
         }
         n2 += __shfl_xor(n2, 32, 64);  // the other half of the pixel
         const bool force = !(n2 < 3.6e9f);  // too large for f16 (or not finite): every coefficient decided exactly
-        const float tau = fminf(fmaxf(kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
+        const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
         const float near_limit = force ? -1.f : 0.5f - tau;
 
 #pragma unroll
@@ -1025,6 +1024,7 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     *n_parts = (int)gx;
     hipError_t el = hipSuccess;
     if (pl.stream) {
+        p.kappa = stream_band(b.C / 16) * b.row_norm * p.inv_delta / p.x_scale;  // (of |S (x - mu)|_2)
         const bool whole = b.C == nct * 32;  // else 16 channels less
         const size_t slds = rows_lds(nct, bits, 4);  // (four histograms whatever the wavefronts)
         int64_t sgx = (p.n_tiles + waves - 1) / waves;

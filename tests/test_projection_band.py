@@ -13,14 +13,16 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_1905_10830_amd", "csrc")
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """The library's own scale, compiled for the host."""
+    """The library's own scale and distance, compiled for the host."""
     tmp = tmp_path_factory.mktemp("rules")
     src, lib = str(tmp / "rules.cpp"), str(tmp / "rules.so")
     with open(src, "w") as f:
         f.write('#include "fmtc_stream_scale.h"\n'
-                'extern "C" float scale(float delta, int bits, float row_norm) { return fmtc::stream_scale(delta, bits, row_norm); }\n')
+                'extern "C" float scale(float delta, int bits, float row_norm) { return fmtc::stream_scale(delta, bits, row_norm); }\n'
+                'extern "C" float band(int steps) { return fmtc::stream_band(steps); }\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
     so = ctypes.CDLL(lib)
+    so.band.restype, so.band.argtypes = ctypes.c_float, [ctypes.c_int]
     so.scale.restype, so.scale.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_int, ctypes.c_float]
     return so
 
@@ -70,7 +72,7 @@ def test_values_that_the_sums_decide(rules, norm, C, bits, kind):
         S = rules.scale(delta, bits, row_norm)
         acc, length = fast_sums(T, x, S)
         inv_delta = np.float32(1.0 / delta)
-        tau = np.clip(1.75 * 2.0 ** -19 * float(row_norm) * float(inv_delta) / S * length, 2.0 ** -21 * half, 0.125)[:, None]
+        tau = np.clip(rules.band(C // 16) * float(row_norm) * float(inv_delta) / S * length, 2.0 ** -21 * half, 0.125)[:, None]
         exact = length >= 60000.0
         t = acc * float(inv_delta) / S
         assert exact.mean() < 0.01, "pixels of the quantizer's range are too large for f16"
@@ -80,3 +82,20 @@ def test_values_that_the_sums_decide(rules, norm, C, bits, kind):
         decided = (np.abs(t - np.rint(t)) <= 0.5 - tau) & ~exact[:, None]
         symbol = np.clip(np.rint(t), -half, half - 1)
         assert np.array_equal(symbol[decided], np.clip(np.rint(y / delta), -half, half - 1)[decided])
+
+
+@pytest.mark.parametrize("C", [112, 128, 144, 160])
+def test_the_distance_covers_every_rounding(rules, C):
+    """Not only what random data show: every rounding of a sum in the same direction, each of half a unit of the largest
+    partial sum, and the f16 parts' errors.  (Tried here: one large product, and small ones that fall below its half unit
+    eight by eight; 18 of 78 units at 160 channels.)"""
+    steps, unit = C // 16, 2.0 ** -24
+    assert rules.band(steps) >= (6 * steps + 14) * unit
+    rng = np.random.default_rng(C)
+    worst = 0.0
+    for trial in range(200):
+        v = f32(np.r_[1.0 + rng.random(), (rng.random(C - 1) * 0.2 + 0.8) * 2.0 ** -rng.integers(10, 16)])
+        T = f32(np.r_[1.0, (rng.random(C - 1) * 0.2 + 0.8) * 2.0 ** -rng.integers(10, 16)])[None, :]
+        acc, _ = fast_sums(T, v[None, :], 64.0)
+        worst = max(worst, abs(acc[0, 0] / 64.0 - float(T[0] @ v)) / (np.linalg.norm(T) * np.linalg.norm(v)))
+    assert worst <= rules.band(steps), worst / unit
