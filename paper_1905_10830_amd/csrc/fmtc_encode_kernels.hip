@@ -188,13 +188,16 @@ void k_project_quantize_rows(RowParams p) {
                 base = n * (int64_t)C * p.HW + (pp - n * p.HW);
                 stride = p.HW;
             }
+            // (The lane's own part of the address first: what is left, (16 j + e) planes, is the same in all lanes and held in
+            // scalar registers.  With a lane's channel times the plane kept in two registers for each value these were spilled: 33
+            // channels, N = 674, 21 x 20, 5 bits 43 -> 29 us; 95, N = 300, 21 x 21, 6 bits 81 -> 59; 64 channels, one image of
+            // 4096 x 4160, whose offsets 32 bits do not hold, 2618 -> 1265.)
+            const float* at = p.x + (base + (int64_t)(8 * half) * stride);
 #pragma unroll
             for (int j = 0; j < NJ; j++)
 #pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const int c = 16 * j + 8 * half + e;
-                    xr[8 * j + e] = (px_ok && c < C) ? p.x[base + (int64_t)c * stride] : 0.f;
-                }
+                for (int e = 0; e < 8; e++)
+                    xr[8 * j + e] = (px_ok && 16 * j + 8 * half + e < C) ? at[(int64_t)(16 * j + e) * stride] : 0.f;
         }
     };
     // the first tile's pixels come from HBM: their loads go out before anything else
