@@ -615,6 +615,7 @@ struct StreamShared {
     unsigned long long tab[256];                 // bit-reversed code | length << 56
     __align__(16) uint32_t image[kStreamRoom];
     uint16_t runs[kStreamWaves][64];
+    uint32_t past[72];                           // what lies past the images' ends: a word and up to four behind it per lane
     // of the chunks of the range: payload words, code bits, where the second window starts (see pack_window)
     uint32_t words[kMaxImages], bits[kMaxImages], from[kMaxImages];
     uint32_t range, next_range;
@@ -694,28 +695,33 @@ __device__ __forceinline__ unsigned long long bits_from_counts(const uint32_t* h
     return (unsigned long long)(uint32_t)(sum * (1.f / 64.f)) * 66ull;
 }
 
-// ORs the up to 64 bits of `c` into the image at bit `pos` of the chunk; what lies past the image's `words` goes to its
-// spare words.
-__device__ __forceinline__ void place_octet(unsigned long long c, uint32_t len, uint32_t pos, uint32_t* img, uint32_t words) {
-    const uint32_t at = (pos < words * 32u ? pos : words * 32u) >> 5, sh = pos & 31u;
+// ORs the up to 64 bits of `c` into the image at bit `pos` of the chunk (the last ones, if they start in its `words`, into its
+// spare words).  What starts past them goes to a place of the lane's own that nobody reads, `past`: with one such word for
+// all lanes the LDS took them one after the other, and where the chunks of a workgroup are larger than their images it
+// served nothing else (see pack_window).
+__device__ __forceinline__ void place_octet(unsigned long long c, uint32_t len, uint32_t pos, uint32_t* img, uint32_t words, uint32_t* past) {
+    const uint32_t sh = pos & 31u;
+    uint32_t* at = pos < words * 32u ? img + (pos >> 5) : past;
     const unsigned long long t0 = c << sh;
-    atomicOr(&img[at], (uint32_t)t0);
-    atomicOr(&img[at + 1u], (uint32_t)(t0 >> 32));
-    if (__any(len + sh > 64u)) atomicOr(&img[at + 2u], sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
+    atomicOr(at, (uint32_t)t0);
+    atomicOr(at + 1, (uint32_t)(t0 >> 32));
+    if (__any(len + sh > 64u)) atomicOr(at + 2, sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
 }
 
 // The same for the usual step, without a test per lane.  Counted from the end of the word that the bits start in: k of them
 // (0 to 31) go there, 32 into the next word, the rest behind that; with k the shift of all three pieces, none of them needs
 // a case of its own for bits that start on a word (k = 0: nothing goes into the word before, which is there in any case).
 // The rest is left to the caller (none where past is not positive).
+// INSIDE: all lanes' bits start in the image.
 struct Placed {
     uint32_t* next;
     uint32_t rest;
     int past;
 };
-__device__ __forceinline__ Placed place_plain(unsigned long long c, uint32_t len, uint32_t pos, uint32_t* img, uint32_t words) {
-    const uint32_t p = pos < words * 32u ? pos : words * 32u, k = (0u - p) & 31u;
-    uint32_t* at = img + ((p + 31u) >> 5);
+template <bool INSIDE>
+__device__ __forceinline__ Placed place_plain(unsigned long long c, uint32_t len, uint32_t pos, uint32_t* img, uint32_t words, uint32_t* past) {
+    const uint32_t k = (0u - pos) & 31u;
+    uint32_t* at = INSIDE || pos < words * 32u ? img + ((pos + 31u) >> 5) : past + 1;
     const uint32_t lo = (uint32_t)c, hi = (uint32_t)(c >> 32);
     atomicOr(at - 1, __builtin_amdgcn_alignbit(lo, 0u, k));
     atomicOr(at, __builtin_amdgcn_alignbit(hi, lo, k));
@@ -863,21 +869,21 @@ __device__ __forceinline__ uint32_t octet_length(uint32_t x, uint32_t y, uint32_
 __device__ __forceinline__ void place_long_octet(uint32_t x, uint32_t y, uint32_t first, unsigned long long lo,
                                                  unsigned long long hi, uint32_t l_lo, uint32_t len, bool single,
                                                  uint32_t clen, const unsigned long long* tab, uint32_t pos,
-                                                 uint32_t* img, uint32_t words) {
+                                                 uint32_t* img, uint32_t words, uint32_t* past) {
     if (!single) {
         // (both halves as one value of up to 126 bits: the leading components of a pixel need 9 to 11 bits a symbol at 8 bits,
         // so most steps of such a tensor come here: the halves one after the other took 67 % more of the kernel's time at
         // chunks of 256 symbols, 301.8 us for 138660 of them, 204.7 this way)
-        const uint32_t at = (pos < words * 32u ? pos : words * 32u) >> 5, sh = pos & 31u, reach = len + sh;
+        const uint32_t sh = pos & 31u, reach = len + sh;
+        uint32_t* at = pos < words * 32u ? img + (pos >> 5) : past;
         const unsigned long long c0 = lo | (hi << l_lo), c1 = l_lo ? hi >> (64u - l_lo) : 0ull;
         const unsigned long long t0 = c0 << sh, t1 = (c1 << sh) | (sh ? c0 >> (64u - sh) : 0ull);
-        atomicOr(&img[at], (uint32_t)t0);
-        atomicOr(&img[at + 1u], (uint32_t)(t0 >> 32));
-        if (__any(reach > 64u)) atomicOr(&img[at + 2u], (uint32_t)t1);
-        if (__any(reach > 96u)) {
-            atomicOr(&img[at + 3u], (uint32_t)(t1 >> 32));
-            // (behind the image's end there are four spare words)
-            atomicOr(&img[at + 4u < words + 4u ? at + 4u : words + 3u], sh ? (uint32_t)(c1 >> (64u - sh)) : 0u);
+        atomicOr(at, (uint32_t)t0);
+        atomicOr(at + 1, (uint32_t)(t0 >> 32));
+        if (__any(reach > 64u)) atomicOr(at + 2, (uint32_t)t1);
+        if (__any(reach > 96u)) {  // (behind the image's end there are four spare words)
+            atomicOr(at + 3, (uint32_t)(t1 >> 32));
+            atomicOr(at + 4, sh ? (uint32_t)(c1 >> (64u - sh)) : 0u);
         }
         return;
     }
@@ -885,7 +891,7 @@ __device__ __forceinline__ void place_long_octet(uint32_t x, uint32_t y, uint32_
     for (uint32_t i = 0; i < 8u; i++) {
         const uint32_t sym = ((i < 4u ? x : y) >> (8u * (i & 3u))) & 255u;
         const unsigned long long e = first + i < clen ? tab[sym] : 0ull;
-        place_octet(e & 0x00ffffffffffffffull, (uint32_t)(e >> 56), pos, img, words);
+        place_octet(e & 0x00ffffffffffffffull, (uint32_t)(e >> 56), pos, img, words, past);
         pos += (uint32_t)(e >> 56);
     }
 }
@@ -897,7 +903,7 @@ __device__ __forceinline__ void place_long_octet(uint32_t x, uint32_t y, uint32_
 // serves both (16 bits each: a chunk has at most 64 x 8 x 48 bits in 512 symbols).
 template <bool PAIRS>
 __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t clen, const unsigned long long* tab,
-                                                uint32_t* img, uint32_t words, int lane, uint16_t* run_bits, uint32_t& last_from) {
+                                                uint32_t* img, uint32_t words, uint32_t* past, int lane, uint16_t* run_bits, uint32_t& last_from) {
     uint32_t base = 0;
     auto step = [&](uint32_t q, uint32_t x0, uint32_t y0, uint32_t x1, uint32_t y1, auto some_c) __attribute__((always_inline)) -> uint32_t {
         constexpr bool some = decltype(some_c)::value;
@@ -934,13 +940,18 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
         if (__builtin_expect(!__any(longer > 64u), 1)) {
             // (one straight run: what is joined fills the waits of the prefix sum)
             add_up(a.len, b.len);
-            const Placed at_a = place_plain(a.whole(), a.len, pos_a, img, words);
-            Placed at_b{at_a.next, 0u, 0};
-            if (two) at_b = place_plain(b.whole(), b.len, pos_b, img, words);
-            if (__any((int)(at_a.past > at_b.past ? at_a.past : at_b.past) > 0)) {
-                atomicOr(at_a.next, at_a.rest);
-                atomicOr(at_b.next, at_b.rest);
-            }
+            auto place = [&](auto inside_c) __attribute__((always_inline)) {
+                constexpr bool inside = decltype(inside_c)::value;
+                const Placed at_a = place_plain<inside>(a.whole(), a.len, pos_a, img, words, past);
+                Placed at_b{at_a.next, 0u, 0};
+                if (two) at_b = place_plain<inside>(b.whole(), b.len, pos_b, img, words, past);
+                if (__any((int)(at_a.past > at_b.past ? at_a.past : at_b.past) > 0)) {
+                    atomicOr(at_a.next, at_a.rest);
+                    atomicOr(at_b.next, at_b.rest);
+                }
+            };
+            if (__builtin_expect(base <= words * 32u, 1)) place(std::true_type{});
+            else place(std::false_type{});
         } else {
             const Halves ha = a.halves(), hb = b.halves();
             uint32_t len_a = octet_length(x0, y0, f0, ha.l_lo, a.len, clen, tab);
@@ -949,8 +960,8 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
             len_a &= 0x7fffffffu;
             len_b &= 0x7fffffffu;
             add_up(len_a, len_b);
-            place_long_octet(x0, y0, f0, ha.lo, ha.hi, ha.l_lo, len_a, single_a, clen, tab, pos_a, img, words);
-            if (two) place_long_octet(x1, y1, f1, hb.lo, hb.hi, hb.l_lo, len_b, single_b, clen, tab, pos_b, img, words);
+            place_long_octet(x0, y0, f0, ha.lo, ha.hi, ha.l_lo, len_a, single_a, clen, tab, pos_a, img, words, past);
+            if (two) place_long_octet(x1, y1, f1, hb.lo, hb.hi, hb.l_lo, len_b, single_b, clen, tab, pos_b, img, words, past);
         }
         return run;
     };
@@ -987,12 +998,13 @@ __device__ __forceinline__ uint32_t pack_octets(const uint2 (&w)[8], uint32_t cl
 // A later window [win, win + words) of a chunk too large for its image, once more from the symbols in memory: an octet per
 // lane and step, the next step's symbols on their way meanwhile, from the step in which the window starts (from: its first
 // symbol | code bits before it << 12; afterwards the next window's) to the one that ends behind it.  Words outside the
-// window go to the image's spare ones.  (Chunks of flat and of busy regions differ several times in size, so a tensor
-// can have many such chunks.  Symbol by symbol, 64 per step, a window took some 50 us: 12544 chunks of which every tenth
-// is large, 118 us for the kernel, 61 this way, and 62 where every wavefront had one image of 2048 words.)
+// window go to `past`.  (Chunks of flat and of busy regions differ several times in size, so a tensor
+// can have many such chunks, and side by side in one workgroup.  12544 chunks of 4096 symbols at 6 bits, a tenth of them
+// large, us: every tenth 39, the first tenth 57; with one word for all that lies outside, which all wavefronts of such a
+// workgroup then wait for, 45 and 137.)
 template <bool PAIRS>
 __device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, const unsigned long long* tab,
-                                            uint32_t* img, uint32_t words, uint32_t win, int lane, uint32_t& from) {
+                                            uint32_t* img, uint32_t words, uint32_t* past, uint32_t win, int lane, uint32_t& from) {
     const uint32_t clen = chunk_len_of(p, ch);
     const uint64_t at = (uint64_t)ch * p.chunk_syms;
     const uint8_t* src = p.syms + at;
@@ -1004,9 +1016,10 @@ __device__ __forceinline__ void pack_window(const PackParams& p, uint32_t ch, co
     auto put = [&](unsigned long long c, uint32_t pos) {
         const uint32_t sh = pos & 31u, rel = (pos >> 5) - win;
         const unsigned long long t0 = c << sh;
-        atomicOr(&img[rel < words ? rel : words], (uint32_t)t0);
-        atomicOr(&img[rel + 1u < words ? rel + 1u : words], (uint32_t)(t0 >> 32));
-        atomicOr(&img[rel + 2u < words ? rel + 2u : words], sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
+        // (each word by itself: the first may lie before the window and the next ones inside)
+        atomicOr(rel < words ? img + rel : past, (uint32_t)t0);
+        atomicOr(rel + 1u < words ? img + (rel + 1u) : past, (uint32_t)(t0 >> 32));
+        atomicOr(rel + 2u < words ? img + (rel + 2u) : past, sh ? (uint32_t)((c >> 32) >> (32u - sh)) : 0u);
     };
     const uint32_t end = 32u * (win + words);
     uint32_t base = from >> 12, s0 = from & 0xfffu;
@@ -1156,7 +1169,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             const uint32_t ch = c0 + slot;
             uint32_t from = 0;
             align_chunk_octets(p, ch, lane, w);
-            const uint32_t bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.image + slot * (words + 4u), words, lane, S.runs[wave], from);
+            const uint32_t bits = pack_octets<PAIRS>(w, chunk_len_of(p, ch), S.tab, S.image + slot * (words + 4u), words, S.past + lane, lane, S.runs[wave], from);
             if (lane == 0) {
                 S.words[slot] = (bits + 31u) >> 5;
                 if constexpr (STATIC) S.bits[slot] = bits;
@@ -1237,7 +1250,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             for (uint32_t win = 0; win < n_words; win += words) {
                 const uint32_t win_words = n_words - win < words ? n_words - win : words;
                 if (win) {
-                    pack_window<PAIRS>(p, first_ch + slot, S.tab, img, words, win, lane, from);
+                    pack_window<PAIRS>(p, first_ch + slot, S.tab, img, words, S.past + lane, win, lane, from);
                     sync_wave();
                 }
                 // four words per lane, to any word of the payload (images start on 16 bytes); then the last one to three
