@@ -18,7 +18,7 @@
 #include "fmtc_device.h"
 #include "fmtc_internal.h"
 #include "fmtc_pack_device.h"
-#include "fmtc_stream_scale.h"
+#include "fmtc_stream_rules.h"
 
 namespace fmtc {
 
@@ -695,14 +695,8 @@ void k_project_quantize_stream(RowParams p) {
         }
     };
     f4_t raw[NJA][2];
-    // Whole rounds of tiles go to the wavefronts of the grid in order (neighbouring tiles to one workgroup: dealt to the
-    // workgroups first, planar tiles lose the lines that they share, 144 channels, 50176 pixels 19.1 -> 21.2 us), the tiles
-    // of the last one to the workgroups first: a few of them have a compute unit each.
-    const int64_t stride = (int64_t)gridDim.x * WAVES, whole = p.n_tiles - (int64_t)((uint32_t)p.n_tiles % (uint32_t)stride);
-    const int64_t last = whole + (int64_t)wave * gridDim.x + blockIdx.x;
-    auto tile_after = [&](int64_t t) { return t + stride < whole ? t + stride : (t < whole ? last : p.n_tiles); };
-    int64_t tile = (int64_t)blockIdx.x * WAVES + wave;
-    if (tile >= whole) tile = last;
+    const TileWalk walk(p.n_tiles, gridDim.x, WAVES, blockIdx.x, (uint32_t)wave);
+    int64_t tile = walk.first;
     {
         const Place here = place_of(tile < p.n_tiles ? tile : 0);
 #pragma unroll
@@ -803,8 +797,8 @@ void k_project_quantize_stream(RowParams p) {
         n_fix = 0u;
     };
 
-    for (; tile < p.n_tiles; tile = tile_after(tile)) {
-        const int64_t next_tile = tile_after(tile);
+    for (; tile < p.n_tiles; tile = walk.after(tile)) {
+        const int64_t next_tile = walk.after(tile);
         const bool more = next_tile < p.n_tiles;
         const Place next = place_of(more ? next_tile : 0);
         const bool px_ok = l32 < p.P - tile * 32;

@@ -1,6 +1,8 @@
-// The scale of the streaming projection's operands (k_project_quantize_stream), and the distance to a rounding boundary from
-// which its sums decide.  Plain C++, for the model of the sums on the CPU.
+// Rules of the streaming projection (k_project_quantize_stream) that can be checked without a device: the scale of its
+// operands, the distance to a rounding boundary from which its sums decide, and the order of its tiles.  Plain C++.
 #pragma once
+#include <stdint.h>
+
 #include <cmath>
 
 namespace fmtc {
@@ -32,5 +34,19 @@ inline float stream_scale(float delta, int bits, float row_norm) {
 //   - 1 for that of 1 / delta;
 //   - 4 that cover the subnormals (see above), the sum of squares behind |x - mu|_2 and 2^-10 of all this.
 constexpr float stream_band(int steps) { return (float)(6 * steps + 18) * (1.f / 16777216.f); }
+
+// The tiles that a wavefront takes, one after the other.  Whole rounds, and a tensor's only one, go to the wavefronts of the
+// grid in order, neighbouring tiles to one workgroup: dealt to the workgroups first, planar tiles lose the lines that they
+// share (144 channels, 255 images of 14 x 14, 1562 tiles 17.8 -> 21.4 us; 160 channels, 61 of 28 x 28 19.9 -> 22.4).  The tiles
+// of a last round that is not full go to the workgroups first: a few of them have a compute unit each.
+struct TileWalk {
+    int64_t n, stride, whole, last, first;
+    constexpr TileWalk(int64_t n_tiles, uint32_t grid, uint32_t waves, uint32_t block, uint32_t wave)
+        : n(n_tiles), stride((int64_t)grid * waves),
+          whole(n_tiles <= stride ? n_tiles : n_tiles - (int64_t)((uint32_t)n_tiles % (uint32_t)stride)),
+          last(whole + (int64_t)wave * grid + block), first((int64_t)block * waves + wave) {}
+    // (n or more: none)
+    constexpr int64_t after(int64_t tile) const { return tile + stride < whole ? tile + stride : (tile < whole ? last : n); }
+};
 
 }  // namespace fmtc

@@ -1,5 +1,5 @@
-"""The streaming projection's sums, modelled on the CPU: whatever the norm of the basis' rows, a value that they decide is
-decided as in 64 bits."""
+"""The streaming projection's rules on the CPU.  Its sums, modelled: whatever the norm of the basis' rows, a value that they
+decide is decided as in 64 bits.  Its tiles: each is taken once, and in which order."""
 import ctypes
 import os
 import subprocess
@@ -13,15 +13,29 @@ CSRC = os.path.join(os.path.dirname(HERE), "paper_1905_10830_amd", "csrc")
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """The library's own scale and distance, compiled for the host."""
+    """The library's own scale, distance and order of tiles, compiled for the host."""
     tmp = tmp_path_factory.mktemp("rules")
     src, lib = str(tmp / "rules.cpp"), str(tmp / "rules.so")
     with open(src, "w") as f:
-        f.write('#include "fmtc_stream_scale.h"\n'
+        f.write('#include "fmtc_stream_rules.h"\n'
                 'extern "C" float scale(float delta, int bits, float row_norm) { return fmtc::stream_scale(delta, bits, row_norm); }\n'
-                'extern "C" float band(int steps) { return fmtc::stream_band(steps); }\n')
+                'extern "C" float band(int steps) { return fmtc::stream_band(steps); }\n'
+                'extern "C" int64_t walk(int64_t n, uint32_t grid, uint32_t waves, int64_t* taken_by, int64_t* order) {\n'
+                '    int64_t taken = 0;\n'
+                '    for (uint32_t b = 0; b < grid; b++)\n'
+                '        for (uint32_t w = 0; w < waves; w++) {\n'
+                '            const fmtc::TileWalk walk(n, grid, waves, b, w);\n'
+                '            int64_t place = 0;\n'
+                '            for (int64_t t = walk.first; t < n; t = walk.after(t), taken++, place++) {\n'
+                '                taken_by[t] = (int64_t)b * waves + w;\n'
+                '                order[t] = place;\n'
+                '            }\n'
+                '        }\n'
+                '    return taken;\n'
+                '}\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
     so = ctypes.CDLL(lib)
+    so.walk.restype, so.walk.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p]
     so.band.restype, so.band.argtypes = ctypes.c_float, [ctypes.c_int]
     so.scale.restype, so.scale.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_int, ctypes.c_float]
     return so
@@ -99,3 +113,19 @@ def test_the_distance_covers_every_rounding(rules, C):
         acc, _ = fast_sums(T, v[None, :], 64.0)
         worst = max(worst, abs(acc[0, 0] / 64.0 - float(T[0] @ v)) / (np.linalg.norm(T) * np.linalg.norm(v)))
     assert worst <= rules.band(steps), worst / unit
+
+
+@pytest.mark.parametrize("waves", [4, 8])
+@pytest.mark.parametrize("n", [1, 3, 8, 9, 784, 785, 1023, 1024, 1025, 1562, 1568, 2047, 2048, 2049, 2063, 4095, 4096, 6272, 6273, 12345])
+def test_every_tile_is_taken_once(rules, n, waves):
+    grid = min(-(-n // waves), 256)
+    taken_by, order = np.full(n, -1, np.int64), np.full(n, -1, np.int64)
+    assert rules.walk(n, grid, waves, taken_by.ctypes.data, order.ctypes.data) == n
+    assert (taken_by >= 0).all()
+    stride = grid * waves
+    whole = n if n <= stride else n - n % stride
+    tile = np.arange(n)
+    # whole rounds and an only one in order, a last one that is not full to the workgroups first
+    assert np.array_equal(taken_by[:whole], tile[:whole] % stride) and np.array_equal(order, tile // stride)
+    rest = tile[whole:] - whole
+    assert np.array_equal(taken_by[whole:], rest % grid * waves + rest // grid)
