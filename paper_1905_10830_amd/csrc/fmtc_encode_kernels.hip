@@ -956,20 +956,16 @@ static RowsPlan plan_rows(int C, int64_t P, int64_t HW, int layout, int bits) {
     r.nct = (C + 31) / 32;
     const bool offsets_fit = layout == FMTC_NHWC || planar_offsets_fit(C, P, HW);
     const int64_t tiles = (P + 31) / 32;
-    // 97 to 128 channels, channels last: eight wavefronts on one copy of the basis, two per SIMD, each working tile by
+    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, with eight wavefronts on one copy of
+    // the basis where there are more tiles than SIMDs.  (Up to 1024 tiles four: 128 channels, 25088 pixels 12.7, 13.7 us with
+    // eight.)  Kernel times, us, the other forms : this one, channels last, 6 bits: 128 channels, 200704 pixels 51.5 : 35.9 (8 bits
+    // 67 : 42.6), 100352 33.0 : 25.1, 32992 18.1 : 14.5 (8 bits 18.9 : 18.3); 112, 32992 15.5 : 12.3.
+    r.stream = r.nct >= 4 && C % 16 == 0 && offsets_fit;
+    // 97 to 127 other channels, channels last: eight wavefronts on one copy of the basis, two per SIMD, each working tile by
     // tile with one pair of accumulators (two four-wavefront workgroups with a copy each would not fit a compute unit's
     // LDS).  (Planar tensors: the loads' addresses do not fit the registers; 8 bits: eight wavefronts' histograms do not
     // fit LDS beside the basis.)
-    bool eight = r.nct == 4 && layout == FMTC_NHWC && tiles > 1024 && rows_lds(r.nct, bits, 8) <= 144 * 1024;
-    // Four and five coefficient tiles, a multiple of 16 channels: the streaming form, with eight wavefronts on one copy of
-    // the basis where there are more tiles than SIMDs.  Kernel times, us, the other forms of this file before : now: 128
-    // channels, channels last, 200704 pixels 51.5 : 39.4 (8 bits 67 : 46, 4 bits 47 : 37), 100352 33.0 : 25.1, 65568 26.2 :
-    // 19.5; planar 57.3 : 42.6 and 50176 pixels 22.3 : 15.7; 112 channels, 100352 31.0 : 22.1; 144, 200704 67.7 : 50.3 (7 bits
-    // 75 : 53, planar 71 : 53), 33000 22.2 : 16.8; 160, 100352 43.2 : 32.4.  Up to 1024 tiles four wavefronts: 128 channels,
-    // 25088 pixels 12.7, 13.7 with eight.  (The first few tiles beyond 1024, channels last, are left to the eight-wavefront
-    // form above.)
-    r.stream = r.nct >= 4 && C % 16 == 0 && offsets_fit && !(eight && tiles <= 1056);
-    if (r.stream) eight = tiles > 1024;
+    const bool eight = tiles > 1024 && (r.stream || (r.nct == 4 && layout == FMTC_NHWC && rows_lds(r.nct, bits, 8) <= 144 * 1024));
     r.waves = eight ? 8 : 4;
     // planar: vec = a multiple of 16 channels and offsets within the images of a pixel tile that fit 32 bits
     r.vec = layout == FMTC_NHWC ? C % 4 == 0 : C % 16 == 0 && offsets_fit;

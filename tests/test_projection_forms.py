@@ -49,6 +49,13 @@ def test_wide_tensors_of_whole_16_channels(C, tiles, layout, bits, want, ahead, 
     assert form(C, 32 * (tiles // -(-C // 32)), layout, bits) == want, f"{ahead} us, {behind} in the other form"
 
 
+@pytest.mark.parametrize("C,P,bits,ahead,behind", [(128, 32992, 6, 14.5, 18.1), (128, 32992, 8, 18.3, 18.9), (128, 33600, 4, 13.4, 16.2),
+                                                    (112, 32992, 6, 12.3, 15.5), (112, 33792, 6, 12.3, 15.4)])
+def test_streaming_form_from_its_first_tile_on(C, P, bits, ahead, behind):
+    """(A multiple of 16 channels; tensors with a few pixel tiles more than SIMDs were left to another form.)"""
+    assert form(C, P, NHWC, bits).startswith("stream 4"), f"{ahead} us, {behind} in the other form"
+
+
 def test_truncated_wide_tensors():
     assert form(768, 1344, NHWC, 8, 307) == "split 1x4"  # 25 us, 37 in the other form
     assert form(768, 1344, NHWC, 8, 700) == "gemm8"
