@@ -2674,14 +2674,14 @@ static ProjectionForm choose_projection(int C, int64_t P, int64_t HW, int layout
     return tiles > 640 && wide_form_is_ahead(C, P, layout, bits) ? ProjectionForm{ProjectionForm::kWide, 0, 0, false} : large;
 }
 
-// The same in words, for tests: "rows 2 vec", "stream 5 half", "gemm8 fill", "split 1x4", ..., the layout, and of the split
+// The same in words, for tests: "rows 2 vec", "stream 5x8 half", "gemm8 fill", "split 1x4", ..., the layout, and of the split
 // form the rows of counts.
 int describe_projection(int C, int64_t P, int64_t HW, int layout, int bits, int active_rows, char* text, size_t size) {
     const ProjectionForm f = choose_projection(C, P, HW, layout, bits, active_rows);
     const char* lay = layout == FMTC_NHWC ? "nhwc" : "nchw";
     if (f.kernel == ProjectionForm::kRows) {
         const RowsPlan r = plan_rows(C, P, HW, layout, bits);
-        if (r.stream) return snprintf(text, size, "stream %d%s %s", r.nct, C == 32 * r.nct ? "" : " half", lay);
+        if (r.stream) return snprintf(text, size, "stream %d%s%s %s", r.nct, r.waves == 8 ? "x8" : "", C == 32 * r.nct ? "" : " half", lay);
         return snprintf(text, size, "rows %d%s%s %s", r.nct, r.waves == 8 ? "x8" : "", r.vec ? " vec" : "", lay);
     }
     if (f.kernel == ProjectionForm::kGemm) {

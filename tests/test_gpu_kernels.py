@@ -393,7 +393,7 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None, keep=
         T = T * np.asarray(T_scale, np.float32)[:, None]
     mu = rng.standard_normal(C).astype(np.float32)
     x = (rng.standard_normal((P, C)) * np.linspace(2.0, 0.1, C) + mu).astype(np.float32)
-    x[P // 2] *= 1.0e5
+    x[[P // 2, max(0, P - 5)]] *= 1.0e5
     A = np.float32(reach if T_scale is None else reach * np.max(T_scale))
     y = (x.astype(np.float64) - mu) @ T.T.astype(np.float64)
     basis = fmtc.basis_import(T, mu, A)
@@ -413,7 +413,8 @@ def check_projection(fmtc, oracle, C, N, H, W, bits, layout, T_scale=None, keep=
 
 
 # Every form of the projection that a tensor can take (the rows' and the streaming kernel's coefficient tiles, loads with and
-# without masks, ...), at a size just beyond where it begins: three images of 7 x w pixels, ragged last tiles.
+# without masks, ...), at a size just beyond where it begins (or where its wavefronts come to a second tile): three images of
+# 7 x w pixels, ragged last tiles, a pixel beyond f16 in the middle and one in the last tile.
 FORM_CASES = [  # form, channels, w, bits, kept components (all of them if not given)
     ("rows 1 nhwc", 5, 77, 4), ("rows 1 nchw", 30, 77, 8), ("rows 1 vec nhwc", 28, 1600, 8), ("rows 1 vec nchw", 32, 77, 3),
     ("rows 2 nhwc", 33, 790, 6), ("rows 2 nchw", 63, 790, 5), ("rows 2 vec nhwc", 64, 790, 6), ("rows 2 vec nchw", 48, 790, 8),
@@ -422,6 +423,9 @@ FORM_CASES = [  # form, channels, w, bits, kept components (all of them if not g
     ("rows 4x8 vec nhwc", 100, 6250, 6), ("rows 5 nhwc", 129, 320, 6), ("rows 5 vec nhwc", 140, 320, 7),
     ("stream 4 nhwc", 128, 400, 6), ("stream 4 nchw", 128, 400, 7), ("stream 4 half nhwc", 112, 400, 5), ("stream 4 half nchw", 112, 400, 6),
     ("stream 5 nhwc", 160, 320, 6), ("stream 5 nchw", 160, 320, 5), ("stream 5 half nhwc", 144, 320, 5), ("stream 5 half nchw", 144, 320, 7),
+    # (2068 tiles: a whole round of the grid's wavefronts, and 20 more)
+    ("stream 4x8 nhwc", 128, 3150, 8), ("stream 4x8 nchw", 128, 3150, 6), ("stream 4x8 half nhwc", 112, 3150, 6), ("stream 4x8 half nchw", 112, 3150, 5),
+    ("stream 5x8 nhwc", 160, 3150, 7), ("stream 5x8 nchw", 160, 3150, 6), ("stream 5x8 half nhwc", 144, 3150, 4), ("stream 5x8 half nchw", 144, 3150, 5),
     ("split 1x1 nhwc", 64, 38, 6), ("split 1x1 nchw", 101, 38, 8), ("split 1x2 nhwc", 300, 70, 8), ("split 1x2 nchw", 64, 500, 6),
     ("split 1x4 nhwc", 250, 390, 6), ("split 1x4 nchw", 256, 570, 5), ("split 2x2 nhwc", 161, 600, 7), ("split 2x2 nchw", 133, 1590, 6),
     ("gemm8 nhwc", 256, 320, 6), ("gemm8 nchw", 176, 720, 4), ("gemm4 nhwc", 176, 785, 8), ("gemm4 nchw", 240, 785, 5),
