@@ -17,6 +17,7 @@
 #include "fmtc_device.h"
 #include "fmtc_internal.h"
 #include "fmtc_pack_device.h"
+#include "fmtc_pack_ranges.h"
 
 namespace fmtc {
 
@@ -1095,15 +1096,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
         __syncthreads();
     }
     // While the first wavefront builds the table, the others clear the images and request their first symbols.
-    uint32_t images = 0, words = 0, per_range = 0, n_ranges = 0, c0 = 0, count = 0;
-    auto cut = [&]() {  // the tensor into ranges (see images_for)
-        const uint32_t rounds = (p.n_chunks + gridDim.x * images - 1u) / (gridDim.x * images);
-        per_range = (p.n_chunks + gridDim.x * rounds - 1u) / (gridDim.x * rounds);
-        n_ranges = (p.n_chunks + per_range - 1u) / per_range;
-    };
-    auto take_range = [&](uint32_t range) {  // (past the last one: no chunks)
-        c0 = range < n_ranges ? range * per_range : p.n_chunks;
-        count = p.n_chunks - c0 < per_range ? p.n_chunks - c0 : per_range;
+    uint32_t images = 0, words = 0, c0 = 0, count = 0;
+    Ranges ranges{0u, 0u};
+    auto take_range = [&](uint32_t range) {
+        const ChunkSpan span = range_chunks(ranges, range, p.n_chunks);
+        c0 = span.first;
+        count = span.count;
     };
     uint2 w[8];
     if (STATIC || wave != 0u) {
@@ -1116,7 +1114,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             S.image_words = words;
             S.gone = 0u;
         }
-        cut();
+        ranges = cut_ranges(p.n_chunks, gridDim.x, images);
         take_range((uint32_t)__builtin_amdgcn_readfirstlane((int)S.range));
         if (wave < count) load_chunk_octets(p, c0 + wave, lane, w);
     } else {
@@ -1134,7 +1132,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     if (!STATIC && wave == 0u) {
         images = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.images);
         words = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.image_words);
-        cut();
+        ranges = cut_ranges(p.n_chunks, gridDim.x, images);
         take_range((uint32_t)__builtin_amdgcn_readfirstlane((int)S.range));
         if (wave < count) load_chunk_octets(p, c0 + wave, lane, w);
     }
@@ -1157,8 +1155,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     uint32_t added = 0;
     unsigned long long added_words = 0, my_bits = 0;
 
-    while (range < n_ranges) {
-        const bool more = n_ranges > gridDim.x;  // (otherwise every workgroup has one range)
+    while (range < ranges.count) {
+        const bool more = claims_another(ranges, gridDim.x);
         if (more && wave == kLast && lane == 0) ticket = claim();
         // ---- the chunks of the range into their images ----
         uint32_t slot = wave;
@@ -1182,7 +1180,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
             for (int q = 0; q < 8; q++) w[q] = wn[q];
         }
-        if (wave == kLast && lane == 0) S.next_range = more ? ticket : n_ranges;
+        if (wave == kLast && lane == 0) S.next_range = more ? ticket : ranges.count;
         __syncthreads();
         // ---- the range's place: its size is published, and the sizes before it are added up ----
         const uint32_t first_ch = c0, n_here = count, next_range = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.next_range);
@@ -1268,7 +1266,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 sync_wave();  // the image is read and clear before the next window or chunk writes it
             }
         }
-        if (wave == 0u && added == n_ranges) {  // the last range: the header
+        if (wave == 0u && added == ranges.count) {  // the last range: the header
             if constexpr (STATIC) {
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) my_bits += __shfl_xor(my_bits, o, 64);
