@@ -741,9 +741,12 @@ void k_project_quantize_stream(RowParams p) {
     __syncthreads();
 
     // exact decision of the listed values (as in k_project_quantize_rows)
-    // ALL: a value's channels all in flight together (after the last tile, where nothing else needs the registers)
-    auto resolve_list = [&](auto all_c) __attribute__((always_inline)) {
-        constexpr int kFlight = decltype(all_c)::value ? NJA : 2;
+    // LAST: after the last tile, where nothing else needs the registers.  Otherwise as many of a value's channels are in flight
+    // together as fit beside the sums: all of them with one wavefront per SIMD, else a half or a third.  (Two steps at a time:
+    // 144 channels, pixels of 25 times the quantizer's range, of which 1.4 % of the values are listed, 70000 pixels, 7 bits 1.44
+    // times the kernel's time, 20000 pixels 1.35 times.)
+    auto resolve_list = [&](auto last_c) __attribute__((always_inline)) {
+        constexpr int kFlight = decltype(last_c)::value || WAVES == 4 ? NJA : (NCT == 4 ? (NJA + 1) / 2 : (NJA == 9 ? 3 : 5));
         __builtin_amdgcn_s_waitcnt(0x0F70);
         // (None of this rare path's addresses is to be kept in registers over the loop outside: where it starts from is made
         // unknown here.)
