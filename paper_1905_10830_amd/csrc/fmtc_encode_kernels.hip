@@ -852,8 +852,9 @@ void k_project_quantize_stream(RowParams p) {
         }
         n2 += __shfl_xor(n2, 32, 64);  // the other half of the pixel
         const bool force = !(n2 < 3.6e9f);  // too large for f16 (or not finite): every coefficient decided exactly
-        const float tau = fminf(fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min), 0.125f);
-        const float near_limit = force ? -1.f : 0.5f - tau;
+        // (not cut off at an eighth of a step, which pixels of 250 times the quantizer's range reach at 8 bits: the error is not
+        // either)
+        const float near_limit = force ? -1.f : 0.5f - fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min);
 
 #pragma unroll
         for (int kt = 0; kt < NCT; kt++) {
@@ -1020,7 +1021,7 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     *n_parts = (int)gx;
     hipError_t el = hipSuccess;
     if (pl.stream) {
-        p.kappa = stream_band(b.C / 16) * b.row_norm * p.inv_delta / p.x_scale;  // (of |S (x - mu)|_2)
+        p.kappa = (float)((double)stream_band(b.C / 16) * b.row_norm * p.inv_delta / p.x_scale);  // (of |S (x - mu)|_2)
         const bool whole = b.C == nct * 32;  // else 16 channels less
         const size_t slds = rows_lds(nct, bits, 4);  // (four histograms whatever the wavefronts)
         int64_t sgx = (p.n_tiles + waves - 1) / waves;

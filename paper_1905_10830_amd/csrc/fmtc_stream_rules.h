@@ -21,7 +21,7 @@ inline float stream_scale(float delta, int bits, float row_norm) {
     int e = 0;
     (void)std::frexp(reach, &e);  // reach in [2^(e-1), 2^e)
     const int k = 7 - e;
-    return std::ldexp(1.f, k < -100 ? -100 : (k > 100 ? 100 : k));  // (what fp32 and its reciprocal hold)
+    return std::ldexp(1.f, k < -126 ? -126 : (k > 126 ? 126 : k));  // (what fp32 holds)
 }
 
 // What a coefficient's sum over `steps` steps of 16 channels is off by at most, per |T_k|_2 |x - mu|_2.  In units of 2^-24:
