@@ -1011,7 +1011,7 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     const bool eight = waves == 8, vec = pl.vec;
     const size_t lds = rows_lds(nct, bits, waves);
     // workgroups a compute unit holds at once: by registers (rows_waves_per_simd) and by LDS
-    const size_t lds_static = (size_t)waves * (2 * kFixList + 1 + 256) * 4 + (size_t)nct * 128 + 512;
+    const size_t lds_static = (size_t)waves * (2 * kFixList + 256) * 4 + (size_t)nct * 128 + 512;
     int per_cu = eight ? 1 : rows_waves_per_simd(nct, false, 4);
     const int by_lds = (int)((160 * 1024) / (lds + lds_static));
     if (per_cu > by_lds) per_cu = by_lds < 1 ? 1 : by_lds;
