@@ -596,7 +596,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // the device added up.  Of its 45 us for those chunks the packing took 8: the wavefronts spent 7 us waiting for their last
 // places, some compute units having four turns and others three, 4.6 on dealing chunks that must not get stuck, 4 on what a
 // turn leaves for its server.)
-// What bounds it, at those 33.8 us: 13 us before the first chunk (partial counts 4.3, table 7.4, pair table 1), 16 of packing,
+// What bounds it, at 33.8 us for those chunks: 13 us before the first one (partial counts 4.3, table 7.4, pair table 1), 16 of packing,
 // two thirds of whose clocks issue vector instructions, 3 from the last size published to the places, 2 of stores.
 // A lane takes eight neighbouring symbols per step, and up to 6 bits the table holds the joined code words of symbol
 // pairs: four lookups, one prefix sum over the lanes and two or three ORs into the image per 512 symbols.

@@ -59,9 +59,9 @@ def test_code_table_of_crafted_counts(fmtc, oracle, bits, kind):
     assert np.array_equal(got, ref)
 
 
-# Packer of large tensors: more than 4096 chunks.  Chunk sizes that are multiples of 8, of 4 only, of neither; one to three
-# groups per workgroup (more: TURN_CASES); four images per packer (fewer: test_packer_with_two_to_four_images); code words of
-# more than 27 bits, chunks larger than an image.
+# Packer of large tensors: more than 4096 chunks.  Chunk sizes that are multiples of 8, of 4 only, of neither; a range of 17
+# chunks and more per workgroup (all its images, and several ranges: RANGE_CASES); 64 images per workgroup (fewer:
+# test_packer_with_two_to_four_images); code words of more than 27 bits, chunks larger than an image.
 STREAM_CASES = [  # P, C, bits, chunk_syms, kind
     (4097 * 4, 16, 6, 64, "steep"),
     (15 * 300, 64, 6, 64, "steep"),
@@ -105,8 +105,8 @@ def test_packer_of_large_tensors(fmtc, oracle, P, C, bits, chunk, kind):
     assert int(err.item()) == 0 and np.array_equal(back.cpu().numpy().reshape(-1), sym)
 
 
-# ... and more: (chunks, symbols a chunk, ...) of four to six turns per workgroup, of a last group of one chunk and of one
-# chunk less than whole groups.
+# ... and more: (chunks, symbols a chunk, ...) in ranges of 61 chunks, nearly all of a workgroup's 64 images, and in two ranges of
+# 45 and of 38 per workgroup, the last ones short.
 TURN_CASES = [(15 * 256 * 4 + 1, 66, 33, 6, "steep"), (15 * 256 * 6 - 1, 64, 16, 4, "gaps"), (15 * 256 * 5 + 1, 99, 9, 7, "gaps"),
               (15 * 256 * 4 + 16, 33, 33, 8, "steep")]
 
@@ -283,9 +283,9 @@ def test_packer_of_long_octets(fmtc, oracle, bits, share, chunk):
     assert int(nbytes.item()) == len(ref) and np.array_equal(stream[:len(ref)].cpu().numpy(), ref)
 
 
-# Images that a packer's room is divided into: four up to 3 bits a symbol of a whole chunk, three up to 4, two beyond; pairs
-# of symbols in the table up to 6 bits, single ones above.  Every tenth chunk is several times larger; the last group has
-# one chunk, or all but one.
+# Images that a workgroup's room is divided into, for each of its 16 wavefronts: four up to 3 bits a symbol of a whole chunk,
+# three up to 4, two beyond; pairs of symbols in the table up to 6 bits, single ones above.  Every tenth chunk is several
+# times larger.
 @pytest.mark.parametrize("images,bits,spread,n_chunks", [(4, 6, 0.8, 4111), (3, 6, 1.6, 4111), (3, 8, 1.2, 4124), (2, 6, 5.0, 4111),
                                                          (2, 7, 6.0, 4124), (2, 8, 14.0, 4111), (2, 8, 40.0, 4096)])
 @pytest.mark.parametrize("chunk,C", [(4096, 64), (4092, 33)])
