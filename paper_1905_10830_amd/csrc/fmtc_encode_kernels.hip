@@ -86,6 +86,7 @@ struct RowParams {
     unsigned long long* lookback;
     uint32_t n_groups;
     float x_scale;            // k_project_quantize_stream: S, a power of two (see there)
+    float kappa_steps;        // ... and beside kappa, per the root of the sum over the steps (see band_of_roundings)
     PackParams pk;            // FUSED only: where the container goes
 };
 
@@ -629,7 +630,7 @@ void k_project_quantize_rows(RowParams p) {
 // magic, and the distance to the level is acc g - (u - magic) in another.  (All products being added to the large sum, its
 // error is larger than that of two sums: in random data of 112 to 160 channels 2^-21.1 |x - mu|_2 against 2^-21.8 was the
 // largest seen where a leading component holds most of the pixel, 2^-22.9 against 2^-23.7 where none does.  The distance
-// below which a value is decided exactly follows from a bound: see stream_band.)
+// below which a value is decided exactly follows from a bound: see band_of_roundings.)
 //
 // A pixel too large for f16 needs no clamp here: what its
 // infinities make of the matrix product stays in its own column of outputs, all of which are decided exactly, and
@@ -807,7 +808,7 @@ void k_project_quantize_stream(RowParams p) {
         const bool px_ok = l32 < p.P - tile * 32;
         f4_t coming[NJA][2];  // (in the registers of `raw`: see below)
         floatx16 acc[NCT];
-        float n2 = 0.f;
+        float n2 = 0.f, n2_steps = 0.f;  // the pixel's squares; their sums after every step added up
         const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJA; j++) {
@@ -829,6 +830,7 @@ void k_project_quantize_stream(RowParams p) {
             // (converted, and their squares added up, before their registers are requested again: the compiler would rather do
             // that behind the branch, with a second set of registers for the loads)
             asm volatile("" : "+v"(vh), "+v"(vl), "+v"(n2));
+            n2_steps += n2;
             if (more) load_step(next, j, coming[j]);
             vt = vh * (_Float16)(1.f / 2048.f);
 #pragma unroll
@@ -851,10 +853,12 @@ void k_project_quantize_stream(RowParams p) {
             __builtin_amdgcn_sched_barrier(0);
         }
         n2 += __shfl_xor(n2, 32, 64);  // the other half of the pixel
+        n2_steps += __shfl_xor(n2_steps, 32, 64);
         const bool force = !(n2 < 3.6e9f);  // too large for f16 (or not finite): every coefficient decided exactly
         // (not cut off at an eighth of a step, which pixels of 250 times the quantizer's range reach at 8 bits: the error is not
         // either)
-        const float near_limit = force ? -1.f : 0.5f - fmaxf(p.kappa * __builtin_sqrtf(n2), p.tau_min);
+        const float tau = fmaxf(p.kappa * __builtin_sqrtf(n2) + p.kappa_steps * __builtin_sqrtf(n2_steps), p.tau_min);
+        const float near_limit = force ? -1.f : 0.5f - tau;
 
 #pragma unroll
         for (int kt = 0; kt < NCT; kt++) {
@@ -1021,7 +1025,9 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     *n_parts = (int)gx;
     hipError_t el = hipSuccess;
     if (pl.stream) {
-        p.kappa = (float)((double)stream_band(b.C / 16) * b.row_norm * p.inv_delta / p.x_scale);  // (of |S (x - mu)|_2)
+        const double per_step = (double)b.row_norm * p.inv_delta / p.x_scale;
+        p.kappa = (float)(kBandOfRest * per_step);  // (both of lengths of S (x - mu))
+        p.kappa_steps = (float)(band_of_roundings(b.C / 16) * per_step);
         const bool whole = b.C == nct * 32;  // else 16 channels less
         const size_t slds = rows_lds(nct, bits, 4);  // (four histograms whatever the wavefronts)
         int64_t sgx = (p.n_tiles + waves - 1) / waves;

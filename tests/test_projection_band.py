@@ -19,7 +19,8 @@ def rules(tmp_path_factory):
     with open(src, "w") as f:
         f.write('#include "fmtc_stream_rules.h"\n'
                 'extern "C" float scale(float delta, int bits, float row_norm) { return fmtc::stream_scale(delta, bits, row_norm); }\n'
-                'extern "C" float band(int steps) { return fmtc::stream_band(steps); }\n'
+                'extern "C" float band_of_roundings(int steps) { return fmtc::band_of_roundings(steps); }\n'
+                'extern "C" float band_of_rest() { return fmtc::kBandOfRest; }\n'
                 'extern "C" int64_t walk(int64_t n, uint32_t grid, uint32_t waves, int64_t* taken_by, int64_t* order) {\n'
                 '    int64_t taken = 0;\n'
                 '    for (uint32_t b = 0; b < grid; b++)\n'
@@ -36,7 +37,8 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
     so = ctypes.CDLL(lib)
     so.walk.restype, so.walk.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p]
-    so.band.restype, so.band.argtypes = ctypes.c_float, [ctypes.c_int]
+    so.band_of_roundings.restype, so.band_of_roundings.argtypes = ctypes.c_float, [ctypes.c_int]
+    so.band_of_rest.restype, so.band_of_rest.argtypes = ctypes.c_float, []
     so.scale.restype, so.scale.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_int, ctypes.c_float]
     return so
 
@@ -61,8 +63,8 @@ def add_eight(acc, a, b):
     return f32((products + np.floor(acc / cut)) * cut)
 
 
-def fast_sums(T, v, scale):
-    """What the matrix instructions make of the f16 parts."""
+def fast_sums(rules, T, v, scale):
+    """What the matrix instructions make of the f16 parts, the pixels' lengths, and how far off the sums may be per row norm."""
     t_hi = f16(T)
     t_lo = f16((T - t_hi) * 2048.0)
     s = f32(v * scale)
@@ -73,7 +75,9 @@ def fast_sums(T, v, scale):
         for a, b in ((s_lo, t_hi), (s_hi_low, t_lo), (s_hi, t_hi)):
             for i in (j, j + 8):
                 acc = add_eight(acc, a[:, i:i + 8], b[:, i:i + 8])
-    return acc, np.sqrt((s * s).sum(axis=1))
+    n2 = np.cumsum((s * s).reshape(len(s), -1, 16).sum(axis=2), axis=1)
+    length = np.sqrt(n2[:, -1])
+    return acc, length, rules.band_of_roundings(n2.shape[1]) * np.sqrt(n2.sum(axis=1)) + rules.band_of_rest() * length
 
 
 def pixels(rng, T, P, kind):
@@ -96,9 +100,9 @@ def test_values_that_the_sums_decide(rules, norm, C, bits, kind):
     for part in (20.0, 1.0, 0.1, 0.01):
         delta = float(np.float32(np.abs(y[:, 0]).max() / part / (half - 1)))
         S = rules.scale(delta, bits, row_norm)
-        acc, length = fast_sums(T, x, S)
+        acc, length, off = fast_sums(rules, T, x, S)
         inv_delta = np.float32(1.0 / delta)
-        tau = np.maximum(rules.band(C // 16) * float(row_norm) * float(inv_delta) / S * length, 2.0 ** -21 * half)[:, None]
+        tau = np.maximum(float(row_norm) * float(inv_delta) / S * off, 2.0 ** -21 * half)[:, None]
         exact = length >= 60000.0
         t = acc * float(inv_delta) / S
         assert exact.mean() < 0.01, "pixels of the quantizer's range are too large for f16"
@@ -115,9 +119,11 @@ def test_the_distance_covers_every_rounding(rules, C):
     """Not only what random data show: every rounding of a sum in the same direction, each of half a unit of the largest
     partial sum, what is cut off before, and the f16 parts' errors.  (Tried here: products of one sign, so that everything is
     cut off in one direction, of like and of very different sizes, and one large product with small ones that fall below its
-    half unit eight by eight: up to 10 units of the 68 to 86.)"""
+    half unit eight by eight: up to a sixth of it.)"""
     steps, unit = C // 16, 2.0 ** -24
-    assert rules.band(steps) >= (6 * steps + 8 + 14) * unit
+    assert rules.band_of_rest() >= (8 + 14) * unit
+    prefix = np.sqrt(np.random.default_rng(C).random((1000, steps)).cumsum(axis=1))  # a pixel's length after each step
+    assert (rules.band_of_roundings(steps) * np.sqrt((prefix ** 2).sum(axis=1)) >= 0.999999 * 6 * unit * prefix.sum(axis=1)).all()
     rng = np.random.default_rng(C)
     worst = 0.0
     for spread in (0, 6, 12):
@@ -127,9 +133,9 @@ def test_the_distance_covers_every_rounding(rules, C):
             if large:
                 T[:, 1:] *= 2.0 ** -10
                 v[:, 1:] *= 2.0 ** -4
-            acc, _ = fast_sums(T, v, 64.0)
-            worst = max(worst, (np.abs(acc / 64.0 - v @ T.T) / (np.linalg.norm(v, axis=1)[:, None] * np.linalg.norm(T, axis=1)[None, :])).max())
-    assert worst <= rules.band(steps), worst / unit
+            acc, _, off = fast_sums(rules, T, v, 64.0)
+            worst = max(worst, (np.abs(acc - 64.0 * (v @ T.T)) / (off[:, None] * np.linalg.norm(T, axis=1)[None, :])).max())
+    assert 0.05 < worst <= 1.0, worst
 
 
 @pytest.mark.parametrize("waves", [4, 8])
