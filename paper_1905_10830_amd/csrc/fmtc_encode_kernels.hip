@@ -994,10 +994,10 @@ static hipError_t launch_rows(const BasisDevice& b, const float* d_x, int64_t P,
     p.active_tiles = (b.active_rows + 31) / 32;
     p.inv_delta = (float)(1.0 / (double)delta);
     p.delta = delta;
-    // The fast pass is off by at most about 2^-22 sum |T[k][c]| |x[c] - mu[c]| (three representation errors of
-    // 2^-22 each and the fp32 accumulation) <= |T[k]|_2 |x - mu|_2 times that; values closer than 8 times this
-    // (in steps) to a rounding boundary are decided in fp64 instead.  The floor covers the rounding of the
-    // scaled value itself (magnitude up to 2^(b-1)).
+    // The fast pass is off by three representation errors of 2^-22 |T[k]|_2 |x - mu|_2 each and the fp32 accumulation (2^-23 a
+    // step of 16 channels and 2^-21 in all at most, mostly far less: random data are off by 2^-22 in all); values closer
+    // than 2^-19 times these lengths (in steps) to a rounding boundary are decided in fp64 instead.  The floor covers the
+    // rounding of the scaled value itself (magnitude up to 2^(b-1)).
     p.kappa = 1.9073486e-6f /* 2^-19 */ * b.row_norm * p.inv_delta;
     p.tau_min = 4.7683716e-7f /* 2^-21 */ * (float)(1 << (bits - 1));
     p.n_tiles = (P + 31) / 32;
